@@ -40,7 +40,7 @@ class AbsbError(RuntimeError):
 class _Layer(C.Structure):
     _fields_ = [("num_q_heads", C.c_int32), ("num_kv_heads", C.c_int32), ("head_dim", C.c_int32),
                 ("page_size", C.c_int32), ("dtype", C.c_int32), ("block_repr", C.c_int32),
-                ("block_size", C.POINTER(C.c_int32)),
+                ("block_size", C.c_void_p),
                 ("kv_stride_page", C.c_int64), ("kv_stride_head", C.c_int64), ("kv_stride_tok", C.c_int64),
                 ("sm_scale", C.c_float), ("sink_tokens", C.c_int32), ("recent_tokens", C.c_int32),
                 ("selection", C.c_int32)]
@@ -53,13 +53,34 @@ class _Opts(C.Structure):
 
 class _Batch(C.Structure):
     _fields_ = [("batch", C.c_int32), ("pt_stride", C.c_int32),
-                ("seq_lens_host", C.POINTER(C.c_int32)), ("seq_lens", C.c_void_p),
+                ("seq_lens_host", C.c_void_p), ("seq_lens", C.c_void_p),
                 ("page_table", C.c_void_p), ("cent_off", C.c_void_p),
-                ("budget_host", C.POINTER(C.c_int32)), ("budget", C.c_void_p),
-                ("cap_lens_host", C.POINTER(C.c_int32)), ("qmin", C.c_void_p), ("opts", _Opts)]
+                ("budget_host", C.c_void_p), ("budget", C.c_void_p),
+                ("cap_lens_host", C.c_void_p), ("qmin", C.c_void_p), ("opts", _Opts)]
 
 
 _lib = None
+
+# Argument types of the entry points: with them declared, integers, None, byref() records and c_void_p
+# objects are converted by ctypes itself, so a call passes plain integers (addresses, sizes) and builds
+# no wrapper objects.  P: an address or None.
+_P, _REC = C.c_void_p, C.c_void_p
+_ARGTYPES = {
+    "absb_plan": [_REC, _REC, _P, _P, _P, _P],
+    "absb_step_form_used": [_REC, _REC],
+    "absb_status_offset": [_REC, _REC, _P],
+    "absb_workspace_init": [_REC, _REC, _P, C.c_size_t, _P],
+    "absb_build_centroids": [_REC, _REC, _P, _P, _P, _P, _P, C.c_size_t, _P],
+    "absb_score": [_REC, _REC, _P, _P, _P, _P, _P, _P],
+    "absb_topk": [_REC, _REC, _P, _P, _P, C.c_int32, _P, C.c_size_t, _P],
+    "absb_sparse_decode": [_REC, _REC, _P, _P, _P, _P, _P, C.c_int32, _P, _P, _P, C.c_size_t, _P],
+    "absb_decode_fused": [_REC, _REC, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P, C.c_size_t, _P],
+    "absb_decode_fused_static": [_REC, _REC, _P, _P, _P, _P, _P, _P, _P, _P, _P, _P],
+    "absb_tail_init": [_REC, _REC, _P, _P, _P],
+    "absb_append_token": [_REC, _REC, _P, _P, _P, _P, _P, _P, _P],
+    "absb_head_recall": [_REC, _REC, _P, _P, _P, _P],
+    "absb_stream_read": [_P, C.c_size_t, _P, _P],
+}
 
 
 def load() -> C.CDLL:
@@ -73,7 +94,9 @@ def load() -> C.CDLL:
         lib.absb_strerror.restype = C.c_char_p
         lib.absb_strerror.argtypes = [C.c_int]
         for name in EXPORTS:
-            getattr(lib, name)            # fail loudly on a stale library
+            f = getattr(lib, name)            # fail loudly on a stale library
+            if name in _ARGTYPES:
+                f.argtypes = _ARGTYPES[name]
         _lib = lib
     return _lib
 
@@ -87,28 +110,38 @@ def _check(status: int, where: str) -> None:
         raise AbsbError(status, where)
 
 
-def _ptr(t) -> Optional[C.c_void_p]:
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return C.c_void_p(t)
-    return C.c_void_p(t.data_ptr())
+def _ptr(t) -> Optional[int]:
+    if t is None or isinstance(t, int):
+        return t
+    return t.data_ptr()
 
 
-def _stream(stream) -> C.c_void_p:
+_raw_stream = None
+
+
+def _stream(stream) -> int:
+    """The raw hipStream_t: of a torch stream, an address, or (None) torch's current stream."""
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        global _raw_stream
+        if _raw_stream is None:
+            import torch
+            get, device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+            device()                            # initialises the runtime, or raises where there is no GPU
+            device = torch._C._cuda_getDevice
+            _raw_stream = lambda: get(device())  # noqa: E731  (no Stream object per call)
+        return _raw_stream()
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _i32_host(a: Optional[Sequence[int]]):
+    """(contiguous int32 array to keep alive, its address); (None, None) for None."""
     if a is None:
         return None, None
-    arr = np.ascontiguousarray(np.asarray(a), dtype=np.int32)
-    return arr, arr.ctypes.data_as(C.POINTER(C.c_int32))
+    if type(a) is not np.ndarray or a.dtype != np.int32 or a.ndim != 1 or not a.flags.c_contiguous:
+        a = np.ascontiguousarray(np.asarray(a), dtype=np.int32)
+    return a, a.__array_interface__["data"][0]
 
 
 @dataclass
@@ -174,25 +207,60 @@ class Batch:
             self.opts = LaunchOpts()
 
     def __setattr__(self, name, value):
-        object.__setattr__(self, name, value)
-        if not name.startswith("_"):
-            object.__setattr__(self, "_c", None)
+        d = self.__dict__
+        d[name] = value
+        if "_dirty" in d:
+            d["_dirty"].add(name)
 
     def c(self) -> _Batch:
-        """The absb_batch record (cached until a field is reassigned; the tensors must stay alive)."""
-        if getattr(self, "_c", None) is None:
-            self._sl, sl_p = _i32_host(self.seq_lens_host)
-            self._bg, bg_p = _i32_host(self.budget_host)
-            pts = self.pt_stride
-            if pts is None:
-                pts = int(self.page_table.shape[1]) if self.page_table is not None else 0
-            self._cl, cl_p = _i32_host(self.cap_lens_host)
-            self._c = _Batch(len(self._sl), int(pts), sl_p, _ptr(self.seq_lens), _ptr(self.page_table),
-                             _ptr(self.cent_off), bg_p, _ptr(self.budget), cl_p, _ptr(self.qmin), _Opts())
-        o = self.opts                   # the options object may have been changed in place: copied every time
-        self._c.opts = _Opts(int(o.step_form), int(o.split_tokens), int(o.score_chunk), int(o.unit_tokens),
-                             int(o.counters_zero))
-        return self._c
+        """The absb_batch record.  Kept between calls: a reassigned field (a decode loop's lengths) is carried
+        over into a copy of the record, so a call in flight on another thread keeps the one it was given
+        (with the host arrays it points into); the tensors must stay alive."""
+        d = self.__dict__
+        rec = d.get("_c")
+        if rec is None:
+            d["_dirty"] = set()
+            rec = _Batch()
+            rec._arrays, rec._opts = {}, None
+            self._fill(rec, _BATCH_FIELDS)
+            d["_c"] = rec
+        elif d["_dirty"]:
+            names, d["_dirty"] = d["_dirty"], set()
+            old, rec = rec, _Batch.from_buffer_copy(rec)
+            rec._arrays, rec._opts = dict(old._arrays), old._opts
+            try:
+                self._fill(rec, names)
+            except Exception:
+                d["_dirty"] |= names
+                raise
+            d["_c"] = rec
+        o = self.opts                   # the options object may have been changed in place: looked at every time
+        opts = (o.step_form, o.split_tokens, o.score_chunk, o.unit_tokens, o.counters_zero)
+        if opts != rec._opts:
+            rec.opts = _Opts(*(int(x) for x in opts))
+            rec._opts = opts
+        return rec
+
+    def _fill(self, rec, names) -> None:
+        for name in names:
+            value = getattr(self, name)
+            if name in _BATCH_HOST_ARRAYS:
+                rec._arrays[name], address = _i32_host(value)
+                setattr(rec, name, address)
+                if name == "seq_lens_host":
+                    rec.batch = len(rec._arrays[name])
+            elif name in _BATCH_TENSORS:
+                setattr(rec, name, _ptr(value))
+            if name in ("page_table", "pt_stride"):
+                pts = self.pt_stride
+                if pts is None:
+                    pts = self.page_table.shape[1] if self.page_table is not None else 0
+                rec.pt_stride = int(pts)
+
+
+_BATCH_HOST_ARRAYS = frozenset(("seq_lens_host", "budget_host", "cap_lens_host"))
+_BATCH_TENSORS = frozenset(("seq_lens", "page_table", "cent_off", "budget", "qmin"))
+_BATCH_FIELDS = (*_BATCH_HOST_ARRAYS, *_BATCH_TENSORS, "pt_stride")
 
 
 @dataclass
@@ -208,7 +276,7 @@ def absb_plan(layer: Layer, batch: Batch) -> PlanResult:
     nseg = cb.batch * layer.num_kv_heads
     off = np.zeros(max(nseg, 0) + 1, dtype=np.int32)
     total, stride, ws = C.c_int64(0), C.c_int32(0), C.c_size_t(0)
-    _check(load().absb_plan(C.byref(cl), C.byref(cb), off.ctypes.data_as(C.POINTER(C.c_int32)),
+    _check(load().absb_plan(C.byref(cl), C.byref(cb), off.ctypes.data,
                             C.byref(total), C.byref(stride), C.byref(ws)), "absb_plan")
     return PlanResult(off, int(total.value), int(stride.value), int(ws.value))
 
@@ -216,7 +284,7 @@ def absb_plan(layer: Layer, batch: Batch) -> PlanResult:
 def absb_build_centroids(layer: Layer, batch: Batch, k_cache, codes, qscale, qmin, workspace, stream=None) -> None:
     cl, cb = layer.c(), batch.c()
     _check(load().absb_build_centroids(C.byref(cl), C.byref(cb), _ptr(k_cache), _ptr(codes), _ptr(qscale),
-                                       _ptr(qmin), _ptr(workspace), C.c_size_t(_nbytes(workspace)),
+                                       _ptr(qmin), _ptr(workspace), _nbytes(workspace),
                                        _stream(stream)), "absb_build_centroids")
 
 
@@ -230,7 +298,7 @@ def absb_topk(layer: Layer, batch: Batch, scores, sel_idx, sel_cnt, sel_stride: 
               stream=None) -> None:
     cl, cb = layer.c(), batch.c()
     _check(load().absb_topk(C.byref(cl), C.byref(cb), _ptr(scores), _ptr(sel_idx), _ptr(sel_cnt),
-                            C.c_int32(sel_stride), _ptr(workspace), C.c_size_t(_nbytes(workspace)),
+                            sel_stride, _ptr(workspace), _nbytes(workspace),
                             _stream(stream)), "absb_topk")
 
 
@@ -238,8 +306,8 @@ def absb_sparse_decode(layer: Layer, batch: Batch, q, k_cache, v_cache, sel_idx,
                        out, lse, workspace, stream=None) -> None:
     cl, cb = layer.c(), batch.c()
     _check(load().absb_sparse_decode(C.byref(cl), C.byref(cb), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                     _ptr(sel_idx), _ptr(sel_cnt), C.c_int32(sel_stride), _ptr(out), _ptr(lse),
-                                     _ptr(workspace), C.c_size_t(_nbytes(workspace)), _stream(stream)),
+                                     _ptr(sel_idx), _ptr(sel_cnt), sel_stride, _ptr(out), _ptr(lse),
+                                     _ptr(workspace), _nbytes(workspace), _stream(stream)),
            "absb_sparse_decode")
 
 
@@ -248,7 +316,7 @@ def absb_decode_fused(layer: Layer, batch: Batch, q, codes, qscale, k_cache, v_c
     cl, cb = layer.c(), batch.c()
     _check(load().absb_decode_fused(C.byref(cl), C.byref(cb), _ptr(q), _ptr(codes), _ptr(qscale), _ptr(k_cache),
                                     _ptr(v_cache), _ptr(out), _ptr(lse), _ptr(sel_idx_out), _ptr(sel_cnt_out),
-                                    _ptr(workspace), C.c_size_t(_nbytes(workspace)), _stream(stream)),
+                                    _ptr(workspace), _nbytes(workspace), _stream(stream)),
            "absb_decode_fused")
 
 
@@ -279,7 +347,7 @@ def absb_status_offset(layer: Layer, batch: Batch) -> int:
 
 def absb_workspace_init(layer: Layer, batch: Batch, workspace, stream=None) -> None:
     cl, cb = layer.c(), batch.c()
-    _check(load().absb_workspace_init(C.byref(cl), C.byref(cb), _ptr(workspace), C.c_size_t(_nbytes(workspace)),
+    _check(load().absb_workspace_init(C.byref(cl), C.byref(cb), _ptr(workspace), _nbytes(workspace),
                                       _stream(stream)), "absb_workspace_init")
 
 
@@ -317,11 +385,11 @@ def absb_assign_block_sizes(recall: np.ndarray, candidates: Sequence[int], tau: 
 
 
 def absb_stream_read(src, sink, stream=None) -> None:
-    _check(load().absb_stream_read(_ptr(src), C.c_size_t(_nbytes(src)), _ptr(sink), _stream(stream)),
+    _check(load().absb_stream_read(_ptr(src), _nbytes(src), _ptr(sink), _stream(stream)),
            "absb_stream_read")
 
 
 def _nbytes(t) -> int:
     if t is None:
         return 0
-    return int(t.numel() * t.element_size())
+    return t.numel() * t.element_size()
