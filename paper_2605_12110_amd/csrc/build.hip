@@ -270,12 +270,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void build_codes_kernel(BuildParams 
   }
 }
 
-// Decode-time maintenance.  A 16-lane row-group per segment (each lane 8 channels): folds the key
-// of the newest token (position L - 1) into the pooled state of the segment's last block and
-// re-emits that block's 4-bit row under the store's frozen ranges; with APPEND == false it only
-// recomputes the state from the cache (the tokens of the last block, in order).  When the new token
-// completes its block the row is final: the number of its values that the frozen range does not
-// hold is then added to the segment's counter (the signal for a re-ranging policy).
+// Decode-time maintenance.  A 16-lane row-group per segment, each lane 8 channels.
 struct AppendParams {
   const uint16_t* k;
   const int32_t* page_table;
@@ -290,60 +285,108 @@ struct AppendParams {
   Geometry g;
 };
 
-template <int DT, int REP, bool APPEND>
-__global__ __launch_bounds__(BUILD_THREADS) void append_kernel(AppendParams p) {
+// One key folded into the pooled state of a block (first: it is the block's first key and starts the state).
+template <int DT, int REP>
+__device__ __forceinline__ void fold_key(float (&st)[REP + 1][8], const uint4& row, bool first) {
+  const uint32_t w[4] = {row.x, row.y, row.z, row.w};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float lo = Elem<DT>::lo(w[c]), hi = Elem<DT>::hi(w[c]);
+    if (REP) {
+      st[0][2 * c] = first ? lo : fmaxf(st[0][2 * c], lo);
+      st[0][2 * c + 1] = first ? hi : fmaxf(st[0][2 * c + 1], hi);
+      st[REP][2 * c] = first ? lo : fminf(st[REP][2 * c], lo);
+      st[REP][2 * c + 1] = first ? hi : fminf(st[REP][2 * c + 1], hi);
+    } else {
+      st[0][2 * c] = first ? lo : st[0][2 * c] + lo;
+      st[0][2 * c + 1] = first ? hi : st[0][2 * c + 1] + hi;
+    }
+  }
+}
+
+template <int REP>
+__device__ __forceinline__ void store_tail(float* tail, const float (&st)[REP + 1][8]) {
+#pragma unroll
+  for (int v = 0; v <= REP; ++v) {
+    *reinterpret_cast<float4*>(tail + v * ABSB_HEAD_DIM) = make_float4(st[v][0], st[v][1], st[v][2], st[v][3]);
+    *reinterpret_cast<float4*>(tail + v * ABSB_HEAD_DIM + 4) = make_float4(st[v][4], st[v][5], st[v][6], st[v][7]);
+  }
+}
+
+// Recomputes the pooled state of every segment's last block from the cache (its tokens, in order).  The
+// keys enter the state one after the other, so the kernel is a chain of memory round trips unless they are
+// requested together: one lane per eight tokens looks up their page (a block of 128 tokens has 16 such
+// runs), then 32 rows are in flight at a time.  One key per round trip cost 33 us for blocks of 64 tokens.
+constexpr int TAIL_ROWS = 32;
+
+template <int DT, int REP>
+__global__ __launch_bounds__(BUILD_THREADS) void tail_kernel(AppendParams p) {
   constexpr int W = ABSB_HEAD_DIM * (REP + 1);
   const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
   const int s = blockIdx.x * BUILD_GROUPS + grp;
   if (s >= p.nseg) return;
   const int b = s / p.g.Hkv, h = s % p.g.Hkv;
   const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
-  const int L = p.seq_lens[b];
-  const int t_new = L - 1, j = t_new >> lb, t0 = j << lb;
+  const int t_new = p.seq_lens[b] - 1, t0 = (t_new >> lb) << lb;
   const int32_t* pt = p.page_table + (size_t)b * p.g.pt_stride;
-  const size_t lane_off = (size_t)h * p.g.s_head + (size_t)li * 8;
-  float* tail = p.tail + (size_t)s * W + li * 8;
+  const uint16_t* k = p.k + (size_t)h * p.g.s_head + (size_t)li * 8;
+  // the page of tokens [t0 + 8*li, +8): they lie in one page (t0 is a multiple of eight, P >= 8)
+  const int my_page = pt[min(t0 + 8 * li, t_new) >> lP];
 
   float st[REP + 1][8];
-  const int t_first = APPEND ? t_new : t0;  // APPEND: one key on top of the stored state
-  if (APPEND && t_new != t0) {
+  for (int base = t0; base <= t_new; base += TAIL_ROWS) {
+    uint4 row[TAIL_ROWS];
 #pragma unroll
-    for (int v = 0; v <= REP; ++v) {
-      const float4 a = *reinterpret_cast<const float4*>(tail + v * ABSB_HEAD_DIM);
-      const float4 z = *reinterpret_cast<const float4*>(tail + v * ABSB_HEAD_DIM + 4);
-      st[v][0] = a.x, st[v][1] = a.y, st[v][2] = a.z, st[v][3] = a.w;
-      st[v][4] = z.x, st[v][5] = z.y, st[v][6] = z.z, st[v][7] = z.w;
+    for (int r = 0; r < TAIL_ROWS; ++r) {  // rows past the newest token repeat it (a legal address), skipped below
+      const int t = min(base + r, t_new);
+      const int page = __shfl(my_page, (t - t0) >> 3, 16);
+      row[r] = *reinterpret_cast<const uint4*>(k + (size_t)page * p.g.s_page + (size_t)(t & ((1 << lP) - 1)) * p.g.s_tok);
     }
-  }
-  for (int t = t_first; t <= t_new; ++t) {
-    const int page = pt[t >> lP];
-    const uint4 row = *reinterpret_cast<const uint4*>(p.k + (size_t)page * p.g.s_page + lane_off +
-                                                      (size_t)(t & ((1 << lP) - 1)) * p.g.s_tok);
-    const uint32_t w[4] = {row.x, row.y, row.z, row.w};
-    const bool first = t == t0;  // the block's first key starts the state
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float lo = Elem<DT>::lo(w[c]), hi = Elem<DT>::hi(w[c]);
-      if (REP) {
-        st[0][2 * c] = first ? lo : fmaxf(st[0][2 * c], lo);
-        st[0][2 * c + 1] = first ? hi : fmaxf(st[0][2 * c + 1], hi);
-        st[REP][2 * c] = first ? lo : fminf(st[REP][2 * c], lo);
-        st[REP][2 * c + 1] = first ? hi : fminf(st[REP][2 * c + 1], hi);
-      } else {
-        st[0][2 * c] = first ? lo : st[0][2 * c] + lo;
-        st[0][2 * c + 1] = first ? hi : st[0][2 * c + 1] + hi;
-      }
-    }
+    for (int r = 0; r < TAIL_ROWS; ++r)
+      if (base + r <= t_new) fold_key<DT, REP>(st, row[r], base + r == t0);
   }
+  store_tail<REP>(p.tail + (size_t)s * W + li * 8, st);
+}
+
+// Folds the key of the newest token (position L - 1) into the pooled state of the segment's last block and
+// re-emits that block's 4-bit row under the store's frozen ranges.  When the new token completes its block
+// the row is final: the number of its values that the frozen range does not hold is then added to the
+// segment's counter (the signal for a re-ranging policy).
+//
+// Bound by latency: length -> page-table entry -> key is the only chain, so everything else (state, ranges,
+// the row's place) is requested before it.
+template <int DT, int REP>
+__global__ __launch_bounds__(BUILD_THREADS) void append_kernel(AppendParams p) {
+  constexpr int W = ABSB_HEAD_DIM * (REP + 1);
+  const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
+  const int s = blockIdx.x * BUILD_GROUPS + grp;
+  if (s >= p.nseg) return;
+  const int b = s / p.g.Hkv, h = s % p.g.Hkv;
+  const int t_new = p.seq_lens[b] - 1;
+  float* tail = p.tail + (size_t)s * W + li * 8;
+  float st[REP + 1][8], scale[REP + 1][8], mn[REP + 1][8];
 #pragma unroll
   for (int v = 0; v <= REP; ++v) {
-    *reinterpret_cast<float4*>(tail + v * ABSB_HEAD_DIM) = make_float4(st[v][0], st[v][1], st[v][2], st[v][3]);
-    *reinterpret_cast<float4*>(tail + v * ABSB_HEAD_DIM + 4) = make_float4(st[v][4], st[v][5], st[v][6], st[v][7]);
+    const size_t at = (size_t)s * W + v * ABSB_HEAD_DIM + li * 8;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      *reinterpret_cast<float4*>(&st[v][4 * q]) = *reinterpret_cast<const float4*>(tail + v * ABSB_HEAD_DIM + 4 * q);
+      *reinterpret_cast<float4*>(&scale[v][4 * q]) = *reinterpret_cast<const float4*>(p.qscale + at + 4 * q);
+      *reinterpret_cast<float4*>(&mn[v][4 * q]) = *reinterpret_cast<const float4*>(p.qmin + at + 4 * q);
+    }
   }
-  if (!APPEND) return;
+  const int off = p.cent_off[s];
+  const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
+  const int j = t_new >> lb, t0 = j << lb;
+  const int page = p.page_table[(size_t)b * p.g.pt_stride + (t_new >> lP)];
+  const uint4 row = *reinterpret_cast<const uint4*>(p.k + (size_t)page * p.g.s_page + (size_t)h * p.g.s_head +
+                                                    (size_t)(t_new & ((1 << lP) - 1)) * p.g.s_tok + (size_t)li * 8);
+  fold_key<DT, REP>(st, row, t_new == t0);
+  store_tail<REP>(tail, st);
 
   const float fn = (float)(t_new - t0 + 1);
-  const size_t row_at = ((size_t)p.cent_off[s] + j) * (W / 2);
+  const size_t row_at = ((size_t)off + j) * (W / 2);
   int outside = 0;
 #pragma unroll
   for (int v = 0; v <= REP; ++v) {
@@ -352,16 +395,16 @@ __global__ __launch_bounds__(BUILD_THREADS) void append_kernel(AppendParams p) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       const float value = REP ? st[v][c] : st[v][c] / fn;
-      const float sc = p.qscale[(size_t)s * W + col + c];
+      const float sc = scale[v][c];
       float r = 0.0f;
       if (sc > 0.0f) {
         const float inv = 1.0f / sc;
-        const float x = value - p.qmin[(size_t)s * W + col + c];
+        const float x = value - mn[v][c];
         r = __builtin_rintf(x * inv);
         outside += !(r >= 0.0f && r <= 15.0f);
         r = fminf(fmaxf(r, 0.0f), 15.0f);  // a NaN ends up at 0
       } else {
-        outside += value != p.qmin[(size_t)s * W + col + c];  // a channel that was constant at build time
+        outside += value != mn[v][c];  // a channel that was constant at build time
       }
       packed |= (uint32_t)r << (4 * c);
     }
@@ -382,9 +425,9 @@ template <int DT, int REP>
 static void launch_append_kernel(bool append, const AppendParams& p, hipStream_t stream) {
   const dim3 grid((unsigned)((p.nseg + BUILD_GROUPS - 1) / BUILD_GROUPS)), block(BUILD_THREADS);
   if (append)
-    hipLaunchKernelGGL((append_kernel<DT, REP, true>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((append_kernel<DT, REP>), grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL((append_kernel<DT, REP, false>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((tail_kernel<DT, REP>), grid, block, 0, stream, p);
 }
 
 int launch_append(const Geometry& g, const Plan& pl, int dtype, bool append, const void* k_cache,

@@ -1082,6 +1082,19 @@ def test_appending_tokens_keeps_the_store_and_the_step_in_parity(repr_, dtype):
     assert clamped.sum() > 0                           # the counters were exercised
 
 
+@pytest.mark.parametrize("repr_,dtype,P", [(O.MEAN, synth.F16, 8), (O.MEAN, synth.BF16, 64), (O.MINMAX, synth.F16, 16)])
+def test_tail_state_of_last_blocks_of_every_length(repr_, dtype, P):
+    """absb_tail_init requests a block's keys in runs of 32 rows whose pages are looked up eight tokens at a
+    time: last blocks of 1 to 128 keys around those edges, pages smaller and larger than blocks."""
+    lens = (1, 7, 8, 9, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 250)
+    wl = synth.tiny_workload(seed=72, dtype=dtype, Hq=5, Hkv=5, P=P, seq_lens=lens, block_size=(8, 16, 32, 64, 128), budget=64)
+    dw = _dev(wl, block_repr=repr_)
+    dw.build()
+    dw.tail.fill_(float("nan"))
+    dw.tail_init(); _sync()
+    assert np.array_equal(dw.tail.cpu().numpy(), O.tail_state(wl, repr_))
+
+
 def test_lists_widen_with_the_context_when_the_budget_exceeds_it():
     """A budget beyond the context selects every block, so K_s and the list width that absb_plan
     reports grow with the lengths: the fused step writes [segments][that width] for the lengths
