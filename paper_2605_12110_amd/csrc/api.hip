@@ -85,7 +85,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.units_max = 1;
   p.nseg = Bt * Hsel;
   p.nstore = Bt * Hkv;
-  p.build_chunk_tokens = 1024;
   int64_t max_len = 0;
   for (int b = 0; b < Bt; ++b) {
     const int64_t L = batch->seq_lens_host[b];
@@ -105,8 +104,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       }
       if (sel_stride_in > 0 && sel_stride_in < K) K = sel_stride_in;
       p.total += ceil_div(cap, B);
-      const int64_t cb = std::max<int64_t>(16, p.build_chunk_tokens / B);  // as build_chunk_blocks() on the device
-      if (ceil_div(N, cb) > p.build_max_chunks) p.build_max_chunks = (int32_t)ceil_div(N, cb);
       if (N > p.max_blocks) p.max_blocks = (int32_t)N;
       const int64_t tok = K * B;
       {
@@ -118,6 +115,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       p.sum_tokens += tok * g.Rk;  // every selection segment of the KV head reads its own tokens
     }
   }
+  p.build_max_chunks = (int32_t)ceil_div(max_len, BUILD_CHUNK);
   if (!batch->budget_host) p.sel_stride = p.max_blocks;
   // entry points that select (they are the ones that need the budgets) refuse on the host what the
   // selection cannot hold, before anything is enqueued

@@ -12,12 +12,9 @@
 // -ffp-contract=off.
 //
 // Three launches:
-//   1. pool: a work-group owns `chunk_tokens` consecutive tokens of a segment (a power-of-two number
-//      of whole blocks, at least one per 16-lane row-group), so work per group is the same for every
-//      block size.  A row-group (each lane 8 channels = one 128-bit load per key) streams its 64+
-//      consecutive tokens eight rows at a time, the next eight in flight while these are pooled,
-//      closes a block whenever the running token index reaches a block boundary, writes the binary32
-//      row to the workspace and folds it into per-work-group minima/maxima per value;
+//   1. pool: a work-group owns BUILD_CHUNK consecutive tokens of a segment, a wave a quarter of them; a block
+//      is closed whenever the running token index reaches its boundary: its binary32 row goes to the
+//      workspace and into the work-group's minima / maxima per value;
 //   2. params: reduces the partial extrema per segment and writes qscale, qmin (and 15/range);
 //   3. codes: quantizes the rows, eight values per lane packed into one 32-bit store.
 #include "common.h"
@@ -35,182 +32,180 @@ struct BuildParams {
   float* qscale;   // [nseg][W]
   float* qmin;     // [nseg][W]
   uint8_t* codes;  // [total][W/2]
-  int32_t chunk_tokens, max_chunks;
+  int32_t max_chunks;
   Geometry g;
 };
 
 constexpr int BUILD_THREADS = 256;
 constexpr int BUILD_GROUPS = BUILD_THREADS / 16;
-constexpr int BUILD_ROWS = 8;  // rows per step: B >= 8 and P >= 8, so a step never straddles a block or a page
+constexpr int BUILD_WAVES = BUILD_THREADS / 64;
+constexpr int BUILD_RUN = BUILD_CHUNK / BUILD_WAVES;  // tokens a wave pools: whole blocks of every size
+constexpr int BUILD_BATCH = 32;                       // rows it requests at once
+constexpr int CODES_BLOCKS = 64;                      // blocks per work-group of the codes kernel
+static_assert(BUILD_RUN % 128 == 0, "a wave's tokens are whole blocks");
 
-// blocks per work-group for a head with blocks of 2^lb tokens
-__device__ __forceinline__ int build_chunk_blocks(int chunk_tokens, int lb) {
-  return max(BUILD_GROUPS, chunk_tokens >> lb);
-}
+// Read-only arrays at wave-uniform addresses: scalar loads, which do not queue behind the rows in flight.
+typedef __attribute__((address_space(4))) const int32_t scalar_i32;
+__device__ __forceinline__ scalar_i32* as_scalar(const int32_t* p) { return (scalar_i32*)(uintptr_t)p; }
 
+// Bound by the stream of keys, 256 bytes a token and KV head.  A wave reads one row per load instruction, a lane
+// two channels: a block's sum stays in one lane in token order, and the row's address is a scalar.  32 rows
+// are in flight while 32 are pooled.  The keys are read once and nothing else wants them, so they pass the
+// caches by (nontemporal loads).  Against 16-lane row-groups of 128-bit loads, whose page lookups sat behind
+// the rows in flight (loads return in order), on a 128K context of 8 heads (268 MB of keys): 72 -> 55 us, of
+// which the rows written out are 10 us (44 us = 6.0 TB/s without them).
 template <int DT, int REP>
-__global__ __launch_bounds__(BUILD_THREADS) void build_pool_kernel(BuildParams p) {
+__global__ __launch_bounds__(BUILD_THREADS, 4) void build_pool_kernel(BuildParams p) {
   constexpr int W = ABSB_HEAD_DIM * (REP + 1);
+  __shared__ float2 s_ext[BUILD_WAVES][2][W / 2];
   const int s = blockIdx.y, chunk = blockIdx.x;
-  const int off = p.cent_off[s];
   const int b = s / p.g.Hkv, h = s % p.g.Hkv;
+  const int L = as_scalar(p.seq_lens)[b];
+  const int t0 = chunk * BUILD_CHUNK;
+  if (t0 >= L) return;
+  const int off = as_scalar(p.cent_off)[s];
   const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
-  const int L = p.seq_lens[b];
-  const int N = blocks_in_use(p.g.tight, p.cent_off[s + 1] - off, p.seq_lens, b, lb);
-  const int cb = build_chunk_blocks(p.chunk_tokens, lb);
-  const int j0 = chunk * cb;
-  if (j0 >= N) return;
-  const int jend = min(N, j0 + cb);
   const int B = 1 << lb;
-  const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
-  const int32_t* pt = p.page_table + (size_t)b * p.g.pt_stride;
-  const size_t lane_off = (size_t)h * p.g.s_head + (size_t)li * 8;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tA = t0 + wave * BUILD_RUN, tB = min(tA + BUILD_RUN, L);
 
-  // running extrema over this row-group's blocks, per vector of the row (v = 0: mean or maxima, 1: minima)
-  float mn[REP + 1][8], mx[REP + 1][8];
+  // extrema over this wave's blocks, per vector of the row (v = 0: mean or maxima, 1: minima)
+  float mn[REP + 1][2], mx[REP + 1][2];
 #pragma unroll
-  for (int v = 0; v <= REP; ++v)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      mn[v][c] = __builtin_inff();
-      mx[v][c] = -__builtin_inff();
-    }
-
-  // this row-group's blocks [ja, jb) = consecutive tokens [tA, tB)
-  const int per = cb / BUILD_GROUPS;
-  const int ja = min(jend, j0 + grp * per), jb = min(jend, ja + per);
-  const int tA = ja << lb, tB = min(jb << lb, L);
-
-  auto row_base = [&](int t) -> const uint16_t* {  // first row of the 8-row step at token t (t < L)
-    const int page = pt[t >> lP];
-    return p.k + (size_t)page * p.g.s_page + lane_off + (size_t)(t & ((1 << lP) - 1)) * p.g.s_tok;
-  };
-
+  for (int v = 0; v <= REP; ++v) {
+    mn[v][0] = mn[v][1] = __builtin_inff();
+    mx[v][0] = mx[v][1] = -__builtin_inff();
+  }
   if (tA < tB) {
-    uint4 cur[BUILD_ROWS], nxt[BUILD_ROWS];
-    const uint16_t* base = row_base(tA);
+    scalar_i32* pt = as_scalar(p.page_table + (size_t)b * p.g.pt_stride);
+    const char* kh = reinterpret_cast<const char*>(p.k + (size_t)h * p.g.s_head) + lane * 4;
+    const int tok_mask = (1 << lP) - 1;
+    const size_t pitch = (size_t)p.g.s_tok * 2;
+    // rows [t, t + BUILD_BATCH); rows past the end repeat earlier ones (legal addresses), skipped below
+    auto load = [&](int t, uint32_t (&r)[BUILD_BATCH]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < BUILD_ROWS; ++r)  // rows past the end repeat the last one (a legal address), masked below
-      cur[r] = *reinterpret_cast<const uint4*>(base + (size_t)min(r, tB - 1 - tA) * p.g.s_tok);
+      for (int q = 0; q < BUILD_BATCH / 8; ++q) {
+        const int tq = min(t + 8 * q, (tB - 1) & ~7);  // eight rows from a multiple of eight lie in one page
+        const char* base = kh + ((size_t)pt[tq >> lP] * p.g.s_page + (size_t)(tq & tok_mask) * p.g.s_tok) * 2;
 #pragma unroll
-    for (int r = 0; r < BUILD_ROWS; ++r) nxt[r] = cur[r];
-    const uint16_t* base_next = row_base(min(tA + BUILD_ROWS, tB - 1));
-
+        for (int i = 0; i < 8; ++i)
+          r[8 * q + i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(base + (size_t)min(i, tB - 1 - tq) * pitch));
+      }
+    };
     // the open block: its running sum (mean pooling) or its maxima / minima so far
-    float acc[REP + 1][8];
-    auto reset = [&]() {
+    float acc[REP + 1][2];
+    auto reset = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) {
+      for (int c = 0; c < 2; ++c) {
         acc[0][c] = REP ? -__builtin_inff() : 0.0f;
         if (REP) acc[REP][c] = __builtin_inff();
       }
     };
+    auto fold = [&](uint32_t w) __attribute__((always_inline)) {
+      const float lo = Elem<DT>::lo(w), hi = Elem<DT>::hi(w);
+      if (REP) {
+        acc[0][0] = fmaxf(acc[0][0], lo);
+        acc[0][1] = fmaxf(acc[0][1], hi);
+        acc[REP][0] = fminf(acc[REP][0], lo);
+        acc[REP][1] = fminf(acc[REP][1], hi);
+      } else {
+        acc[0][0] = acc[0][0] + lo;
+        acc[0][1] = acc[0][1] + hi;
+      }
+    };
+    auto pool = [&](int t, const uint32_t (&r)[BUILD_BATCH]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < BUILD_BATCH / 8; ++q) {
+        const int tq = t + 8 * q;
+        if (tq >= tB) continue;
+        if (tq + 8 <= tB) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) fold(r[8 * q + i]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (tq + i < tB) fold(r[8 * q + i]);
+        }
+        if (((tq + 8) & (B - 1)) == 0 || tq + 8 >= tB) {  // the block that holds token tq is complete
+          const int j = tq >> lb;
+          const float fn = (float)min(B, L - (j << lb));
+#pragma unroll
+          for (int v = 0; v <= REP; ++v) {
+            const float x = REP ? acc[v][0] : acc[v][0] / fn, y = REP ? acc[v][1] : acc[v][1] / fn;
+            mn[v][0] = fminf(mn[v][0], x);
+            mn[v][1] = fminf(mn[v][1], y);
+            mx[v][0] = fmaxf(mx[v][0], x);
+            mx[v][1] = fmaxf(mx[v][1], y);
+            *reinterpret_cast<float2*>(p.cent + ((size_t)off + j) * W + v * ABSB_HEAD_DIM + lane * 2) = make_float2(x, y);
+          }
+          reset();
+        }
+      }
+    };
     reset();
-    for (int i = tA; i < tB; i += BUILD_ROWS) {
-      const int in = i + BUILD_ROWS;
-      if (in < tB) {
-#pragma unroll
-        for (int r = 0; r < BUILD_ROWS; ++r)
-          nxt[r] = *reinterpret_cast<const uint4*>(base_next + (size_t)min(r, tB - 1 - in) * p.g.s_tok);
-        base_next = row_base(min(in + BUILD_ROWS, tB - 1));
-      }
-#pragma unroll
-      for (int r = 0; r < BUILD_ROWS; ++r) {
-        if (i + r < tB) {
-          const uint32_t w[4] = {cur[r].x, cur[r].y, cur[r].z, cur[r].w};
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const float lo = Elem<DT>::lo(w[c]), hi = Elem<DT>::hi(w[c]);
-            if (REP) {
-              acc[0][2 * c] = fmaxf(acc[0][2 * c], lo);
-              acc[0][2 * c + 1] = fmaxf(acc[0][2 * c + 1], hi);
-              acc[REP][2 * c] = fminf(acc[REP][2 * c], lo);
-              acc[REP][2 * c + 1] = fminf(acc[REP][2 * c + 1], hi);
-            } else {
-              acc[0][2 * c] = acc[0][2 * c] + lo;
-              acc[0][2 * c + 1] = acc[0][2 * c + 1] + hi;
-            }
-          }
-        }
-      }
-      if ((in & (B - 1)) == 0 || in >= tB) {  // the block that holds token i is complete
-        const int j = i >> lb;
-        const float fn = (float)min(B, L - (j << lb));
-#pragma unroll
-        for (int v = 0; v <= REP; ++v) {
-          float val[8];
-#pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            val[c] = REP ? acc[v][c] : acc[v][c] / fn;
-            mn[v][c] = fminf(mn[v][c], val[c]);
-            mx[v][c] = fmaxf(mx[v][c], val[c]);
-          }
-          float4* dst = reinterpret_cast<float4*>(p.cent + ((size_t)off + j) * W + v * ABSB_HEAD_DIM + li * 8);
-          dst[0] = make_float4(val[0], val[1], val[2], val[3]);
-          dst[1] = make_float4(val[4], val[5], val[6], val[7]);
-        }
-        reset();
-      }
-#pragma unroll
-      for (int r = 0; r < BUILD_ROWS; ++r) cur[r] = nxt[r];
+    uint32_t even[BUILD_BATCH], odd[BUILD_BATCH];
+    load(tA, even);
+    for (int t = tA;;) {
+      const int t1 = t + BUILD_BATCH, t2 = t1 + BUILD_BATCH;
+      if (t1 < tB) load(t1, odd);
+      pool(t, even);
+      if (t1 >= tB) break;
+      if (t2 < tB) load(t2, even);
+      pool(t1, odd);
+      if (t2 >= tB) break;
+      t = t2;
     }
   }
 
-  // fold the 16 row-groups: value index = v*128 + li*8 + c
-  __shared__ float s_mn[BUILD_GROUPS][W], s_mx[BUILD_GROUPS][W];
+  // ---- fold the waves: thread -> (kind, two values)
 #pragma unroll
-  for (int v = 0; v <= REP; ++v)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      s_mn[grp][v * ABSB_HEAD_DIM + li * 8 + c] = mn[v][c];
-      s_mx[grp][v * ABSB_HEAD_DIM + li * 8 + c] = mx[v][c];
-    }
+  for (int v = 0; v <= REP; ++v) {
+    s_ext[wave][0][v * 64 + lane] = make_float2(mn[v][0], mn[v][1]);
+    s_ext[wave][1][v * 64 + lane] = make_float2(mx[v][0], mx[v][1]);
+  }
   __syncthreads();
   if (tid < W) {
-    float a = s_mn[0][tid], z = s_mx[0][tid];
+    const int kind = tid / (W / 2), c = tid % (W / 2);
+    float2 x = s_ext[0][kind][c];
 #pragma unroll
-    for (int g2 = 1; g2 < BUILD_GROUPS; ++g2) {
-      a = fminf(a, s_mn[g2][tid]);
-      z = fmaxf(z, s_mx[g2][tid]);
+    for (int w = 1; w < BUILD_WAVES; ++w) {
+      const float2 y = s_ext[w][kind][c];
+      x.x = kind ? fmaxf(x.x, y.x) : fminf(x.x, y.x);
+      x.y = kind ? fmaxf(x.y, y.y) : fminf(x.y, y.y);
     }
     float* dst = p.minmax + ((size_t)s * p.max_chunks + chunk) * 2 * W;
-    dst[tid] = a;
-    dst[W + tid] = z;
+    *reinterpret_cast<float2*>(dst + kind * W + 2 * c) = x;
   }
 }
 
-// One work-group per (segment, vector of the row): 128 values x 8 chunk lanes; min/max are exact
-// in any order.
+// grid (segment, 32 values of the row): 32 values x 32 chunk lanes; min/max are exact in any order.
 constexpr int PARAMS_THREADS = 1024;
-constexpr int PARAMS_LANES = PARAMS_THREADS / ABSB_HEAD_DIM;
+constexpr int PARAMS_VALUES = 32;
+constexpr int PARAMS_LANES = PARAMS_THREADS / PARAMS_VALUES;
 
 __global__ __launch_bounds__(PARAMS_THREADS) void build_params_kernel(BuildParams p) {
   const int W = ABSB_HEAD_DIM * (p.g.repr + 1);
-  const int s = blockIdx.x, cl = threadIdx.x / ABSB_HEAD_DIM;
-  const int ch = blockIdx.y * ABSB_HEAD_DIM + (threadIdx.x & (ABSB_HEAD_DIM - 1));  // value index in the row
-  const int h = s % p.g.Hkv;
-  const int N = blocks_in_use(p.g.tight, p.cent_off[s + 1] - p.cent_off[s], p.seq_lens, s / p.g.Hkv,
-                              p.g.heads.log2_block[h]);
-  const int cb = build_chunk_blocks(p.chunk_tokens, p.g.heads.log2_block[h]);
-  const int nchunks = (N + cb - 1) / cb;
+  const int s = blockIdx.x, cl = threadIdx.x / PARAMS_VALUES, c = threadIdx.x % PARAMS_VALUES;
+  const int ch = blockIdx.y * PARAMS_VALUES + c;  // value index in the row
+  const int nchunks = (p.seq_lens[s / p.g.Hkv] + BUILD_CHUNK - 1) / BUILD_CHUNK;
   float mn = __builtin_inff(), mx = -__builtin_inff();
-  for (int i0 = cl; i0 < nchunks; i0 += 4 * PARAMS_LANES) {
-    float a[4], z[4];
+  for (int i0 = cl; i0 < nchunks; i0 += 8 * PARAMS_LANES) {
+    float a[8], z[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 8; ++u) {
       const int i = min(i0 + u * PARAMS_LANES, nchunks - 1);  // the tail repeats a chunk: harmless for min/max
       const float* src = p.minmax + ((size_t)s * p.max_chunks + i) * 2 * W;
       a[u] = src[ch];
       z[u] = src[W + ch];
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 8; ++u) {
       mn = fminf(mn, a[u]);
       mx = fmaxf(mx, z[u]);
     }
   }
-  __shared__ float s_mn[PARAMS_LANES][ABSB_HEAD_DIM], s_mx[PARAMS_LANES][ABSB_HEAD_DIM];
-  const int c = threadIdx.x & (ABSB_HEAD_DIM - 1);
+  __shared__ float s_mn[PARAMS_LANES][PARAMS_VALUES], s_mx[PARAMS_LANES][PARAMS_VALUES];
   s_mn[cl][c] = mn;
   s_mx[cl][c] = mx;
   __syncthreads();
@@ -226,23 +221,21 @@ __global__ __launch_bounds__(PARAMS_THREADS) void build_params_kernel(BuildParam
     sc = rng / 15.0f;
     inv = 15.0f / rng;
   }
-  if (N == 0) mn = 0.0f;
   p.qscale[(size_t)s * W + ch] = sc;
   p.qmin[(size_t)s * W + ch] = mn;
   p.qinv[(size_t)s * W + ch] = inv;
 }
 
-// grid (chunk, segment, vector of the row)
+// grid (64 blocks, segment, vector of the row)
 __global__ __launch_bounds__(BUILD_THREADS) void build_codes_kernel(BuildParams p) {
   const int W = ABSB_HEAD_DIM * (p.g.repr + 1);
   const int s = blockIdx.y, v = blockIdx.z;
   const int off = p.cent_off[s];
   const int lb = p.g.heads.log2_block[s % p.g.Hkv];
   const int N = blocks_in_use(p.g.tight, p.cent_off[s + 1] - off, p.seq_lens, s / p.g.Hkv, lb);
-  const int cb = build_chunk_blocks(p.chunk_tokens, lb);
-  const int j0 = blockIdx.x * cb;
+  const int j0 = blockIdx.x * CODES_BLOCKS;
   if (j0 >= N) return;
-  const int jend = min(N, j0 + cb);
+  const int jend = min(N, j0 + CODES_BLOCKS);
   const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
   const int col = v * ABSB_HEAD_DIM + li * 8;  // first of this lane's eight values in the row
   float mn[8], inv[8];
@@ -470,7 +463,6 @@ int launch_build(const Geometry& g, const Plan& pl, int dtype, const void* k_cac
   p.qscale = qscale;
   p.qmin = qmin;
   p.codes = codes;
-  p.chunk_tokens = pl.build_chunk_tokens;
   p.max_chunks = pl.build_max_chunks;
   p.g = g;
   const unsigned R = (unsigned)g.repr + 1;
@@ -485,10 +477,10 @@ int launch_build(const Geometry& g, const Plan& pl, int dtype, const void* k_cac
     hipLaunchKernelGGL((build_pool_kernel<ABSB_BF16, 1>), grid, block, 0, stream, p);
   int rc = check_launch();
   if (rc != ABSB_OK) return rc;
-  hipLaunchKernelGGL(build_params_kernel, dim3((unsigned)pl.nstore, R), dim3(PARAMS_THREADS), 0, stream, p);
+  hipLaunchKernelGGL(build_params_kernel, dim3((unsigned)pl.nstore, R * ABSB_HEAD_DIM / PARAMS_VALUES), dim3(PARAMS_THREADS), 0, stream, p);
   rc = check_launch();
   if (rc != ABSB_OK) return rc;
-  hipLaunchKernelGGL(build_codes_kernel, dim3(grid.x, grid.y, R), block, 0, stream, p);
+  hipLaunchKernelGGL(build_codes_kernel, dim3((unsigned)((pl.max_blocks + CODES_BLOCKS - 1) / CODES_BLOCKS), grid.y, R), block, 0, stream, p);
   return check_launch();
 }
 

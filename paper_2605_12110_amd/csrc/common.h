@@ -14,6 +14,7 @@
 // Split counters sit 256 bytes apart: counters that share a memory line serialise each other's
 // atomic updates (measured: 8 segments x 32 arrivals on one line cost 2.7 us, apart 0.x us).
 #define ABSB_TICKET_STRIDE 64
+#define BUILD_CHUNK 512          // tokens per work-group of the store build's pooling
 #define ABSB_STEP_MAX_UNITS 64   // work-groups that share a segment in the one-launch step
 
 namespace absb {
@@ -57,8 +58,7 @@ struct Plan {
   int32_t units_max;        // max_s units of a segment
   int32_t bitmap_words;     // words of a segment's selection bitmap
   int32_t score_chunk;      // centroids per work-group in score
-  int32_t build_chunk_tokens;  // tokens per work-group in build (a head's chunk: max(16, that / B_h) blocks)
-  int32_t build_max_chunks;    // max_s ceil(N_s / chunk_h)
+  int32_t build_max_chunks; // max_b ceil(L_b / BUILD_CHUNK)
   // workspace carving (byte offsets, 256-aligned)
   size_t ws_part_o, ws_part_ml, ws_tickets;       // decode partials, per-segment split counters
   size_t ws_score_tickets, ws_flags, ws_status;   // more counters of the one-launch step
