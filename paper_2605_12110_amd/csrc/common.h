@@ -52,6 +52,7 @@ struct Plan {
   int64_t sum_tokens;       // sum_s of the same bound
   int32_t split_tokens;     // tokens per split-K work-group
   int32_t max_splits;       // grid.x of the decode kernels
+  int32_t stream_rows;      // attention: K and V rows are read past the caches
   int32_t one_launch;       // absb_decode_fused: the whole step as one launch (else one launch per stage)
   int32_t step_form;        // absb_step_form actually used (never ABSB_STEP_AUTO)
   int32_t unit_tokens;      // one-launch step: selected tokens a unit should get

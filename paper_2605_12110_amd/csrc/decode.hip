@@ -5,7 +5,7 @@
 namespace absb {
 
 template <int DT, int G>
-__global__ __launch_bounds__(DEC_THREADS, 3) void decode_kernel(DecodeParams p) {
+__global__ __launch_bounds__(DEC_THREADS, 4) void decode_kernel(DecodeParams p) {
   __shared__ __align__(16) char s_lds[DEC_LDS_BYTES];
   decode_split<DT, G, false>(p, (int)blockIdx.y, (int)blockIdx.x, s_lds);
 }

@@ -14,20 +14,25 @@
 // counters hold; they must be zero at launch (the selection kernel of the fused step clears them,
 // the stand-alone entry point runs a clearing kernel first).
 //
-// Data path of one wave step (16 rows):
-//   * global -> registers: a row is 256 bytes = 16 lanes x 16 bytes; each 16-lane group loads
-//     four consecutive rows with 128-bit loads, so every wave load instruction covers whole rows;
-//   * registers -> LDS: K rows as they are (row pitch 272 B, conflict-free for the reads below),
-//     V transposed in registers first (4 rows x 8 channels per lane -> 8 channels x 4 rows), so
-//     that the four rows a matrix operand needs at one channel sit in one 8-byte LDS word;
-//   * the next step's global loads are issued here, and fly while this step computes from LDS;
-//   * S = K Q^T and O += P V run on the 16x16x16 matrix instruction: with G <= 8 query rows
-//     per K/V row the tile is mostly padding, but the vector pipeline (q.k dots, lane reductions,
-//     P.V multiply-adds) was measured to cost as much time as the HBM stream itself, and the
-//     matrix pipeline is idle otherwise.  The logits tile comes out in exactly the lane layout
-//     the P operand of the second product needs (head = lane % 16, rows 4*(lane/16)..+3), so the
-//     softmax runs in place with two cross-group maxima per step.
+// Data path of one wave step (16 rows), without LDS:
+//   * K rows are loaded in the layout of the matrix operand itself: lane (token = lane % 16, group = lane / 16)
+//     loads the 16-byte pieces 4c + group, c = 0..3, of its token's row (a contraction may take the channels in any
+//     order that Q follows too);  S = K Q^T is four 16x16x32 products;
+//   * V rows are loaded one row per instruction, a lane two channels, at scalar addresses; byte permutes put four
+//     rows of a channel side by side, which is the operand of the 4x4x4 product of 16 blocks: 4 query heads x
+//     64 channels per instruction, so O of four heads takes 8 registers a lane (16x16 tiles, mostly padding
+//     at G <= 8 query rows, took 32);
+//   * Q's columns are repeated over the tile (head = column % 4, or % 8 for G > 4), so the logits of every head
+//     come out in all lanes, the softmax runs in place, and the weights only have to cross between the four
+//     groups of 16 lanes (register swaps);
+//   * K of the next step is requested once the S product has consumed this step's, V four rows at a time behind the
+//     product that consumed them: with ~100 registers a work-group has 32 KB of rows in flight nearly always,
+//     and five work-groups fit a compute unit.
+// The addresses of a wave's steps come from its lanes: lane j looks up the block and page of eight consecutive
+// tokens (half j % 2 of step j / 2; B >= 8 and P >= 8, so they lie in one block and one page), for 32 steps at once.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace absb {
@@ -51,6 +56,7 @@ struct DecodeParams {
   void* out;       // [Bt][Hq][128]
   float* lse;      // [Bt][Hq] or null
   int32_t sel_stride, split_tokens, max_splits;
+  int32_t stream_rows;  // 1: K and V rows pass the caches by
   float scale_log2;  // sm_scale * log2(e)
   Geometry g;
 };
@@ -79,6 +85,7 @@ inline DecodeParams make_decode_params(const Geometry& g, const Plan& pl, float 
   p.sel_stride = sel_stride;
   p.split_tokens = pl.split_tokens;
   p.max_splits = pl.max_splits;
+  p.stream_rows = pl.stream_rows;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
   p.g = g;
   return p;
@@ -87,15 +94,12 @@ inline DecodeParams make_decode_params(const Geometry& g, const Plan& pl, float 
 constexpr float M_INIT = -1.0e30f;  // finite stand-in for "no token seen yet"
 constexpr int DEC_THREADS = 256;
 constexpr int DEC_WAVES = DEC_THREADS / 64;
-constexpr int ROWS_PER_WAVE_STEP = 16;        // 4 row-groups x 4 consecutive rows
-constexpr int K_PITCH = 272;                  // bytes per staged K row (256 + 16: spreads rows over banks)
-constexpr int K_TILE_BYTES = ROWS_PER_WAVE_STEP * K_PITCH;
-constexpr int V_TILE_BYTES = 8 * 512;         // [channel % 8][channel / 8][16 rows] 16-bit
-constexpr int STAGE_BYTES = K_TILE_BYTES + V_TILE_BYTES;
-constexpr int MRG_UNROLL = 16;                // splits a thread merges per memory round trip
-// LDS of one work-group: the waves' staging areas (reused by the epilogue), per-wave maxima and
-// the two sums per head, two words for work-group broadcasts
-constexpr int DEC_LDS_STATE = DEC_WAVES * STAGE_BYTES;
+constexpr int ROWS_PER_WAVE_STEP = 16;        // two halves of eight consecutive rows
+constexpr int DEC_STEP = DEC_WAVES * ROWS_PER_WAVE_STEP;  // positions per work-group step
+constexpr int MRG_UNROLL = 8;                 // splits a thread merges per memory round trip (half as many for few splits)
+// LDS of one work-group, all of it for the epilogue: the waves' outputs, per-wave maxima and the two sums per
+// head, two words for work-group broadcasts
+constexpr int DEC_LDS_STATE = DEC_WAVES * ABSB_MAX_GROUP * ABSB_HEAD_DIM * 4;
 constexpr int DEC_LDS_BYTES = DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4 + 16;
 // a work-group that waits for its segment's list gives up after this long (100 MHz ticks): the
 // wait cannot outlast the launch whatever the rest of the grid does
@@ -105,30 +109,53 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
-// D(16x16) += A(16x16) B(16x16), operands as four 16-bit values per lane:
-// A[m = lane%16][k = 4*(lane/16)+i], B[k = 4*(lane/16)+i][n = lane%16], D[m = 4*(lane/16)+i][n = lane%16].
+// D(16x16) += A(16x32) B(32x16), operands as eight 16-bit values per lane:
+// A[m = lane%16][k = 8*(lane/16)+i], B[k = 8*(lane/16)+i][n = lane%16], D[m = 4*(lane/16)+i][n = lane%16].
 template <int DT>
-__device__ __forceinline__ float4_t mma16(uint2 a, uint2 b, float4_t c) {
+__device__ __forceinline__ float4_t mma_16x16x32(u32x4 a, u32x4 b, float4_t c) {
   if (DT == ABSB_F16)
-    return __builtin_amdgcn_mfma_f32_16x16x16f16(bitcast<half4_t>(a), bitcast<half4_t>(b), c, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(bitcast<short4_t>(a), bitcast<short4_t>(b), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(bitcast<half8_t>(a), bitcast<half8_t>(b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(bitcast<bf16x8_t>(a), bitcast<bf16x8_t>(b), c, 0, 0, 0);
+}
+// 16 independent D(4x4) += A(4x4) B(4x4), one per block of four lanes, operands as four 16-bit values per lane:
+// A[m = lane%4][k = i], B[k = i][n = lane%4], D[m = i][n = lane%4].
+template <int DT>
+__device__ __forceinline__ float4_t mma_4x4x4(u32x2 a, u32x2 b, float4_t c) {
+  if (DT == ABSB_F16) return __builtin_amdgcn_mfma_f32_4x4x4f16(bitcast<half4_t>(a), bitcast<half4_t>(b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(bitcast<short4_t>(a), bitcast<short4_t>(b), c, 0, 0, 0);
 }
 
-// The same 32-bit word (two adjacent channels) of four consecutive V rows -> two LDS words, one per
-// channel, each holding that channel's four rows.  `dst` addresses the even channel's word.
-__device__ __forceinline__ void stage_v_word(char* dst, uint32_t r0, uint32_t r1, uint32_t r2, uint32_t r3) {
-  const uint32_t e01 = __builtin_amdgcn_perm(r1, r0, 0x05040100u);  // low halves: even channel, rows 0,1
-  const uint32_t e23 = __builtin_amdgcn_perm(r3, r2, 0x05040100u);
-  const uint32_t o01 = __builtin_amdgcn_perm(r1, r0, 0x07060302u);  // high halves: odd channel
-  const uint32_t o23 = __builtin_amdgcn_perm(r3, r2, 0x07060302u);
-  *reinterpret_cast<uint2*>(dst) = make_uint2(e01, e23);
-  *reinterpret_cast<uint2*>(dst + 512) = make_uint2(o01, o23);
+// Exchanges between the four rows of 16 lanes by register swaps (no LDS crossbar round trip).
+// The value of row `t` in every row, t = 0..3.
+struct RowsOf {
+  uint32_t of[4];
+};
+__device__ __forceinline__ RowsOf spread_rows(uint32_t x) {
+  const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);        // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+  const auto e = __builtin_amdgcn_permlane32_swap(h[0], h[0], false, false);  // rows (0, 0, 0, 0) and (2, 2, 2, 2)
+  const auto o = __builtin_amdgcn_permlane32_swap(h[1], h[1], false, false);
+  return RowsOf{{e[0], o[0], e[1], o[1]}};
 }
+template <typename Op>
+__device__ __forceinline__ float across_rows(float x, Op op) {
+  const auto h = __builtin_amdgcn_permlane16_swap(bitcast<uint32_t>(x), bitcast<uint32_t>(x), false, false);
+  const float y = op(bitcast<float>(h[0]), bitcast<float>(h[1]));
+  const auto e = __builtin_amdgcn_permlane32_swap(bitcast<uint32_t>(y), bitcast<uint32_t>(y), false, false);
+  return op(bitcast<float>(e[0]), bitcast<float>(e[1]));
+}
+struct FAdd {
+  __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct FMax {
+  __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
 
 // Where the attention loop takes a segment's block list from.
 enum : int {
@@ -164,149 +191,163 @@ struct PageRef {
   }
 };
 
-// Running state of the online softmax of one wave: per head (= lane % 16) the running maximum, common
-// to the wave's four row groups; partial sums over the lane's rows of the weights as rounded for the
-// P V product (the output's normaliser: the output stays a convex combination of value rows) and of
-// the weights before rounding (the log-sum-exp: rounding to bf16 would bias it by up to 2^-8 when all
-// weights round the same way); O[head = 4*grp + i][channel = 8*li + j], j = 0..7.
+// Query heads are taken in sets of four (the rows of a 4x4x4 product).
+constexpr int head_sets(int G) { return (G + 3) / 4; }
+
+// Running state of the online softmax of one wave.  Lane l works for head l % 4 (l % 8 with two sets): the running
+// maximum, common to the wave's four row groups; partial sums over the group's rows of the weights as rounded
+// for the P V product (the output's normaliser: the output stays a convex combination of value rows) and of the
+// weights before rounding (the log-sum-exp: rounding to bf16 would bias it by up to 2^-8 when all weights
+// round the same way); o[set][j][i] = O[head 4*set + i][channel 2*l + j].
+template <int G>
 struct AttnState {
   float m, l, lx;
-  float4_t oacc[8];
+  float4_t o[head_sets(G)][2];
   __device__ __forceinline__ void reset() {
     m = M_INIT;
     l = 0.0f;
     lx = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) oacc[j] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s = 0; s < head_sets(G); ++s) o[s][0] = o[s][1] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
   }
 };
 
-// What a work-group needs to know about its segment and its place in LDS.
+// What a work-group needs to know about its segment.
 struct SplitCtx {
   int b, hs, hk, lb, L, lP;
-  size_t lane_off;
-  char* kt;  // this wave's staging areas
-  char* vt;
 };
 
-// Q as the B operand of S = K Q^T: lane (head = li, k-group = grp) holds Q[head][16*ks + 4*grp + i];
-// heads beyond G are zero rows of the tile.
+// Q as the B operand of S = K Q^T: lane (column = lane % 16, group) holds the 16-byte pieces 4c + group of its head's
+// row; columns repeat the heads, and heads beyond G are zero.
 template <int G>
-__device__ __forceinline__ void load_q(const DecodeParams& p, int b, int hs, uint2 (&qb)[8]) {
-  const int lane = threadIdx.x & 63, grp = lane >> 4, li = lane & 15;
+__device__ __forceinline__ void load_q(const DecodeParams& p, int b, int hs, u32x4 (&qb)[4]) {
+  const int lane = threadIdx.x & 63, grp = lane >> 4, head = lane & (4 * head_sets(G) - 1);
 #pragma unroll
-  for (int ks = 0; ks < 8; ++ks) {
-    qb[ks] = make_uint2(0u, 0u);
-    if (li < G)
-      qb[ks] = *reinterpret_cast<const uint2*>(p.q + ((size_t)b * p.g.Hq + (size_t)hs * G + li) * ABSB_HEAD_DIM + 16 * ks +
-                                               4 * grp);
+  for (int c = 0; c < 4; ++c) {
+    qb[c] = u32x4{0u, 0u, 0u, 0u};
+    if (head < G)
+      qb[c] = *reinterpret_cast<const u32x4*>(p.q + ((size_t)b * p.g.Hq + (size_t)hs * G + head) * ABSB_HEAD_DIM +
+                                              (4 * c + grp) * 8);
   }
+}
+
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane) |
+         ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32);
 }
 
 // Attention of this wave over positions [pos_begin, pos_end) of the virtual token sequence of a block
 // list (position -> list entry pos >> lb -> token -> page/slot), folded into `st`.  A work-group step
-// covers DEC_WAVES * 16 consecutive positions, 16 per wave; pos_begin must be a multiple of 4.  `sj`:
-// the list entry of this lane's first rows, fetched by the caller (so that the load is in flight early).
+// covers DEC_STEP consecutive positions, 16 per wave; pos_begin must be a multiple of eight.
 //
 // `after_first_issue()` runs once the first step's row loads are in flight (work that has to wait for
 // memory anyway can hide behind them; it may contain barriers: every wave of the work-group calls this
 // function).  `live(entry)`: false for list entries whose rows were requested but must not count
-// (evaluated when a step is computed, after after_first_issue()).
+// (evaluated after after_first_issue()).
 struct NoHook {
   __device__ __forceinline__ void operator()() const {}
 };
 struct AllLive {
   __device__ __forceinline__ bool operator()(int) const { return true; }
 };
-template <int DT, int G, int SRC, class Hook = NoHook, class Live = AllLive>
-__device__ __forceinline__ void attend_positions(const DecodeParams& p, const SplitCtx& c, const ListRef<SRC>& list,
-                                                 const PageRef& pages, int pos_begin, int pos_end, int sj,
-                                                 const uint2 (&qb)[8], AttnState& st, Hook&& after_first_issue = Hook(),
-                                                 Live&& live = Live()) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, grp = lane >> 4, li = lane & 15;
+template <int DT, int G, bool STREAM, class List, class Hook, class Live>
+__device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCtx& c, const List& list,
+                                                 const PageRef& pages, int pos_begin, int pos_end,
+                                                 const u32x4 (&qb)[4], AttnState<G>& st, Hook&& after_first_issue,
+                                                 Live&& live) {
+  constexpr int SETS = head_sets(G);
+  const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, li = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lb = c.lb, L = c.L, lP = c.lP;
-  char* kt = c.kt;
-  char* vt = c.vt;
-  constexpr int STEP = DEC_WAVES * ROWS_PER_WAVE_STEP;  // positions per work-group step
-  u32x4 k0, k1, k2, k3, v0, v1, v2, v3;
+  const int wave_pos = pos_begin + wave * ROWS_PER_WAVE_STEP;
+  const int nsteps = pos_end > wave_pos ? (pos_end - wave_pos + DEC_STEP - 1) / DEC_STEP : 0;
+  const size_t head_off = (size_t)c.hk * p.g.s_head * 2;
+  const char* kbase = reinterpret_cast<const char*>(p.k) + head_off + grp * 16;
+  const char* vbase = reinterpret_cast<const char*>(p.v) + head_off;
+  const uint32_t lane4 = lane * 4;
+  const uint32_t pitch = (uint32_t)p.g.s_tok * 2;
 
-  // The address chain list entry -> page-table entry -> row is kept two steps deep so that only
-  // the row loads themselves wait on memory inside the loop: issuing step k's rows uses the page
-  // requested during step k-1, requests the page of step k+1 (whose list entry has arrived by
-  // then) and the list entry of step k+2.
-  //   tcb: first token of the lane's four rows (clamped into the context, so every address is
-  //        legal), pg: its physical page, vb: which of the four rows are real.
-#define ABSB_GROUP_TOKEN(base_of_step)                                                                \
-  {                                                                                                   \
-    const int pos = (base_of_step) + grp * 4;                                                         \
-    const int t = (sj << lb) + (pos & ((1 << lb) - 1));                                               \
-    vb = 0;                                                                                           \
-    _Pragma("unroll") for (int r = 0; r < 4; ++r)                                                     \
-        vb |= (uint32_t)(pos + r < pos_end && t + r < L) << r; /* a selected last block may be partial */ \
-    tcb = max(0, min(t, L - 1)) & ~3;                                                                 \
-    pg = pages.at(tcb >> lP);                                                                         \
-  }
-#define ABSB_ISSUE(base_expr)                                                                         \
-  {                                                                                                   \
-    const int base_ = (base_expr);                                                                    \
-    const size_t row0 = (size_t)pg * p.g.s_page + c.lane_off;                                         \
-    const size_t off0 = row0 + (size_t)(min(tcb + 0, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;           \
-    const size_t off1 = row0 + (size_t)(min(tcb + 1, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;           \
-    const size_t off2 = row0 + (size_t)(min(tcb + 2, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;           \
-    const size_t off3 = row0 + (size_t)(min(tcb + 3, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;           \
-    valid_next = vb;                                                                                  \
-    k0 = *reinterpret_cast<const u32x4*>(p.k + off0);                                                 \
-    k1 = *reinterpret_cast<const u32x4*>(p.k + off1);                                                 \
-    k2 = *reinterpret_cast<const u32x4*>(p.k + off2);                                                 \
-    k3 = *reinterpret_cast<const u32x4*>(p.k + off3);                                                 \
-    v0 = *reinterpret_cast<const u32x4*>(p.v + off0);                                                 \
-    v1 = *reinterpret_cast<const u32x4*>(p.v + off1);                                                 \
-    v2 = *reinterpret_cast<const u32x4*>(p.v + off2);                                                 \
-    v3 = *reinterpret_cast<const u32x4*>(p.v + off3);                                                 \
-    ABSB_GROUP_TOKEN(base_ + STEP)                                                                    \
-    sj = list.at((base_ + 2 * STEP + grp * 4) >> lb);                                                 \
-  }
+  // ---- lane j: half j % 2 of step j / 2 of the current 32 steps.  `off`: byte offset of its first row (of a
+  // legal token, whatever the list holds), `most`: last of its eight rows that exists, in bytes from the first;
+  // `nv`: how many of them count
+  uint64_t off = 0;
+  int most = 0, nv = 0, entry = 0;
+  auto look_up = [&](int step0) __attribute__((always_inline)) {
+    const int pos8 = wave_pos + (step0 + (lane >> 1)) * DEC_STEP + (lane & 1) * 8;
+    entry = pos8 >> lb;
+    const int t8 = (list.at(entry) << lb) + (pos8 & ((1 << lb) - 1));
+    const int tc = max(0, min(t8, L - 1)) & ~7;
+    off = ((uint64_t)pages.at(tc >> lP) * (uint64_t)p.g.s_page + (uint64_t)(tc & ((1 << lP) - 1)) * (uint64_t)p.g.s_tok) * 2;
+    nv = min(8, min(pos_end - pos8, L - t8));
+    most = (nv > 0 ? min(7, L - 1 - tc) : 0) * (int)pitch;  // rows nobody needs: one line, not eight
+  };
+  u32x4 k[4];
+  uint32_t v[16];
+  int nv0 = 0, nv1 = 0;      // rows of the two halves that count, of the step being computed
+  uint64_t v_off[2];         // of the step whose V rows are being requested
+  uint32_t v_most[2];
+  auto issue_k = [&](int j) __attribute__((always_inline)) {  // j: even lane of the step's pair
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      v_off[h] = readlane_u64(off, j + h);
+      v_most[h] = (uint32_t)__builtin_amdgcn_readlane(most, j + h);
+    }
+    const uint64_t o = li < 8 ? v_off[0] : v_off[1];
+    const uint32_t r = min((uint32_t)(li & 7) * pitch, li < 8 ? v_most[0] : v_most[1]);
+    const char* row = kbase + o + r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x4* piece = reinterpret_cast<const u32x4*>(row + 64 * i);
+      k[i] = *piece;  // cached even when V passes by: half a line a token, the other half is the next piece's
+    }
+  };
+  auto issue_v = [&](int t) __attribute__((always_inline)) {  // rows 4t .. 4t+3
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 4 * t + i;
+      const char* row = vbase + (v_off[r >> 3] + min((uint32_t)(r & 7) * pitch, v_most[r >> 3]));  // a scalar
+      const uint32_t* pair = reinterpret_cast<const uint32_t*>(row + lane4);
+      v[r] = STREAM ? __builtin_nontemporal_load(pair) : *pair;
+    }
+  };
 
-  int base = pos_begin + wave * ROWS_PER_WAVE_STEP;
-  uint32_t valid_next = 0, vb;
-  int tcb, pg;
-  ABSB_GROUP_TOKEN(base)                           // first step: entry -> page, in order
-  sj = list.at((base + STEP + grp * 4) >> lb);     // second step's entry
-  if (base < pos_end) ABSB_ISSUE(base)
+  look_up(0);
+  if (nsteps > 0) {
+    issue_k(0);
+    __builtin_amdgcn_sched_barrier(0);  // rows arrive in the order they are asked for: K first
+#pragma unroll
+    for (int t = 0; t < 4; ++t) issue_v(t);
+  }
   after_first_issue();
+  if (!live(entry)) nv = 0;
   float m = st.m, l = st.l, lx = st.lx;
-  while (base < pos_end) {  // trip count depends on the wave only: every branch here is wave-uniform
-    // ---- stage the step's rows in LDS
-    const uint32_t valid = live((base + grp * 4) >> lb) ? valid_next : 0u;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 0) * K_PITCH + li * 16) = k0;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 1) * K_PITCH + li * 16) = k1;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 2) * K_PITCH + li * 16) = k2;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 3) * K_PITCH + li * 16) = k3;
-    // 32-bit word d of a row = channels 2d, 2d+1 of the lane's eight
-    stage_v_word(vt + 0 * 1024 + li * 32 + grp * 8, v0.x, v1.x, v2.x, v3.x);
-    stage_v_word(vt + 1 * 1024 + li * 32 + grp * 8, v0.y, v1.y, v2.y, v3.y);
-    stage_v_word(vt + 2 * 1024 + li * 32 + grp * 8, v0.z, v1.z, v2.z, v3.z);
-    stage_v_word(vt + 3 * 1024 + li * 32 + grp * 8, v0.w, v1.w, v2.w, v3.w);
-    // ---- next step's rows go in flight now; they land while this step computes
-    const int next = base + STEP;
-    if (next < pos_end) ABSB_ISSUE(next)
-
+  // One step from the rows in registers; MORE: the next step's rows are requested as registers come free.  (The last
+  // step is a copy of its own: requests under a condition would be copied into place, after a wait for them.)
+  auto compute = [&](int step, auto more) __attribute__((always_inline)) {
+    constexpr bool MORE = decltype(more)::value;
+    const int j = 2 * (step & 31);
+    nv0 = __builtin_amdgcn_readlane(nv, j);
+    nv1 = __builtin_amdgcn_readlane(nv, j + 1);
     // ---- S[row][head] = K Q^T over the 128 channels (two accumulators: shorter dependent chain)
     float4_t s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < 8; ks += 2) {
-      const uint2 a0 = *reinterpret_cast<const uint2*>(kt + li * K_PITCH + (16 * ks + 4 * grp) * 2);
-      const uint2 a1 = *reinterpret_cast<const uint2*>(kt + li * K_PITCH + (16 * (ks + 1) + 4 * grp) * 2);
-      s0 = mma16<DT>(a0, qb[ks], s0);
-      s1 = mma16<DT>(a1, qb[ks + 1], s1);
+    s0 = mma_16x16x32<DT>(k[0], qb[0], s0);
+    s1 = mma_16x16x32<DT>(k[1], qb[1], s1);
+    s0 = mma_16x16x32<DT>(k[2], qb[2], s0);
+    s1 = mma_16x16x32<DT>(k[3], qb[3], s1);
+    if (MORE) {
+      if (j == 62) {
+        look_up(step + 1);
+        if (!live(entry)) nv = 0;
+      }
+      issue_k(2 * ((step + 1) & 31));
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // ---- online softmax in place: this lane holds rows 4*grp..4*grp+3 of head li
+    // ---- online softmax in place: this lane holds rows 4*grp..4*grp+3 of its head
     float sc[4];
+    const int live_rows = (grp < 2 ? nv0 : nv1) - 4 * (grp & 1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sc[i] = ((valid >> i) & 1u) ? (s0[i] + s1[i]) * p.scale_log2 : -__builtin_inff();
-    float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    for (int i = 0; i < 4; ++i) sc[i] = i < live_rows ? (s0[i] + s1[i]) * p.scale_log2 : -__builtin_inff();
+    const float mx = across_rows(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), FMax());
     const float mn = fmaxf(m, mx);
     const float alpha = fast_exp2(m - mn);
     m = mn;
@@ -322,35 +363,68 @@ __device__ __forceinline__ void attend_positions(const DecodeParams& p, const Sp
     }
     l = __builtin_fmaf(l, alpha, psum);
     lx = __builtin_fmaf(lx, alpha, esum);
-    const uint2 pa = make_uint2(pb[0] | (pb[1] << 16), pb[2] | (pb[3] << 16));
     // ---- rescale O when some head's maximum moved (rare once the maxima have settled)
     if (__any(alpha != 1.0f)) {
-      float ah[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float a_lo = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(alpha), i));
-        const float a_hi = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(alpha), (G > 4 ? 4 + i : i)));
-        ah[i] = (G > 4 && grp == 1) ? a_hi : a_lo;  // groups beyond the heads hold zeros: any factor does
-      }
+      for (int s = 0; s < SETS; ++s)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+        for (int i = 0; i < 4; ++i) {
+          const float a = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(alpha), 4 * s + i));
+          st.o[s][0][i] *= a;
+          st.o[s][1][i] *= a;
+        }
+    }
+    // ---- the weights of rows 4t..4t+3 (group t's) for head 4*set + lane % 4, in every lane
+    uint32_t w[SETS][2];
+    const uint32_t own[2] = {pb[0] | (pb[1] << 16), pb[2] | (pb[3] << 16)};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) st.oacc[j][i] *= ah[i];
+    for (int x = 0; x < 2; ++x) {
+      if (SETS == 1) {
+        w[0][x] = own[x];
+      } else {  // lanes l and l ^ 4 hold heads l % 8 and (l ^ 4) % 8: each needs both
+        const uint32_t other = (uint32_t)dpp_i<0x1B>(dpp_i<DPP_ROW_HALF_MIRROR>((int)own[x]));  // quad_perm [3,2,1,0]
+        w[0][x] = (lane & 4) ? other : own[x];
+        w[SETS - 1][x] = (lane & 4) ? own[x] : other;
       }
     }
-    // ---- O[head][channel] += P V: B operand = four rows of one channel, one LDS word
+    RowsOf wt[SETS][2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint2 bv = *reinterpret_cast<const uint2*>(vt + j * 512 + li * 32 + grp * 8);
-      st.oacc[j] = mma16<DT>(pa, bv, st.oacc[j]);
+    for (int s = 0; s < SETS; ++s)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) wt[s][x] = spread_rows(w[s][x]);
+    // ---- O[head][channel] += P V, four rows at a time: four rows of a channel side by side in two registers
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const u32x2 ev = {__builtin_amdgcn_perm(v[4 * t + 1], v[4 * t], 0x05040100u),       // low halves: channel 2l
+                        __builtin_amdgcn_perm(v[4 * t + 3], v[4 * t + 2], 0x05040100u)};
+      const u32x2 od = {__builtin_amdgcn_perm(v[4 * t + 1], v[4 * t], 0x07060302u),       // high halves: channel 2l + 1
+                        __builtin_amdgcn_perm(v[4 * t + 3], v[4 * t + 2], 0x07060302u)};
+      if (MORE) issue_v(t);
+#pragma unroll
+      for (int s = 0; s < SETS; ++s) {
+        const u32x2 a = {wt[s][0].of[t], wt[s][1].of[t]};
+        st.o[s][0] = mma_4x4x4<DT>(a, ev, st.o[s][0]);
+        st.o[s][1] = mma_4x4x4<DT>(a, od, st.o[s][1]);
+      }
     }
-    base = next;
-  }
-#undef ABSB_ISSUE
-#undef ABSB_GROUP_TOKEN
+  };
+  // trip counts depend on the wave only: every branch here is wave-uniform
+  for (int step = 0; step + 1 < nsteps; ++step) compute(step, std::true_type());
+  if (nsteps > 0) compute(nsteps - 1, std::false_type());
   st.m = m;
   st.l = l;
   st.lx = lx;
+}
+
+template <int DT, int G, class List, class Hook = NoHook, class Live = AllLive>
+__device__ __forceinline__ void attend_positions(const DecodeParams& p, const SplitCtx& c, const List& list,
+                                                 const PageRef& pages, int pos_begin, int pos_end,
+                                                 const u32x4 (&qb)[4], AttnState<G>& st, Hook&& after_first_issue = Hook(),
+                                                 Live&& live = Live()) {
+  if (p.stream_rows)
+    attend_rows<DT, G, true>(p, c, list, pages, pos_begin, pos_end, qb, st, after_first_issue, live);
+  else
+    attend_rows<DT, G, false>(p, c, list, pages, pos_begin, pos_end, qb, st, after_first_issue, live);
 }
 
 // An empty selection: the output rows are zero, the log-sum-exp -inf.
@@ -385,8 +459,8 @@ __device__ __forceinline__ void poison_rows(const DecodeParams& p, int b, int hs
 // thread of the work-group must call.
 template <int DT, int G, class OnLast>
 __device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b, int hs, int split, int nsplit, int slots,
-                                             AttnState& st, char* lds, OnLast&& on_last) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, grp = lane >> 4, li = lane & 15;
+                                             AttnState<G>& st, char* lds, OnLast&& on_last) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   char* s_stage = lds;
   float (*s_m)[DEC_WAVES] = reinterpret_cast<float (*)[DEC_WAVES]>(lds + DEC_LDS_STATE);
   float (*s_l)[DEC_WAVES] = s_m + ABSB_MAX_GROUP;
@@ -394,33 +468,25 @@ __device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b
   int* s_bcast = reinterpret_cast<int*>(lds + DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4);
   float m = st.m, l = st.l, lx = st.lx;
 
-  // ---- the wave's state: m per head (lane li), l summed over the four groups, O in groups 0 (and 1)
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
-  lx += __shfl_xor(lx, 16);
-  lx += __shfl_xor(lx, 32);
-  if (grp == 0 && li < G) s_m[li][wave] = m;
-  __syncthreads();  // also: every wave is done with its staging area, which the merge reuses below
+  // ---- the wave's state: m per head (lane = head), l summed over the four groups
+  l = across_rows(l, FAdd());
+  lx = across_rows(lx, FAdd());
+  if (lane < G) s_m[lane][wave] = m;
+  __syncthreads();
   // work-group maximum per head; own state rescaled to it, so that the four states simply add up
   float* s_o = reinterpret_cast<float*>(s_stage);  // [DEC_WAVES][G][128]
-  if (grp == 0 && li < G) {
-    const float M = fmaxf(fmaxf(s_m[li][0], s_m[li][1]), fmaxf(s_m[li][2], s_m[li][3]));
+  if (lane < G) {
+    const float M = fmaxf(fmaxf(s_m[lane][0], s_m[lane][1]), fmaxf(s_m[lane][2], s_m[lane][3]));
     const float a = fast_exp2(m - M);
-    s_l[li][wave] = l * a;
-    s_lx[li][wave] = lx * a;
+    s_l[lane][wave] = l * a;
+    s_lx[lane][wave] = lx * a;
   }
-  if (grp * 4 < G) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int hd = grp * 4 + i;
-      if (hd < G) {
-        const float M = fmaxf(fmaxf(s_m[hd][0], s_m[hd][1]), fmaxf(s_m[hd][2], s_m[hd][3]));
-        const float a = fast_exp2(s_m[hd][wave] - M);
-        float4* dst = reinterpret_cast<float4*>(s_o + ((size_t)wave * G + hd) * ABSB_HEAD_DIM + li * 8);
-        dst[0] = make_float4(st.oacc[0][i] * a, st.oacc[1][i] * a, st.oacc[2][i] * a, st.oacc[3][i] * a);
-        dst[1] = make_float4(st.oacc[4][i] * a, st.oacc[5][i] * a, st.oacc[6][i] * a, st.oacc[7][i] * a);
-      }
-    }
+  for (int hd = 0; hd < G; ++hd) {
+    const float M = fmaxf(fmaxf(s_m[hd][0], s_m[hd][1]), fmaxf(s_m[hd][2], s_m[hd][3]));
+    const float a = fast_exp2(s_m[hd][wave] - M);
+    *reinterpret_cast<float2*>(s_o + ((size_t)wave * G + hd) * ABSB_HEAD_DIM + lane * 2) =
+        make_float2(st.o[hd >> 2][0][hd & 3] * a, st.o[hd >> 2][1][hd & 3] * a);
   }
   __syncthreads();
   // ---- the work-group's partial: thread -> column (head g, channels 4*c4..4*c4+3), G*32 columns
@@ -477,34 +543,41 @@ __device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b
     Lsum = 0.0f;
     Lx = 0.0f;
     O = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int i0 = sl; i0 < nsplit; i0 += SL * MRG_UNROLL) {
-      float4_t mlv[MRG_UNROLL];
-      float4_t ov[MRG_UNROLL];
+    auto merge = [&](auto unroll) __attribute__((always_inline)) {
+      constexpr int U = decltype(unroll)::value;
+      for (int i0 = sl; i0 < nsplit; i0 += SL * U) {
+        float4_t mlv[U];
+        float4_t ov[U];
 #pragma unroll
-      for (int u = 0; u < MRG_UNROLL; ++u) {
-        const int i = min(i0 + u * SL, nsplit - 1);  // the tail repeats the last slot, with weight 0
-        mlv[u] = bitcast<float4_t>(__builtin_amdgcn_raw_buffer_load_b128(part_ml, (i * G + g) * 16, 0, COHERENT));
-        ov[u] = bitcast<float4_t>(
-            __builtin_amdgcn_raw_buffer_load_b128(part_o, ((i * G + g) * ABSB_HEAD_DIM + c4 * 4) * 4, 0, COHERENT));
+        for (int u = 0; u < U; ++u) {
+          const int i = min(i0 + u * SL, nsplit - 1);  // the tail repeats the last slot, with weight 0
+          mlv[u] = bitcast<float4_t>(__builtin_amdgcn_raw_buffer_load_b128(part_ml, (i * G + g) * 16, 0, COHERENT));
+          ov[u] = bitcast<float4_t>(
+              __builtin_amdgcn_raw_buffer_load_b128(part_o, ((i * G + g) * ABSB_HEAD_DIM + c4 * 4) * 4, 0, COHERENT));
+        }
+        float bm = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u) bm = fmaxf(bm, mlv[u].x);
+        const float a = fast_exp2(M - bm);
+        O *= a;
+        Lsum *= a;
+        Lx *= a;
+        M = bm;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float w = i0 + u * SL < nsplit ? fast_exp2(mlv[u].x - bm) : 0.0f;
+          O += ov[u] * w;
+          Lsum = __builtin_fmaf(mlv[u].y, w, Lsum);
+          Lx = __builtin_fmaf(mlv[u].z, w, Lx);
+        }
       }
-      float bm = M;
-#pragma unroll
-      for (int u = 0; u < MRG_UNROLL; ++u) bm = fmaxf(bm, mlv[u].x);
-      const float a = fast_exp2(M - bm);
-      O *= a;
-      Lsum *= a;
-      Lx *= a;
-      M = bm;
-#pragma unroll
-      for (int u = 0; u < MRG_UNROLL; ++u) {
-        const float w = i0 + u * SL < nsplit ? fast_exp2(mlv[u].x - bm) : 0.0f;
-        O += ov[u] * w;
-        Lsum = __builtin_fmaf(mlv[u].y, w, Lsum);
-        Lx = __builtin_fmaf(mlv[u].z, w, Lx);
-      }
-    }
+    };
+    if (nsplit <= SL * (MRG_UNROLL / 2))
+      merge(std::integral_constant<int, MRG_UNROLL / 2>());
+    else
+      merge(std::integral_constant<int, MRG_UNROLL>());
     if (SL > 1) {  // fold the split lanes of a column (the staging area is free again)
-      float* s_red = reinterpret_cast<float*>(s_stage);  // [SL][CP][8]
+      float* s_red = reinterpret_cast<float*>(s_stage);  // [SL][CP][8] (at most 8 KB)
       __syncthreads();
       float* mine = s_red + ((size_t)sl * CP + col) * 8;
       *reinterpret_cast<float4_t*>(mine) = float4_t{M, Lsum, Lx, 0.0f};
@@ -582,18 +655,9 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   const SegMap sm = seg_map(s, p.g.Hsel, p.g.Rk, p.g.Hkv);
   const int b = sm.b, hs = sm.hs, hk = sm.hk;
   const int lb = p.g.heads.log2_block[hk];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, grp = lane >> 4, li = lane & 15;
   constexpr int SRC = LISTED ? LIST_COHERENT : LIST_PLAIN;
   const ListRef<SRC> list{p.sel_idx + (size_t)s * p.sel_stride, p.sel_stride - 1};
   const int pos_begin = split * p.split_tokens;
-
-  // A lane's four rows of a step are four consecutive positions starting at a multiple of four:
-  // they lie in one block (B >= 8) and one page (P >= 8), so one list entry and one page-table
-  // entry serve all four.  The first step's list entry is fetched before the list length is known
-  // (the index is clamped to the list's storage, so the read is always legal); this takes one
-  // memory round trip off the dependent chain count -> entry -> page -> row.
-  int sj = 0;
-  if (!LISTED) sj = list.at((pos_begin + wave * ROWS_PER_WAVE_STEP + grp * 4) >> lb);
 
   // never beyond what the launch covers (a list longer than promised is cut, not overrun)
   int nsel;
@@ -615,14 +679,11 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   c.lb = lb;
   c.L = p.seq_lens[b];
   c.lP = p.g.log2_page;
-  c.lane_off = (size_t)hk * p.g.s_head + (size_t)li * 8;
-  c.kt = lds + wave * STAGE_BYTES;
-  c.vt = c.kt + K_TILE_BYTES;
   const PageRef pages{p.page_table + (size_t)b * p.g.pt_stride, nullptr, 0, 0};
   int* s_bcast = reinterpret_cast<int*>(lds + DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4);
   const int nsplit = (ntok + p.split_tokens - 1) / p.split_tokens;
 
-  uint2 qb[8];
+  u32x4 qb[4];
   load_q<G>(p, b, hs, qb);
 
   int32_t* flag = LISTED ? p.flags + (size_t)s * ABSB_TICKET_STRIDE : nullptr;
@@ -633,12 +694,11 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
       if (split == 0) poison_rows<DT, G>(p, b, hs);  // nobody will complete this segment's rows
       return;
     }
-    sj = list.at((pos_begin + wave * ROWS_PER_WAVE_STEP + grp * 4) >> lb);
   }
 
-  AttnState st;
+  AttnState<G> st;
   st.reset();
-  attend_positions<DT, G, SRC>(p, c, list, pages, pos_begin, pos_end, sj, qb, st);
+  attend_positions<DT, G>(p, c, list, pages, pos_begin, pos_end, qb, st);
   finish_split<DT, G>(p, s, b, hs, split, nsplit, p.max_splits, st, lds, [&]() {
     if (LISTED) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
   });

@@ -47,7 +47,7 @@ constexpr int FUSED_THREADS = DEC_THREADS;
 __host__ __device__ constexpr size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
 template <int DT, int G, int REP>
-__global__ __launch_bounds__(FUSED_THREADS, 3) void fused_step_kernel(FusedParams p) {
+__global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(FusedParams p) {
   extern __shared__ __align__(16) char lds[];
   const int bid = blockIdx.x, tid = threadIdx.x;
   if (bid >= p.n_score) {

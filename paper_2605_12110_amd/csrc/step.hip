@@ -84,7 +84,9 @@ struct StepParams {
 };
 
 // LDS of a unit, behind the attention kernel's: what has to survive the attention loop
-constexpr int STEP_LDS_LIST = DEC_LDS_BYTES;                                 // int32 [STEP_MAX_UNIT_BLOCKS]
+constexpr int STEP_LDS_BASE = 34 * 1024;
+static_assert(DEC_LDS_BYTES <= STEP_LDS_BASE, "attention LDS");
+constexpr int STEP_LDS_LIST = STEP_LDS_BASE;                                 // int32 [STEP_MAX_UNIT_BLOCKS]
 constexpr int STEP_LDS_CAND_J = STEP_LDS_LIST + STEP_MAX_UNIT_BLOCKS * 4;    // int32 [STEP_MAX_CAND] own candidates: block
 constexpr int STEP_LDS_CAND_KEY = STEP_LDS_CAND_J + STEP_MAX_CAND * 4;       // uint32 [STEP_MAX_CAND] ... and score
 constexpr int STEP_LDS_PT = STEP_LDS_CAND_KEY + STEP_MAX_CAND * 4;           // int32 [STEP_PT_CACHE]
@@ -230,132 +232,6 @@ __device__ __forceinline__ Verdict read_verdict(const StepParams& p, int t, int 
   return v;
 }
 
-// Attention of this wave over positions [pos_begin, pos_end) of the virtual token sequence of the
-// unit's block list in LDS, folded into `st`: the loop of attend_positions (decode_dev.h) with the
-// rows of TWO steps in flight.  A unit that got more than its share of the selection works through
-// several steps of 64 positions; at batch 1 every step waits a full trip to cold memory for its rows,
-// and with list and page-table entries in LDS nothing keeps the step after next from being requested
-// as well.  `after_first_issue` and `live` as in attend_positions.
-struct StepRows {
-  u32x4 k0, k1, k2, k3, v0, v1, v2, v3;
-  uint32_t valid;
-};
-template <int DT, int G, class Hook, class Live>
-__device__ __forceinline__ void attend_local(const DecodeParams& p, const SplitCtx& c, const int32_t* s_list, int last_entry,
-                                             const PageRef& pages, int pos_begin, int pos_end, const uint2 (&qb)[8],
-                                             AttnState& st, Hook&& after_first_issue, Live&& live) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, grp = lane >> 4, li = lane & 15;
-  const int lb = c.lb, L = c.L, lP = c.lP;
-  char* kt = c.kt;
-  char* vt = c.vt;
-  constexpr int STEP = DEC_WAVES * ROWS_PER_WAVE_STEP;
-  auto issue = [&](int base, StepRows& r) __attribute__((always_inline)) {
-    // the lane's four rows: consecutive positions from a multiple of four, in one block and one page
-    const int pos = base + grp * 4;
-    const int sj = s_list[min(pos >> lb, last_entry)];
-    const int t = (sj << lb) + (pos & ((1 << lb) - 1));
-    uint32_t vb = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) vb |= (uint32_t)(pos + i < pos_end && t + i < L) << i;  // a selected last block may be partial
-    const int tcb = max(0, min(t, L - 1)) & ~3;
-    const int pg = pages.at(tcb >> lP);
-    const size_t row0 = (size_t)pg * p.g.s_page + c.lane_off;
-    const size_t off0 = row0 + (size_t)(min(tcb + 0, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;
-    const size_t off1 = row0 + (size_t)(min(tcb + 1, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;
-    const size_t off2 = row0 + (size_t)(min(tcb + 2, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;
-    const size_t off3 = row0 + (size_t)(min(tcb + 3, L - 1) & ((1 << lP) - 1)) * p.g.s_tok;
-    r.valid = vb;
-    r.k0 = *reinterpret_cast<const u32x4*>(p.k + off0);
-    r.k1 = *reinterpret_cast<const u32x4*>(p.k + off1);
-    r.k2 = *reinterpret_cast<const u32x4*>(p.k + off2);
-    r.k3 = *reinterpret_cast<const u32x4*>(p.k + off3);
-    r.v0 = *reinterpret_cast<const u32x4*>(p.v + off0);
-    r.v1 = *reinterpret_cast<const u32x4*>(p.v + off1);
-    r.v2 = *reinterpret_cast<const u32x4*>(p.v + off2);
-    r.v3 = *reinterpret_cast<const u32x4*>(p.v + off3);
-  };
-  float m = st.m, l = st.l, lx = st.lx;
-  // one step: the rows in `r` go to LDS, `r` is refilled with the rows of the step after next, then
-  // S = K Q^T, the online softmax and O += P V from LDS
-  auto step = [&](int base, StepRows& r) __attribute__((always_inline)) {
-    const uint32_t valid = live((base + grp * 4) >> lb) ? r.valid : 0u;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 0) * K_PITCH + li * 16) = r.k0;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 1) * K_PITCH + li * 16) = r.k1;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 2) * K_PITCH + li * 16) = r.k2;
-    *reinterpret_cast<u32x4*>(kt + (grp * 4 + 3) * K_PITCH + li * 16) = r.k3;
-    stage_v_word(vt + 0 * 1024 + li * 32 + grp * 8, r.v0.x, r.v1.x, r.v2.x, r.v3.x);
-    stage_v_word(vt + 1 * 1024 + li * 32 + grp * 8, r.v0.y, r.v1.y, r.v2.y, r.v3.y);
-    stage_v_word(vt + 2 * 1024 + li * 32 + grp * 8, r.v0.z, r.v1.z, r.v2.z, r.v3.z);
-    stage_v_word(vt + 3 * 1024 + li * 32 + grp * 8, r.v0.w, r.v1.w, r.v2.w, r.v3.w);
-    if (base + 2 * STEP < pos_end) issue(base + 2 * STEP, r);
-    float4_t s0 = {0.0f, 0.0f, 0.0f, 0.0f}, s1 = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < 8; ks += 2) {
-      const uint2 a0 = *reinterpret_cast<const uint2*>(kt + li * K_PITCH + (16 * ks + 4 * grp) * 2);
-      const uint2 a1 = *reinterpret_cast<const uint2*>(kt + li * K_PITCH + (16 * (ks + 1) + 4 * grp) * 2);
-      s0 = mma16<DT>(a0, qb[ks], s0);
-      s1 = mma16<DT>(a1, qb[ks + 1], s1);
-    }
-    float sc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sc[i] = ((valid >> i) & 1u) ? (s0[i] + s1[i]) * p.scale_log2 : -__builtin_inff();
-    float mx = fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mn = fmaxf(m, mx);
-    const float alpha = fast_exp2(m - mn);
-    m = mn;
-    uint32_t pb[4];
-    float psum = 0.0f, esum = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float e = fast_exp2(sc[i] - mn);
-      const uint16_t ph = Elem<DT>::narrow(e);  // the weight as the product will see it
-      psum += Elem<DT>::widen(ph);
-      esum += e;
-      pb[i] = ph;
-    }
-    l = __builtin_fmaf(l, alpha, psum);
-    lx = __builtin_fmaf(lx, alpha, esum);
-    const uint2 pa = make_uint2(pb[0] | (pb[1] << 16), pb[2] | (pb[3] << 16));
-    if (__any(alpha != 1.0f)) {  // rescale O when some head's maximum moved
-      float ah[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float a_lo = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(alpha), i));
-        const float a_hi = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(alpha), (G > 4 ? 4 + i : i)));
-        ah[i] = (G > 4 && grp == 1) ? a_hi : a_lo;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) st.oacc[j][i] *= ah[i];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint2 bv = *reinterpret_cast<const uint2*>(vt + j * 512 + li * 32 + grp * 8);
-      st.oacc[j] = mma16<DT>(pa, bv, st.oacc[j]);
-    }
-  };
-  int base = pos_begin + wave * ROWS_PER_WAVE_STEP;
-  StepRows ra, rb;
-  ra.valid = rb.valid = 0;
-  if (base < pos_end) issue(base, ra);
-  if (base + STEP < pos_end) issue(base + STEP, rb);
-  after_first_issue();
-  while (base < pos_end) {  // trip count depends on the wave only: every branch here is wave-uniform
-    step(base, ra);
-    base += STEP;
-    if (base >= pos_end) break;
-    step(base, rb);
-    base += STEP;
-  }
-  st.m = m;
-  st.l = l;
-  st.lx = lx;
-}
-
 // ------------------------------------------------------------------ coordinator
 template <int DT, int G>
 __device__ __forceinline__ void step_coordinator(const StepParams& p, int t, char* lds) {
@@ -410,7 +286,7 @@ template <int DT, int G, int REP>
 __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, char* lds) {
   const SegShape g = seg_shape(p, t);
   if (c >= g.units) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = lane >> 4, li = lane & 15;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = g.sm.b, hs = g.sm.hs, hk = g.sm.hk, lb = g.lb;
   const int U = g.units;
   const int j0 = c * g.unit_blocks, j1 = min(g.Nall, j0 + g.unit_blocks), n = j1 - j0;
@@ -437,9 +313,6 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
   cx.lb = lb;
   cx.L = p.dc.seq_lens[b];
   cx.lP = p.dc.g.log2_page;
-  cx.lane_off = (size_t)hk * p.dc.g.s_head + (size_t)li * 8;
-  cx.kt = lds + wave * STAGE_BYTES;
-  cx.vt = cx.kt + K_TILE_BYTES;
   const int32_t* pt_row = p.dc.page_table + (size_t)b * p.dc.g.pt_stride;
   const int tok0 = j0 << lb, tok1 = min(cx.L, j1 << lb);
   const int page0 = tok0 >> cx.lP, npages = ((max(tok1, tok0 + 1) - 1) >> cx.lP) - page0 + 1;
@@ -448,8 +321,9 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
 #pragma unroll 1
     for (int i = tid; i < npages; i += STEP_THREADS) s_pt[i] = pt_row[page0 + i];
   }
+  const ListRef<LIST_LOCAL> local_list{s_list, STEP_MAX_UNIT_BLOCKS - 1};
   const PageRef pages{pt_row, pt_cached ? (lds_const_i32*)s_pt : (lds_const_i32*)nullptr, page0, npages};
-  uint2 qb[8];
+  u32x4 qb[4];
   load_q<G>(p.dc, b, hs, qb);
 
   int nsure = 0, ncand = 0;
@@ -577,7 +451,7 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
     }
   }
 
-  AttnState st;
+  AttnState<G> st;
   st.reset();
   auto clear_words = [&]() __attribute__((always_inline)) {  // by the segment's last unit: every other one is past all its waits
     if (compete) {
@@ -594,8 +468,7 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
     if (pos_begin < pos_end) {
       const ListRef<LIST_COHERENT> list{p.tk.sel_idx + (size_t)t * p.tk.sel_stride, p.tk.sel_stride - 1};
       const PageRef anywhere{pt_row, nullptr, 0, 0};  // the stretch's tokens lie anywhere in the context
-      const int sj = list.at((pos_begin + wave * ROWS_PER_WAVE_STEP + grp * 4) >> lb);
-      attend_positions<DT, G, LIST_COHERENT>(p.dc, cx, list, anywhere, pos_begin, pos_end, sj, qb, st);
+      attend_positions<DT, G>(p.dc, cx, list, anywhere, pos_begin, pos_end, qb, st);
     }
     finish_split<DT, G>(p.dc, t, b, hs, c, U, p.units_max, st, lds, clear_words);
     return;
@@ -606,7 +479,7 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
   // for anyway
   {
     const int pos_end = nsure << lb;
-    attend_local<DT, G>(p.dc, cx, s_list, STEP_MAX_UNIT_BLOCKS - 1, pages, 0, pos_end, qb, st, [&]() __attribute__((always_inline)) {
+    attend_positions<DT, G>(p.dc, cx, local_list, pages, 0, pos_end, qb, st, [&]() __attribute__((always_inline)) {
       if (ncand > 0) {  // the same in every wave
         wait_stores_acknowledged();
         __syncthreads();
@@ -624,8 +497,8 @@ __device__ __forceinline__ void step_unit(const StepParams& p, int t, int c, cha
     uint32_t* s_rank = reinterpret_cast<uint32_t*>(lds + STEP_LDS_RANK);
     bool timed_out = false;
     const int pos_begin = nsure << lb, pos_end = (nsure + ncand) << lb;
-    attend_local<DT, G>(
-        p.dc, cx, s_list, STEP_MAX_UNIT_BLOCKS - 1, pages, pos_begin, pos_end, qb, st,
+    attend_positions<DT, G>(
+        p.dc, cx, local_list, pages, pos_begin, pos_end, qb, st,
         [&]() __attribute__((always_inline)) {
           const int n_in = v.n_in;
           if (!wait_for_count(cand_done, n_in, p.dc.status, reinterpret_cast<int*>(s_misc + 32))) {
