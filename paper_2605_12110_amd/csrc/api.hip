@@ -92,7 +92,10 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     const int64_t cap = batch->cap_lens_host ? batch->cap_lens_host[b] : L;  // the layout's length
     if (cap < L) return ABSB_ERR_BAD_SHAPE;
     if (L > max_len) max_len = L;
-    if (batch->budget_host && batch->budget_host[b] < 1) return ABSB_ERR_BAD_SHAPE;
+    if (batch->budget_host) {
+      if (batch->budget_host[b] < 1) return ABSB_ERR_BAD_SHAPE;
+      (batch->budget_host[b] >= L ? p.some_dense : p.all_dense) = 1;  // (all_dense holds "some are not" until the end)
+    }
     for (int h = 0; h < Hkv; ++h) {
       const int64_t B = layer->block_size[h];
       const int64_t N = ceil_div(L, B);
@@ -116,6 +119,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     }
   }
   p.build_max_chunks = (int32_t)ceil_div(max_len, BUILD_CHUNK);
+  p.all_dense = p.some_dense && !p.all_dense;
   if (!batch->budget_host) p.sel_stride = p.max_blocks;
   // entry points that select (they are the ones that need the budgets) refuse on the host what the
   // selection cannot hold, before anything is enqueued
@@ -356,6 +360,15 @@ int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const vo
   if (p.step_form == ABSB_STEP_PIPELINED && fused_one_launch_fits(p))
     return launch_fused(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
+  if (p.all_dense) {
+    // no score decides anything; the lists (0, 1, 2, ...) are only written if the caller wants them
+    if (sel_idx_out || sel_cnt_out) {
+      rc = launch_topk(g, p, scores, batch->cent_off, batch->budget, batch->seq_lens, sel_idx, sel_cnt, p.sel_stride, nullptr, st);
+      if (rc != ABSB_OK) return rc;
+    }
+    return launch_decode_dense(g, p, layer->dtype, resolve_scale(layer), q, k_cache, v_cache, batch->page_table,
+                               batch->seq_lens, batch->cent_off, out, lse, ws, st);
+  }
   rc = launch_score(g, p, layer->dtype, q, codes, qscale, batch->qmin, batch->cent_off, batch->seq_lens, scores, nullptr, st);
   if (rc != ABSB_OK) return rc;
   // the selection kernel also clears the split counters of the attention kernel behind it

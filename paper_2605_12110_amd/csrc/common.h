@@ -52,6 +52,7 @@ struct Plan {
   int64_t sum_tokens;       // sum_s of the same bound
   int32_t split_tokens;     // tokens per split-K work-group
   int32_t max_splits;       // grid.x of the decode kernels
+  int32_t some_dense, all_dense;  // requests whose budget covers their context (everything is selected): any, all
   int32_t stream_rows;      // attention: K and V rows are read past the caches
   int32_t one_launch;       // absb_decode_fused: the whole step as one launch (else one launch per stage)
   int32_t step_form;        // absb_step_form actually used (never ABSB_STEP_AUTO)
@@ -98,6 +99,11 @@ ABSB_HIDDEN int launch_decode(const Geometry& g, const Plan& pl, int dtype, floa
                               const int32_t* seq_lens, const int32_t* sel_idx, const int32_t* sel_cnt,
                               int32_t sel_stride, void* out, float* lse, char* ws, bool tickets_cleared,
                               hipStream_t stream);
+// ... over all blocks of every context: the list is the identity and is not read
+ABSB_HIDDEN int launch_decode_dense(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
+                                    const void* k_cache, const void* v_cache, const int32_t* page_table,
+                                    const int32_t* seq_lens, const int32_t* cent_off, void* out, float* lse, char* ws,
+                                    hipStream_t stream);
 
 // The whole step in one launch (estimation, selection and attention work-groups in one grid).
 ABSB_HIDDEN bool fused_one_launch_fits(const Plan& pl);

@@ -30,12 +30,7 @@ static void launch_partial(const DecodeParams& p, dim3 grid, hipStream_t stream)
   }
 }
 
-int launch_decode(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
-                  const void* k_cache, const void* v_cache, const int32_t* page_table, const int32_t* seq_lens,
-                  const int32_t* sel_idx, const int32_t* sel_cnt, int32_t sel_stride, void* out, float* lse,
-                  char* ws, bool tickets_cleared, hipStream_t stream) {
-  const DecodeParams p = make_decode_params(g, pl, sm_scale, q, k_cache, v_cache, page_table, seq_lens, sel_idx, sel_cnt,
-                                            sel_stride, out, lse, ws);
+static int launch(const DecodeParams& p, const Plan& pl, int dtype, bool tickets_cleared, hipStream_t stream) {
   if (!tickets_cleared && pl.max_splits > 1) {
     hipLaunchKernelGGL(decode_clear_tickets_kernel, dim3((unsigned)((pl.nseg + 255) / 256)), dim3(256), 0, stream,
                        p.tickets, (int)pl.nseg);
@@ -48,6 +43,24 @@ int launch_decode(const Geometry& g, const Plan& pl, int dtype, float sm_scale, 
   else
     launch_partial<ABSB_BF16>(p, grid, stream);
   return check_launch();
+}
+
+int launch_decode(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
+                  const void* k_cache, const void* v_cache, const int32_t* page_table, const int32_t* seq_lens,
+                  const int32_t* sel_idx, const int32_t* sel_cnt, int32_t sel_stride, void* out, float* lse,
+                  char* ws, bool tickets_cleared, hipStream_t stream) {
+  const DecodeParams p = make_decode_params(g, pl, sm_scale, q, k_cache, v_cache, page_table, seq_lens, sel_idx, sel_cnt,
+                                            sel_stride, out, lse, ws);
+  return launch(p, pl, dtype, tickets_cleared, stream);
+}
+
+int launch_decode_dense(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q, const void* k_cache,
+                        const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
+                        void* out, float* lse, char* ws, hipStream_t stream) {
+  DecodeParams p = make_decode_params(g, pl, sm_scale, q, k_cache, v_cache, page_table, seq_lens, nullptr, nullptr,
+                                      pl.sel_stride, out, lse, ws);
+  p.cent_off = cent_off;
+  return launch(p, pl, dtype, false, stream);
 }
 
 }  // namespace absb

@@ -38,6 +38,11 @@
 namespace absb {
 
 struct DecodeParams {
+  // (what a work-group reads first comes first: the arguments are a few cold lines of memory)
+  int32_t sel_stride, split_tokens, max_splits;
+  int32_t some_dense;   // LISTED: some budgets cover their context; nobody selects for those requests
+  int32_t stream_rows;  // 1: V rows pass the caches by
+  float scale_log2;     // sm_scale * log2(e)
   const uint16_t* q;
   const uint16_t* k;
   const uint16_t* v;
@@ -55,9 +60,6 @@ struct DecodeParams {
   int32_t* status;   // one word: set non-zero when a wait ran into its time limit
   void* out;       // [Bt][Hq][128]
   float* lse;      // [Bt][Hq] or null
-  int32_t sel_stride, split_tokens, max_splits;
-  int32_t stream_rows;  // 1: K and V rows pass the caches by
-  float scale_log2;  // sm_scale * log2(e)
   Geometry g;
 };
 
@@ -85,6 +87,7 @@ inline DecodeParams make_decode_params(const Geometry& g, const Plan& pl, float 
   p.sel_stride = sel_stride;
   p.split_tokens = pl.split_tokens;
   p.max_splits = pl.max_splits;
+  p.some_dense = 0;
   p.stream_rows = pl.stream_rows;
   p.scale_log2 = sm_scale * 1.4426950408889634f;
   p.g = g;
@@ -164,7 +167,8 @@ enum : int {
   LIST_LOCAL = 2      // this work-group's LDS
 };
 
-// A block list: entry i is a block index of the segment.  Indices beyond `last` read entry `last`
+// A block list: entry i is a block index of the segment (i itself where there is no list: everything is
+// selected).  Indices beyond `last` read entry `last`
 // (the loop prefetches ahead of the range it works on; the clamp keeps every read inside the storage).
 template <int SRC>
 struct ListRef {
@@ -172,6 +176,7 @@ struct ListRef {
   int last;
   __device__ __forceinline__ int at(int i) const {
     i = min(i, last);
+    if (SRC != LIST_LOCAL && !ptr) return i;
     if (SRC == LIST_COHERENT) return ld_i32<true>(ptr + i);
     return ptr[i];
   }
@@ -656,17 +661,23 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   const int b = sm.b, hs = sm.hs, hk = sm.hk;
   const int lb = p.g.heads.log2_block[hk];
   constexpr int SRC = LISTED ? LIST_COHERENT : LIST_PLAIN;
-  const ListRef<SRC> list{p.sel_idx + (size_t)s * p.sel_stride, p.sel_stride - 1};
   const int pos_begin = split * p.split_tokens;
 
   // never beyond what the launch covers (a list longer than promised is cut, not overrun)
   int nsel;
-  if (LISTED) {
+  bool listed = LISTED || p.sel_cnt;  // false: everything is selected, there is no list
+  if (LISTED || !p.sel_cnt) {
     const int rows = p.cent_off[sm.s + 1] - p.cent_off[sm.s];
-    nsel = budget_blocks(p.budget[b], lb, blocks_in_use(p.g.tight, rows, p.seq_lens, b, lb), p.sel_stride);
+    nsel = blocks_in_use(p.g.tight, rows, p.seq_lens, b, lb);
+    if (LISTED) {
+      const int T = p.budget[b];
+      if (p.some_dense && T >= p.seq_lens[b]) listed = false;
+      nsel = budget_blocks(T, lb, nsel, p.sel_stride);
+    }
   } else {
     nsel = p.sel_cnt[s];
   }
+  const ListRef<SRC> list{listed ? p.sel_idx + (size_t)s * p.sel_stride : nullptr, (listed ? p.sel_stride : max(nsel, 1)) - 1};
   const int ntok = min(nsel << lb, p.max_splits * p.split_tokens);
   if (ntok == 0 && split == 0) write_empty_rows<G>(p, b, hs);
   if (pos_begin >= ntok) return;
@@ -687,7 +698,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   load_q<G>(p, b, hs, qb);
 
   int32_t* flag = LISTED ? p.flags + (size_t)s * ABSB_TICKET_STRIDE : nullptr;
-  if (LISTED) {
+  if (LISTED && listed) {
     // The list comes from a work-group with a lower index, which never waits for anything and was
     // dispatched before this one: the wait ends.  The time limit only makes that unconditional.
     if (!wait_for_flag(flag, p.status, s_bcast + 1)) {
@@ -700,7 +711,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   st.reset();
   attend_positions<DT, G>(p, c, list, pages, pos_begin, pos_end, qb, st);
   finish_split<DT, G>(p, s, b, hs, split, nsplit, p.max_splits, st, lds, [&]() {
-    if (LISTED) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
+    if (LISTED && listed) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
   });
 }
 

@@ -35,11 +35,12 @@
 namespace absb {
 
 struct FusedParams {
+  int32_t n_score, chunks_per_seg;  // first: every work-group starts by reading these
+  int32_t some_dense;
   ScoreParams sc;
   TopkParams tk;
   DecodeParams dc;
   int32_t* score_tickets;  // [nseg], ABSB_TICKET_STRIDE apart
-  int32_t n_score, chunks_per_seg;
 };
 
 constexpr int FUSED_THREADS = DEC_THREADS;
@@ -56,6 +57,19 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(FusedParam
     return;
   }
   const int s = bid / p.chunks_per_seg;
+  if (p.some_dense) {
+    // requests whose budget covers their context: no score decides anything, the attention knows its list
+    const SegMap sm = seg_map(s, p.tk.Hsel, p.tk.Rk, p.tk.Hkv);
+    if (p.tk.budget[sm.b] >= p.tk.seq_lens[sm.b]) {
+      if (bid % p.chunks_per_seg) return;
+      const int rows = p.tk.cent_off[sm.s + 1] - p.tk.cent_off[sm.s];
+      const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, p.tk.heads.log2_block[sm.hk]);
+      if (tid == 0) p.tk.sel_cnt[s] = N;
+      if (p.tk.sel_idx)
+        for (int i = tid; i < p.tk.sel_stride; i += FUSED_THREADS) p.tk.sel_idx[(size_t)s * p.tk.sel_stride + i] = i < N ? i : -1;
+      return;
+    }
+  }
   const int N = score_chunk<DT, REP, true>(p.sc, s, bid % p.chunks_per_seg, lds);
   if (N == 0) return;
 
@@ -149,11 +163,13 @@ int launch_fused(const Geometry& g, const Plan& pl, int dtype, float sm_scale, c
   p.dc = make_decode_params(g, pl, sm_scale, q, k_cache, v_cache, page_table, seq_lens, work_list, sel_cnt,
                             pl.sel_stride, out, lse, ws);
   p.dc.budget = budget;
+  p.some_dense = p.dc.some_dense = pl.some_dense;
   p.dc.cent_off = cent_off;
   p.dc.flags = reinterpret_cast<int32_t*>(ws + pl.ws_flags);
   p.dc.status = reinterpret_cast<int32_t*>(ws + pl.ws_status);
   p.score_tickets = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
-  p.chunks_per_seg = (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
+  // (one work-group a segment writes the lists when every context is covered)
+  p.chunks_per_seg = pl.all_dense ? 1 : (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
   p.n_score = p.chunks_per_seg * pl.nseg;
   const dim3 grid((unsigned)(p.n_score + pl.nseg * pl.max_splits));
   const size_t lds = max_sz(max_sz((size_t)DEC_LDS_BYTES, topk_lds_bytes(pl.max_blocks)), score_lds_bytes<1>());

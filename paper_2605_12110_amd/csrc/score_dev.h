@@ -26,18 +26,18 @@
 namespace absb {
 
 struct ScoreParams {
+  int32_t Hsel, Rk, Hkv, Hq, G;  // G: query heads folded into one selection segment (Gd)
+  int32_t agg_max;          // the group's score is the maximum over its query heads (mean pooling only)
+  int32_t chunk, tight;
   const uint16_t* q;        // [Bt][Hq][128]
-  const uint8_t* codes;     // [total][64 * R], R vectors per block
   const float* qscale;      // [nseg][128 * R]
-  const float* qmin;        // [nseg][128]: read only when agg_max
   const int32_t* cent_off;  // [nseg+1]
+  const uint8_t* codes;     // [total][64 * R], R vectors per block
   const int32_t* seq_lens;  // [Bt]
-  HeadTable heads;
   int32_t* scores;          // [total]
+  const float* qmin;        // [nseg][128]: read only when agg_max
   int32_t* score_exp;       // [nseg] or null
-  int32_t Hq, Hkv, G, chunk, tight;  // G: query heads folded into one selection segment (Gd)
-  int32_t Hsel, Rk;
-  int32_t agg_max;  // the group's score is the maximum over its query heads (mean pooling only)
+  HeadTable heads;
 };
 
 constexpr int SCORE_PLANES = 5;
