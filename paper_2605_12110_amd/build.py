@@ -26,6 +26,7 @@ _SOURCES = {
     "decode.hip": ["-ffp-contract=off"],   # FMAs are written explicitly there
     "fused.hip": ["-ffp-contract=off"],    # holds the estimation stage too
     "step.hip": ["-ffp-contract=off"],     # likewise
+    "small.hip": ["-ffp-contract=off"],    # likewise
     "util.hip": [],
 }
 

@@ -143,6 +143,14 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.step_form = opts.step_form != ABSB_STEP_AUTO ? opts.step_form
                 : by_shape ? ABSB_STEP_PIPELINED : by_units ? ABSB_STEP_UNITS : ABSB_STEP_PER_STAGE;
   p.one_launch = p.step_form != ABSB_STEP_PER_STAGE;
+  // Short segments: every attention work-group scores and selects for itself (small.hip) as long as reading all
+  // of a segment's codes takes less than the hand-overs it saves.  Measured, budgets of 512 and 2048, pipelined /
+  // this: 1 request of 64 blocks 12.2 / 10.2 us, 512 13.1 / 10.8, 1024 13.2 / 11.9, 1536 13.3 / 13.1, 2048 13.3 /
+  // 14.3; 16 requests of 1024 19.2 / 17.9 and 34.9 / 35.0.  Two vectors a block, or a pass per query head, make
+  // the scores dearer (even at 768 blocks; at 2048 blocks x heads).  With a selection per query head the
+  // scores are G times as many: never better there.
+  const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : g.repr == ABSB_REPR_MINMAX ? 768 : SMALL_MAX_BLOCKS;
+  p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
   p.bitmap_words = (p.max_blocks + 31) / 32;
   // split-K shape, in 64-token granules (one work-group step).  Measured on MI355X (256 CUs, three
   // resident work-groups each): the kernel is fastest with about two work-groups per CU, all
@@ -357,6 +365,9 @@ int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const vo
     return launch_step(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache,
                        batch->page_table, batch->seq_lens, batch->cent_off, batch->budget, sel_idx, sel_cnt,
                        sel_idx_out != nullptr, out, lse, ws, st);
+  if (p.small)
+    return launch_small(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
+                        batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
   if (p.step_form == ABSB_STEP_PIPELINED && fused_one_launch_fits(p))
     return launch_fused(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);

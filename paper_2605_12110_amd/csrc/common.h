@@ -52,6 +52,7 @@ struct Plan {
   int64_t sum_tokens;       // sum_s of the same bound
   int32_t split_tokens;     // tokens per split-K work-group
   int32_t max_splits;       // grid.x of the decode kernels
+  int32_t small;            // the pipelined step in the form of small.hip
   int32_t some_dense, all_dense;  // requests whose budget covers their context (everything is selected): any, all
   int32_t stream_rows;      // attention: K and V rows are read past the caches
   int32_t one_launch;       // absb_decode_fused: the whole step as one launch (else one launch per stage)
@@ -108,6 +109,13 @@ ABSB_HIDDEN int launch_decode_dense(const Geometry& g, const Plan& pl, int dtype
 // The whole step in one launch (estimation, selection and attention work-groups in one grid).
 ABSB_HIDDEN bool fused_one_launch_fits(const Plan& pl);
 ABSB_HIDDEN int launch_fused(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
+                             const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
+                             const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
+                             const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
+                             char* ws, hipStream_t stream);
+// The whole step in one launch for short segments: every attention work-group scores and selects for itself.
+constexpr int SMALL_MAX_BLOCKS = 1024;
+ABSB_HIDDEN int launch_small(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
                              const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
                              const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
                              const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,

@@ -296,6 +296,17 @@ def test_decode_accepts_any_list_order_partial_last_block_and_empty_lists():
     assert not dw.out_f32()[1, 0:G].any() and np.all(np.isneginf(dw.lse.cpu().numpy()[1, 0:G]))
 
 
+@pytest.mark.parametrize("L,repr_,gmax,G", [(8, 0, False, 4), (1024 * 8, 0, False, 4), (1024 * 8 + 1, 0, False, 4), (768 * 8, 1, False, 2),
+                                            (769 * 8, 1, False, 2), (512 * 8 - 3, 0, True, 4), (1023 * 8 + 5, 0, True, 2)])
+def test_short_segments_around_the_limit_of_the_form_that_selects_for_itself(L, repr_, gmax, G):
+    """Up to a number of blocks the default step lets every attention work-group score and select for itself:
+    one block, the limits of each score kind and one beyond, beside a request of a few blocks and one whose
+    budget covers it; the output must be the pipelined form's bit for bit (run_all_stages checks that)."""
+    wl = synth.tiny_workload(seed=37, dtype=synth.F16, Hq=2 * G, Hkv=2, P=16, seq_lens=(L, 100, 333), block_size=(8, 32),
+                             budget=(max(8, L // 5), 24, 400))
+    run_all_stages(wl, f"short segments L={L}", O.MINMAX if repr_ else O.MEAN, group_max=gmax)
+
+
 def test_split_shapes_do_not_change_the_selection_and_stay_within_tolerance():
     wl = synth.make_workload(1, context=8192, budget=2048)
     st = O.build_centroids(wl)
