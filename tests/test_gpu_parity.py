@@ -449,6 +449,31 @@ def test_selection_at_the_largest_supported_segment(kind):
     assert np.array_equal(sel_idx.cpu().numpy(), want_idx)
 
 
+@pytest.mark.parametrize("blocks", [16384, 16385, 32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("kind", ["random", "few_values_forced"])
+def test_selection_at_the_edges_of_its_register_tiles(blocks, kind):
+    """Segments that just fill, and just overflow, the longest register tiles of the stand-alone selection."""
+    import torch
+    from paper_2605_12110_amd import absb
+    L, T, dev = np.array([8 * blocks - 3], np.int32), np.array([8 * 1500], np.int32), "cuda:0"
+    sink, recent = (1000, 4000) if kind.endswith("forced") else (0, 0)
+    layer = absb.Layer(1, 1, 128, 64, synth.F16, np.array([8], np.int32), (64 * 128, 64 * 128, 128), sink_tokens=sink,
+                       recent_tokens=recent)
+    batch = absb.Batch(seq_lens_host=L, budget_host=T, seq_lens=torch.from_numpy(L).to(dev), page_table=None,
+                       budget=torch.from_numpy(T).to(dev), pt_stride=-(-int(L[0]) // 64))
+    plan = absb.absb_plan(layer, batch)
+    batch.cent_off = torch.from_numpy(plan.cent_off).to(dev)
+    rng = np.random.default_rng(78)
+    sc = rng.integers(-2 ** 31, 2 ** 31, size=blocks) if kind == "random" else rng.integers(-9, 10, size=blocks) * 100003
+    sc = sc.astype(np.int32)
+    sel_idx = torch.full((1, plan.sel_stride), -7, dtype=torch.int32, device=dev)
+    sel_cnt = torch.full((1,), -7, dtype=torch.int32, device=dev)
+    absb.absb_topk(layer, batch, torch.from_numpy(sc).to(dev), sel_idx, sel_cnt, plan.sel_stride)
+    _sync()
+    want_idx, want_cnt = O.topk_raw(1, 1, plan.cent_off.astype(np.int64), np.array([8], np.int32), T, sc, plan.sel_stride, L, sink, recent)
+    assert np.array_equal(sel_cnt.cpu().numpy(), want_cnt) and np.array_equal(sel_idx.cpu().numpy(), want_idx)
+
+
 # ------------------------------------------------------------------ max-min block representation
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
 def test_minmax_ragged_small_batch(dtype):
