@@ -136,15 +136,16 @@ typedef enum absb_step_form {
   ABSB_STEP_AUTO = 0,       /* by shape (see absb_decode_fused)                                    */
   ABSB_STEP_PIPELINED = 1,  /* one launch: estimation work-groups, a segment's last one selects, then
                                attention work-groups that start on the segment's flag              */
-  ABSB_STEP_UNITS = 2,      /* one launch: every work-group scores, selects and attends for its own
-                               stretch of a segment's blocks                                       */
+  ABSB_STEP_UNITS = 2,      /* one launch: the work-groups that score a segment, each a stretch of its
+                               blocks, select for it together; attention work-groups as above      */
   ABSB_STEP_PER_STAGE = 3   /* one launch per stage: score, top-k, sparse decode                   */
 } absb_step_form;
 typedef struct absb_launch_opts {
   int32_t step_form;     /* absb_step_form; read by absb_decode_fused(_static), absb_step_form_used */
   int32_t split_tokens;  /* tokens per split-K work-group of the attention kernel; multiple of 64    */
   int32_t score_chunk;   /* blocks per estimation work-group; multiple of 64                        */
-  int32_t unit_tokens;   /* ABSB_STEP_UNITS: selected tokens a work-group should get; multiple of 64 */
+  int32_t unit_tokens;   /* ABSB_STEP_UNITS without split_tokens: selected tokens an attention work-group
+                            should get; multiple of 64                                            */
   int32_t counters_zero; /* absb_sparse_decode only: 1 = the split counters at the start of the
                             workspace are known to be zero, the kernel that clears them is skipped.
                             That holds after any completed absb_sparse_decode / absb_decode_fused call
@@ -264,13 +265,15 @@ ABSB_API int absb_workspace_init(const absb_layer* layer, const absb_batch* batc
  *                        work-groups; a segment's last estimation work-group runs its selection and
  *                        raises a flag, the segment's attention work-groups start on that flag.
  *                        Chosen while no segment exceeds 16384 blocks and no list 4096 blocks.
- *   ABSB_STEP_UNITS      one launch.  Every segment is cut into units of consecutive blocks; a unit's
- *                        work-group scores its blocks, publishes a histogram row of its scores,
- *                        derives the segment's threshold from all rows, and attends over its own
- *                        selected blocks; blocks inside the threshold bin are settled by an exact
- *                        ranking among the segment's candidates.  No work-group ever passes over a
- *                        whole segment, so the cost hardly grows with the context.  Chosen for
- *                        segments beyond 16384 blocks when the chip holds all units at once.
+ *                        (Inside that range: short segments are scored and selected by every attention
+ *                        work-group for itself, long ones by their estimation work-groups together.)
+ *   ABSB_STEP_UNITS      one launch.  Every segment is cut into stretches of consecutive blocks; a stretch's
+ *                        work-group scores its blocks, adds a histogram of its scores to the segment's, and
+ *                        once all have, derives the segment's threshold from it and hands its selected
+ *                        blocks over; blocks inside the threshold bin are settled by an exact ranking among
+ *                        the segment's candidates.  No work-group ever passes over a whole segment, so the
+ *                        cost hardly grows with the context.  Chosen for segments beyond 16384 blocks when
+ *                        the chip holds all those work-groups at once.
  *   ABSB_STEP_PER_STAGE  three launches (score, top-k, sparse decode).  Otherwise.
  * The one-launch forms hand work between work-groups through the counters at the start of the
  * workspace: they must be zero when the call starts (absb_workspace_init) and are zero again when its

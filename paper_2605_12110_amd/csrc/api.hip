@@ -69,20 +69,11 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   }
 
   Plan p = {};
-  // selected tokens a unit of the one-launch step should get: two attention steps at batch 1; large
-  // batches, whose work-groups queue for the compute units anyway, do better with longer units
-  int64_t budget_tokens = 0;
-  if (batch->budget_host)
-    for (int b = 0; b < Bt; ++b) budget_tokens += (int64_t)std::min(batch->budget_host[b], batch->seq_lens_host[b]) * Hsel;
   const absb_launch_opts& opts = batch->opts;
   if (opts.step_form < ABSB_STEP_AUTO || opts.step_form > ABSB_STEP_PER_STAGE) return ABSB_ERR_BAD_SHAPE;
   if (opts.split_tokens < 0 || opts.split_tokens % 64 || opts.score_chunk < 0 || opts.score_chunk % 64 ||
       opts.unit_tokens < 0 || opts.unit_tokens % 64 || opts.counters_zero < 0 || opts.counters_zero > 1)
     return ABSB_ERR_BAD_SHAPE;
-  int unit_tokens = opts.unit_tokens;
-  if (unit_tokens <= 0) unit_tokens = budget_tokens >= 131072 ? 256 : 128;
-  p.unit_tokens = unit_tokens;
-  p.units_max = 1;
   p.nseg = Bt * Hsel;
   p.nstore = Bt * Hkv;
   int64_t max_len = 0;
@@ -109,11 +100,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       p.total += ceil_div(cap, B);
       if (N > p.max_blocks) p.max_blocks = (int32_t)N;
       const int64_t tok = K * B;
-      {
-        int su = 1, sb = 32;
-        step_units((int)K, g.heads.log2_block[h], (int)N, unit_tokens, &su, &sb);
-        if (su > p.units_max) p.units_max = su;
-      }
       if (tok > p.max_tokens) p.max_tokens = tok;
       p.sum_tokens += tok * g.Rk;  // every selection segment of the KV head reads its own tokens
     }
@@ -135,11 +121,14 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // 36 us at 256K context).  Very long lists (budgets near the context) go to the per-stage path: its
   // attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
-  // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything
-  // else together (measured at 256K context: 35.9 us per stage against 31.4 us),
-  // and the step runs as units that select among themselves, as long as the chip holds all of a
-  // batch's units at once (two work-groups per compute unit).
-  const bool by_units = !by_shape && p.max_blocks > 16384 && (int64_t)p.nseg * (p.units_max + 1) <= 480;
+  // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything else
+  // together, and the work-groups that score a segment share its selection, as long as the chip holds all
+  // of them at once: two per compute unit, or four if hardly any of the grid's places are empty.  256K context,
+  // batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 21.0 / 23.0, 25.3 / 25.6, 37.0 / 29.7 us.
+  const int shared_chunk = shared_chunk_blocks(p.max_blocks);
+  const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk);
+  const bool shared_resident = shared_grid <= 512 || (shared_grid <= 1024 && 2 * ceil_div(p.total * g.Rk, shared_chunk) >= shared_grid);
+  const bool by_units = !by_shape && p.max_blocks > 16384 && shared_resident;
   p.step_form = opts.step_form != ABSB_STEP_AUTO ? opts.step_form
                 : by_shape ? ABSB_STEP_PIPELINED : by_units ? ABSB_STEP_UNITS : ABSB_STEP_PER_STAGE;
   p.one_launch = p.step_form != ABSB_STEP_PER_STAGE;
@@ -151,7 +140,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // scores are G times as many: never better there.
   const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : g.repr == ABSB_REPR_MINMAX ? 768 : SMALL_MAX_BLOCKS;
   p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
-  p.bitmap_words = (p.max_blocks + 31) / 32;
   // split-K shape, in 64-token granules (one work-group step).  Measured on MI355X (256 CUs, three
   // resident work-groups each): the kernel is fastest with about two work-groups per CU, all
   // resident at once and each streaming as long as possible; a work-group needs at least two steps
@@ -160,6 +148,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // (the shape follows the batch, not the enqueue knob: every form of the step then cuts the
   // segments alike and gives the same bits)
   int st_tok = opts.split_tokens;
+  if (st_tok <= 0 && p.step_form == ABSB_STEP_UNITS) st_tok = opts.unit_tokens;
   if (st_tok <= 0) {
     const int64_t target_wgs = 640;
     int64_t t = ceil_div(ceil_div(p.sum_tokens, target_wgs), 64) * 64;
@@ -184,6 +173,14 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if (p.max_splits > 65535) return ABSB_ERR_BAD_SHAPE;
   if ((int64_t)p.max_splits * st_tok >= (int64_t(1) << 31)) return ABSB_ERR_BAD_SHAPE;  // positions are 32-bit
 
+  // The pipelined form shares the selection, too, where one work-group's passes over a segment take longer than the
+  // two more hand-overs (8 heads, lists of 1024 / 4096 tokens, one work-group / shared: 8192 blocks 17.0 / 17.2
+  // and 19.8 / 19.7 us, 12288 19.2 / 18.0 and 21.8 / 20.0, 16384 19.4 / 18.3 and 21.7 / 19.5).  (Forced beyond 16384
+  // blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
+  p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && p.max_blocks > 8192 &&
+                                                p.max_blocks <= 16384 && shared_resident);
+  p.shared = p.shared && shared_fits(p);
+
   // blocks per estimation work-group: 256 (one batch of loads per lane); in the one-launch step,
   // where estimation work-groups share the CUs with attention work-groups, a large batch does
   // better with two batches per work-group (the prologue is amortised, half as many work-groups)
@@ -198,10 +195,12 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.ws_score_tickets = ctr;
   p.ws_flags = 2 * ctr;
   p.ws_status = 3 * ctr;
-  p.ws_cand_done = 3 * ctr + 256;
+  p.ws_finished = 3 * ctr + 256;
   p.ws_listed = 4 * ctr + 256;
-  p.ws_cutoff = 5 * ctr + 256;
-  const size_t head = 6 * ctr + 256;
+  p.ws_counts = 5 * ctr + 256;  // SHARED_MAX_CHUNKS words a segment: as far apart as the counters
+  static_assert(SHARED_MAX_CHUNKS <= ABSB_TICKET_STRIDE, "a segment's counts words take the place of one counter");
+  p.ws_hist = 6 * ctr + 256;
+  const size_t head = p.ws_hist + (p.nseg <= SHARED_MAX_SEGMENTS ? (size_t)p.nseg * SHARED_HIST_BINS * 4 : 0);
   p.ws_head_bytes = head;
   size_t o = head;
   p.ws_scores = o;
@@ -216,17 +215,8 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.ws_part_ml = o;
   o += align256((size_t)p.nseg * p.max_splits * g.Gd * 4 * 4);  // (max, rounded sum, exact sum, -) per split and head
   p.ws_decode_bytes = o;  // the stand-alone decode uses the same offsets (the head is left unused)
-  // the unit form of the one-launch step: histogram rows, candidates, bitmaps, one partial per unit
-  p.ws_rows = o;
-  o += align256((size_t)p.nseg * p.units_max * 256 * 2);
-  p.ws_cand = o;
-  o += align256((size_t)p.total * g.Rk * 8);
-  p.ws_bitmap = o;
-  o += align256((size_t)p.nseg * p.bitmap_words * 4);
-  p.ws_unit_o = o;
-  o += align256((size_t)p.nseg * p.units_max * g.Gd * ABSB_HEAD_DIM * 4);
-  p.ws_unit_ml = o;
-  o += align256((size_t)p.nseg * p.units_max * g.Gd * 4 * 4);
+  p.ws_cand = o;  // the shared selection's candidates
+  if (p.nseg <= SHARED_MAX_SEGMENTS) o += align256((size_t)p.total * g.Rk * 8);
   p.ws_fused_bytes = o;
   (void)fused_head;
   size_t bo = head;
@@ -361,10 +351,9 @@ int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const vo
   int32_t* scores = reinterpret_cast<int32_t*>(ws + p.ws_scores);
   int32_t* sel_idx = sel_idx_out ? sel_idx_out : reinterpret_cast<int32_t*>(ws + p.ws_sel_idx);
   int32_t* sel_cnt = sel_cnt_out ? sel_cnt_out : reinterpret_cast<int32_t*>(ws + p.ws_sel_cnt);
-  if (p.step_form == ABSB_STEP_UNITS && step_fits(p))
-    return launch_step(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache,
-                       batch->page_table, batch->seq_lens, batch->cent_off, batch->budget, sel_idx, sel_cnt,
-                       sel_idx_out != nullptr, out, lse, ws, st);
+  if (p.shared)
+    return launch_shared(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
+                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
   if (p.small)
     return launch_small(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
@@ -395,7 +384,7 @@ int absb_step_form_used(const absb_layer* layer, const absb_batch* batch) {
   Plan p;
   int rc = make_plan(layer, batch, true, 0, &g, &p);
   if (rc != ABSB_OK) return rc;
-  if (p.step_form == ABSB_STEP_UNITS && step_fits(p)) return ABSB_STEP_UNITS;
+  if (p.step_form == ABSB_STEP_UNITS && p.shared) return ABSB_STEP_UNITS;
   if (p.step_form == ABSB_STEP_PIPELINED && fused_one_launch_fits(p)) return ABSB_STEP_PIPELINED;
   return ABSB_STEP_PER_STAGE;
 }

@@ -15,7 +15,6 @@
 // atomic updates (measured: 8 segments x 32 arrivals on one line cost 2.7 us, apart 0.x us).
 #define ABSB_TICKET_STRIDE 64
 #define BUILD_CHUNK 512          // tokens per work-group of the store build's pooling
-#define ABSB_STEP_MAX_UNITS 64   // work-groups that share a segment in the one-launch step
 
 namespace absb {
 
@@ -57,16 +56,14 @@ struct Plan {
   int32_t stream_rows;      // attention: K and V rows are read past the caches
   int32_t one_launch;       // absb_decode_fused: the whole step as one launch (else one launch per stage)
   int32_t step_form;        // absb_step_form actually used (never ABSB_STEP_AUTO)
-  int32_t unit_tokens;      // one-launch step: selected tokens a unit should get
-  int32_t units_max;        // max_s units of a segment
-  int32_t bitmap_words;     // words of a segment's selection bitmap
+  int32_t shared;           // the one-launch step in the form of shared.hip
   int32_t score_chunk;      // centroids per work-group in score
   int32_t build_max_chunks; // max_b ceil(L_b / BUILD_CHUNK)
   // workspace carving (byte offsets, 256-aligned)
   size_t ws_part_o, ws_part_ml, ws_tickets;       // decode partials, per-segment split counters
   size_t ws_score_tickets, ws_flags, ws_status;   // more counters of the one-launch step
-  size_t ws_cand_done, ws_listed, ws_cutoff;      // ... and of its unit form
-  size_t ws_rows, ws_cand, ws_bitmap, ws_unit_o, ws_unit_ml;
+  size_t ws_finished, ws_listed, ws_counts, ws_hist;  // ... and of its form with a shared selection
+  size_t ws_cand;
   size_t ws_head_bytes;                           // all counters: the part absb_workspace_init clears
   size_t ws_scores, ws_sel_idx, ws_sel_cnt;       // fused step intermediates
   size_t ws_cent, ws_minmax, ws_qinv;             // build intermediates
@@ -121,30 +118,22 @@ ABSB_HIDDEN int launch_small(const Geometry& g, const Plan& pl, int dtype, float
                              const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
                              char* ws, hipStream_t stream);
 ABSB_HIDDEN int launch_workspace_init(const Plan& pl, char* ws, hipStream_t stream);
-// The whole step in one launch, units of a segment doing score, selection and attention for their own blocks.
-ABSB_HIDDEN bool step_fits(const Plan& pl);
-ABSB_HIDDEN int launch_step(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
-                            const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
-                            const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
-                            const int32_t* budget, int32_t* sel_idx, int32_t* sel_cnt, bool want_list, void* out, float* lse,
-                            char* ws, hipStream_t stream);
-
-// How a segment of N blocks in use, K of them to be selected, is cut into units of the one-launch step:
-// enough units that each gets about `unit_tokens` selected tokens and scores at most 512 blocks, at
-// most ABSB_STEP_MAX_UNITS; a unit's blocks start at a multiple of 32.  Host and device agree on it.
-__host__ __device__ inline void step_units(int K, int log2_block, int N, int unit_tokens, int* units, int* unit_blocks) {
-  const long long tok = (long long)K << log2_block;
-  long long u = (tok + unit_tokens - 1) / unit_tokens;
-  const long long by_blocks = ((long long)N + 511) / 512;
-  if (u < by_blocks) u = by_blocks;
-  if (u < 1) u = 1;
-  if (u > ABSB_STEP_MAX_UNITS) u = ABSB_STEP_MAX_UNITS;
-  int cb = (int)(((long long)N + u - 1) / u);
-  cb = (cb + 31) & ~31;
-  if (cb < 32) cb = 32;
-  *unit_blocks = cb;
-  *units = N > 0 ? (N + cb - 1) / cb : 1;
+// The whole step in one launch for long segments: the work-groups that score a segment select for it together.
+constexpr int SHARED_MAX_CHUNKS = 64;     // of a segment
+constexpr int SHARED_MAX_CHUNK = 2048;    // blocks of a chunk: 2^17 blocks / 64 chunks
+constexpr int SHARED_HIST_BINS = 1024;    // words of a segment's histogram row
+constexpr int SHARED_MAX_SEGMENTS = 512;  // beyond, workspaces have no histogram rows
+constexpr int SHARED_LIST = 2048;         // list entries an attention work-group holds
+__host__ __device__ inline int shared_chunk_blocks(int max_blocks) {
+  const int cb = ((max_blocks + SHARED_MAX_CHUNKS - 1) / SHARED_MAX_CHUNKS + 63) & ~63;
+  return cb < 512 ? 512 : cb;
 }
+ABSB_HIDDEN bool shared_fits(const Plan& pl);
+ABSB_HIDDEN int launch_shared(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
+                              const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
+                              const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
+                              const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
+                              char* ws, hipStream_t stream);
 
 ABSB_HIDDEN int launch_stream_read(const void* src, size_t bytes, uint32_t* sink, int num_cus, hipStream_t stream);
 

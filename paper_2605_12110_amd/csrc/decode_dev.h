@@ -461,9 +461,9 @@ __device__ __forceinline__ void poison_rows(const DecodeParams& p, int b, int hs
 // `slots`: partial slots per segment (the stride of the partial arrays).  `on_last`: called by thread 0
 // of the segment's last work-group (the merging one, or the only one), for flags of the segment that
 // have to go back to zero: every other work-group of the segment has drawn its ticket by then.  Every
-// thread of the work-group must call.
+// thread of the work-group must call; returns (to all of them) whether this was the segment's last one.
 template <int DT, int G, class OnLast>
-__device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b, int hs, int split, int nsplit, int slots,
+__device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b, int hs, int split, int nsplit, int slots,
                                              AttnState<G>& st, char* lds, OnLast&& on_last) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   char* s_stage = lds;
@@ -535,7 +535,7 @@ __device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b
       s_last = __hip_atomic_fetch_add(p.tickets + (size_t)s * ABSB_TICKET_STRIDE, 1, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
     __syncthreads();
-    if (!s_last) return;
+    if (!s_last) return false;
     // every counter a launch touches is back at zero when the launch ends
     if (tid == 0) {
       __hip_atomic_store(p.tickets + (size_t)s * ABSB_TICKET_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -622,6 +622,7 @@ __device__ __forceinline__ void finish_split(const DecodeParams& p, int s, int b
     *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + row * ABSB_HEAD_DIM + c4 * 4) = make_uint2(lo, hi);
     if (p.lse && c4 == 0) p.lse[row] = any ? (M + __builtin_log2f(Lx)) * 0.6931471805599453f : -__builtin_inff();
   }
+  return true;
 }
 
 // Waits (thread 0, bounded in time) until the 32-bit word at `flag` is non-zero; every thread of the

@@ -104,9 +104,12 @@ struct IAdd {
 // for the group; see absb_score.  Same work split as score_chunk below: four lanes per block, the
 // packed 4-bit dots once per query head against that head's digit planes (read from LDS per head),
 // the sum of the codes shared by all heads.
-template <int DT, bool RANGE, int PF, class Sink>
+struct NoLoads {
+  __device__ __forceinline__ void operator()() const {}
+};
+template <int DT, bool RANGE, int PF, class Sink, class Hook>
 __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t, int j0, int jcount, char* lds,
-                                                     Sink&& sink, ScoreRange* range) {
+                                                     Sink&& sink, ScoreRange* range, Hook&& behind_codes) {
   constexpr int W = ABSB_HEAD_DIM, ROW_BYTES = W / 2;
   const SegMap sm = seg_map(t, p.Hsel, p.Rk, p.Hkv);
   const int b = sm.b, s = sm.s;
@@ -144,6 +147,7 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t
     pre[u] = *reinterpret_cast<const uint4*>(base + (size_t)j * ROW_BYTES);
   }
 
+  behind_codes();
   // ---- prologue (threads 0..127, one channel each): weights of every head, their largest
   // magnitude, and the heads' zero-point products summed pairwise over each run of 16 channels
   float w[ABSB_MAX_GROUP];
@@ -262,12 +266,13 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t
 // Scores of blocks [j0, j0 + jcount) of selection segment t by one work-group of 256 threads; every score is
 // handed to sink(block index, score) by one lane.  Returns the segment's block count N_s, or 0 (nothing
 // done, *range untouched) when the segment has no such blocks.  RANGE: *range receives the bounds of the
-// segment's scores.  PF: steps of 64 blocks whose codes are requested at once (a batch).
+// segment's scores.  PF: steps of 64 blocks whose codes are requested at once (a batch).  `behind_codes`: for
+// loads of the caller's that should be requested behind the first batch's.
 // `lds`: score_lds_bytes<REP>() bytes, 16-byte aligned.
-template <int DT, int REP, bool RANGE, int PF, class Sink>
+template <int DT, int REP, bool RANGE, int PF, class Sink, class Hook = NoLoads>
 __device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0, int jcount, char* lds, Sink&& sink,
-                                            ScoreRange* range) {
-  if (REP == 0 && p.agg_max) return score_blocks_groupmax<DT, RANGE, PF>(p, t, j0, jcount, lds, sink, range);
+                                            ScoreRange* range, Hook&& behind_codes = Hook()) {
+  if (REP == 0 && p.agg_max) return score_blocks_groupmax<DT, RANGE, PF>(p, t, j0, jcount, lds, sink, range, behind_codes);
   constexpr int R = REP + 1;                 // vectors per block: the mean, or maxima and minima
   constexpr int W = ABSB_HEAD_DIM * R;       // weights = values per block
   constexpr int ROW_BYTES = W / 2;
@@ -308,6 +313,7 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0,
     for (int v = 0; v < R; ++v) pre[u][v] = *reinterpret_cast<const uint4*>(base + (size_t)j * ROW_BYTES + v * 64);
   }
 
+  behind_codes();
   // ---- prologue: fixed-point image of the weights, by threads 0..W-1 (weight index = tid).
   // Mean pooling: w = (sum_g q_g) * scale.  Maxima / minima: the maxima meet the sum of the
   // group's positive q_g, the minima the sum of its negative q_g (each in order of g, from +0).

@@ -873,6 +873,35 @@ def test_one_launch_step_on_segments_longer_than_the_default_allows(context, siz
     assert int(head.abs().sum().item()) == 0, "the step left a counter, a flag or the status word set"
 
 
+@pytest.mark.parametrize("blocks,distinct,sink", [(511, 0, 0), (512, 0, 64), (513, 0, 0), (1025, 2, 0), (2049, 30, 200), (5000, 600, 0)])
+def test_shared_selection_around_its_chunks_and_in_crowded_bins(blocks, distinct, sink):
+    """The form whose estimation work-groups select together, on segments around the edges of their stretches
+    (512 blocks) and with few distinct keys, so that the threshold bin holds more blocks than are ranked and the
+    last work-group takes over; with and without the list, twice on one workspace, beside a request whose
+    budget covers it and one that the forced blocks fill."""
+    import torch
+    wl = synth.tiny_workload(seed=38, dtype=synth.F16, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 5, 300, 700), block_size=(8, 32),
+                             budget=(max(16, 2 * blocks), 300, 40))
+    if distinct:
+        rng = np.random.default_rng(distinct)
+        pal = synth.f32_to_bits(rng.standard_normal((distinct, wl.head_dim)).astype(np.float32), wl.dtype)
+        k = wl.k_cache.reshape(-1, wl.num_kv_heads, wl.page_size, wl.head_dim)
+        k[:, 0] = pal[rng.integers(0, distinct, size=k.shape[0])][:, None, :]
+    ref = O.decode_step(wl, O.build_centroids(wl), sink_tokens=sink, recent_tokens=sink)
+    dw = _dev(wl, opts=dict(step_form=2), sink_tokens=sink, recent_tokens=sink)
+    dw.build()
+    first = None
+    for want in (True, False, True):
+        dw.out.fill_(float("nan")); dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7)
+        dw.decode_fused(want_sel=want)
+        _check_out(dw, ref["out"], ref["lse"], f"shared selection, {blocks} blocks, {distinct} distinct keys, list {want}")
+        if want:
+            assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+            assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+        first = dw.out.clone() if first is None else first
+        assert torch.equal(dw.out, first) and dw.status() == 0
+
+
 @pytest.mark.parametrize("form", [1, 2])
 def test_one_launch_steps_back_to_back_and_on_two_streams(form):
     """The one-launch forms keep their hand-off counters in the workspace and leave them at zero: many
