@@ -300,8 +300,10 @@ ABSB_API int absb_decode_fused(const absb_layer* layer, const absb_batch* batch,
  * its own copy from the first use until the process ends.  The call allocates and frees nothing and
  * calls no runtime routine that does; inputs and outputs are still the caller's.  Same results as
  * absb_decode_fused with a cleared workspace of the caller's.
- *   - A (layer, batch) whose absb_plan workspace_bytes exceeds ABSB_STATIC_WORKSPACE_BYTES is refused
- *     with ABSB_ERR_STATIC_WORKSPACE before anything is enqueued.
+ *   - A (layer, batch) whose step needs more than ABSB_STATIC_WORKSPACE_BYTES is refused with
+ *     ABSB_ERR_STATIC_WORKSPACE before anything is enqueued; one whose absb_plan workspace_bytes fits never
+ *     is.  In between, the step runs without the selection shared by work-groups (ABSB_STEP_UNITS),
+ *     whose scratch memory it then does without.
  *   - The array keeps what the last call left; the call clears what must start at zero itself (a
  *     small fill kernel on `stream` whenever the batch shape's counter area differs from the last
  *     call's on that GPU), so no absb_workspace_init is needed.

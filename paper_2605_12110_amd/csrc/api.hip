@@ -18,7 +18,7 @@ static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget, int32_t sel_stride_in,
-              Geometry* geo, Plan* pl) {
+              Geometry* geo, Plan* pl, bool lean) {
   if (!layer || !batch) return ABSB_ERR_NULL;
   if (!layer->block_size || !batch->seq_lens_host) return ABSB_ERR_NULL;
   if (need_budget && !batch->budget_host) return ABSB_ERR_NULL;
@@ -148,7 +148,9 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // (the shape follows the batch, not the enqueue knob: every form of the step then cuts the
   // segments alike and gives the same bits)
   int st_tok = opts.split_tokens;
-  if (st_tok <= 0 && p.step_form == ABSB_STEP_UNITS) st_tok = opts.unit_tokens;
+  const int64_t cap_tok = ceil_div(ceil_div(p.max_tokens, 64), 64) * 64;  // at most 64 work-groups a segment
+  if (st_tok <= 0 && p.step_form == ABSB_STEP_UNITS && !lean && opts.unit_tokens > 0)
+    st_tok = (int)std::max<int64_t>(opts.unit_tokens, cap_tok);
   if (st_tok <= 0) {
     const int64_t target_wgs = 640;
     int64_t t = ceil_div(ceil_div(p.sum_tokens, target_wgs), 64) * 64;
@@ -158,7 +160,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     // steps (config 4 43.5 -> 42.0 us, config 5 at budget 8192 41.4 -> 39.2).
     if (by_shape && batch->budget_host && p.sum_tokens >= 65536)
       t = std::max<int64_t>(256, ceil_div(ceil_div(p.sum_tokens, 1100), 64) * 64);
-    const int64_t cap_tok = ceil_div(ceil_div(p.max_tokens, 64), 64) * 64;
     if (t < cap_tok) t = cap_tok;
     st_tok = (int)t;
   }
@@ -179,7 +180,8 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
   p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && p.max_blocks > 8192 &&
                                                 p.max_blocks <= 16384 && shared_resident);
-  p.shared = p.shared && shared_fits(p);
+  const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
+  p.shared = p.shared && rows && shared_fits(p);
 
   // blocks per estimation work-group: 256 (one batch of loads per lane); in the one-launch step,
   // where estimation work-groups share the CUs with attention work-groups, a large batch does
@@ -200,7 +202,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.ws_counts = 5 * ctr + 256;  // SHARED_MAX_CHUNKS words a segment: as far apart as the counters
   static_assert(SHARED_MAX_CHUNKS <= ABSB_TICKET_STRIDE, "a segment's counts words take the place of one counter");
   p.ws_hist = 6 * ctr + 256;
-  const size_t head = p.ws_hist + (p.nseg <= SHARED_MAX_SEGMENTS ? (size_t)p.nseg * SHARED_HIST_BINS * 4 : 0);
+  const size_t head = p.ws_hist + (rows ? (size_t)p.nseg * SHARED_HIST_BINS * 4 : 0);
   p.ws_head_bytes = head;
   size_t o = head;
   p.ws_scores = o;
@@ -209,16 +211,14 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   o += align256((size_t)p.nseg * (size_t)(p.sel_stride > 0 ? p.sel_stride : 1) * 4);
   p.ws_sel_cnt = o;
   o += align256((size_t)p.nseg * 4);
-  const size_t fused_head = o;
   p.ws_part_o = o;
   o += align256((size_t)p.nseg * p.max_splits * g.Gd * ABSB_HEAD_DIM * 4);
   p.ws_part_ml = o;
   o += align256((size_t)p.nseg * p.max_splits * g.Gd * 4 * 4);  // (max, rounded sum, exact sum, -) per split and head
   p.ws_decode_bytes = o;  // the stand-alone decode uses the same offsets (the head is left unused)
   p.ws_cand = o;  // the shared selection's candidates
-  if (p.nseg <= SHARED_MAX_SEGMENTS) o += align256((size_t)p.total * g.Rk * 8);
+  if (rows) o += align256((size_t)p.total * g.Rk * 8);
   p.ws_fused_bytes = o;
-  (void)fused_head;
   size_t bo = head;
   p.ws_cent = bo;
   const size_t width = (size_t)ABSB_HEAD_DIM * (g.repr + 1);  // values per block
@@ -332,13 +332,13 @@ int absb_sparse_decode(const absb_layer* layer, const absb_batch* batch, const v
                        batch->opts.counters_zero == 1, static_cast<hipStream_t>(stream));
 }
 
-int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const void* q, const uint8_t* codes,
-                      const float* qscale, const void* k_cache, const void* v_cache, void* out, float* lse,
-                      int32_t* sel_idx_out, int32_t* sel_cnt_out, void* workspace, size_t workspace_bytes,
-                      void* stream) {
+static int decode_fused(const absb_layer* layer, const absb_batch* batch, bool lean, const void* q, const uint8_t* codes,
+                        const float* qscale, const void* k_cache, const void* v_cache, void* out, float* lse,
+                        int32_t* sel_idx_out, int32_t* sel_cnt_out, void* workspace, size_t workspace_bytes,
+                        void* stream) {
   Geometry g;
   Plan p;
-  int rc = make_plan(layer, batch, true, 0, &g, &p);
+  int rc = make_plan(layer, batch, true, 0, &g, &p, lean);
   if (rc != ABSB_OK) return rc;
   if (!q || !codes || !qscale || !k_cache || !v_cache || !out || !batch->seq_lens || !batch->page_table ||
       !batch->cent_off || !batch->budget)
@@ -377,6 +377,14 @@ int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const vo
   if (rc != ABSB_OK) return rc;
   return launch_decode(g, p, layer->dtype, resolve_scale(layer), q, k_cache, v_cache, batch->page_table,
                        batch->seq_lens, sel_idx, sel_cnt, p.sel_stride, out, lse, ws, true, st);
+}
+
+int absb_decode_fused(const absb_layer* layer, const absb_batch* batch, const void* q, const uint8_t* codes,
+                      const float* qscale, const void* k_cache, const void* v_cache, void* out, float* lse,
+                      int32_t* sel_idx_out, int32_t* sel_cnt_out, void* workspace, size_t workspace_bytes,
+                      void* stream) {
+  return decode_fused(layer, batch, false, q, codes, qscale, k_cache, v_cache, out, lse, sel_idx_out, sel_cnt_out, workspace,
+                      workspace_bytes, stream);
 }
 
 int absb_step_form_used(const absb_layer* layer, const absb_batch* batch) {
@@ -549,7 +557,13 @@ int absb_decode_fused_static(const absb_layer* layer, const absb_batch* batch, c
   Plan p;
   int rc = make_plan(layer, batch, true, 0, &g, &p);
   if (rc != ABSB_OK) return rc;
-  if (p.ws_fused_bytes > (size_t)ABSB_STATIC_WORKSPACE_BYTES) return ABSB_ERR_STATIC_WORKSPACE;
+  // Near the array's size the shared selection's memory (4 KB a segment, 8 bytes a block) is given up before the call is.
+  const bool lean = p.ws_fused_bytes > (size_t)ABSB_STATIC_WORKSPACE_BYTES;
+  if (lean) {
+    rc = make_plan(layer, batch, true, 0, &g, &p, true);
+    if (rc != ABSB_OK) return rc;
+    if (p.ws_fused_bytes > (size_t)ABSB_STATIC_WORKSPACE_BYTES) return ABSB_ERR_STATIC_WORKSPACE;
+  }
   std::lock_guard<std::mutex> hold(g_static_ws_lock);
   int dev = 0;
   StaticWorkspace* w = nullptr;
@@ -564,8 +578,8 @@ int absb_decode_fused_static(const absb_layer* layer, const absb_batch* batch, c
     if (rc != ABSB_OK) return rc;
     w->head_bytes = p.ws_head_bytes;
   }
-  return absb_decode_fused(layer, batch, q, codes, qscale, k_cache, v_cache, out, lse, sel_idx_out, sel_cnt_out, w->ptr,
-                           (size_t)ABSB_STATIC_WORKSPACE_BYTES, stream);
+  return decode_fused(layer, batch, lean, q, codes, qscale, k_cache, v_cache, out, lse, sel_idx_out, sel_cnt_out, w->ptr,
+                      (size_t)ABSB_STATIC_WORKSPACE_BYTES, stream);
 }
 
 }  // extern "C"

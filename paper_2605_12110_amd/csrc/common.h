@@ -72,9 +72,10 @@ struct Plan {
 
 // Validates the host-visible arguments and fills geometry + plan.  `need_budget`: budget_host
 // must be present (topk, fused); otherwise it is used when present.  `sel_stride_in` > 0 bounds
-// the selected-token estimate for the stand-alone decode.
+// the selected-token estimate for the stand-alone decode.  `lean`: a workspace without the shared
+// selection's histogram rows and candidates, and so a step without it.
 ABSB_HIDDEN int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget,
-                          int32_t sel_stride_in, Geometry* geo, Plan* plan);
+                          int32_t sel_stride_in, Geometry* geo, Plan* plan, bool lean = false);
 
 // Launchers (one per stage); all enqueue on `stream` and return an absb_status.
 ABSB_HIDDEN int launch_build(const Geometry& g, const Plan& pl, int dtype, const void* k_cache,

@@ -14,14 +14,14 @@ pytestmark = pytest.mark.gpu
 TOL = {synth.F16: 2e-3, synth.BF16: 1e-2}
 
 
-def _both_entry_points(wl, what):
+def _both_entry_points(wl, what, opts=None, fits=True):
     import torch
     from paper_2605_12110_amd import absb
     from paper_2605_12110_amd.device import DeviceWorkload
     print(f"[no-alloc {what}] Bt={wl.batch} L={wl.seq_lens.tolist()} B={wl.block_size.tolist()} "
           f"T={wl.budget.tolist()} dtype={wl.dtype}", flush=True)
-    dw = DeviceWorkload(wl)
-    assert dw.plan.workspace_bytes <= absb.STATIC_WORKSPACE_BYTES
+    dw = DeviceWorkload(wl, opts=opts)
+    assert (dw.plan.workspace_bytes <= absb.STATIC_WORKSPACE_BYTES) == fits
     dw.build()
     # the existing entry point, on the caller's workspace
     dw.decode_fused()
@@ -57,6 +57,17 @@ def test_zz_static_scratch_step_matches_workspace_step_twice_second_call_smaller
     small = synth.make_workload(1, batch=1, context=1100, budget=200, seed=72)       # 8 segments, ragged tail
     _both_entry_points(big, "first call")
     _both_entry_points(small, "second call, smaller")
+
+
+@pytest.mark.parametrize("form", [0, 2])
+def test_zz_static_scratch_gives_up_the_shared_selection_before_the_call(form):
+    """512 segments: the step needs 15.3 MiB, with the shared selection's rows 17.4: more than the array has.  The call
+    is taken all the same (asked for the form that shares, too), and so is a smaller one after it."""
+    near = synth.tiny_workload(seed=73, Hq=128, Hkv=32, P=16, seq_lens=(18,) * 15 + (1200,), block_size=(8, 32, 16, 128) * 8,
+                               budget=(16,) * 15 + (832,))
+    small = synth.make_workload(1, batch=1, context=1100, budget=200, seed=74)
+    _both_entry_points(near, f"near the array's size, form {form}", dict(step_form=form, split_tokens=64), fits=False)
+    _both_entry_points(small, "smaller, after it", dict(step_form=form))
 
 
 def test_zz_static_scratch_refuses_what_it_cannot_hold():
