@@ -568,7 +568,7 @@ def main():
                     help="block representation: mean pooling (headline) or channel-wise maxima and minima")
     ap.add_argument("--form", type=int, default=0, choices=(0, 1, 2, 3),
                     help="how absb_decode_fused is enqueued (absb_step_form): 0 = the library's choice by shape "
-                         "(default), 1 = pipelined one-launch step, 2 = one-launch step of units, 3 = one launch per stage")
+                         "(default), 1 = pipelined one-launch step, 2 = one launch with the selection shared by work-groups, 3 = one launch per stage")
     ap.add_argument("--split-tokens", type=int, default=0, help="absb_launch_opts.split_tokens (0 = the library's choice)")
     ap.add_argument("--unit-tokens", type=int, default=0, help="absb_launch_opts.unit_tokens (0 = the library's choice)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
@@ -619,7 +619,7 @@ def main():
     wl = wl0
     headline = (args.config == 3 and args.context is None and args.batch is None and args.budget is None
                 and block_repr == 0 and args.select == "group")
-    form_name = {absb.STEP_PIPELINED: "pipelined (one launch)", absb.STEP_UNITS: "units (one launch)",
+    form_name = {absb.STEP_PIPELINED: "pipelined (one launch)", absb.STEP_UNITS: "shared selection (one launch)",
                  absb.STEP_PER_STAGE: "per stage (three launches)"}[m["form"]]
     stages = {k: round(v, 3) for k, v in m["stages"].items()}
     if headline:
@@ -670,8 +670,9 @@ def main():
         },
     }
     if m["launches"] == 1:
-        # the step is one launch: the dominant kernel is the step itself
-        kern = "fused_step_kernel" if m["form"] == absb.STEP_PIPELINED else "step_kernel"
+        # the step is one launch: the dominant kernel is the step itself (csrc/shared.hip selects for long segments,
+        # small.hip for short ones, fused.hip in between; the rule is the library's)
+        kern = "shared_step_kernel" if headline and args.form == 0 or m["form"] == absb.STEP_UNITS else "one-launch step"
         result["roofline"] = {
             "bound": "hbm",
             "kernel": f"{kern} (one absb_decode_fused call = one launch: estimation, selection, attention)",

@@ -26,8 +26,8 @@
 //     come out in all lanes, the softmax runs in place, and the weights only have to cross between the four
 //     groups of 16 lanes (register swaps);
 //   * K of the next step is requested once the S product has consumed this step's, V four rows at a time behind the
-//     product that consumed them: with ~100 registers a work-group has 32 KB of rows in flight nearly always,
-//     and five work-groups fit a compute unit.
+//     product that consumed them: a work-group has 32 KB of rows in flight nearly always, and with at most 128
+//     registers a lane (112-114 in the stand-alone kernel) four work-groups fit a compute unit.
 // The addresses of a wave's steps come from its lanes: lane j looks up the block and page of eight consecutive
 // tokens (half j % 2 of step j / 2; B >= 8 and P >= 8, so they lie in one block and one page), for 32 steps at once.
 #pragma once
