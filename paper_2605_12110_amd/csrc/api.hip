@@ -114,12 +114,11 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if ((int64_t)batch->pt_stride < ceil_div(max_len, P)) return ABSB_ERR_BAD_SHAPE;
 
   // How absb_decode_fused is enqueued.  Measured on MI355X with cold caches (every step on a copy
-  // of the layer that the last-level cache has forgotten): the pipelined one-launch step wins by
-  // 6-12 % (config 1: 16.6 against 18.9 us, config 2: 30.5 / 32.6, config 3: 22.2 / 24.3, config 4:
-  // 52.5 / 56.5) wherever no segment is longer than 16384 blocks, the longest register tile of its
-  // 256-thread selection; beyond (keys re-read) that selection takes several times longer (69 against
-  // 36 us at 256K context).  Very long lists (budgets near the context) go to the per-stage path: its
-  // attention kernel reads the lists through the L2.
+  // of the layer that the last-level cache has forgotten): one launch against one per stage, 1 request of 4K
+  // 14.4 / 16.3 us, 8 of 32K 28.3 / 30.4, 1 of 128K 21.1 / 23.7, 16 of 8K-128K 49.5 / 55.2.  A selection by one
+  // work-group holds 16384 blocks in its registers; beyond (keys re-read) it takes several times longer (67
+  // against 28 us a step at 256K context).  Very long lists (budgets near the context) go to the per-stage
+  // path: its attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
   // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything else
   // together, and the work-groups that score a segment share its selection, as long as the chip holds all
