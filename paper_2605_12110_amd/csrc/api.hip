@@ -175,10 +175,11 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
 
   // The pipelined form shares the selection, too, where one work-group's passes over a segment take longer than the
   // two more hand-overs (8 heads, lists of 1024 / 4096 tokens, one work-group / shared: 8192 blocks 17.0 / 17.2
-  // and 19.8 / 19.7 us, 12288 19.2 / 18.0 and 21.8 / 20.0, 16384 19.4 / 18.3 and 21.7 / 19.5).  (Forced beyond 16384
+  // and 19.8 / 19.7 us, 12288 19.2 / 18.0 and 21.8 / 20.0, 16384 19.4 / 18.3 and 21.7 / 19.5).  Not with the
+  // group's maximum, whose scores come a pass per query head: 128K, batch 1, 23.9 / 25.4 us.  (Forced beyond 16384
   // blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
-  p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && p.max_blocks > 8192 &&
-                                                p.max_blocks <= 16384 && shared_resident);
+  p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && !g.agg_max &&
+                                                p.max_blocks > 8192 && p.max_blocks <= 16384 && shared_resident);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
   p.shared = p.shared && rows && shared_fits(p);
 
