@@ -270,11 +270,11 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
   const char* kbase = reinterpret_cast<const char*>(p.k) + head_off + grp * 16;
   const char* vbase = reinterpret_cast<const char*>(p.v) + head_off;
   const uint32_t lane4 = lane * 4;
-  const uint32_t pitch = (uint32_t)p.g.s_tok * 2;
+  const uint64_t pitch = (uint64_t)p.g.s_tok * 2;  // (any stride that fits the card: eight rows can span more than 4 GB)
 
   // ---- lane j: half j % 2 of step j / 2 of the current 32 steps.  `off`: byte offset of its first row (of a
-  // legal token, whatever the list holds), `most`: last of its eight rows that exists, in bytes from the first;
-  // `nv`: how many of them count
+  // legal token, whatever the list holds), `most`: which of its eight rows is the last that exists; `nv`: how
+  // many of them count
   uint64_t off = 0;
   int most = 0, nv = 0, entry = 0;
   auto look_up = [&](int step0) __attribute__((always_inline)) {
@@ -284,7 +284,7 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
     const int tc = max(0, min(t8, L - 1)) & ~7;
     off = ((uint64_t)pages.at(tc >> lP) * (uint64_t)p.g.s_page + (uint64_t)(tc & ((1 << lP) - 1)) * (uint64_t)p.g.s_tok) * 2;
     nv = min(8, min(pos_end - pos8, L - t8));
-    most = (nv > 0 ? min(7, L - 1 - tc) : 0) * (int)pitch;  // rows nobody needs: one line, not eight
+    most = nv > 0 ? min(7, L - 1 - tc) : 0;  // rows nobody needs: one line, not eight
   };
   u32x4 k[4];
   uint32_t v[16];
@@ -298,8 +298,8 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
       v_most[h] = (uint32_t)__builtin_amdgcn_readlane(most, j + h);
     }
     const uint64_t o = li < 8 ? v_off[0] : v_off[1];
-    const uint32_t r = min((uint32_t)(li & 7) * pitch, li < 8 ? v_most[0] : v_most[1]);
-    const char* row = kbase + o + r;
+    const uint32_t r = min((uint32_t)(li & 7), li < 8 ? v_most[0] : v_most[1]);
+    const char* row = kbase + (o + r * pitch);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u32x4* piece = reinterpret_cast<const u32x4*>(row + 64 * i);
@@ -310,7 +310,7 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = 4 * t + i;
-      const char* row = vbase + (v_off[r >> 3] + min((uint32_t)(r & 7) * pitch, v_most[r >> 3]));  // a scalar
+      const char* row = vbase + (v_off[r >> 3] + min((uint32_t)(r & 7), v_most[r >> 3]) * pitch);  // a scalar
       const uint32_t* pair = reinterpret_cast<const uint32_t*>(row + lane4);
       v[r] = STREAM ? __builtin_nontemporal_load(pair) : *pair;
     }

@@ -353,6 +353,40 @@ def test_nonstandard_cache_strides_nhd_layout():
     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
 
 
+@pytest.mark.parametrize("stride_tok", [153391696, 320 << 20])
+def test_token_strides_whose_eight_rows_span_gigabytes(stride_tok):
+    """The slot as the outermost dimension of a cache: eight rows of a block lie up to 7 * stride_tok elements apart.
+    From 153391696 elements on seven strides pass 2^31 bytes, from 306783384 on 2^32.  Every form of the step, the
+    stand-alone attention and the store build must address such a cache as they address the same data in pages."""
+    import torch
+    from paper_2605_12110_amd import absb
+    wl = synth.tiny_workload(seed=36, dtype=synth.F16, Hq=8, Hkv=2, P=8, seq_lens=(151, 1290), block_size=(8, 32), budget=(48, 400))
+    ref = O.decode_step(wl, O.build_centroids(wl))
+    H, P, d = wl.num_kv_heads, wl.page_size, wl.head_dim
+    plain, far = _dev(wl), _dev(wl)
+    pages = plain.k_cache.shape[0]
+    assert pages * H * d <= stride_tok
+    for name in ("k_cache", "v_cache"):
+        buf = torch.empty((P - 1) * stride_tok + pages * H * d, dtype=plain.torch_dtype, device="cuda")
+        view = buf.as_strided((pages, H, P, d), (H * d, d, stride_tok, 1))
+        view.copy_(getattr(plain, name).view(pages, H, P, d))
+        setattr(far, name, buf)
+    far.layer = absb.Layer(wl.num_q_heads, H, d, P, wl.dtype, wl.block_size, (H * d, d, stride_tok))
+    for dw in (plain, far):
+        dw.build()
+    assert torch.equal(far.codes, plain.codes) and torch.equal(far.qscale, plain.qscale)
+    for form in (0, 1, 2, 3):
+        for dw in (plain, far):
+            with _opts(dw, step_form=form):
+                dw.out.fill_(float("nan"))
+                dw.decode_fused()
+        _check_out(far, ref["out"], ref["lse"], f"token stride {stride_tok}, form {form}")
+        assert torch.equal(far.out, plain.out) and torch.equal(far.lse, plain.lse) and torch.equal(far.sel_idx, plain.sel_idx)
+    far.out.fill_(float("nan"))
+    far.sparse_decode()
+    _check_out(far, ref["out"], ref["lse"], f"token stride {stride_tok}, stand-alone attention")
+
+
 def test_many_splits_per_segment_and_split_counters_left_at_zero():
     """More splits than one merge round trip covers; then the stand-alone attention call with the
     caller's promise that the split counters are zero (they are: every launch leaves them so, and
