@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
 from dataclasses import dataclass
 from typing import Optional, Sequence
 
@@ -208,15 +209,20 @@ class Batch:
 
     def __setattr__(self, name, value):
         d = self.__dict__
-        d[name] = value
-        if "_dirty" in d:
-            d["_dirty"].add(name)
+        with _record_lock:
+            d[name] = value
+            if "_dirty" in d:
+                d["_dirty"].add(name)
 
     def c(self) -> _Batch:
         """The absb_batch record.  Kept between calls: a reassigned field (a decode loop's lengths) is carried
         over into a copy of the record, so a call in flight on another thread keeps the one it was given
-        (with the host arrays it points into); the tensors must stay alive."""
-        d = self.__dict__
+        (with the host arrays it points into), and no thread gets a record from before a reassignment; the
+        tensors must stay alive."""
+        with _record_lock:
+            return self._record(self.__dict__)
+
+    def _record(self, d) -> _Batch:
         rec = d.get("_c")
         if rec is None:
             d["_dirty"] = set()
@@ -258,6 +264,7 @@ class Batch:
                 rec.pt_stride = int(pts)
 
 
+_record_lock = threading.RLock()    # of every batch: held for microseconds, and never around a call into the library
 _BATCH_HOST_ARRAYS = frozenset(("seq_lens_host", "budget_host", "cap_lens_host"))
 _BATCH_TENSORS = frozenset(("seq_lens", "page_table", "cent_off", "budget", "qmin"))
 _BATCH_FIELDS = (*_BATCH_HOST_ARRAYS, *_BATCH_TENSORS, "pt_stride")

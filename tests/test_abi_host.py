@@ -3,6 +3,7 @@ symbol the header declares, plans sizes correctly and rejects bad arguments befo
 import ctypes as C
 import os
 import re
+import threading
 
 import numpy as np
 import pytest
@@ -185,6 +186,32 @@ def test_launch_options_are_per_call_and_validated():
                dict(step_form=1), dict(step_form=2), dict(step_form=3)):
         absb.absb_plan(layer, batch(**ok))
     assert not hasattr(absb.load(), "absb_set_tuning")
+
+
+def test_a_second_thread_gets_the_reassigned_fields_while_the_first_carries_them_over(monkeypatch):
+    """A scheduler reassigns a batch's lengths, then two threads call with it: whichever comes second must not be
+    handed the record from before the reassignment while the first one is still at work on the new one."""
+    batch = _batch((64,), (8,))
+    batch.c()
+    batch.seq_lens_host = [128]
+    real, inside, go, got = absb._i32_host, threading.Event(), threading.Event(), []
+
+    def slow(a):
+        inside.set()
+        go.wait(10)
+        return real(a)
+    monkeypatch.setattr(absb, "_i32_host", slow)
+    length = lambda: C.cast(batch.c().seq_lens_host, C.POINTER(C.c_int32))[0]  # noqa: E731
+    threads = [threading.Thread(target=lambda: got.append(length())) for _ in range(2)]
+    threads[0].start()
+    assert inside.wait(10)
+    monkeypatch.setattr(absb, "_i32_host", real)
+    threads[1].start()
+    threads[1].join(0.2)                       # (returns at once with a stale record, or waits for the first thread)
+    go.set()
+    for t in threads:
+        t.join(10)
+    assert got == [128, 128]
 
 
 def test_enqueue_form_of_the_fused_step_follows_the_longest_segment():
