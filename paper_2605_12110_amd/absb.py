@@ -215,10 +215,10 @@ class Batch:
                 d["_dirty"].add(name)
 
     def c(self) -> _Batch:
-        """The absb_batch record.  Kept between calls: a reassigned field (a decode loop's lengths) is carried
-        over into a copy of the record, so a call in flight on another thread keeps the one it was given
-        (with the host arrays it points into), and no thread gets a record from before a reassignment; the
-        tensors must stay alive."""
+        """The absb_batch record.  Kept until a field is reassigned (a decode loop's lengths); then that field, and
+        any other that was changed in place since, is carried over into a copy of the record, so a call in flight on
+        another thread keeps the one it was given (with the host arrays it points into), and no thread gets
+        a record from before a reassignment; the tensors must stay alive."""
         with _record_lock:
             return self._record(self.__dict__)
 
@@ -227,13 +227,22 @@ class Batch:
         if rec is None:
             d["_dirty"] = set()
             rec = _Batch()
-            rec._arrays, rec._opts = {}, None
+            rec._arrays, rec._at, rec._opts = {}, {}, None
             self._fill(rec, _BATCH_FIELDS)
             d["_c"] = rec
         elif d["_dirty"]:
             names, d["_dirty"] = d["_dirty"], set()
             old, rec = rec, _Batch.from_buffer_copy(rec)
-            rec._arrays, rec._opts = dict(old._arrays), old._opts
+            rec._arrays, rec._at, rec._opts = dict(old._arrays), dict(old._at), old._opts
+            # what is held by address only (tensors), or as a converted copy (lists), may have changed in place
+            for name, arr in old._arrays.items():
+                if d[name] is not arr:
+                    names.add(name)
+            for name, at in old._at.items():
+                if _ptr(d[name]) != at:
+                    names.add(name)
+            if self.pt_stride is None:
+                names.add("pt_stride")
             try:
                 self._fill(rec, names)
             except Exception:
@@ -256,7 +265,8 @@ class Batch:
                 if name == "seq_lens_host":
                     rec.batch = len(rec._arrays[name])
             elif name in _BATCH_TENSORS:
-                setattr(rec, name, _ptr(value))
+                rec._at[name] = address = _ptr(value)
+                setattr(rec, name, address)
             if name in ("page_table", "pt_stride"):
                 pts = self.pt_stride
                 if pts is None:

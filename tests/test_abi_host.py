@@ -188,6 +188,23 @@ def test_launch_options_are_per_call_and_validated():
     assert not hasattr(absb.load(), "absb_set_tuning")
 
 
+@pytest.mark.parametrize("make", [list, lambda v: np.array(v, np.int64), lambda v: np.array(v, np.int32)])
+def test_reassigning_one_field_takes_in_what_changed_in_place_in_the_others(make):
+    """Lists and arrays of another type are converted, tensors held by address: edited in place, they are as the
+    caller sees them once any field has been reassigned."""
+    import torch
+    lens, table = make([64, 100]), torch.zeros((2, 4), dtype=torch.int32)
+    batch = absb.Batch(seq_lens_host=lens, budget_host=[8, 8], page_table=table)
+    batch.c()
+    lens[0] = 256
+    table.resize_((2, 64))
+    batch.budget_host = [16, 16]
+    rec = batch.c()
+    assert C.cast(rec.seq_lens_host, C.POINTER(C.c_int32))[0] == 256
+    assert C.cast(rec.budget_host, C.POINTER(C.c_int32))[1] == 16
+    assert rec.page_table == table.data_ptr() and rec.pt_stride == 64
+
+
 def test_a_second_thread_gets_the_reassigned_fields_while_the_first_carries_them_over(monkeypatch):
     """A scheduler reassigns a batch's lengths, then two threads call with it: whichever comes second must not be
     handed the record from before the reassignment while the first one is still at work on the new one."""
