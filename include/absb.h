@@ -182,7 +182,10 @@ typedef struct absb_batch {
  *                              cap_lens_host is given                          (may be NULL)
  *   total_centroids          : off[Bt*Hkv] (rows of the code array, used or not)
  *   sel_stride               : max_s K_s, K_s = min(N_s, ceil(T_b/B_h)) (Sec. 3.4 kernel 2)
- *   workspace_bytes          : enough for any entry point below on this (layer, batch) */
+ *   workspace_bytes          : enough for any entry point below on this (layer, batch); with cap_lens_host,
+ *                              also at every other lengths that cap_lens_host allows, so that one
+ *                              workspace serves contexts while they grow (a step's need is not
+ *                              monotone in the lengths: longer lists are cut into longer splits)  */
 ABSB_API int absb_plan(const absb_layer* layer, const absb_batch* batch, int32_t* cent_off_host,
                        int64_t* total_centroids, int32_t* sel_stride, size_t* workspace_bytes);
 

@@ -17,6 +17,13 @@ static inline int ilog2(int64_t v) {
 static inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The split-K partials of a step with that many splits a segment: outputs, and (max, rounded sum, exact sum, -) a head.
+static size_t partial_bytes(const Geometry& g, const Plan& p, int64_t splits) {
+  const size_t rows = (size_t)p.nseg * (size_t)splits * g.Gd;
+  return align256(rows * ABSB_HEAD_DIM * 4) + align256(rows * 4 * 4);
+}
+constexpr int MAX_SPLITS_CHOSEN = 64;  // of a segment, unless the caller says what a split is
+
 int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget, int32_t sel_stride_in,
               Geometry* geo, Plan* pl, bool lean) {
   if (!layer || !batch) return ABSB_ERR_NULL;
@@ -147,7 +154,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // (the shape follows the batch, not the enqueue knob: every form of the step then cuts the
   // segments alike and gives the same bits)
   int st_tok = opts.split_tokens;
-  const int64_t cap_tok = ceil_div(ceil_div(p.max_tokens, 64), 64) * 64;  // at most 64 work-groups a segment
+  const int64_t cap_tok = ceil_div(ceil_div(p.max_tokens, MAX_SPLITS_CHOSEN), 64) * 64;
   if (st_tok <= 0 && p.step_form == ABSB_STEP_UNITS && !lean && opts.unit_tokens > 0)
     st_tok = (int)std::max<int64_t>(opts.unit_tokens, cap_tok);
   if (st_tok <= 0) {
@@ -212,9 +219,8 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.ws_sel_cnt = o;
   o += align256((size_t)p.nseg * 4);
   p.ws_part_o = o;
-  o += align256((size_t)p.nseg * p.max_splits * g.Gd * ABSB_HEAD_DIM * 4);
-  p.ws_part_ml = o;
-  o += align256((size_t)p.nseg * p.max_splits * g.Gd * 4 * 4);  // (max, rounded sum, exact sum, -) per split and head
+  p.ws_part_ml = o + align256((size_t)p.nseg * p.max_splits * g.Gd * ABSB_HEAD_DIM * 4);
+  o += partial_bytes(g, p, p.max_splits);
   p.ws_decode_bytes = o;  // the stand-alone decode uses the same offsets (the head is left unused)
   p.ws_cand = o;  // the shared selection's candidates
   if (rows) o += align256((size_t)p.total * g.Rk * 8);
@@ -233,6 +239,20 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if (geo) *geo = g;
   if (pl) *pl = p;
   return ABSB_OK;
+}
+
+// A workspace for every length on the way to the capacity.  All parts grow with the lengths except the partials: longer
+// lists get longer splits, and so at times fewer of them.
+static size_t growing_workspace_bytes(const absb_layer* layer, const absb_batch* batch, const Plan& now) {
+  absb_batch longest = *batch;
+  longest.seq_lens_host = batch->cap_lens_host;
+  longest.pt_stride = INT32_MAX;  // (the page table may grow with the contexts)
+  Geometry g;
+  Plan p;
+  if (make_plan(layer, &longest, false, 0, &g, &p) != ABSB_OK) return now.ws_bytes;
+  const int64_t most = batch->opts.split_tokens > 0 ? p.max_splits : std::min<int64_t>(MAX_SPLITS_CHOSEN, ceil_div(p.max_tokens, 64));
+  const size_t step = p.ws_fused_bytes - partial_bytes(g, p, p.max_splits) + partial_bytes(g, p, std::max<int64_t>(most, p.max_splits));
+  return std::max({now.ws_bytes, p.ws_build_bytes, step});
 }
 
 static int check_ws(const void* ws, size_t have, size_t need) {
@@ -270,7 +290,7 @@ int absb_plan(const absb_layer* layer, const absb_batch* batch, int32_t* cent_of
   }
   if (total_centroids) *total_centroids = p.total;
   if (sel_stride) *sel_stride = p.sel_stride;
-  if (workspace_bytes) *workspace_bytes = p.ws_bytes;
+  if (workspace_bytes) *workspace_bytes = batch->cap_lens_host ? growing_workspace_bytes(layer, batch, p) : p.ws_bytes;
   return ABSB_OK;
 }
 

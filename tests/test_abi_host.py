@@ -349,3 +349,23 @@ def test_plan_lays_the_store_out_for_the_capacity_lengths_when_given():
     with pytest.raises(absb.AbsbError) as e:                          # a layout shorter than the context
         absb.absb_plan(layer, absb.Batch(seq_lens_host=[1000], budget_host=[64], pt_stride=64, cap_lens_host=[999]))
     assert e.value.status == absb.ERR_BAD_SHAPE
+
+
+def test_a_workspace_planned_for_the_capacity_serves_every_length_on_the_way():
+    """Longer lists get longer splits, and so at times fewer partials: the plan of a layout with room to grow covers
+    the lengths before the last ones, too (what the step needs at lengths L is at least the tight plan's)."""
+    rng = np.random.default_rng(3)
+    for trial in range(60):
+        kv, G = int(rng.choice([2, 8])), int(rng.choice([1, 4, 8]))
+        layer = _layer(num_q_heads=kv * G, num_kv_heads=kv, block_size=[int(x) for x in rng.choice([8, 16, 32, 64], kv)],
+                       selection=int(rng.integers(0, 3)))
+        n = int(rng.integers(1, 17))
+        cap = rng.integers(40, 20000 if trial % 2 else 1200, n)
+        budget = [int(rng.choice([300, 2048, 9310]))] * n
+        wide = dict(pt_stride=1 << 16)
+        room = absb.absb_plan(layer, _batch(cap.tolist(), budget, cap_lens_host=cap.tolist(), **wide)).workspace_bytes
+        for back in (0, 1, 7, 30, *rng.integers(1, 20000, 12)):
+            lens = np.maximum(1, cap - back).tolist()
+            assert room >= absb.absb_plan(layer, _batch(lens, budget, **wide)).workspace_bytes, (trial, lens)
+            grown = absb.absb_plan(layer, _batch(lens, budget, cap_lens_host=cap.tolist(), **wide)).workspace_bytes
+            assert grown >= room                   # ... whatever lengths it is asked at
