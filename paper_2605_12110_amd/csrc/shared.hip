@@ -483,20 +483,25 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   // ---- the segment's last split: what the launch used goes back to zero.  Every other split has drawn its ticket, and
   // every chunk has counted itself finished before its counts word could be complete for the splits, or does
   // so right after; the last chunk may still be reading counts words for the caller's list.
+  int* s_gone = s_word + 1;  // (finish_split uses the word before it)
   if (tid == 0) {
     const int32_t* fin = p.finished + (size_t)t * ABSB_TICKET_STRIDE;
     const int32_t* listed = p.listed + (size_t)t * ABSB_TICKET_STRIDE;
     const bool crowd = ld_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE) != 0;
     const uint64_t t0 = wall_clock64();
-    while ((ld_i32<true>(fin) != C || (p.want_list && !crowd && !ld_i32<true>(listed))) &&
+    bool there;
+    while (!(there = ld_i32<true>(fin) == C && (!p.want_list || crowd || ld_i32<true>(listed))) &&
            wall_clock64() - t0 < DEC_WAIT_LIMIT_TICKS)
       __builtin_amdgcn_s_sleep(2);
+    if (!there) st_i32<true>(d.status, 1);
+    *s_gone = !there;
     st_i32<true>(p.arrive + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.listed + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
   }
   __syncthreads();
+  if (*s_gone) poison_rows<DT, G>(d, b, hs);  // (the list may be missing, and a straggler may count after the clearing)
   if (tid < SHARED_MAX_CHUNKS) p.counts[(size_t)t * SHARED_MAX_CHUNKS + tid] = 0;
   u32x4* row = reinterpret_cast<u32x4*>(p.hist + (size_t)t * SHARED_BINS);
   for (int i = tid; i < SHARED_BINS / 4; i += SHARED_THREADS) row[i] = u32x4{0u, 0u, 0u, 0u};

@@ -1038,6 +1038,36 @@ def test_one_launch_step_gives_up_waiting_and_says_so_when_a_counter_was_not_cle
     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
 
 
+def test_shared_selection_reports_a_chunk_that_never_counts_itself_finished():
+    """The last split of a segment waits (bounded) until every estimation work-group of the segment has counted itself
+    finished, before it clears their counters.  Forced from the host: one segment's count starts at a value from
+    which it never gets there.  Like every wait that runs out, this one sets the status word and leaves NaN
+    in the segment's rows, and only there; after the counters are cleared again the step works."""
+    import torch
+    wl = synth.make_workload(1, context=4096, budget=256)
+    ref = O.decode_step(wl, O.build_centroids(wl))
+    dw = _dev(wl, opts=dict(step_form=2))
+    dw.build()
+    stuck, G = 3, wl.group
+    dw.workspace.view(torch.int32)[(3 * dw.nsel * 256 + 256) // 4 + stuck * 64] = 1000
+    t0 = time.time()
+    dw.decode_fused(); _sync()
+    assert time.time() - t0 < 5.0
+    assert dw.status() == 1
+    got = dw.out_f32().astype(np.float64)
+    for s in range(dw.nsel):
+        rows = slice(s * G, (s + 1) * G)
+        if s == stuck:
+            assert np.isnan(got[0, rows]).all() and np.isnan(dw.lse.cpu().numpy()[0, rows]).all()
+        else:
+            assert np.abs(got[0, rows] - ref["out"][0, rows]).max() <= TOL[wl.dtype]
+    dw.scribble(0x77)
+    dw.decode_fused()
+    _check_out(dw, ref["out"], ref["lse"], "after clearing the counters again")
+    assert dw.status() == 0
+    assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+
+
 def test_one_launch_step_with_constant_keys_takes_the_tie_paths():
     """All keys of a head equal: every block of it scores the same, the threshold bin holds the whole
     segment (the crowded path of the selection) and the lowest indices must win, in both enqueue modes."""
