@@ -50,7 +50,14 @@ def _opts(dw, **kw):
             setattr(dw.batch.opts, k, v)
 
 
-FORMS = {1: "pipelined", 2: "units", 3: "per stage"}      # absb_step_form
+FORMS = {1: "pipelined", 2: "shared selection", 3: "per stage"}      # absb_step_form
+
+
+def _hand_over_state(dw):
+    """Counters, flags, the status word and the histogram rows at the start of the workspace (of at most 512 segments):
+    zero before and after every step."""
+    import torch
+    return dw.workspace[:dw.nsel * (6 * 256 + 4096) + 256].view(torch.int32)
 
 
 def _check_out(dw, want_out, want_lse, what):
@@ -872,11 +879,10 @@ def test_group_maximum_selection_needs_the_offsets_and_mean_pooling():
 # ------------------------------------------------------------------ the one-launch step beyond its default range
 @pytest.mark.parametrize("context,sizes", [(131072, (8, 16)), (163840, (8, 8))])
 def test_one_launch_step_on_segments_longer_than_the_default_allows(context, sizes):
-    """By default a batch with a segment of more than 8192 blocks does not run as the pipelined
-    one-launch step.  Forced into it, it must select the same blocks and give the same bits on every
-    call: 16384 blocks (the longest register tile of the 256-thread selection) and 20480 blocks (keys
-    re-read, no register tile: there the work list is the ascending list, and the bits are those of
-    the per-stage form).  The unit form, the default beyond 16384 blocks, selects the same blocks."""
+    """Segments of 16384 blocks (the default shares their selection in both one-launch forms) and of 20480, where the
+    default no longer takes the pipelined form: forced into it, the selection is one work-group's (keys re-read,
+    no register tile: the work list is the ascending list, and the bits are those of the per-stage form).  Every
+    form must select the same blocks and give the same bits on every call."""
     import torch
     from paper_2605_12110_amd import absb
     wl = synth.make_workload(3, context=context, budget=4096, block_sizes=sizes)
@@ -903,8 +909,7 @@ def test_one_launch_step_on_segments_longer_than_the_default_allows(context, siz
                 assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
                 assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
                 assert dw.status() == 0
-    head = dw.workspace[:dw.nseg * 6 * 256 + 256].view(torch.int32)
-    assert int(head.abs().sum().item()) == 0, "the step left a counter, a flag or the status word set"
+    assert int(_hand_over_state(dw).abs().sum().item()) == 0, "the step left a counter, a flag or the status word set"
 
 
 @pytest.mark.parametrize("blocks,distinct,sink", [(511, 0, 0), (512, 0, 64), (513, 0, 0), (1025, 2, 0), (2049, 30, 200), (5000, 600, 0)])
@@ -966,9 +971,74 @@ def test_one_launch_steps_back_to_back_and_on_two_streams(form):
         _check_out(dw, ref["out"], ref["lse"], "25 steps back to back, two streams")
         assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
         assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
-        head = dw.workspace[:dw.nsel * 6 * 256 + 256].view(torch.int32)
-        assert int(head.abs().sum().item()) == 0
+        assert int(_hand_over_state(dw).abs().sum().item()) == 0
         assert dw.status() == 0 and absb.absb_status_offset(dw.layer, dw.batch) == dw.nsel * 3 * 256
+
+
+@pytest.mark.parametrize("form,lens", [(2, (24570, 5000)), (1, (66000, 300)), (0, (140000, 9000))])
+def test_chunks_of_a_segment_wait_for_each_other_on_two_streams(form, lens):
+    """Segments of several stretches (6 in the forced shared form; 17 where the pipelined form shares its selection; 35,
+    the default beyond 16384 blocks), whose work-groups wait for one another's scores: two streams, each with steps
+    enqueued back to back on a workspace of its own, with and without the list, leave every counter and
+    histogram row at zero."""
+    import torch
+    wls = [synth.tiny_workload(seed=51 + i, dtype=synth.F16, Hq=8, Hkv=2, P=16, seq_lens=lens, block_size=(8, 32),
+                               budget=(2048, 400)) for i in range(2)]
+    refs = [O.decode_step(wl, O.build_centroids(wl)) for wl in wls]
+    dws = [_dev(wl, opts=dict(step_form=form)) for wl in wls]
+    for dw in dws:
+        dw.build()
+    _sync()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for rep in range(25):                                   # interleaved enqueues, no synchronisation
+        for dw, st_ in zip(dws, streams):
+            with torch.cuda.stream(st_):
+                dw.decode_fused(stream=st_, want_sel=rep % 2 == 0)
+    for st_ in streams:
+        st_.synchronize()
+    for dw, ref in zip(dws, refs):
+        _check_out(dw, ref["out"], ref["lse"], f"25 steps back to back, two streams, form {form}, {lens}")
+        assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+        assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+        assert int(_hand_over_state(dw).abs().sum().item()) == 0
+
+
+@pytest.mark.parametrize("group_max", [False, True])
+@pytest.mark.parametrize("blocks,distinct", [(8193, 0), (16384, 0), (8193, 30), (16384, 3), (16384, 700)])
+def test_pipelined_step_whose_long_segments_are_selected_by_one_work_group(blocks, distinct, group_max):
+    """8193 to 16384 blocks where the selection is not shared: with the group's maximum, and in a batch whose
+    estimation work-groups the chip does not hold all at once (34 segments here, 32 of them short).  The
+    selection then keeps 64 keys a thread in registers: its common path on plain keys, long lists of candidates
+    and ties with few distinct ones.  The scores in the workspace say that the segment went this way (the shared
+    selection leaves lists in their place)."""
+    import torch
+    from paper_2605_12110_amd import absb
+    short = (300, 64, 7, 1000) * 4 if not group_max else (300,)
+    wl = synth.tiny_workload(seed=52, dtype=synth.F16, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 5, *short), block_size=(8, 64),
+                             budget=(4096, *[128] * len(short)))
+    if distinct:
+        rng = np.random.default_rng(distinct)
+        pal = synth.f32_to_bits(rng.standard_normal((distinct, wl.head_dim)).astype(np.float32), wl.dtype)
+        k = wl.k_cache.reshape(-1, wl.num_kv_heads, wl.page_size, wl.head_dim)
+        k[:, 0] = pal[rng.integers(0, distinct, size=k.shape[0])][:, None, :]
+    ref = O.decode_step(wl, O.build_centroids(wl), group_max=group_max)
+    dw = _dev(wl, selection=absb.SELECT_GROUP_MAX if group_max else absb.SELECT_GROUP)
+    dw.build()
+    assert absb.absb_step_form_used(dw.layer, dw.batch) == absb.STEP_PIPELINED
+    first = None
+    for want in (True, False, True):
+        dw.scribble(0xA5)
+        dw.out.fill_(float("nan")); dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7)
+        dw.decode_fused(want_sel=want)
+        _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, {distinct} distinct keys, group_max {group_max}, list {want}")
+        if want:
+            assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+            assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+        scores = dw.workspace[dw.nsel * (6 * 256 + 4096) + 256:].view(torch.int32)[:blocks].cpu().numpy()
+        assert np.array_equal(scores, ref["scores"][:blocks])
+        first = dw.out.clone() if first is None else first
+        assert torch.equal(dw.out, first)
+        assert int(_hand_over_state(dw).abs().sum().item()) == 0
 
 
 def test_one_workspace_serves_batches_of_different_shapes_when_cleared_in_between():
@@ -1001,7 +1071,7 @@ def test_one_workspace_serves_batches_of_different_shapes_when_cleared_in_betwee
 def test_one_launch_step_gives_up_waiting_and_says_so_when_a_counter_was_not_cleared(form):
     """Work-groups of the one-launch forms wait for each other with a time limit.  Forced from the host:
     one segment's arrival counter starts at a value from which the count its work-groups wait for is
-    never reached, so its list (pipelined form) or its threshold (unit form) never comes.  The launch
+    never reached, so its list (pipelined form) or its threshold (shared selection) never comes.  The launch
     must end by itself (about a quarter of a second per wait), set the status word, leave the other
     segments right, and write NaN into the stuck segment's output rows; after the counters
     are cleared again the step works."""
@@ -1095,11 +1165,11 @@ def test_one_launch_step_with_constant_keys_takes_the_tie_paths():
 
 @pytest.mark.parametrize("distinct", [3, 40, 700])
 def test_one_launch_step_on_long_segments_whose_scores_take_few_values(distinct):
-    """Segments of 8192 and 16384 blocks (register tiles of 32 and 64 keys per thread in the pipelined
-    form's selection) whose pages each hold one key out of a palette of 3, 40 or 700: the threshold bin holds
-    from a few to thousands of equal scores, so the selection leaves its common path (members handed
-    to the attention as they are found) for the ones that cut a long candidate list down, admit ties by
-    index, or re-read a crowded bin, while other segments of the same launch stay on the common path.
+    """Segments of up to 16384 blocks (whose selection the pipelined form shares among work-groups) and pages that each
+    hold one key out of a palette of 3, 40 or 700: the threshold bin holds from a few to thousands of equal
+    scores, so the selection leaves its common path for the one where the last work-group takes a crowded
+    bin over (and, per stage, for the ones that cut a long candidate list down, admit ties by index or re-read
+    a crowded bin), while other segments of the same launch stay on the common path.
     Every enqueue form must select the oracle's blocks, with and without the caller asking for the list."""
     wl = synth.make_workload(3, context=131072, budget=4096, block_sizes=(8, 16, 64))
     rng = np.random.default_rng(77 + distinct)
