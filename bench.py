@@ -619,7 +619,7 @@ def main():
     wl = wl0
     headline = (args.config == 3 and args.context is None and args.batch is None and args.budget is None
                 and block_repr == 0 and args.select == "group")
-    form_name = {absb.STEP_PIPELINED: "pipelined (one launch)", absb.STEP_UNITS: "shared selection (one launch)",
+    form_name = {absb.STEP_PIPELINED: "pipelined (one launch; by size in the form of small.hip, fused.hip or shared.hip)", absb.STEP_UNITS: "shared selection (one launch)",
                  absb.STEP_PER_STAGE: "per stage (three launches)"}[m["form"]]
     stages = {k: round(v, 3) for k, v in m["stages"].items()}
     if headline:
@@ -672,7 +672,7 @@ def main():
     if m["launches"] == 1:
         # the step is one launch: the dominant kernel is the step itself (csrc/shared.hip selects for long segments,
         # small.hip for short ones, fused.hip in between; the rule is the library's)
-        kern = "shared_step_kernel" if headline and args.form == 0 or m["form"] == absb.STEP_UNITS else "one-launch step"
+        kern = "shared_step_kernel" if headline and args.form in (0, 1) or m["form"] == absb.STEP_UNITS else "one-launch step"
         result["roofline"] = {
             "bound": "hbm",
             "kernel": f"{kern} (one absb_decode_fused call = one launch: estimation, selection, attention)",

@@ -275,8 +275,9 @@ ABSB_API int absb_workspace_init(const absb_layer* layer, const absb_batch* batc
  *                        once all have, derives the segment's threshold from it and hands its selected
  *                        blocks over; blocks inside the threshold bin are settled by an exact ranking among
  *                        the segment's candidates.  No work-group ever passes over a whole segment, so the
- *                        cost hardly grows with the context.  Chosen for segments beyond 16384 blocks when
- *                        the chip holds all those work-groups at once.
+ *                        cost hardly grows with the context.  Chosen for segments beyond 16384 blocks while
+ *                        there are at most two of those work-groups per compute unit, or four if at least
+ *                        half of them have blocks to score.
  *   ABSB_STEP_PER_STAGE  three launches (score, top-k, sparse decode).  Otherwise.
  * The one-launch forms hand work between work-groups through the counters at the start of the
  * workspace: they must be zero when the call starts (absb_workspace_init) and are zero again when its

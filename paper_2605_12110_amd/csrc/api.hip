@@ -128,13 +128,16 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // path: its attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
   // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything else
-  // together, and the work-groups that score a segment share its selection, as long as the chip holds all
-  // of them at once: two per compute unit, or four if hardly any of the grid's places are empty.  256K context,
-  // batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 21.0 / 23.0, 25.3 / 25.6, 37.0 / 29.7 us.
+  // together, and the work-groups that score a segment share its selection, unless the grid of them is large and
+  // mostly empty (mixed lengths) or outgrows the chip: two per compute unit, or four if hardly any of its places
+  // are empty.  256K context, batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 21.0 / 23.0, 25.3 /
+  // 25.6, 37.0 / 29.7 us.  (This is a limit on time, not what makes the waits end: beyond 96128 blocks a
+  // segment three fit a compute unit, not four, and 1024 of them still take 58 us against 92 at 16 segments of
+  // 131072 blocks.  See "Progress" in shared.hip.)
   const int shared_chunk = shared_chunk_blocks(p.max_blocks);
   const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk);
-  const bool shared_resident = shared_grid <= 512 || (shared_grid <= 1024 && 2 * ceil_div(p.total * g.Rk, shared_chunk) >= shared_grid);
-  const bool by_units = !by_shape && p.max_blocks > 16384 && shared_resident;
+  const bool shared_pays = shared_grid <= 512 || (shared_grid <= 1024 && 2 * ceil_div(p.total * g.Rk, shared_chunk) >= shared_grid);
+  const bool by_units = !by_shape && p.max_blocks > 16384 && shared_pays;
   p.step_form = opts.step_form != ABSB_STEP_AUTO ? opts.step_form
                 : by_shape ? ABSB_STEP_PIPELINED : by_units ? ABSB_STEP_UNITS : ABSB_STEP_PER_STAGE;
   p.one_launch = p.step_form != ABSB_STEP_PER_STAGE;
@@ -146,13 +149,13 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // scores are G times as many: never better there.
   const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : g.repr == ABSB_REPR_MINMAX ? 768 : SMALL_MAX_BLOCKS;
   p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
-  // split-K shape, in 64-token granules (one work-group step).  Measured on MI355X (256 CUs, three
-  // resident work-groups each): the kernel is fastest with about two work-groups per CU, all
-  // resident at once and each streaming as long as possible; a work-group needs at least two steps
-  // to amortise its set-up; and since one work-group merges a segment's partials, a segment should
-  // not be cut into more than 64.
+  // split-K shape, in 64-token granules (one work-group step).  Swept on MI355X (256 CUs) when three
+  // work-groups fitted a compute unit; four do now, and the sweep has not been repeated: the kernel was
+  // fastest with about two work-groups per CU, all resident at once and each streaming as long as
+  // possible; a work-group needs at least two steps to amortise its set-up; and since one work-group
+  // merges a segment's partials, a segment should not be cut into more than 64.
   // (the shape follows the batch, not the enqueue knob: every form of the step then cuts the
-  // segments alike and gives the same bits)
+  // segments alike)
   int st_tok = opts.split_tokens;
   const int64_t cap_tok = ceil_div(ceil_div(p.max_tokens, MAX_SPLITS_CHOSEN), 64) * 64;
   if (st_tok <= 0 && p.step_form == ABSB_STEP_UNITS && !lean && opts.unit_tokens > 0)
@@ -186,7 +189,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // group's maximum, whose scores come a pass per query head: 128K, batch 1, 23.9 / 25.4 us.  (Forced beyond 16384
   // blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
   p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && !g.agg_max &&
-                                                p.max_blocks > 8192 && p.max_blocks <= 16384 && shared_resident);
+                                                p.max_blocks > 8192 && p.max_blocks <= 16384 && shared_pays);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
   p.shared = p.shared && rows && shared_fits(p);
 

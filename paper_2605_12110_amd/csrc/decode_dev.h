@@ -27,7 +27,7 @@
 //     groups of 16 lanes (register swaps);
 //   * K of the next step is requested once the S product has consumed this step's, V four rows at a time behind the
 //     product that consumed them: a work-group has 32 KB of rows in flight nearly always, and with at most 128
-//     registers a lane (112-114 in the stand-alone kernel) four work-groups fit a compute unit.
+//     registers a lane (110-120 in the stand-alone kernel) four work-groups fit a compute unit.
 // The addresses of a wave's steps come from its lanes: lane j looks up the block and page of eight consecutive
 // tokens (half j % 2 of step j / 2; B >= 8 and P >= 8, so they lie in one block and one page), for 32 steps at once.
 #pragma once
@@ -182,20 +182,6 @@ struct ListRef {
   }
 };
 
-// Logical page -> physical page of one request: the page table row in device memory, or a copy of the
-// entries [first, first + count) that the work-group holds in LDS.
-typedef __attribute__((address_space(3))) const int32_t lds_const_i32;
-struct PageRef {
-  const int32_t* row;    // device memory
-  lds_const_i32* local;  // LDS copy, or null (typed as LDS: a generic pointer would make these reads wait
-                         // for every row load in flight)
-  int first, count;
-  __device__ __forceinline__ int at(int page) const {
-    if (local) return local[min(max(page - first, 0), count - 1)];
-    return row[page];
-  }
-};
-
 // Query heads are taken in sets of four (the rows of a 4x4x4 product).
 constexpr int head_sets(int G) { return (G + 3) / 4; }
 
@@ -244,22 +230,10 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
 // Attention of this wave over positions [pos_begin, pos_end) of the virtual token sequence of a block
 // list (position -> list entry pos >> lb -> token -> page/slot), folded into `st`.  A work-group step
 // covers DEC_STEP consecutive positions, 16 per wave; pos_begin must be a multiple of eight.
-//
-// `after_first_issue()` runs once the first step's row loads are in flight (work that has to wait for
-// memory anyway can hide behind them; it may contain barriers: every wave of the work-group calls this
-// function).  `live(entry)`: false for list entries whose rows were requested but must not count
-// (evaluated after after_first_issue()).
-struct NoHook {
-  __device__ __forceinline__ void operator()() const {}
-};
-struct AllLive {
-  __device__ __forceinline__ bool operator()(int) const { return true; }
-};
-template <int DT, int G, bool STREAM, class List, class Hook, class Live>
-__device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCtx& c, const List& list,
-                                                 const PageRef& pages, int pos_begin, int pos_end,
-                                                 const u32x4 (&qb)[4], AttnState<G>& st, Hook&& after_first_issue,
-                                                 Live&& live) {
+// `pages`: the request's row of the page table.
+template <int DT, int G, bool STREAM, class List>
+__device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCtx& c, const List& list, const int32_t* pages,
+                                            int pos_begin, int pos_end, const u32x4 (&qb)[4], AttnState<G>& st) {
   constexpr int SETS = head_sets(G);
   const int tid = threadIdx.x, lane = tid & 63, grp = lane >> 4, li = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -276,13 +250,12 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
   // legal token, whatever the list holds), `most`: which of its eight rows is the last that exists; `nv`: how
   // many of them count
   uint64_t off = 0;
-  int most = 0, nv = 0, entry = 0;
+  int most = 0, nv = 0;
   auto look_up = [&](int step0) __attribute__((always_inline)) {
     const int pos8 = wave_pos + (step0 + (lane >> 1)) * DEC_STEP + (lane & 1) * 8;
-    entry = pos8 >> lb;
-    const int t8 = (list.at(entry) << lb) + (pos8 & ((1 << lb) - 1));
+    const int t8 = (list.at(pos8 >> lb) << lb) + (pos8 & ((1 << lb) - 1));
     const int tc = max(0, min(t8, L - 1)) & ~7;
-    off = ((uint64_t)pages.at(tc >> lP) * (uint64_t)p.g.s_page + (uint64_t)(tc & ((1 << lP) - 1)) * (uint64_t)p.g.s_tok) * 2;
+    off = ((uint64_t)pages[tc >> lP] * (uint64_t)p.g.s_page + (uint64_t)(tc & ((1 << lP) - 1)) * (uint64_t)p.g.s_tok) * 2;
     nv = min(8, min(pos_end - pos8, L - t8));
     most = nv > 0 ? min(7, L - 1 - tc) : 0;  // rows nobody needs: one line, not eight
   };
@@ -323,8 +296,6 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
 #pragma unroll
     for (int t = 0; t < 4; ++t) issue_v(t);
   }
-  after_first_issue();
-  if (!live(entry)) nv = 0;
   float m = st.m, l = st.l, lx = st.lx;
   // One step from the rows in registers; MORE: the next step's rows are requested as registers come free.  (The last
   // step is a copy of its own: requests under a condition would be copied into place, after a wait for them.)
@@ -340,10 +311,7 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
     s0 = mma_16x16x32<DT>(k[2], qb[2], s0);
     s1 = mma_16x16x32<DT>(k[3], qb[3], s1);
     if (MORE) {
-      if (j == 62) {
-        look_up(step + 1);
-        if (!live(entry)) nv = 0;
-      }
+      if (j == 62) look_up(step + 1);
       issue_k(2 * ((step + 1) & 31));
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -421,15 +389,13 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
   st.lx = lx;
 }
 
-template <int DT, int G, class List, class Hook = NoHook, class Live = AllLive>
-__device__ __forceinline__ void attend_positions(const DecodeParams& p, const SplitCtx& c, const List& list,
-                                                 const PageRef& pages, int pos_begin, int pos_end,
-                                                 const u32x4 (&qb)[4], AttnState<G>& st, Hook&& after_first_issue = Hook(),
-                                                 Live&& live = Live()) {
+template <int DT, int G, class List>
+__device__ __forceinline__ void attend_positions(const DecodeParams& p, const SplitCtx& c, const List& list, const int32_t* pages,
+                                                 int pos_begin, int pos_end, const u32x4 (&qb)[4], AttnState<G>& st) {
   if (p.stream_rows)
-    attend_rows<DT, G, true>(p, c, list, pages, pos_begin, pos_end, qb, st, after_first_issue, live);
+    attend_rows<DT, G, true>(p, c, list, pages, pos_begin, pos_end, qb, st);
   else
-    attend_rows<DT, G, false>(p, c, list, pages, pos_begin, pos_end, qb, st, after_first_issue, live);
+    attend_rows<DT, G, false>(p, c, list, pages, pos_begin, pos_end, qb, st);
 }
 
 // An empty selection: the output rows are zero, the log-sum-exp -inf.
@@ -691,7 +657,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   c.lb = lb;
   c.L = p.seq_lens[b];
   c.lP = p.g.log2_page;
-  const PageRef pages{p.page_table + (size_t)b * p.g.pt_stride, nullptr, 0, 0};
+  const int32_t* pages = p.page_table + (size_t)b * p.g.pt_stride;
   int* s_bcast = reinterpret_cast<int*>(lds + DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4);
   const int nsplit = (ntok + p.split_tokens - 1) / p.split_tokens;
 

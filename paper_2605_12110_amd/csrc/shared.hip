@@ -23,10 +23,14 @@
 // 128 independent channels that is about 45 standard deviations, so a bin holds 0.2 % of the blocks in the
 // tail where the threshold lies.
 //
-// Progress.  Estimation work-groups come first in the grid, chunk by chunk; they wait only for the other chunks of
-// their segment, at most SHARED_MAX_CHUNKS, which the hardware starts right beside them.  Attention
-// work-groups wait only for work-groups with lower indices.  Every wait is bounded in time; one that runs out sets
-// the status word and leaves NaN in the segment's rows.
+// Progress rests on work-groups starting in the grid's order, not on the whole grid being resident (a caller may
+// ask for this form at any size, a large segment's LDS lets three work-groups into a compute unit, and other
+// streams may hold places).  Estimation work-groups come first, a segment's chunks side by side, and wait only
+// for the other chunks of their segment.  So of those that have started, only the segment that is being
+// dispatched can be waiting for one that has not, with at most SHARED_MAX_CHUNKS - 1 work-groups: every
+// segment before it finishes and gives its places back.  Attention work-groups wait only for work-groups
+// with lower indices.  Several launches at once hold back at most that many places each.  Every wait is
+// bounded in time; one that runs out sets the status word and leaves NaN in the segment's rows.
 //
 // Counters, histogram rows and counts words must be zero when the launch starts and are zero again when it ends
 // (the work-group that merges a segment's partials clears them).
@@ -474,7 +478,7 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
     }
   }
 
-  const PageRef pages{d.page_table + (size_t)b * d.g.pt_stride, nullptr, 0, 0};
+  const int32_t* pages = d.page_table + (size_t)b * d.g.pt_stride;
   AttnState<G> st;
   st.reset();
   attend_positions<DT, G>(d, c, StretchRef{s_list, e0, e1 - 1}, pages, pos_begin, pos_end, qb, st);

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(SmallParam
   __syncthreads();
 
   const ListRef<LIST_LOCAL> list{s_list, nsel - 1};
-  const PageRef pages{p.dc.page_table + (size_t)b * p.dc.g.pt_stride, nullptr, 0, 0};
+  const int32_t* pages = p.dc.page_table + (size_t)b * p.dc.g.pt_stride;
   AttnState<G> st;
   st.reset();
   attend_positions<DT, G>(p.dc, c, list, pages, pos_begin, pos_end, qb, st);

@@ -232,10 +232,10 @@ def test_a_second_thread_gets_the_reassigned_fields_while_the_first_carries_them
 
 
 def test_enqueue_form_of_the_fused_step_follows_the_longest_segment():
-    """Pipelined one-launch step while no segment has more than 16384 blocks and no list more than
-    4096 entries; beyond 16384 blocks the unit form, as long as
-    the chip holds all units at once; one launch per stage otherwise; the option forces any of them; the
-    workspace always has room for the counters of the one-launch forms."""
+    """Pipelined one-launch step while no segment has more than 16384 blocks and no list more than 4096
+    entries; beyond 16384 blocks the shared selection, while its estimation work-groups are few enough or mostly
+    have work; one launch per stage otherwise; the option forces any of them; the workspace always has room
+    for the counters of the one-launch forms."""
     def form(L, B, batch_size=2, budget=64, **opts):
         layer = absb.Layer(8, 2, 128, 64, absb.F16, [B, 128], (2 * 64 * 128, 64 * 128, 128))
         batch = absb.Batch(seq_lens_host=[L] + [100] * (batch_size - 1), budget_host=[budget] * batch_size,
@@ -245,8 +245,8 @@ def test_enqueue_form_of_the_fused_step_follows_the_longest_segment():
     assert form(8192 * 8, 8)[0] == P
     assert form(16384 * 8, 8)[0] == P
     assert form(131072, 16)[0] == P
-    assert form(16384 * 8 + 1, 8, batch_size=4)[0] == U        # beyond: units select among themselves
-    assert form(16384 * 8 + 1, 8, batch_size=8)[0] == S        # ... unless there are more units than the chip holds
+    assert form(16384 * 8 + 1, 8, batch_size=4)[0] == U        # beyond: the selection is shared
+    assert form(16384 * 8 + 1, 8, batch_size=8)[0] == S        # ... unless most of a large grid is empty
     assert form(8192 * 8, 8, budget=4096 * 8)[0] == P
     assert form(8192 * 8, 8, budget=4096 * 8 + 1)[0] == S      # lists of more than 4096 blocks
     assert form(4096, 8, step_form=S)[0] == S

@@ -329,7 +329,7 @@ def test_split_shapes_do_not_change_the_selection_and_stay_within_tolerance():
         dw = _dev(wl, opts=dict(unit_tokens=unit, step_form=2))
         dw.build()
         dw.decode_fused()
-        _check_out(dw, ref["out"], ref["lse"], f"unit_tokens={unit}, units")
+        _check_out(dw, ref["out"], ref["lse"], f"unit_tokens={unit}, shared selection")
         assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
         assert dw.status() == 0
     for chunk in (64, 1024):
