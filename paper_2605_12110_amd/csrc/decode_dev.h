@@ -27,7 +27,7 @@
 //     groups of 16 lanes (register swaps);
 //   * K of the next step is requested once the S product has consumed this step's, V four rows at a time behind the
 //     product that consumed them: a work-group has 32 KB of rows in flight nearly always, and with at most 128
-//     registers a lane (110-120 in the stand-alone kernel) four work-groups fit a compute unit.
+//     registers a lane (114-122 in the stand-alone kernel) four work-groups fit a compute unit.
 // The addresses of a wave's steps come from its lanes: lane j looks up the block and page of eight consecutive
 // tokens (half j % 2 of step j / 2; B >= 8 and P >= 8, so they lie in one block and one page), for 32 steps at once.
 #pragma once
@@ -262,17 +262,14 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
   u32x4 k[4];
   uint32_t v[16];
   int nv0 = 0, nv1 = 0;      // rows of the two halves that count, of the step being computed
-  uint64_t v_off[2];         // of the step whose V rows are being requested
-  uint32_t v_most[2];
+  // of row `li` of the step whose rows are being requested, for V read back lane by lane (a 64-bit product per row
+  // on the scalar unit: 43.4 -> 43.6 us a step on 16 x 8K-128K)
+  uint64_t row_off = 0;
   auto issue_k = [&](int j) __attribute__((always_inline)) {  // j: even lane of the step's pair
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      v_off[h] = readlane_u64(off, j + h);
-      v_most[h] = (uint32_t)__builtin_amdgcn_readlane(most, j + h);
-    }
-    const uint64_t o = li < 8 ? v_off[0] : v_off[1];
-    const uint32_t r = min((uint32_t)(li & 7), li < 8 ? v_most[0] : v_most[1]);
-    const char* row = kbase + (o + r * pitch);
+    const uint64_t o0 = readlane_u64(off, j), o1 = readlane_u64(off, j + 1);
+    const uint32_t m0 = (uint32_t)__builtin_amdgcn_readlane(most, j), m1 = (uint32_t)__builtin_amdgcn_readlane(most, j + 1);
+    row_off = (li < 8 ? o0 : o1) + min((uint32_t)(li & 7), li < 8 ? m0 : m1) * pitch;
+    const char* row = kbase + row_off;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u32x4* piece = reinterpret_cast<const u32x4*>(row + 64 * i);
@@ -282,10 +279,9 @@ __device__ __forceinline__ void attend_rows(const DecodeParams& p, const SplitCt
   auto issue_v = [&](int t) __attribute__((always_inline)) {  // rows 4t .. 4t+3
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int r = 4 * t + i;
-      const char* row = vbase + (v_off[r >> 3] + min((uint32_t)(r & 7), v_most[r >> 3]) * pitch);  // a scalar
+      const char* row = vbase + readlane_u64(row_off, 4 * t + i);  // a scalar
       const uint32_t* pair = reinterpret_cast<const uint32_t*>(row + lane4);
-      v[r] = STREAM ? __builtin_nontemporal_load(pair) : *pair;
+      v[4 * t + i] = STREAM ? __builtin_nontemporal_load(pair) : *pair;
     }
   };
 
