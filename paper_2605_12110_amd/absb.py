@@ -136,13 +136,19 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+_INT32 = np.dtype(np.int32)
+
+
 def _i32_host(a: Optional[Sequence[int]]):
     """(contiguous int32 array to keep alive, its address); (None, None) for None."""
     if a is None:
         return None, None
-    if type(a) is not np.ndarray or a.dtype != np.int32 or a.ndim != 1 or not a.flags.c_contiguous:
+    if type(a) is not np.ndarray or a.dtype != _INT32 or a.ndim != 1 or not a.flags.c_contiguous:
         a = np.ascontiguousarray(np.asarray(a), dtype=np.int32)
-    return a, a.__array_interface__["data"][0]
+    try:
+        return a, C.addressof(C.c_byte.from_buffer(a))
+    except (TypeError, ValueError):             # a read-only or an empty array: the slower way
+        return a, a.__array_interface__["data"][0]
 
 
 @dataclass
@@ -239,10 +245,12 @@ class Batch:
                 if d[name] is not arr:
                     names.add(name)
             for name, at in old._at.items():
-                if _ptr(d[name]) != at:
+                t = d[name]
+                if (t if t is None or t.__class__ is int else t.data_ptr()) != at:
                     names.add(name)
-            if self.pt_stride is None:
-                names.add("pt_stride")
+            table = d["page_table"]
+            if d["pt_stride"] is None and table is not None and table.shape[1] != rec.pt_stride:
+                names.add("page_table")
             try:
                 self._fill(rec, names)
             except Exception:
