@@ -225,21 +225,27 @@ class Batch:
         any other that was changed in place since, is carried over into a copy of the record, so a call in flight on
         another thread keeps the one it was given (with the host arrays it points into), and no thread gets
         a record from before a reassignment; the tensors must stay alive."""
-        with _record_lock:
-            return self._record(self.__dict__)
+        d = self.__dict__
+        if d.get("_dirty", True):       # no record yet, or fields reassigned since (cleared only once the new one is in place)
+            with _record_lock:
+                self._renew(d)
+        rec = d["_c"]
+        o = self.opts                   # the options object may have been changed in place: looked at every time
+        opts = (o.step_form, o.split_tokens, o.score_chunk, o.unit_tokens, o.counters_zero)
+        if opts != rec._opts:
+            rec.opts = _Opts(*(int(x) for x in opts))
+            rec._opts = opts
+        return rec
 
-    def _record(self, d) -> _Batch:
-        rec = d.get("_c")
-        if rec is None:
-            d["_dirty"] = set()
-            rec = _Batch()
+    def _renew(self, d) -> None:
+        old = d.get("_c")
+        rec = _Batch() if old is None else _Batch.from_buffer_copy(old)
+        if old is None:
             rec._arrays, rec._at, rec._opts = {}, {}, None
-            self._fill(rec, _BATCH_FIELDS)
-            d["_c"] = rec
-        elif d["_dirty"]:
-            names, d["_dirty"] = d["_dirty"], set()
-            old, rec = rec, _Batch.from_buffer_copy(rec)
+            names = _BATCH_FIELDS
+        else:
             rec._arrays, rec._at, rec._opts = dict(old._arrays), dict(old._at), old._opts
+            names = set(d["_dirty"])
             # what is held by address only (tensors), or as a converted copy (lists), may have changed in place
             for name, arr in old._arrays.items():
                 if d[name] is not arr:
@@ -251,18 +257,9 @@ class Batch:
             table = d["page_table"]
             if d["pt_stride"] is None and table is not None and table.shape[1] != rec.pt_stride:
                 names.add("page_table")
-            try:
-                self._fill(rec, names)
-            except Exception:
-                d["_dirty"] |= names
-                raise
-            d["_c"] = rec
-        o = self.opts                   # the options object may have been changed in place: looked at every time
-        opts = (o.step_form, o.split_tokens, o.score_chunk, o.unit_tokens, o.counters_zero)
-        if opts != rec._opts:
-            rec.opts = _Opts(*(int(x) for x in opts))
-            rec._opts = opts
-        return rec
+        self._fill(rec, names)
+        d["_c"] = rec
+        d["_dirty"] = set()
 
     def _fill(self, rec, names) -> None:
         for name in names:
