@@ -90,6 +90,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     const int64_t cap = batch->cap_lens_host ? batch->cap_lens_host[b] : L;  // the layout's length
     if (cap < L) return ABSB_ERR_BAD_SHAPE;
     if (L > max_len) max_len = L;
+    p.build_max_chunks = std::max(p.build_max_chunks, build_chunks((int)L));
     if (batch->budget_host) {
       if (batch->budget_host[b] < 1) return ABSB_ERR_BAD_SHAPE;
       (batch->budget_host[b] >= L ? p.some_dense : p.all_dense) = 1;  // (all_dense holds "some are not" until the end)
@@ -111,7 +112,6 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       p.sum_tokens += tok * g.Rk;  // every selection segment of the KV head reads its own tokens
     }
   }
-  p.build_max_chunks = (int32_t)ceil_div(max_len, BUILD_CHUNK);
   p.all_dense = p.some_dense && !p.all_dense;
   if (!batch->budget_host) p.sel_stride = p.max_blocks;
   // entry points that select (they are the ones that need the budgets) refuse on the host what the
@@ -232,10 +232,12 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.ws_cent = bo;
   const size_t width = (size_t)ABSB_HEAD_DIM * (g.repr + 1);  // values per block
   bo += align256((size_t)p.total * width * 4);
-  p.ws_minmax = bo;
-  bo += align256((size_t)p.nstore * p.build_max_chunks * 2 * width * 4);
-  p.ws_qinv = bo;
-  bo += align256((size_t)p.nstore * width * 4);
+  p.ws_meet = bo;
+  // the chunks of a segment share its words in groups of at most 16 (~10 ns an update of a line), or in the most groups
+  p.build_copies = 1;
+  while (p.build_copies < BUILD_MAX_COPIES && p.build_copies * 16 < p.build_max_chunks) p.build_copies *= 2;
+  p.build_pitch = (int32_t)(align256((size_t)meet_words((int)width, p.build_copies, p.build_max_chunks) * 4) / 4);
+  bo += (size_t)p.nstore * p.build_pitch * 4;
   p.ws_build_bytes = bo;
   p.ws_bytes = p.ws_fused_bytes > p.ws_build_bytes ? p.ws_fused_bytes : p.ws_build_bytes;
 

@@ -14,7 +14,8 @@
 // Split counters sit 256 bytes apart: counters that share a memory line serialise each other's
 // atomic updates (measured: 8 segments x 32 arrivals on one line cost 2.7 us, apart 0.x us).
 #define ABSB_TICKET_STRIDE 64
-#define BUILD_CHUNK 512          // tokens per work-group of the store build's pooling
+#define BUILD_RUNS_OF 512        // tokens a work-group of the store build pools at a time
+#define BUILD_MAX_COPIES 8       // of the words that its work-groups raise together
 
 namespace absb {
 
@@ -58,7 +59,9 @@ struct Plan {
   int32_t step_form;        // absb_step_form actually used (never ABSB_STEP_AUTO)
   int32_t shared;           // the one-launch step in the form of shared.hip
   int32_t score_chunk;      // centroids per work-group in score
-  int32_t build_max_chunks; // max_b ceil(L_b / BUILD_CHUNK)
+  int32_t build_max_chunks; // max_b build_chunks(L_b)
+  int32_t build_copies;     // of a segment's ranges while its chunks are pooled
+  int32_t build_pitch;      // words between what two segments' chunks share
   // workspace carving (byte offsets, 256-aligned)
   size_t ws_part_o, ws_part_ml, ws_tickets;       // decode partials, per-segment split counters
   size_t ws_score_tickets, ws_flags, ws_status;   // more counters of the one-launch step
@@ -66,7 +69,7 @@ struct Plan {
   size_t ws_cand;
   size_t ws_head_bytes;                           // all counters: the part absb_workspace_init clears
   size_t ws_scores, ws_sel_idx, ws_sel_cnt;       // fused step intermediates
-  size_t ws_cent, ws_minmax, ws_qinv;             // build intermediates
+  size_t ws_cent, ws_meet;                        // build intermediates
   size_t ws_decode_bytes, ws_fused_bytes, ws_build_bytes, ws_bytes;
 };
 
@@ -76,6 +79,34 @@ struct Plan {
 // selection's histogram rows and candidates, and so a step without it.
 ABSB_HIDDEN int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget,
                           int32_t sel_stride_in, Geometry* geo, Plan* plan, bool lean = false);
+
+// The store build cuts a segment into chunks of a few runs of BUILD_RUNS_OF tokens, a work-group each: one run as long as
+// that makes at most BUILD_CHUNKS of them (1280 work-groups fit the chip; while one segment takes most of the places, the
+// next one's cannot fill the gaps: 400000 tokens of 8 heads 207 us as 782 chunks of a run, 169 as 391 of two; with at
+// most 256 chunks more rows than need to go through memory: 180000 tokens 83 us against 72), and never more than
+// BUILD_MAX_RUNS.
+constexpr int BUILD_CHUNKS = 512, BUILD_MAX_RUNS = 8;
+__host__ __device__ constexpr int build_runs(int L) {
+  const int runs = (int)(((int64_t)L + BUILD_RUNS_OF * BUILD_CHUNKS - 1) / (BUILD_RUNS_OF * BUILD_CHUNKS));
+  return runs < BUILD_MAX_RUNS ? runs : BUILD_MAX_RUNS;
+}
+__host__ __device__ constexpr int build_chunks(int L) {
+  const int tokens = build_runs(L) * BUILD_RUNS_OF;
+  return (int)(((int64_t)L + tokens - 1) / tokens);
+}
+
+// What the build's chunks of a segment share, in words (zero when its kernel starts; W values per block): copies of the
+// minima and maxima per value, a flag per copy, a 64-bit counter (each on memory lines of its own), a bit per chunk
+// that left, and copies of those bits.
+__host__ __device__ constexpr int meet_flags(int W, int copies) { return copies * 2 * W; }
+__host__ __device__ constexpr int meet_state(int W, int copies) { return meet_flags(W, copies) + copies * 32; }
+__host__ __device__ constexpr int meet_left(int W, int copies) { return meet_state(W, copies) + 32; }
+__host__ __device__ constexpr int meet_used(int W, int copies, int chunks) {  // (the copies of the bits need not be zero)
+  return meet_left(W, copies) + (chunks + 31) / 32;
+}
+__host__ __device__ constexpr int meet_words(int W, int copies, int chunks) {
+  return meet_left(W, copies) + (copies + 1) * ((chunks + 31) / 32);
+}
 
 // Launchers (one per stage); all enqueue on `stream` and return an absb_status.
 ABSB_HIDDEN int launch_build(const Geometry& g, const Plan& pl, int dtype, const void* k_cache,

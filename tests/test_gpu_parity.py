@@ -634,6 +634,39 @@ def test_one_million_token_context(L, sizes, G, budget):
     run_all_stages(wl, f"context {L}, blocks {sizes}, budget {budget}")
 
 
+@pytest.mark.parametrize("lens,sizes,repr_,dtype", [
+    ((1, 7, 8, 9), (8, 128), 0, synth.F16),                           # a chunk each, hardly filled
+    ((511, 512, 513, 1024), (16, 8, 64), 1, synth.BF16),              # one chunk, two
+    ((8 * 512 * 16 + 1, 8 * 512 * 16, 640), (32, 8), 0, synth.BF16),  # the most chunks that four copies serve, and more
+    (((1 << 18) - 5, (1 << 18) + 1, 3), (128, 8), 0, synth.F16),      # the longest chunks of one run, the shortest of two
+    (((1 << 18) + 777, 100), (64, 8), 1, synth.F16),
+    ((513 * 4096 + 1,), (8,), 0, synth.BF16),                         # 514 chunks of eight runs: the first ones leave
+    ((640 * 4096 - 13,), (16,), 1, synth.F16),                        # an eighth of the chunks leaves
+])
+def test_store_build_around_its_chunks_and_runs(lens, sizes, repr_, dtype):
+    """The store against the oracle bit for bit, twice on a workspace full of old values, on two streams at once."""
+    import torch
+    wl = synth.tiny_workload(seed=len(lens) + lens[0] % 97, dtype=dtype, Bt=len(lens), Hq=len(sizes), Hkv=len(sizes), P=64,
+                             seq_lens=lens, block_size=sizes, budget=(64,) * len(lens))
+    st = O.build_centroids(wl, repr_)
+    dw = _dev(wl, block_repr=repr_)
+    other = dw.clone()
+    streams = [torch.cuda.current_stream(), torch.cuda.Stream()]
+    for i in range(2):
+        for d in (dw, other):
+            d.workspace.fill_(0xA5 + i)
+            d.codes.fill_(0x5A)
+        _sync()
+        for d, stream in zip((dw, other), streams):
+            with torch.cuda.stream(stream):
+                d.build()
+        _sync()
+        for d in (dw, other):
+            assert np.array_equal(d.qscale.cpu().numpy(), st.qscale), "qscale"
+            assert np.array_equal(d.qmin.cpu().numpy(), st.qmin), "qmin"
+            assert np.array_equal(d.codes.cpu().numpy(), st.codes), "codes"
+
+
 @pytest.mark.parametrize("P", [2048, 65536])
 def test_pages_much_larger_than_blocks(P):
     """Up to the largest page the plan accepts (65536 tokens): hundreds of blocks per page."""
