@@ -16,6 +16,8 @@ LIB_PATH = os.path.join(_HERE, "libabsb.so")
 # the host pass does not know the feature and says so, which is harmless.
 _COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           # leading kernel arguments arrive in scalar registers (the dispatcher fetches them ahead of the first wave)
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",
            "-Wall", "-Wextra", "-Wno-unused-parameter", f"-I{_INCLUDE}", f"-I{_CSRC}"]
 # per-file extras: the files that decide integers keep every binary32 step a single IEEE operation
 _SOURCES = {

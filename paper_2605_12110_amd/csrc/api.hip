@@ -72,7 +72,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     const int B = layer->block_size[h];
     if (!is_pow2(B) || B < 8 || B > 128) return ABSB_ERR_BAD_BLOCK_SIZE;
     // both are powers of two, so B | P or P | B holds: blocks never straddle a page partially
-    g.heads.log2_block[h] = (uint8_t)ilog2(B);
+    g.heads.packed[h >> 2] |= (uint32_t)ilog2(B) << (8 * (h & 3));
   }
 
   Plan p = {};

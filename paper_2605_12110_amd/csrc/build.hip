@@ -134,7 +134,7 @@ __global__ __launch_bounds__(BUILD_THREADS, REP ? 4 : 5) void build_kernel(Build
   if (t0 >= L) return;
   const int last_run = min(runs, (L - t0 + BUILD_RUNS_OF - 1) / BUILD_RUNS_OF) - 1;
   const int off = as_scalar(p.cent_off)[s];
-  const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
+  const int lb = p.g.heads.log2_block(h), lP = p.g.log2_page;
   const int B = 1 << lb;
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void tail_kernel(AppendParams p) {
   const int s = blockIdx.x * BUILD_GROUPS + grp;
   if (s >= p.nseg) return;
   const int b = s / p.g.Hkv, h = s % p.g.Hkv;
-  const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
+  const int lb = p.g.heads.log2_block(h), lP = p.g.log2_page;
   const int t_new = p.seq_lens[b] - 1, t0 = (t_new >> lb) << lb;
   const int32_t* pt = p.page_table + (size_t)b * p.g.pt_stride;
   const uint16_t* k = p.k + (size_t)h * p.g.s_head + (size_t)li * 8;
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(BUILD_THREADS) void append_kernel(AppendParams p) {
     }
   }
   const int off = p.cent_off[s];
-  const int lb = p.g.heads.log2_block[h], lP = p.g.log2_page;
+  const int lb = p.g.heads.log2_block(h), lP = p.g.log2_page;
   const int j = t_new >> lb, t0 = j << lb;
   const int page = p.page_table[(size_t)b * p.g.pt_stride + (t_new >> lP)];
   const uint4 row = *reinterpret_cast<const uint4*>(p.k + (size_t)page * p.g.s_page + (size_t)h * p.g.s_head +

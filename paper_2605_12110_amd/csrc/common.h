@@ -19,9 +19,11 @@
 
 namespace absb {
 
-// Per-KV-head block sizes as log2, passed to kernels by value.
+// Per-KV-head block sizes as log2, passed to kernels by value.  Four to a word: a byte of the kernel's arguments at an
+// index known only at run time would be a vector load, half a microsecond in front of everything else.
 struct HeadTable {
-  uint8_t log2_block[ABSB_MAX_KV_HEADS];
+  uint32_t packed[ABSB_MAX_KV_HEADS / 4];
+  __host__ __device__ int log2_block(int h) const { return (int)(packed[h >> 2] >> (8 * (h & 3)) & 255u); }
 };
 
 // Shape of the layer and of the paged cache, passed to kernels by value.
@@ -176,6 +178,26 @@ inline int check_launch() { return hipGetLastError() == hipSuccess ? ABSB_OK : A
 
 // ------------------------------------------------------------------ device helpers
 #ifdef __HIPCC__
+// Brings the kernel's arguments from byte FROM on into the scalar cache, all lines at once (together with whatever has been
+// asked for before): a dozen cold lines, which the code would else ask for one after the other, wherever it first
+// needs something from one, 0.3 us each.
+template <int FROM, int BYTES>
+__device__ __forceinline__ void fetch_arguments() {
+  constexpr int FIRST = FROM / 64, LINES = (FROM + BYTES + 63) / 64 - FIRST;
+  uint32_t got;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile(
+      ".set absb_at, %2\n\t"
+      ".rept %3\n\t"
+      "s_load_dword %0, %1, absb_at\n\t"
+      ".set absb_at, absb_at + 64\n\t"
+      ".endr\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&s"(got)
+      : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "n"(FIRST * 64), "n"(LINES));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 // Selection segment t -> request b, selection head hs (first query head = hs * Gd), KV head hk,
 // store segment s = b * Hkv + hk, and where the segment's scores start in the score array:
 // the Rk selection segments of a store segment lie side by side, Rk * off[s] + (hs % Rk) * rows.
@@ -220,9 +242,11 @@ __device__ __forceinline__ int budget_blocks(int T, int log2_block, int blocks, 
 
 // Blocks in use of a segment: all rows of a tight layout (no need to wait for the length then);
 // otherwise N_s = ceil(L_b / B_h), never more than the layout has rows for.
+__device__ __forceinline__ int blocks_in_use(bool tight, int rows, int L, int log2_block) {
+  return tight ? rows : min(rows, (int)(((int64_t)L + (1 << log2_block) - 1) >> log2_block));
+}
 __device__ __forceinline__ int blocks_in_use(bool tight, int rows, const int32_t* seq_lens, int b, int log2_block) {
-  if (tight) return rows;
-  return min(rows, (int)(((int64_t)seq_lens[b] + (1 << log2_block) - 1) >> log2_block));
+  return tight ? rows : blocks_in_use(tight, rows, seq_lens[b], log2_block);
 }
 
 template <typename To, typename From>

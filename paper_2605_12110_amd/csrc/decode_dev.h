@@ -208,17 +208,16 @@ struct SplitCtx {
   int b, hs, hk, lb, L, lP;
 };
 
-// Q as the B operand of S = K Q^T: lane (column = lane % 16, group) holds the 16-byte pieces 4c + group of its head's
+// Q (the group's rows, from the first head's on) as the B operand of S = K Q^T: lane (column = lane % 16, group) holds the 16-byte pieces 4c + group of its head's
 // row; columns repeat the heads, and heads beyond G are zero.
 template <int G>
-__device__ __forceinline__ void load_q(const DecodeParams& p, int b, int hs, u32x4 (&qb)[4]) {
+__device__ __forceinline__ void load_q(const uint16_t* rows, u32x4 (&qb)[4]) {
   const int lane = threadIdx.x & 63, grp = lane >> 4, head = lane & (4 * head_sets(G) - 1);
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     qb[c] = u32x4{0u, 0u, 0u, 0u};
     if (head < G)
-      qb[c] = *reinterpret_cast<const u32x4*>(p.q + ((size_t)b * p.g.Hq + (size_t)hs * G + head) * ABSB_HEAD_DIM +
-                                              (4 * c + grp) * 8);
+      qb[c] = *reinterpret_cast<const u32x4*>(rows + head * ABSB_HEAD_DIM + (4 * c + grp) * 8);
   }
 }
 
@@ -622,7 +621,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   // KV head whose rows they read
   const SegMap sm = seg_map(s, p.g.Hsel, p.g.Rk, p.g.Hkv);
   const int b = sm.b, hs = sm.hs, hk = sm.hk;
-  const int lb = p.g.heads.log2_block[hk];
+  const int lb = p.g.heads.log2_block(hk);
   constexpr int SRC = LISTED ? LIST_COHERENT : LIST_PLAIN;
   const int pos_begin = split * p.split_tokens;
 
@@ -658,7 +657,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   const int nsplit = (ntok + p.split_tokens - 1) / p.split_tokens;
 
   u32x4 qb[4];
-  load_q<G>(p, b, hs, qb);
+  load_q<G>(p.q + ((size_t)b * p.g.Hq + (size_t)hs * G) * ABSB_HEAD_DIM, qb);
 
   int32_t* flag = LISTED ? p.flags + (size_t)s * ABSB_TICKET_STRIDE : nullptr;
   if (LISTED && listed) {

@@ -63,15 +63,17 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(FusedParam
     if (p.tk.budget[sm.b] >= p.tk.seq_lens[sm.b]) {
       if (bid % p.chunks_per_seg) return;
       const int rows = p.tk.cent_off[sm.s + 1] - p.tk.cent_off[sm.s];
-      const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, p.tk.heads.log2_block[sm.hk]);
+      const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, p.tk.heads.log2_block(sm.hk));
       if (tid == 0) p.tk.sel_cnt[s] = N;
       if (p.tk.sel_idx)
         for (int i = tid; i < p.tk.sel_stride; i += FUSED_THREADS) p.tk.sel_idx[(size_t)s * p.tk.sel_stride + i] = i < N ? i : -1;
       return;
     }
   }
-  const int N = score_chunk<DT, REP, true>(p.sc, s, bid % p.chunks_per_seg, lds);
-  if (N == 0) return;
+  const SegMap sm = seg_map(s, p.sc.Hsel, p.sc.Rk, p.sc.Hkv);
+  const int off = p.sc.cent_off[sm.s], rows = p.sc.cent_off[sm.s + 1] - off;
+  const int N = blocks_in_use(p.sc.tight, rows, p.sc.seq_lens, sm.b, p.sc.heads.log2_block(sm.hk));
+  if (!score_chunk<DT, REP, true>(p.sc, sm, off, rows, N, G, s, bid % p.chunks_per_seg, lds)) return;
 
   // ---- hand the chunk's scores over; the segment's last chunk goes on to select
   wait_stores_acknowledged();

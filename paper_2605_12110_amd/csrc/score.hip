@@ -8,7 +8,10 @@ namespace absb {
 template <int DT, int REP>
 __global__ __launch_bounds__(256) void score_kernel(ScoreParams p) {
   __shared__ __align__(16) char s_lds[score_lds_bytes<REP>()];
-  score_chunk<DT, REP, false>(p, (int)blockIdx.y, (int)blockIdx.x, s_lds);
+  const SegMap sm = seg_map((int)blockIdx.y, p.Hsel, p.Rk, p.Hkv);
+  const int off = p.cent_off[sm.s], rows = p.cent_off[sm.s + 1] - off;
+  const int N = blocks_in_use(p.tight, rows, p.seq_lens, sm.b, p.heads.log2_block(sm.hk));
+  score_chunk<DT, REP, false>(p, sm, off, rows, N, p.G, (int)blockIdx.y, (int)blockIdx.x, s_lds);
 }
 
 int launch_score(const Geometry& g, const Plan& pl, int dtype, const void* q, const uint8_t* codes,

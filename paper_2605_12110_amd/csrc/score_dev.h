@@ -100,6 +100,21 @@ struct IAdd {
   __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; }
 };
 
+// Where a segment's scores come from: the store segment, its first query head's row, its scales, its codes, its blocks.
+struct ScoreSource {
+  int s;
+  const uint16_t* q;
+  const float* qscale;
+  const uint8_t* codes;
+  int N;
+};
+template <int REP>
+__device__ __forceinline__ ScoreSource score_source(const uint16_t* q, const float* qscale, const uint8_t* codes, const SegMap& sm,
+                                                    int Hq, int G, int off, int N) {
+  constexpr int W = ABSB_HEAD_DIM * (REP + 1);
+  return {sm.s, q + ((size_t)sm.b * Hq + (size_t)sm.hs * G) * ABSB_HEAD_DIM, qscale + (size_t)sm.s * W, codes + (size_t)off * (W / 2), N};
+}
+
 // Group-maximum score (mean pooling): S_j = max_g ( sum_c wq_gc * code_jc + zq_g ) with one exponent
 // for the group; see absb_score.  Same work split as score_chunk below: four lanes per block, the
 // packed 4-bit dots once per query head against that head's digit planes (read from LDS per head),
@@ -108,24 +123,20 @@ struct NoLoads {
   __device__ __forceinline__ void operator()() const {}
 };
 template <int DT, bool RANGE, int PF, class Sink, class Hook>
-__device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t, int j0, int jcount, char* lds,
-                                                     Sink&& sink, ScoreRange* range, Hook&& behind_codes) {
+__device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, const ScoreSource& src, int G, int t, int j0, int jcount,
+                                                     char* lds, Sink&& sink, ScoreRange* range, Hook&& behind_codes) {
   constexpr int W = ABSB_HEAD_DIM, ROW_BYTES = W / 2;
-  const SegMap sm = seg_map(t, p.Hsel, p.Rk, p.Hkv);
-  const int b = sm.b, s = sm.s;
-  const int tid = threadIdx.x, G = p.G;
+  const int tid = threadIdx.x;
   uint16_t qraw[ABSB_MAX_GROUP];
   float scale = 0.0f, zero = 0.0f;
   if (tid < W) {
-    const uint16_t* qrow = p.q + ((size_t)b * p.Hq + (size_t)sm.hs * G) * ABSB_HEAD_DIM + tid;
+    const uint16_t* qrow = src.q + tid;
 #pragma unroll
     for (int g = 0; g < ABSB_MAX_GROUP; ++g) qraw[g] = g < G ? qrow[(size_t)g * ABSB_HEAD_DIM] : (uint16_t)0;
-    scale = p.qscale[(size_t)s * W + tid];
-    zero = p.qmin[(size_t)s * W + tid];
+    scale = src.qscale[tid];
+    zero = p.qmin[(size_t)src.s * W + tid];
   }
-  const int off = p.cent_off[s];
-  const int rows = p.cent_off[s + 1] - off;
-  const int N = blocks_in_use(p.tight, rows, p.seq_lens, b, p.heads.log2_block[sm.hk]);
+  const int N = src.N;
   if (j0 >= N) return 0;
 
   float* s_absmax = reinterpret_cast<float*>(lds);                                   // [4]
@@ -139,7 +150,7 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t
 
   const int quarter = tid & 3;
   const int jend = min(N, j0 + jcount);
-  const uint8_t* base = p.codes + (size_t)off * ROW_BYTES + quarter * 16;
+  const uint8_t* base = src.codes + quarter * 16;
   uint4 pre[PF];
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
@@ -263,36 +274,31 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, int t
   return N;
 }
 
-// Scores of blocks [j0, j0 + jcount) of selection segment t by one work-group of 256 threads; every score is
+// Scores of blocks [j0, j0 + jcount) of selection segment t (its G query heads) by one work-group of 256 threads; every score is
 // handed to sink(block index, score) by one lane.  Returns the segment's block count N_s, or 0 (nothing
 // done, *range untouched) when the segment has no such blocks.  RANGE: *range receives the bounds of the
 // segment's scores.  PF: steps of 64 blocks whose codes are requested at once (a batch).  `behind_codes`: for
 // loads of the caller's that should be requested behind the first batch's.
 // `lds`: score_lds_bytes<REP>() bytes, 16-byte aligned.
 template <int DT, int REP, bool RANGE, int PF, class Sink, class Hook = NoLoads>
-__device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0, int jcount, char* lds, Sink&& sink,
-                                            ScoreRange* range, Hook&& behind_codes = Hook()) {
-  if (REP == 0 && p.agg_max) return score_blocks_groupmax<DT, RANGE, PF>(p, t, j0, jcount, lds, sink, range, behind_codes);
+__device__ __forceinline__ int score_blocks(const ScoreParams& p, const ScoreSource& src, int G, int t, int j0, int jcount, char* lds,
+                                            Sink&& sink, ScoreRange* range, Hook&& behind_codes = Hook()) {
+  if (REP == 0 && p.agg_max) return score_blocks_groupmax<DT, RANGE, PF>(p, src, G, t, j0, jcount, lds, sink, range, behind_codes);
   constexpr int R = REP + 1;                 // vectors per block: the mean, or maxima and minima
   constexpr int W = ABSB_HEAD_DIM * R;       // weights = values per block
   constexpr int ROW_BYTES = W / 2;
-  const SegMap sm = seg_map(t, p.Hsel, p.Rk, p.Hkv);
-  const int b = sm.b, s = sm.s;
   const int tid = threadIdx.x;
   // ---- the group's query values and the scale of this thread's weight go in flight first, all at
   // once: their addresses need nothing from memory, and everything below waits for them
   uint16_t qraw[ABSB_MAX_GROUP];
   float scale = 0.0f;
   if (tid < W) {
-    const uint16_t* qrow =
-        p.q + ((size_t)b * p.Hq + (size_t)sm.hs * p.G) * ABSB_HEAD_DIM + (tid & (ABSB_HEAD_DIM - 1));
+    const uint16_t* qrow = src.q + (tid & (ABSB_HEAD_DIM - 1));
 #pragma unroll
-    for (int g = 0; g < ABSB_MAX_GROUP; ++g) qraw[g] = g < p.G ? qrow[(size_t)g * ABSB_HEAD_DIM] : (uint16_t)0;
-    scale = p.qscale[(size_t)s * W + tid];
+    for (int g = 0; g < ABSB_MAX_GROUP; ++g) qraw[g] = g < G ? qrow[(size_t)g * ABSB_HEAD_DIM] : (uint16_t)0;
+    scale = src.qscale[tid];
   }
-  const int off = p.cent_off[s];
-  const int rows = p.cent_off[s + 1] - off;
-  const int N = blocks_in_use(p.tight, rows, p.seq_lens, b, p.heads.log2_block[sm.hk]);
+  const int N = src.N;
   if (j0 >= N) return 0;
 
   float* s_absmax = reinterpret_cast<float*>(lds);
@@ -304,7 +310,7 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0,
   // 64 blocks per work-group step, PF steps per batch
   const int quarter = tid & 3;
   const int jend = min(N, j0 + jcount);
-  const uint8_t* base = p.codes + (size_t)off * ROW_BYTES + quarter * 16;
+  const uint8_t* base = src.codes + quarter * 16;
   uint4 pre[PF][R];
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
@@ -325,13 +331,13 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0,
       u = Elem<DT>::widen(qraw[0]);
 #pragma unroll
       for (int g = 1; g < ABSB_MAX_GROUP; ++g)
-        if (g < p.G) u = u + Elem<DT>::widen(qraw[g]);
+        if (g < G) u = u + Elem<DT>::widen(qraw[g]);
     } else {
       u = 0.0f;
 #pragma unroll
       for (int g = 0; g < ABSB_MAX_GROUP; ++g) {
         const float x = Elem<DT>::widen(qraw[g]);
-        if (g < p.G && (v == 0 ? x > 0.0f : x < 0.0f)) u = u + x;
+        if (g < G && (v == 0 ? x > 0.0f : x < 0.0f)) u = u + x;
       }
     }
     w = u * scale;
@@ -429,20 +435,15 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, int t, int j0,
   return N;
 }
 
-// Where selection segment t's scores start in the score array.
-__device__ __forceinline__ int32_t* scores_of(const ScoreParams& p, int t) {
-  const SegMap sm = seg_map(t, p.Hsel, p.Rk, p.Hkv);
-  const int off = p.cent_off[sm.s];
-  return p.scores + score_base(sm, p.Rk, off, p.cent_off[sm.s + 1] - off);
-}
-
 // The stand-alone form: blocks [chunk_idx * p.chunk, + p.chunk), scores stored to the score array.
 // COH: they are read by another work-group of the same launch.
 template <int DT, int REP, bool COH>
-__device__ __forceinline__ int score_chunk(const ScoreParams& p, int t, int chunk_idx, char* lds) {
-  int32_t* scores_t = scores_of(p, t);
+__device__ __forceinline__ int score_chunk(const ScoreParams& p, const SegMap& sm, int off, int rows, int N, int G, int t, int chunk_idx,
+                                           char* lds) {
+  int32_t* scores_t = p.scores + score_base(sm, p.Rk, off, rows);
   return score_blocks<DT, REP, false, 4>(
-      p, t, chunk_idx * p.chunk, p.chunk, lds, [&](int j, int32_t sc) { st_i32<COH>(scores_t + j, sc); }, nullptr);
+      p, score_source<REP>(p.q, p.qscale, p.codes, sm, p.Hq, G, off, N), G, t, chunk_idx * p.chunk, p.chunk, lds,
+      [&](int j, int32_t sc) { st_i32<COH>(scores_t + j, sc); }, nullptr);
 }
 
 }  // namespace absb

@@ -140,20 +140,21 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, int t, int c
   // loads behind those of the codes do not.
   const SegMap sm = seg_map(t, p.tk.Hsel, p.tk.Rk, p.tk.Hkv);
   int T = 0, L = 0;
-  const int N = score_blocks<DT, REP, true, 8>(
-      p.sc, t, j0, chunk, lds, [&](int j, int32_t sc) __attribute__((always_inline)) { s_score[j - j0] = sc; }, &range,
+  const int off = p.tk.cent_off[sm.s];
+  const int rows = p.tk.cent_off[sm.s + 1] - off;
+  const int lb = p.tk.heads.log2_block(sm.hk);
+  const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, lb);
+  const bool any = score_blocks<DT, REP, true, 8>(
+      p.sc, score_source<REP>(p.sc.q, p.sc.qscale, p.sc.codes, sm, p.sc.Hq, G, off, N), G, t, j0, chunk, lds, [&](int j, int32_t sc) __attribute__((always_inline)) { s_score[j - j0] = sc; }, &range,
       [&]() __attribute__((always_inline)) {
         const int same = sm.b + (tid >> 10);  // (a lane's own index as far as the compiler can tell)
         T = p.tk.budget[same];
         L = p.tk.seq_lens[same];
       });
-  if (N == 0) return;
+  if (!any) return;
   const int n = min(N - j0, chunk), C = (N + chunk - 1) / chunk;
   __syncthreads();
 
-  const int lb = p.tk.heads.log2_block[sm.hk];
-  const int off = p.tk.cent_off[sm.s];
-  const int rows = p.tk.cent_off[sm.s + 1] - off;
   const SegShape g = seg_shape(p.tk, N, lb, __builtin_amdgcn_readfirstlane(L), __builtin_amdgcn_readfirstlane(T));
   int32_t* out = p.want_list ? p.tk.sel_idx + (size_t)t * p.tk.sel_stride : nullptr;
   if (!g.compete()) {  // nobody waits for this segment's chunks
@@ -363,7 +364,7 @@ template <int DT, int G>
 __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int split, char* lds) {
   const DecodeParams& d = p.dc;
   const SegMap sm = seg_map(t, d.g.Hsel, d.g.Rk, d.g.Hkv);
-  const int b = sm.b, hs = sm.hs, lb = d.g.heads.log2_block[sm.hk];
+  const int b = sm.b, hs = sm.hs, lb = d.g.heads.log2_block(sm.hk);
   const int tid = threadIdx.x, lane = tid & 63;
   const int pos_begin = split * d.split_tokens;
   const int off = d.cent_off[sm.s];
@@ -383,7 +384,7 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   c.L = L;
   c.lP = d.g.log2_page;
   u32x4 qb[4];
-  load_q<G>(d, b, hs, qb);
+  load_q<G>(d.q + ((size_t)b * d.g.Hq + (size_t)hs * G) * ABSB_HEAD_DIM, qb);
 
   const int e0 = pos_begin >> lb, e1 = ((pos_end - 1) >> lb) + 1;  // at most SHARED_LIST entries (checked on the host)
   int32_t* s_list = reinterpret_cast<int32_t*>(lds + SHARED_LDS_LIST);

@@ -188,26 +188,16 @@ __device__ __forceinline__ void pick_bin(TopkShared& sh, int tid, int lane, int 
 //     written after the flag, off the path the attention waits on.  On the rare paths (a long
 //     candidate list, ties, more blocks than a register tile holds) the work list is the ascending
 //     list and the flag goes up at the end.
-//   LOCAL (an EARLY selection whose reader is this work-group itself): the segment's scores are in LDS, and so
-//     is the work list; nothing is published.  Several work-groups may select for the same segment: only the one
-//     with `lead` writes the caller's list and count.
 //   sh, bitmap: LDS as sized by topk_lds_bytes().
-// Every thread of the work-group must call it; all of them return together (LOCAL: behind a barrier).
-struct LocalSelection {
-  const int32_t* scores;  // LDS [blocks in use]
-  int32_t* list;          // LDS [K_s]
-  bool lead;
-};
-template <int NT, int KPT, bool COH, bool EARLY = false, bool LOCAL = false>
-__device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkShared& sh, uint32_t* s_bitmap,
-                                             LocalSelection loc = LocalSelection{nullptr, nullptr, true}) {
-  static_assert(!LOCAL || (EARLY && !COH), "a local selection hands its work list over early, to itself");
+// Every thread of the work-group must call it; all of them return together.
+template <int NT, int KPT, bool COH, bool EARLY = false>
+__device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkShared& sh, uint32_t* s_bitmap) {
   constexpr int WAVES = NT / 64;
   const SegMap sm = seg_map(t, p.Hsel, p.Rk, p.Hkv);
   const int b = sm.b;
   const int off = p.cent_off[sm.s];
   const int rows = p.cent_off[sm.s + 1] - off;
-  const int lb = p.heads.log2_block[sm.hk];
+  const int lb = p.heads.log2_block(sm.hk);
   const int Nall = blocks_in_use(p.tight, rows, p.seq_lens, b, lb);
   int K = budget_blocks(p.budget[b], lb, Nall, p.sel_stride);
   // Forced blocks are a prefix [0, lo) (they hold the first sink_tokens tokens) and a suffix
@@ -219,14 +209,14 @@ __device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkSha
   const int nforced = lo + (Nall - hi);
   const int N = hi - lo;  // competing blocks; the code below indexes them from 0
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int32_t* sc = (LOCAL ? loc.scores : p.scores + score_base(sm, p.Rk, off, rows)) + (N > 0 ? lo : 0);
+  const int32_t* sc = p.scores + score_base(sm, p.Rk, off, rows) + (N > 0 ? lo : 0);
   // `out`: the ascending list (null: not wanted; only possible with EARLY); `wl`: the work list
-  int32_t* out = (!EARLY || (p.sel_idx && loc.lead)) ? p.sel_idx + (size_t)t * p.sel_stride : nullptr;
-  int32_t* wl = LOCAL ? loc.list : EARLY ? p.work_list + (size_t)t * p.sel_stride : nullptr;
+  int32_t* out = (!EARLY || p.sel_idx) ? p.sel_idx + (size_t)t * p.sel_stride : nullptr;
+  int32_t* wl = EARLY ? p.work_list + (size_t)t * p.sel_stride : nullptr;
   auto publish = [&]() __attribute__((always_inline)) {  // EARLY: the work list is complete
-    if (!LOCAL) wait_stores_acknowledged();
+    wait_stores_acknowledged();
     __syncthreads();
-    if (!LOCAL && tid == 0) st_i32<true>(p.flags + (size_t)t * ABSB_TICKET_STRIDE, 1);
+    if (tid == 0) st_i32<true>(p.flags + (size_t)t * ABSB_TICKET_STRIDE, 1);
   };
   constexpr int R = KPT > 0 ? KPT : 1;
   const int ntiles = KPT > 0 ? KPT : (N + NT - 1) / NT;
@@ -248,14 +238,14 @@ __device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkSha
   };
 
   if (tid == 0) {
-    if (loc.lead) st_i32<COH>(p.sel_cnt + t, K);
+    st_i32<COH>(p.sel_cnt + t, K);
     if (p.tickets) p.tickets[(size_t)t * ABSB_TICKET_STRIDE] = 0;
   }
   // entry i of the ascending list (and of the work list, while that one is kept ascending)
   bool wl_ascending = EARLY;
   auto put = [&](int i, int v) __attribute__((always_inline)) {
     if (!EARLY || out) st_i32<COH>(out + i, v);
-    if (EARLY && wl_ascending) st_i32<!LOCAL>(wl + i, v);
+    if (EARLY && wl_ascending) st_i32<true>(wl + i, v);
   };
   if (!EARLY || out) {
 #pragma unroll 1
@@ -371,7 +361,7 @@ __device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkSha
     wl_ascending = !direct;
     const int at = direct ? lo : lo + K;
 #pragma unroll 1
-    for (int i = tid; i < Nall - hi; i += NT) st_i32<!LOCAL>(wl + at + i, hi + i);
+    for (int i = tid; i < Nall - hi; i += NT) st_i32<true>(wl + at + i, hi + i);
   }
 
   if (shift == 0 || ncand <= (uint32_t)TOPK_MAX_CAND) {
@@ -410,7 +400,7 @@ __device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkSha
           left &= left - 1;
           if (use_bm) atomicOr(&bm_gt[j >> 5], 1u << (j & 31));
           if (direct) {
-            if (wl_pos < wl_cand0) st_i32<!LOCAL>(wl + wl_pos, j + lo);  // always true for consistent counts
+            if (wl_pos < wl_cand0) st_i32<true>(wl + wl_pos, j + lo);  // always true for consistent counts
             ++wl_pos;
           }
         }
@@ -507,7 +497,7 @@ __device__ __forceinline__ void topk_segment(const TopkParams& p, int t, TopkSha
           }
           if (rank < need) {
             if (use_bm) atomicOr(&bm_gt[mi >> 5], 1u << (mi & 31));
-            if (direct) st_i32<!LOCAL>(wl + wl_cand0 + rank, (int)mi + lo);
+            if (direct) st_i32<true>(wl + wl_cand0 + rank, (int)mi + lo);
           }
         }
       } else {

@@ -314,6 +314,38 @@ def test_short_segments_around_the_limit_of_the_form_that_selects_for_itself(L, 
     run_all_stages(wl, f"short segments L={L}", O.MINMAX if repr_ else O.MEAN, group_max=gmax)
 
 
+@pytest.mark.parametrize("sink,recent", [(0, 0), (24, 40)])
+@pytest.mark.parametrize("distinct", [0, 3, 40])
+@pytest.mark.parametrize("blocks", [63, 64, 65, 255, 256, 257, 512, 513, 1024])
+def test_selection_by_single_waves_at_the_edges_of_its_tiles(blocks, distinct, sink, recent):
+    """Short segments, selected by waves on their own: numbers of blocks around the register tiles; keys that are all
+    different, or so few (one value a page) that the threshold bin holds dozens or hundreds of blocks that tie.  The list
+    against the oracle, the output bit for bit against the form whose selection is one work-group's."""
+    import torch
+    wl = synth.tiny_workload(seed=blocks + distinct, dtype=synth.F16, Bt=2, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 3, 8 * blocks),
+                             block_size=(8, 16), budget=(max(8, 2 * blocks), 8 * max(1, blocks - 2)))
+    if distinct:
+        rng = np.random.default_rng(blocks)
+        pal = synth.f32_to_bits(rng.standard_normal((distinct, wl.head_dim)).astype(np.float32), wl.dtype)
+        wl.k_cache[:] = pal[rng.integers(0, distinct, size=wl.k_cache.shape[:2])][:, :, None, :]
+    st = O.build_centroids(wl)
+    ref = O.decode_step(wl, st, sink_tokens=sink, recent_tokens=recent)
+    dw = _dev(wl, sink_tokens=sink, recent_tokens=recent)
+    dw.build()
+    outs = []
+    for form in (0, 1):
+        with _opts(dw, step_form=form):
+            for want in (True, False):
+                dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7); dw.out.fill_(float("nan"))
+                dw.decode_fused(want_sel=want)
+                _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, form {form}, list {want}")
+                if want:
+                    assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+                    assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+                outs.append(dw.out.clone())
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
 def test_split_shapes_do_not_change_the_selection_and_stay_within_tolerance():
     wl = synth.make_workload(1, context=8192, budget=2048)
     st = O.build_centroids(wl)
