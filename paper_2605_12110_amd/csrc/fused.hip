@@ -47,33 +47,39 @@ constexpr int FUSED_THREADS = DEC_THREADS;
 
 __host__ __device__ constexpr size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
+// (What an estimation work-group needs first comes as arguments of their own: see small.hip.)
+constexpr int FUSED_LEADING = 5 * 8 + 4 * 4;  // bytes of them
 template <int DT, int G, int REP>
-__global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(FusedParams p) {
+__global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(const int32_t* cent_off, const int32_t* seq_lens, const uint8_t* codes,
+                                                                      const uint16_t* q, const float* qscale, int32_t n_score,
+                                                                      int32_t chunks_per_seg, int32_t Rk, int32_t tight, FusedParams p) {
   extern __shared__ __align__(16) char lds[];
   const int bid = blockIdx.x, tid = threadIdx.x;
-  if (bid >= p.n_score) {
-    const int id = bid - p.n_score;
+  if (bid >= n_score) {
+    const int id = bid - n_score;
     decode_split<DT, G, true>(p.dc, id / p.dc.max_splits, id % p.dc.max_splits, lds);
     return;
   }
-  const int s = bid / p.chunks_per_seg;
+  const int s = bid / chunks_per_seg, chunk = bid % chunks_per_seg, store = Rk == 1 ? s : s / Rk;
+  const int off = cent_off[store], end = cent_off[store + 1];
+  fetch_arguments<FUSED_LEADING, sizeof(FusedParams)>();
+  const int rows = end - off;
+  const SegMap sm = seg_map(s, p.sc.Hsel, Rk, p.sc.Hkv);
   if (p.some_dense) {
     // requests whose budget covers their context: no score decides anything, the attention knows its list
-    const SegMap sm = seg_map(s, p.tk.Hsel, p.tk.Rk, p.tk.Hkv);
-    if (p.tk.budget[sm.b] >= p.tk.seq_lens[sm.b]) {
-      if (bid % p.chunks_per_seg) return;
-      const int rows = p.tk.cent_off[sm.s + 1] - p.tk.cent_off[sm.s];
-      const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, p.tk.heads.log2_block(sm.hk));
+    if (p.tk.budget[sm.b] >= seq_lens[sm.b]) {
+      if (chunk) return;
+      const int N = blocks_in_use(tight, rows, seq_lens, sm.b, p.tk.heads.log2_block(sm.hk));
       if (tid == 0) p.tk.sel_cnt[s] = N;
       if (p.tk.sel_idx)
         for (int i = tid; i < p.tk.sel_stride; i += FUSED_THREADS) p.tk.sel_idx[(size_t)s * p.tk.sel_stride + i] = i < N ? i : -1;
       return;
     }
   }
-  const SegMap sm = seg_map(s, p.sc.Hsel, p.sc.Rk, p.sc.Hkv);
-  const int off = p.sc.cent_off[sm.s], rows = p.sc.cent_off[sm.s + 1] - off;
-  const int N = blocks_in_use(p.sc.tight, rows, p.sc.seq_lens, sm.b, p.sc.heads.log2_block(sm.hk));
-  if (!score_chunk<DT, REP, true>(p.sc, sm, off, rows, N, G, s, bid % p.chunks_per_seg, lds)) return;
+  const int N = blocks_in_use(tight, rows, seq_lens, sm.b, p.sc.heads.log2_block(sm.hk));
+  if (!score_chunk<DT, REP, true>(p.sc, score_source<REP>(q, qscale, codes, s, store, G, off, N), G, s, chunk,
+                                  p.sc.scores + score_base(sm, Rk, off, rows), lds))
+    return;
 
   // ---- hand the chunk's scores over; the segment's last chunk goes on to select
   wait_stores_acknowledged();
@@ -122,10 +128,14 @@ int launch_workspace_init(const Plan& pl, char* ws, hipStream_t stream) {
 
 template <int DT, int G>
 static void launch_fused_rep(const FusedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(FUSED_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.sc.codes, p.sc.q, p.sc.qscale,
+                       p.n_score, p.chunks_per_seg, p.sc.Rk, p.sc.tight, p);
+  };
   if (repr == ABSB_REPR_MEAN)
-    hipLaunchKernelGGL((fused_step_kernel<DT, G, 0>), grid, dim3(FUSED_THREADS), lds, stream, p);
+    launch(fused_step_kernel<DT, G, 0>);
   else
-    hipLaunchKernelGGL((fused_step_kernel<DT, G, 1>), grid, dim3(FUSED_THREADS), lds, stream, p);
+    launch(fused_step_kernel<DT, G, 1>);
 }
 
 template <int DT>

@@ -11,7 +11,9 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreParams p) {
   const SegMap sm = seg_map((int)blockIdx.y, p.Hsel, p.Rk, p.Hkv);
   const int off = p.cent_off[sm.s], rows = p.cent_off[sm.s + 1] - off;
   const int N = blocks_in_use(p.tight, rows, p.seq_lens, sm.b, p.heads.log2_block(sm.hk));
-  score_chunk<DT, REP, false>(p, sm, off, rows, N, p.G, (int)blockIdx.y, (int)blockIdx.x, s_lds);
+  const int t = (int)blockIdx.y;
+  score_chunk<DT, REP, false>(p, score_source<REP>(p.q, p.qscale, p.codes, t, sm.s, p.G, off, N), p.G, t, (int)blockIdx.x,
+                              p.scores + score_base(sm, p.Rk, off, rows), s_lds);
 }
 
 int launch_score(const Geometry& g, const Plan& pl, int dtype, const void* q, const uint8_t* codes,

@@ -108,11 +108,12 @@ struct ScoreSource {
   const uint8_t* codes;
   int N;
 };
+// (Selection segment t's query heads are rows t * G and on, whoever selects: Hq = Hsel * G.)
 template <int REP>
-__device__ __forceinline__ ScoreSource score_source(const uint16_t* q, const float* qscale, const uint8_t* codes, const SegMap& sm,
-                                                    int Hq, int G, int off, int N) {
+__device__ __forceinline__ ScoreSource score_source(const uint16_t* q, const float* qscale, const uint8_t* codes, int t, int s, int G,
+                                                    int off, int N) {
   constexpr int W = ABSB_HEAD_DIM * (REP + 1);
-  return {sm.s, q + ((size_t)sm.b * Hq + (size_t)sm.hs * G) * ABSB_HEAD_DIM, qscale + (size_t)sm.s * W, codes + (size_t)off * (W / 2), N};
+  return {s, q + (size_t)t * G * ABSB_HEAD_DIM, qscale + (size_t)s * W, codes + (size_t)off * (W / 2), N};
 }
 
 // Group-maximum score (mean pooling): S_j = max_g ( sum_c wq_gc * code_jc + zq_g ) with one exponent
@@ -435,15 +436,12 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, const ScoreSou
   return N;
 }
 
-// The stand-alone form: blocks [chunk_idx * p.chunk, + p.chunk), scores stored to the score array.
+// Blocks [chunk_idx * chunk, + chunk), scores stored to the segment's part of the score array.
 // COH: they are read by another work-group of the same launch.
 template <int DT, int REP, bool COH>
-__device__ __forceinline__ int score_chunk(const ScoreParams& p, const SegMap& sm, int off, int rows, int N, int G, int t, int chunk_idx,
-                                           char* lds) {
-  int32_t* scores_t = p.scores + score_base(sm, p.Rk, off, rows);
+__device__ __forceinline__ int score_chunk(const ScoreParams& p, const ScoreSource& src, int G, int t, int chunk_idx, int32_t* scores_t, char* lds) {
   return score_blocks<DT, REP, false, 4>(
-      p, score_source<REP>(p.q, p.qscale, p.codes, sm, p.Hq, G, off, N), G, t, chunk_idx * p.chunk, p.chunk, lds,
-      [&](int j, int32_t sc) { st_i32<COH>(scores_t + j, sc); }, nullptr);
+      p, src, G, t, chunk_idx * p.chunk, p.chunk, lds, [&](int j, int32_t sc) { st_i32<COH>(scores_t + j, sc); }, nullptr);
 }
 
 }  // namespace absb

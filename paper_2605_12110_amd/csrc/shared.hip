@@ -126,7 +126,7 @@ __device__ __forceinline__ int chunk_of(const int32_t* before, int C, int i) {
 
 // ------------------------------------------------------------------ estimation
 template <int DT, int G, int REP>
-__device__ __forceinline__ void shared_chunk(const SharedParams& p, int t, int c, char* lds) {
+__device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreSource& src, int t, int c, int off, int rows, char* lds) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int32_t* s_score = reinterpret_cast<int32_t*>(lds + SHARED_LDS_SCORE);
   uint32_t* s_hist = reinterpret_cast<uint32_t*>(lds + SHARED_LDS_HIST);
@@ -140,12 +140,9 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, int t, int c
   // loads behind those of the codes do not.
   const SegMap sm = seg_map(t, p.tk.Hsel, p.tk.Rk, p.tk.Hkv);
   int T = 0, L = 0;
-  const int off = p.tk.cent_off[sm.s];
-  const int rows = p.tk.cent_off[sm.s + 1] - off;
-  const int lb = p.tk.heads.log2_block(sm.hk);
-  const int N = blocks_in_use(p.tk.tight, rows, p.tk.seq_lens, sm.b, lb);
+  const int lb = p.tk.heads.log2_block(sm.hk), N = src.N;
   const bool any = score_blocks<DT, REP, true, 8>(
-      p.sc, score_source<REP>(p.sc.q, p.sc.qscale, p.sc.codes, sm, p.sc.Hq, G, off, N), G, t, j0, chunk, lds, [&](int j, int32_t sc) __attribute__((always_inline)) { s_score[j - j0] = sc; }, &range,
+      p.sc, src, G, t, j0, chunk, lds, [&](int j, int32_t sc) __attribute__((always_inline)) { s_score[j - j0] = sc; }, &range,
       [&]() __attribute__((always_inline)) {
         const int same = sm.b + (tid >> 10);  // (a lane's own index as far as the compiler can tell)
         T = p.tk.budget[same];
@@ -512,22 +509,39 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   for (int i = tid; i < SHARED_BINS / 4; i += SHARED_THREADS) row[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
+// (What an estimation work-group needs first comes as arguments of their own: see small.hip.)
+constexpr int SHARED_LEADING = 5 * 8 + 4 * 4;  // bytes of them
 template <int DT, int G, int REP>
-__global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(SharedParams p) {
+__global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(const int32_t* cent_off, const int32_t* seq_lens, const uint8_t* codes,
+                                                                        const uint16_t* q, const float* qscale, int32_t n_score,
+                                                                        int32_t chunks_per_seg, int32_t Rk, int32_t tight, SharedParams p) {
   extern __shared__ __align__(16) char lds[];
   const int bid = blockIdx.x;
-  if (bid < p.n_score)
-    shared_chunk<DT, G, REP>(p, bid / p.chunks_per_seg, bid % p.chunks_per_seg, lds);
-  else
-    shared_split<DT, G>(p, (bid - p.n_score) / p.dc.max_splits, (bid - p.n_score) % p.dc.max_splits, lds);
+  if (bid >= n_score) {
+    shared_split<DT, G>(p, (bid - n_score) / p.dc.max_splits, (bid - n_score) % p.dc.max_splits, lds);
+    return;
+  }
+  const int t = bid / chunks_per_seg, store = Rk == 1 ? t : t / Rk;
+  const int off = cent_off[store], end = cent_off[store + 1];
+  fetch_arguments<SHARED_LEADING, sizeof(SharedParams)>();
+  int N = end - off;
+  if (!tight) {
+    const SegMap sm = seg_map(t, p.tk.Hsel, Rk, p.tk.Hkv);
+    N = blocks_in_use(false, end - off, seq_lens[sm.b], p.tk.heads.log2_block(sm.hk));
+  }
+  shared_chunk<DT, G, REP>(p, score_source<REP>(q, qscale, codes, t, store, G, off, N), t, bid % chunks_per_seg, off, end - off, lds);
 }
 
 template <int DT, int G>
 static void launch_shared_rep(const SharedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(SHARED_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.sc.codes, p.sc.q, p.sc.qscale,
+                       p.n_score, p.chunks_per_seg, p.sc.Rk, p.sc.tight, p);
+  };
   if (repr == ABSB_REPR_MEAN)
-    hipLaunchKernelGGL((shared_step_kernel<DT, G, 0>), grid, dim3(SHARED_THREADS), lds, stream, p);
+    launch(shared_step_kernel<DT, G, 0>);
   else
-    hipLaunchKernelGGL((shared_step_kernel<DT, G, 1>), grid, dim3(SHARED_THREADS), lds, stream, p);
+    launch(shared_step_kernel<DT, G, 1>);
 }
 
 template <int DT>

@@ -167,7 +167,6 @@ __global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(const int3
   extern __shared__ __align__(16) char lds[];
   // split-major: with a multiple of eight segments, the splits of a segment land on one die
   const int hs = blockIdx.x, b = blockIdx.y, split = blockIdx.z, t = b * Hsel + hs, tid = threadIdx.x;
-  const SegMap sm{b, hs, hs, t};
   // cold lines, all asked for at once
   const int off = cent_off[t], end = cent_off[t + 1], T = budget[b];
   SplitCtx c;
@@ -188,7 +187,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(const int3
   c.lP = p.dc.g.log2_page;
   if (!p.dc.some_dense || T < c.L)  // (else the budget covers the context: no score decides anything)
     score_blocks<DT, REP, false, 4>(
-        p.sc, score_source<REP>(q, qscale, codes, sm, Hsel * G, G, off, N), G, t, 0, p.max_blocks, lds,
+        p.sc, score_source<REP>(q, qscale, codes, t, t, G, off, N), G, t, 0, p.max_blocks, lds,
         [&](int j, int32_t sc) __attribute__((always_inline)) { s_score[j] = sc; }, nullptr);
 
   const int nsel = budget_blocks(T, lb, N, p.dc.sel_stride);
