@@ -7,8 +7,9 @@
 //   estimation work-group (chunk c of segment t):
 //     1. scores its blocks into LDS (score_dev.h) and counts them in bins that follow from the query's fixed-point
 //        weights alone, so that every chunk of the segment uses the same ones; adds its counts to the segment's row
-//        in memory (device atomics), signs in on the segment's arrival counter;
-//     2. when all chunks have signed in, reads the row: every chunk finds the bin that holds the K_s-th largest score;
+//        in memory (device atomics);
+//     2. reads the row until it holds all blocks that compete: every chunk finds the bin that holds the K_s-th largest
+//        score;
 //     3. writes its blocks above the bin to its own stretch of the segment's list area, the few inside it
 //        (candidates) as (score, index) pairs, and how many of each it has to its counts word;
 //     4. the chunk that gets here last writes the caller's list and count if asked, and takes over where the
@@ -55,7 +56,7 @@ struct SharedParams {
   ScoreParams sc;
   TopkParams tk;
   DecodeParams dc;
-  int32_t* arrive;     // [nseg], ABSB_TICKET_STRIDE apart: chunks whose scores are in the histogram
+  int32_t* gave_up;    // [nseg], ABSB_TICKET_STRIDE apart: 1 = a chunk has waited too long for the segment's histogram
   int32_t* finished;   // [nseg] likewise: chunks whose counts word is out
   int32_t* listed;     // [nseg] likewise: 1 = the last chunk has read what it needs for the caller's list
   int32_t* crowd_flag; // [nseg] likewise: 1 = the crowded segment's work list is complete
@@ -186,40 +187,36 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     const uint32_t v = s_hist[k * SHARED_THREADS + tid];
     if (v) __hip_atomic_fetch_add(row + k * SHARED_THREADS + tid, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  wait_stores_acknowledged();
-  __syncthreads();
-  int32_t* arrive = p.arrive + (size_t)t * ABSB_TICKET_STRIDE;
-  if (tid == 0) {
-    int v = __hip_atomic_fetch_add(arrive, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
-    if (v != C) {
-      const uint64_t t0 = wall_clock64();
-      do {
-        __builtin_amdgcn_s_sleep(2);
-        v = ld_i32<true>(arrive);
-      } while (v != C && wall_clock64() - t0 < DEC_WAIT_LIMIT_TICKS);
-    }
-    if (v != C) st_i32<true>(p.dc.status, 1);
-    s_words[32] = v == C;
-  }
-  __syncthreads();
-  if (!s_words[32]) return;  // the attention work-groups of the segment run into their limit, too
-
-  // ---- 2. the threshold bin: thread tid owns SHARED_BPT bins, thread 0 the highest
+  // ---- 2. the threshold bin: thread tid owns SHARED_BPT bins, thread 0 the highest.  The row is complete when it holds
+  // every block that competes: nobody counts itself in, and whoever reads the row for the last time has it.  (A counter
+  // of the chunks, raised when their additions are acknowledged and read before the row, took two more trips to memory.)
   const int first = SHARED_BINS - SHARED_BPT * (tid + 1);
-  uint32_t cnt[SHARED_BPT], sum = 0;
-  {
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(row, 0, SHARED_BINS * 4, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(row, 0, SHARED_BINS * 4, 0x00020000);
+  int32_t* gave_up = p.gave_up + (size_t)t * ABSB_TICKET_STRIDE;
+  const uint64_t since = wall_clock64();
+  uint32_t cnt[SHARED_BPT], total, above;
+  for (int turn = 0;; turn ^= 1) {  // (scratch words in turns: a wave is at most one barrier ahead)
+    uint32_t sum = 0;
 #pragma unroll
     for (int k = 0; k < SHARED_BPT; k += 4) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (first + k) * 4, 0, 16 /* sc1 */);
       cnt[k] = v.x, cnt[k + 1] = v.y, cnt[k + 2] = v.z, cnt[k + 3] = v.w;
     }
+    if (tid == 0) s_words[40 + turn] = ld_i32<true>(gave_up) || wall_clock64() - since >= DEC_WAIT_LIMIT_TICKS;
 #pragma unroll
     for (int k = 0; k < SHARED_BPT; ++k) sum += cnt[k];
+    above = block_excl_scan<SHARED_THREADS>(sum, s_words + 16 * turn, lane, wave, &total);
+    if (s_words[40 + turn]) {  // one chunk that gives up speaks for all; the segment's attention runs into its limit, too
+      if (tid == 0) {
+        st_i32<true>(gave_up, 1);
+        st_i32<true>(p.dc.status, 1);
+      }
+      return;
+    }
+    if (total == (uint32_t)(g.hi - g.lo)) break;
+    __builtin_amdgcn_s_sleep(2);
   }
   const uint32_t Kc = (uint32_t)(g.K - g.nforced);
-  uint32_t total;
-  uint32_t above = block_excl_scan<SHARED_THREADS>(sum, s_words, lane, wave, &total);
 #pragma unroll
   for (int k = SHARED_BPT - 1; k >= 0; --k) {
     if (above < Kc && Kc <= above + cnt[k]) {
@@ -497,7 +494,7 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
       __builtin_amdgcn_s_sleep(2);
     if (!there) st_i32<true>(d.status, 1);
     *s_gone = !there;
-    st_i32<true>(p.arrive + (size_t)t * ABSB_TICKET_STRIDE, 0);
+    st_i32<true>(p.gave_up + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.listed + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
@@ -579,7 +576,7 @@ int launch_shared(const Geometry& g, const Plan& pl, int dtype, float sm_scale, 
   p.dc.budget = budget;
   p.dc.cent_off = cent_off;
   p.dc.status = reinterpret_cast<int32_t*>(ws + pl.ws_status);
-  p.arrive = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
+  p.gave_up = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
   p.finished = reinterpret_cast<int32_t*>(ws + pl.ws_finished);
   p.listed = reinterpret_cast<int32_t*>(ws + pl.ws_listed);
   p.crowd_flag = reinterpret_cast<int32_t*>(ws + pl.ws_flags);
