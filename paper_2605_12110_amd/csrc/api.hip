@@ -169,6 +169,21 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     // steps (config 4 43.5 -> 42.0 us, config 5 at budget 8192 41.4 -> 39.2).
     if (by_shape && batch->budget_host && p.sum_tokens >= 65536)
       t = std::max<int64_t>(256, ceil_div(ceil_div(p.sum_tokens, 1100), 64) * 64);
+    // Segments of (nearly) equal lists: all splits the same size, if that makes two or four work-groups a compute unit (of
+    // 256) or hardly fewer, of at least 512 tokens each while two are left: a split's set-up and its part of the
+    // merge are paid less often, and no compute unit has one more than the others.  Before / with: 4 x 64K group maximum,
+    // lists of 8192 tokens 39.7 / 36.3 us a step, 4 x 16K, 8192 31.7 / 30.3, 8 x 64K, 16384 96.6 / 91.0, 3 x 30K, 6000 26.0 /
+    // 24.8.  Other numbers lose: 920 work-groups 61.7 / 62.1 (5 x 40K, 14519), 576 35.3 / 37.6 (9 x 60K, 4096), 768 45.7 /
+    // 47.6 (8 x 40K, 16 heads, 3200); so do splits of which the last is hardly filled, and segments whose selection is
+    // shared (below), whose estimation work-groups keep the attention's from spreading evenly: 36.8 / 43.3 (5 x 72K-150K,
+    // 6506).
+    if (by_shape && batch->budget_host && p.max_blocks <= 8192 && p.sum_tokens >= 131072 &&
+        20 * p.sum_tokens >= 19 * p.nseg * p.max_tokens) {
+      int64_t even = std::max<int64_t>({256, std::min<int64_t>(512, ceil_div(p.sum_tokens, 512)), ceil_div(p.sum_tokens, 1024)});
+      even = ceil_div(ceil_div(p.max_tokens, std::max<int64_t>(1, p.max_tokens / even)), 64) * 64;
+      const int64_t splits = ceil_div(p.max_tokens, even), wgs = p.nseg * splits;
+      if (25 * splits * even <= 26 * p.max_tokens && ((wgs >= 448 && wgs <= 512) || (wgs >= 960 && wgs <= 1024))) t = even;
+    }
     if (t < cap_tok) t = cap_tok;
     st_tok = (int)t;
   }
