@@ -1135,8 +1135,8 @@ def test_one_workspace_serves_batches_of_different_shapes_when_cleared_in_betwee
 @pytest.mark.parametrize("form", [1, 2])
 def test_one_launch_step_gives_up_waiting_and_says_so_when_a_counter_was_not_cleared(form):
     """Work-groups of the one-launch forms wait for each other with a time limit.  Forced from the host:
-    one segment's arrival counter starts at a value from which the count its work-groups wait for is
-    never reached, so its list (pipelined form) or its threshold (shared selection) never comes.  The launch
+    one segment's counter starts at a value from which the count its work-groups wait for is never reached
+    (pipelined form), or as the mark of a chunk that has given up (shared selection), so its list never comes.  The launch
     must end by itself (about a quarter of a second per wait), set the status word, leave the other
     segments right, and write NaN into the stuck segment's output rows; after the counters
     are cleared again the step works."""
@@ -1149,7 +1149,7 @@ def test_one_launch_step_gives_up_waiting_and_says_so_when_a_counter_was_not_cle
     assert dw.status() == 0
     ctr = dw.workspace.view(torch.int32)
     stuck = 2
-    ctr[(dw.nsel * 256) // 4 + stuck * 64] = 1000                # the arrival counters follow the attention tickets
+    ctr[(dw.nsel * 256) // 4 + stuck * 64] = 1000                # these counters follow the attention tickets
     dw.sel_cnt.fill_(-7)
     t0 = time.time()
     dw.decode_fused(); _sync()
