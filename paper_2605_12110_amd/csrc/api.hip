@@ -249,9 +249,16 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   bo += align256((size_t)p.total * width * 4);
   p.ws_meet = bo;
   // the chunks of a segment share its words in groups of at most 16 (~10 ns an update of a line), or in the most groups
-  p.build_copies = 1;
-  while (p.build_copies < BUILD_MAX_COPIES && p.build_copies * 16 < p.build_max_chunks) p.build_copies *= 2;
-  p.build_pitch = (int32_t)(align256((size_t)meet_words((int)width, p.build_copies, p.build_max_chunks) * 4) / 4);
+  const auto copies_for = [](int chunks) {
+    int copies = 1;
+    while (copies < BUILD_MAX_COPIES && copies * 16 < chunks) copies *= 2;
+    return copies;
+  };
+  p.build_copies = copies_for(p.build_max_chunks);
+  // ... in a place that never shrinks as contexts grow, as every other part: a workspace for a capacity has room for every
+  // length on the way
+  const int most = build_most_chunks((int)max_len);
+  p.build_pitch = (int32_t)(align256((size_t)meet_words((int)width, copies_for(most), most) * 4) / 4);
   bo += (size_t)p.nstore * p.build_pitch * 4;
   p.ws_build_bytes = bo;
   p.ws_bytes = p.ws_fused_bytes > p.ws_build_bytes ? p.ws_fused_bytes : p.ws_build_bytes;
@@ -261,8 +268,9 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   return ABSB_OK;
 }
 
-// A workspace for every length on the way to the capacity.  All parts grow with the lengths except the partials: longer
-// lists get longer splits, and so at times fewer of them.
+// A workspace for every length on the way to the capacity.  All parts grow with the lengths (the build's shared words
+// because they are placed for the most chunks of any shorter context) except the partials: longer lists get longer splits,
+// and so at times fewer of them.
 static size_t growing_workspace_bytes(const absb_layer* layer, const absb_batch* batch, const Plan& now) {
   absb_batch longest = *batch;
   longest.seq_lens_host = batch->cap_lens_host;

@@ -62,7 +62,7 @@ struct Plan {
   int32_t shared;           // the one-launch step in the form of shared.hip
   int32_t score_chunk;      // centroids per work-group in score
   int32_t build_max_chunks; // max_b build_chunks(L_b)
-  int32_t build_copies;     // of a segment's ranges while its chunks are pooled
+  int32_t build_copies;     // of a segment's ranges while its chunks are pooled (a power of two)
   int32_t build_pitch;      // words between what two segments' chunks share
   // workspace carving (byte offsets, 256-aligned)
   size_t ws_part_o, ws_part_ml, ws_tickets;       // decode partials, per-segment split counters
@@ -96,6 +96,14 @@ __host__ __device__ constexpr int build_chunks(int L) {
   const int tokens = build_runs(L) * BUILD_RUNS_OF;
   return (int)(((int64_t)L + tokens - 1) / tokens);
 }
+// The most chunks that a context of L tokens or any shorter one makes: longer chunks can make fewer of them (262144 tokens
+// 512, 262145 257).
+__host__ __device__ constexpr int build_most_chunks(int L) {
+  const int one_run = (int)(((int64_t)L + BUILD_RUNS_OF - 1) / BUILD_RUNS_OF), now = build_chunks(L);
+  return one_run < BUILD_CHUNKS ? one_run : now > BUILD_CHUNKS ? now : BUILD_CHUNKS;
+}
+static_assert(build_chunks(BUILD_RUNS_OF * BUILD_CHUNKS) == BUILD_CHUNKS && build_chunks(BUILD_RUNS_OF * BUILD_CHUNKS + 1) < BUILD_CHUNKS &&
+              build_chunks(BUILD_RUNS_OF * BUILD_CHUNKS * BUILD_MAX_RUNS) == BUILD_CHUNKS, "at most BUILD_CHUNKS while chunks grow");
 
 // What the build's chunks of a segment share, in words (zero when its kernel starts; W values per block): copies of the
 // minima and maxima per value, a flag per copy, a 64-bit counter (each on memory lines of its own), a bit per chunk

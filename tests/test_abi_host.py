@@ -369,3 +369,22 @@ def test_a_workspace_planned_for_the_capacity_serves_every_length_on_the_way():
             assert room >= absb.absb_plan(layer, _batch(lens, budget, **wide)).workspace_bytes, (trial, lens)
             grown = absb.absb_plan(layer, _batch(lens, budget, cap_lens_host=cap.tolist(), **wide)).workspace_bytes
             assert grown >= room                   # ... whatever lengths it is asked at
+
+
+@pytest.mark.parametrize("repr_", [0, 1])
+def test_a_workspace_planned_for_a_long_capacity_serves_the_builds_on_the_way(repr_):
+    """A longer context can be built by fewer work-groups (more tokens each), which share less: the plan of a layout with
+    room to grow covers the shorter ones, too.  Every part of it follows from the capacity then, so that it is the same
+    at whatever lengths it is asked; lengths and capacities around all changes of the work-groups' size, alone and mixed."""
+    rng = np.random.default_rng(5 + repr_)
+    edge = 512 * 512                                     # tokens that 512 work-groups of one run of 512 take
+    caps = [edge - 1, edge, edge + 1, 270000, 300000, 2 * edge + 1, 3 * edge + 1, 7 * edge + 1, 8 * edge, 8 * edge + 1, 9 * edge]
+    layer = _layer(num_q_heads=8, num_kv_heads=8, block_repr=repr_)
+    for cap in caps:
+        on_the_way = {1, 1000, cap // 2, cap - 1, cap, *rng.integers(1, cap, 8).tolist()}
+        on_the_way |= {k * edge + d for k in range(1, 10) for d in (-30000, -5, 0, 1, 4096) if 0 < k * edge + d <= cap}
+        for other in (None, 700, edge):
+            caps_b = [cap] if other is None else [cap, other]
+            sizes = {absb.absb_plan(layer, _batch([L] + caps_b[1:], [512] * len(caps_b), cap_lens_host=caps_b,
+                                                  pt_stride=1 << 16)).workspace_bytes for L in sorted(on_the_way)}
+            assert len(sizes) == 1, (cap, other, sorted(sizes))

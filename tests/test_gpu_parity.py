@@ -1391,6 +1391,27 @@ def test_lists_widen_with_the_context_when_the_budget_exceeds_it():
     assert len(widths) > 1
 
 
+@pytest.mark.parametrize("repr_", [O.MEAN, O.MINMAX])
+def test_a_store_is_rebuilt_at_every_length_under_one_planned_workspace(repr_):
+    """The workspace of a layout with room for 300000 tokens, planned at 1000 and not a byte more: builds at lengths around
+    the one from which chunks are longer (262144 tokens are 512 of them, 262145 are 257), against the oracle."""
+    from paper_2605_12110_amd import absb
+    full = synth.tiny_workload(seed=76, dtype=synth.F16, Bt=1, Hq=2, Hkv=2, P=64, seq_lens=(300000,), block_size=(128, 64), budget=(512,))
+    dw = _dev(_view_at(full, [1000]), block_repr=repr_, cap_lens=full.seq_lens)
+    dw.workspace = dw.workspace[:absb.absb_plan(dw.layer, dw.batch).workspace_bytes]
+    for L in (1000, 262144, 262145, 240001, 300000):
+        view = _view_at(full, [L])
+        dw.wl = view
+        dw.set_lens([L])
+        dw.workspace.fill_(0xA5)
+        dw.codes.fill_(0x5A)
+        dw.build()
+        _sync()
+        st = O.build_centroids(view, repr_)
+        assert np.array_equal(dw.qscale.cpu().numpy(), st.qscale) and np.array_equal(dw.qmin.cpu().numpy(), st.qmin), L
+        assert np.array_equal(_tight(dw, [L]), st.codes), L
+
+
 def test_one_request_of_a_batch_is_re_ranged_in_place():
     """Re-ranging one request without touching the others: a batch of one (that request's lengths,
     page-table row and capacity) whose code, scale and offset pointers point into the batch's arrays
