@@ -8,8 +8,8 @@
 //     1. scores its blocks into LDS (score_dev.h) and counts them in bins that follow from the query's fixed-point
 //        weights alone, so that every chunk of the segment uses the same ones; adds its counts to the segment's row
 //        in memory (device atomics);
-//     2. reads the row until it holds all blocks that compete: every chunk finds the bin that holds the K_s-th largest
-//        score;
+//     2. waits until the segment's chunks have counted themselves in, then reads the row until it holds all blocks that
+//        compete: every chunk finds the bin that holds the K_s-th largest score;
 //     3. writes its blocks above the bin to its own stretch of the segment's list area, the few inside it
 //        (candidates) as (score, index) pairs, and how many of each it has to its counts word;
 //     4. the chunk that gets here last writes the caller's list and count if asked, and takes over where the
@@ -50,13 +50,14 @@ constexpr int SHARED_PER = SHARED_MAX_CHUNK / SHARED_THREADS;         // blocks 
 constexpr int SHARED_MAX_CAND = 512;                                  // longest list of candidates that is ranked
 constexpr uint32_t SHARED_CROWDED = 0x40000000u;                      // counts word: the list comes from the last chunk
 constexpr uint32_t SHARED_THERE = 0x80000000u;                        // counts word: always set (zero = not yet)
+constexpr int SHARED_GAVE_UP = 1 << 20;                               // arrived: beyond any number of chunks
 
 struct SharedParams {
   int32_t n_score, chunks_per_seg, want_list;
   ScoreParams sc;
   TopkParams tk;
   DecodeParams dc;
-  int32_t* gave_up;    // [nseg], ABSB_TICKET_STRIDE apart: 1 = a chunk has waited too long for the segment's histogram
+  int32_t* arrived;    // [nseg], ABSB_TICKET_STRIDE apart: chunks that have sent their counts; more: one has waited too long
   int32_t* finished;   // [nseg] likewise: chunks whose counts word is out
   int32_t* listed;     // [nseg] likewise: 1 = the last chunk has read what it needs for the caller's list
   int32_t* crowd_flag; // [nseg] likewise: 1 = the crowded segment's work list is complete
@@ -188,12 +189,23 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     if (v) __hip_atomic_fetch_add(row + k * SHARED_THREADS + tid, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // ---- 2. the threshold bin: thread tid owns SHARED_BPT bins, thread 0 the highest.  The row is complete when it holds
-  // every block that competes: nobody counts itself in, and whoever reads the row for the last time has it.  (A counter
-  // of the chunks, raised when their additions are acknowledged and read before the row, took two more trips to memory.)
+  // every block that competes; that alone says so, and whoever reads it then has it.  The counter of the chunks only says
+  // when looking is worth while, so nobody waits for his additions to be acknowledged before he raises it; it is one word.
+  // (Looking at the row itself, 4 KB a chunk and turn, keeps a large grid from its scores: 2 x 504807 tokens in blocks of
+  // 16, 1024 estimation work-groups, 33.4 us a step against 29.0; 3 x 325527 51.2 / 47.6; 1 x 131072 17.7 / 17.4.  With
+  // the additions acknowledged first: 30.5, 48.0 and 17.7.)
   const int first = SHARED_BINS - SHARED_BPT * (tid + 1);
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(row, 0, SHARED_BINS * 4, 0x00020000);
-  int32_t* gave_up = p.gave_up + (size_t)t * ABSB_TICKET_STRIDE;
+  int32_t* arrived = p.arrived + (size_t)t * ABSB_TICKET_STRIDE;
   const uint64_t since = wall_clock64();
+  if (tid == 0) {
+    int v = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    while (v < C && wall_clock64() - since < DEC_WAIT_LIMIT_TICKS) {
+      __builtin_amdgcn_s_sleep(2);
+      v = ld_i32<true>(arrived);
+    }
+  }
+  __syncthreads();
   uint32_t cnt[SHARED_BPT], total, above;
   for (int turn = 0;; turn ^= 1) {  // (scratch words in turns: a wave is at most one barrier ahead)
     uint32_t sum = 0;
@@ -202,13 +214,13 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (first + k) * 4, 0, 16 /* sc1 */);
       cnt[k] = v.x, cnt[k + 1] = v.y, cnt[k + 2] = v.z, cnt[k + 3] = v.w;
     }
-    if (tid == 0) s_words[40 + turn] = ld_i32<true>(gave_up) || wall_clock64() - since >= DEC_WAIT_LIMIT_TICKS;
+    if (tid == 0) s_words[40 + turn] = ld_i32<true>(arrived) > C || wall_clock64() - since >= DEC_WAIT_LIMIT_TICKS;
 #pragma unroll
     for (int k = 0; k < SHARED_BPT; ++k) sum += cnt[k];
     above = block_excl_scan<SHARED_THREADS>(sum, s_words + 16 * turn, lane, wave, &total);
     if (s_words[40 + turn]) {  // one chunk that gives up speaks for all; the segment's attention runs into its limit, too
       if (tid == 0) {
-        st_i32<true>(gave_up, 1);
+        st_i32<true>(arrived, SHARED_GAVE_UP);
         st_i32<true>(p.dc.status, 1);
       }
       return;
@@ -494,7 +506,7 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
       __builtin_amdgcn_s_sleep(2);
     if (!there) st_i32<true>(d.status, 1);
     *s_gone = !there;
-    st_i32<true>(p.gave_up + (size_t)t * ABSB_TICKET_STRIDE, 0);
+    st_i32<true>(p.arrived + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.listed + (size_t)t * ABSB_TICKET_STRIDE, 0);
     st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
@@ -576,7 +588,7 @@ int launch_shared(const Geometry& g, const Plan& pl, int dtype, float sm_scale, 
   p.dc.budget = budget;
   p.dc.cent_off = cent_off;
   p.dc.status = reinterpret_cast<int32_t*>(ws + pl.ws_status);
-  p.gave_up = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
+  p.arrived = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
   p.finished = reinterpret_cast<int32_t*>(ws + pl.ws_finished);
   p.listed = reinterpret_cast<int32_t*>(ws + pl.ws_listed);
   p.crowd_flag = reinterpret_cast<int32_t*>(ws + pl.ws_flags);
