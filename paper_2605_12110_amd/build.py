@@ -11,6 +11,9 @@ _CSRC = os.path.join(_HERE, "csrc")
 _INCLUDE = os.path.join(os.path.dirname(_HERE), "include")
 _OBJ = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libabsb.so")
+# the same library for the tests, except that a work-group of the store build hardly waits for the others of its segment:
+# the rows of nearly all of them go through memory
+NOWAIT_PATH = os.path.join(_HERE, "libabsb_nowait.so")
 
 # -packed-fp32-ops is switched off on purpose (v_pk_*_f32 forms are not trusted on this target);
 # the host pass does not know the feature and says so, which is harmless.
@@ -45,8 +48,8 @@ _HOST_SANITIZE = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitiz
                   "-fno-sanitize-recover=undefined", "-Xarch_host", "-fno-omit-frame-pointer", "-g"]
 
 
-def _compile(name: str, extra) -> str:
-    obj = os.path.join(_OBJ, name.replace(".hip", ".o"))
+def _compile(name: str, extra, obj_name: str = "") -> str:
+    obj = os.path.join(_OBJ, obj_name or name.replace(".hip", ".o"))
     cmd = [_hipcc(), *_COMMON, *extra, "-c", os.path.join(_CSRC, name), "-o", obj]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
@@ -76,16 +79,20 @@ def build_sanitized(jobs: int = 8) -> str:
 
 
 def build_library(force: bool = True, jobs: int = 8) -> str:
-    """Compile every HIP source and link libabsb.so.  `force=False` skips when up to date."""
+    """Compile every HIP source and link libabsb.so (and the tests' libabsb_nowait.so).  `force=False` skips when up to date."""
     srcs = [os.path.join(_CSRC, n) for n in os.listdir(_CSRC)] + [os.path.join(_INCLUDE, "absb.h")]
-    if not force and os.path.exists(LIB_PATH) and all(os.path.getmtime(LIB_PATH) >= os.path.getmtime(s) for s in srcs):
+    libs = (LIB_PATH, NOWAIT_PATH)
+    if not force and all(os.path.exists(l) and os.path.getmtime(l) >= os.path.getmtime(s) for l in libs for s in srcs):
         return LIB_PATH
     os.makedirs(_OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        nowait = ex.submit(_compile, "build.hip", [*_SOURCES["build.hip"], "-DABSB_BUILD_WAIT_TICKS=1"], "build_nowait.o")
         objs = list(ex.map(lambda kv: _compile(*kv), _SOURCES.items()))
-    tmp = LIB_PATH + f".tmp{os.getpid()}"
-    subprocess.check_call([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp])
-    os.replace(tmp, LIB_PATH)
+        other = [nowait.result() if name == "build.hip" else obj for name, obj in zip(_SOURCES, objs)]
+    for lib, parts in zip(libs, (objs, other)):
+        tmp = lib + f".tmp{os.getpid()}"
+        subprocess.check_call([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", *parts, "-o", tmp])
+        os.replace(tmp, lib)
     return LIB_PATH
 
 

@@ -52,9 +52,13 @@ constexpr int BUILD_BATCH = 32;                       // rows it requests at onc
 constexpr int BUILD_EIGHTS = BUILD_RUN / 8;           // rows it may end up with (blocks of eight tokens)
 static_assert(BUILD_RUN == 128, "a wave's tokens are whole blocks of every size, in four batches");
 // A chunk waits while at most so many of its segment's chunks are missing (it would keep their places from them
-// otherwise: 1280 fit the chip, and another launch may want some), and at most so long (100 MHz ticks).
+// otherwise: 1280 fit the chip with mean pooling, 1024 with extrema, and another launch may want some), and at most so
+// long (100 MHz ticks; the tests' second library is built with 1: whoever is not there at the first look leaves).
+#ifndef ABSB_BUILD_WAIT_TICKS
+#define ABSB_BUILD_WAIT_TICKS 20000
+#endif
 constexpr uint32_t BUILD_MISSING = 512;
-constexpr uint64_t BUILD_WAIT_TICKS = 20000;
+constexpr uint64_t BUILD_WAIT_TICKS = ABSB_BUILD_WAIT_TICKS;
 
 // What the chunks of a segment share (meet_...: common.h).  Chunk c raises copy c % copies of the minima and maxima (as
 // keys, below); the chunk that signs in last makes all copies equal to their common maximum and raises the flags.  One

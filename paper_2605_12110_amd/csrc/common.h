@@ -83,8 +83,8 @@ ABSB_HIDDEN int make_plan(const absb_layer* layer, const absb_batch* batch, bool
                           int32_t sel_stride_in, Geometry* geo, Plan* plan, bool lean = false);
 
 // The store build cuts a segment into chunks of a few runs of BUILD_RUNS_OF tokens, a work-group each: one run as long as
-// that makes at most BUILD_CHUNKS of them (1280 work-groups fit the chip; while one segment takes most of the places, the
-// next one's cannot fill the gaps: 400000 tokens of 8 heads 207 us as 782 chunks of a run, 169 as 391 of two; with at
+// that makes at most BUILD_CHUNKS of them (1280 work-groups fit the chip, 1024 that pool extrema; while one segment takes
+// most of the places, the next one's cannot fill the gaps: 400000 tokens of 8 heads 207 us as 782 chunks of a run, 169 as 391 of two; with at
 // most 256 chunks more rows than need to go through memory: 180000 tokens 83 us against 72), and never more than
 // BUILD_MAX_RUNS.
 constexpr int BUILD_CHUNKS = 512, BUILD_MAX_RUNS = 8;

@@ -669,11 +669,17 @@ def test_one_million_token_context(L, sizes, G, budget):
 @pytest.mark.parametrize("lens,sizes,repr_,dtype", [
     ((1, 7, 8, 9), (8, 128), 0, synth.F16),                           # a chunk each, hardly filled
     ((511, 512, 513, 1024), (16, 8, 64), 1, synth.BF16),              # one chunk, two
-    ((8 * 512 * 16 + 1, 8 * 512 * 16, 640), (32, 8), 0, synth.BF16),  # the most chunks that four copies serve, and more
+    ((8 * 512 * 16 + 1, 8 * 512 * 16, 640), (32, 8), 0, synth.BF16),  # 129 chunks, 128 and 2, all with eight copies
+    ((16 * 512,), (8, 32), 0, synth.BF16),                            # 16 chunks, the most with one copy
+    ((16 * 512 + 1, 300), (16, 64), 1, synth.F16),                    # 17, two copies
+    ((32 * 512, 32 * 512 - 1), (8, 128), 1, synth.BF16),              # 32, the most with two
+    ((32 * 512 + 1,), (8, 16), 0, synth.F16),                         # 33, four copies
+    ((64 * 512, 1), (32, 8), 0, synth.F16),                           # 64, the most with four
+    ((64 * 512 + 1, 16 * 512), (64, 8), 1, synth.BF16),               # 65, eight copies
     (((1 << 18) - 5, (1 << 18) + 1, 3), (128, 8), 0, synth.F16),      # the longest chunks of one run, the shortest of two
     (((1 << 18) + 777, 100), (64, 8), 1, synth.F16),
-    ((513 * 4096 + 1,), (8,), 0, synth.BF16),                         # 514 chunks of eight runs: the first ones leave
-    ((640 * 4096 - 13,), (16,), 1, synth.F16),                        # an eighth of the chunks leaves
+    ((513 * 4096 + 1,), (8,), 0, synth.BF16),                         # 514 chunks of eight runs: the first to sign in leaves
+    ((640 * 4096 - 13,), (16,), 1, synth.F16),                        # the first 127 of 640 leave
 ])
 def test_store_build_around_its_chunks_and_runs(lens, sizes, repr_, dtype):
     """The store against the oracle bit for bit, twice on a workspace full of old values, on two streams at once."""
@@ -697,6 +703,41 @@ def test_store_build_around_its_chunks_and_runs(lens, sizes, repr_, dtype):
             assert np.array_equal(d.qscale.cpu().numpy(), st.qscale), "qscale"
             assert np.array_equal(d.qmin.cpu().numpy(), st.qmin), "qmin"
             assert np.array_equal(d.codes.cpu().numpy(), st.codes), "codes"
+
+
+@pytest.mark.parametrize("patient", [True, False])
+@pytest.mark.parametrize("lens,sizes,repr_,dtype", [
+    ((513, 1024, 5000), (8, 32), 0, synth.F16),                        # 2, 2 and 10 chunks of one run
+    ((33 * 512 - 7, 32 * 512), (16, 128), 1, synth.BF16),              # two words of bits, and one
+    ((511 * 512 + 3, 70000), (8, 64), 0, synth.BF16),                  # the most chunks of one run
+    (((1 << 18) + 1, 3 * (1 << 18) - 5), (32, 8), 1, synth.F16),       # two and three runs
+    ((2300 * 4096 + 11,), (128,), 0, synth.F16),                       # 2301 chunks of eight runs: more than 64 words of bits
+])
+def test_store_build_whose_chunks_leave(lens, sizes, repr_, dtype, patient, monkeypatch):
+    """The rows of chunks that do not wait for their segment's ranges, taken on by those that are there: with the library whose
+    chunks leave unless the segment is complete at their first look (nearly all do), and with the library as it is.  Long
+    contexts are laid over a few pages.  The store against the oracle bit for bit, three times on old values."""
+    from paper_2605_12110_amd import absb, build
+    if not patient:
+        monkeypatch.setattr(absb, "LIB_PATH", build.NOWAIT_PATH)
+        monkeypatch.setattr(absb, "_lib", None)
+    held = [min(L, 200000 + 37 * i) for i, L in enumerate(lens)]
+    wl = synth.tiny_workload(seed=len(lens) + lens[0] % 97, dtype=dtype, Bt=len(lens), Hq=len(sizes), Hkv=len(sizes), P=64,
+                             seq_lens=held, block_size=sizes, budget=(64,) * len(lens))
+    wl.page_table = np.stack([np.resize(row[:-(-n // 64)], -(-max(lens) // 64)) for row, n in zip(wl.page_table, held)]).astype(np.int32)
+    wl.seq_lens = np.asarray(lens, np.int32)
+    st = O.build_centroids(wl, repr_)
+    dw = _dev(wl, block_repr=repr_)
+    for i in range(3):
+        dw.workspace.fill_(0x33 + i)
+        dw.codes.fill_(0x5A)
+        dw.build()
+        _sync()
+        rows = dw.plan.total_centroids * (repr_ + 1) * 512        # bytes of binary32 rows, if all of them go through memory
+        assert patient or int((dw.workspace != 0x33 + i).sum()) > rows / 2, "chunks that left"   # (0.87 of them and more do)
+        assert np.array_equal(dw.qscale.cpu().numpy(), st.qscale), "qscale"
+        assert np.array_equal(dw.qmin.cpu().numpy(), st.qmin), "qmin"
+        assert np.array_equal(dw.codes.cpu().numpy(), st.codes), "codes"
 
 
 @pytest.mark.parametrize("P", [2048, 65536])
