@@ -35,7 +35,6 @@
 namespace absb {
 
 struct FusedParams {
-  int32_t n_score, chunks_per_seg;  // first: every work-group starts by reading these
   int32_t some_dense, nseg;
   ScoreParams sc;
   TopkParams tk;
@@ -152,10 +151,10 @@ int launch_workspace_init(const Plan& pl, char* ws, hipStream_t stream) {
 }
 
 template <int DT, int G>
-static void launch_fused_rep(const FusedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+static void launch_fused_rep(const FusedParams& p, int n_score, int chunks_per_seg, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(FUSED_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.sc.codes, p.sc.q, p.sc.qscale,
-                       p.n_score, p.chunks_per_seg, p.sc.Rk, p.sc.tight, p);
+                       n_score, chunks_per_seg, p.sc.Rk, p.sc.tight, p);
   };
   if (repr == ABSB_REPR_MEAN)
     launch(fused_step_kernel<DT, G, 0>);
@@ -164,16 +163,16 @@ static void launch_fused_rep(const FusedParams& p, int repr, dim3 grid, size_t l
 }
 
 template <int DT>
-static void launch_fused_group(const FusedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+static void launch_fused_group(const FusedParams& p, int n_score, int chunks_per_seg, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   switch (p.dc.g.Gd) {
-    case 1: launch_fused_rep<DT, 1>(p, repr, grid, lds, stream); break;
-    case 2: launch_fused_rep<DT, 2>(p, repr, grid, lds, stream); break;
-    case 3: launch_fused_rep<DT, 3>(p, repr, grid, lds, stream); break;
-    case 4: launch_fused_rep<DT, 4>(p, repr, grid, lds, stream); break;
-    case 5: launch_fused_rep<DT, 5>(p, repr, grid, lds, stream); break;
-    case 6: launch_fused_rep<DT, 6>(p, repr, grid, lds, stream); break;
-    case 7: launch_fused_rep<DT, 7>(p, repr, grid, lds, stream); break;
-    default: launch_fused_rep<DT, 8>(p, repr, grid, lds, stream); break;
+    case 1: launch_fused_rep<DT, 1>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 2: launch_fused_rep<DT, 2>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 3: launch_fused_rep<DT, 3>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 4: launch_fused_rep<DT, 4>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 5: launch_fused_rep<DT, 5>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 6: launch_fused_rep<DT, 6>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 7: launch_fused_rep<DT, 7>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    default: launch_fused_rep<DT, 8>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
   }
 }
 
@@ -206,15 +205,15 @@ int launch_fused(const Geometry& g, const Plan& pl, int dtype, float sm_scale, c
   p.dc.status = reinterpret_cast<int32_t*>(ws + pl.ws_status);
   p.score_tickets = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
   // (one work-group a segment writes the lists when every context is covered)
-  p.chunks_per_seg = pl.all_dense ? 1 : (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
+  const int chunks_per_seg = pl.all_dense ? 1 : (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
   p.nseg = pl.nseg;
-  p.n_score = (int)row_of_parts(pl.nseg, p.chunks_per_seg, g.Rk);
-  const dim3 grid((unsigned)(p.n_score + row_of_parts(pl.nseg, pl.max_splits, g.Rk)));
+  const int n_score = (int)row_of_parts(pl.nseg, chunks_per_seg, g.Rk);
+  const dim3 grid((unsigned)(n_score + row_of_parts(pl.nseg, pl.max_splits, g.Rk)));
   const size_t lds = max_sz(max_sz((size_t)DEC_LDS_BYTES, topk_lds_bytes(pl.max_blocks)), score_lds_bytes<1>());
   if (dtype == ABSB_F16)
-    launch_fused_group<ABSB_F16>(p, g.repr, grid, lds, stream);
+    launch_fused_group<ABSB_F16>(p, n_score, chunks_per_seg, g.repr, grid, lds, stream);
   else
-    launch_fused_group<ABSB_BF16>(p, g.repr, grid, lds, stream);
+    launch_fused_group<ABSB_BF16>(p, n_score, chunks_per_seg, g.repr, grid, lds, stream);
   return check_launch();
 }
 

@@ -26,7 +26,7 @@
 namespace absb {
 
 struct ScoreParams {
-  int32_t Hsel, Rk, Hkv, Hq, G;  // G: query heads folded into one selection segment (Gd)
+  int32_t Hsel, Rk, Hkv, G;  // G: query heads folded into one selection segment (Gd)
   int32_t agg_max;          // the group's score is the maximum over its query heads (mean pooling only)
   int32_t chunk, tight;
   const uint16_t* q;        // [Bt][Hq][128]
@@ -57,7 +57,6 @@ inline ScoreParams make_score_params(const Geometry& g, const Plan& pl, const vo
   p.tight = g.tight;
   p.scores = scores;
   p.score_exp = score_exp;
-  p.Hq = g.Hq;
   p.Hkv = g.Hkv;
   p.G = g.Gd;
   p.Hsel = g.Hsel;

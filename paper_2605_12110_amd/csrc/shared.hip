@@ -53,7 +53,7 @@ constexpr uint32_t SHARED_THERE = 0x80000000u;                        // counts 
 constexpr int SHARED_GAVE_UP = 1 << 20;                               // arrived: beyond any number of chunks
 
 struct SharedParams {
-  int32_t n_score, chunks_per_seg, want_list;
+  int32_t want_list;
   ScoreParams sc;
   TopkParams tk;
   DecodeParams dc;
@@ -542,10 +542,10 @@ __global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(const in
 }
 
 template <int DT, int G>
-static void launch_shared_rep(const SharedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+static void launch_shared_rep(const SharedParams& p, int n_score, int chunks_per_seg, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(SHARED_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.sc.codes, p.sc.q, p.sc.qscale,
-                       p.n_score, p.chunks_per_seg, p.sc.Rk, p.sc.tight, p);
+                       n_score, chunks_per_seg, p.sc.Rk, p.sc.tight, p);
   };
   if (repr == ABSB_REPR_MEAN)
     launch(shared_step_kernel<DT, G, 0>);
@@ -554,16 +554,16 @@ static void launch_shared_rep(const SharedParams& p, int repr, dim3 grid, size_t
 }
 
 template <int DT>
-static void launch_shared_group(const SharedParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
+static void launch_shared_group(const SharedParams& p, int n_score, int chunks_per_seg, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   switch (p.dc.g.Gd) {
-    case 1: launch_shared_rep<DT, 1>(p, repr, grid, lds, stream); break;
-    case 2: launch_shared_rep<DT, 2>(p, repr, grid, lds, stream); break;
-    case 3: launch_shared_rep<DT, 3>(p, repr, grid, lds, stream); break;
-    case 4: launch_shared_rep<DT, 4>(p, repr, grid, lds, stream); break;
-    case 5: launch_shared_rep<DT, 5>(p, repr, grid, lds, stream); break;
-    case 6: launch_shared_rep<DT, 6>(p, repr, grid, lds, stream); break;
-    case 7: launch_shared_rep<DT, 7>(p, repr, grid, lds, stream); break;
-    default: launch_shared_rep<DT, 8>(p, repr, grid, lds, stream); break;
+    case 1: launch_shared_rep<DT, 1>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 2: launch_shared_rep<DT, 2>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 3: launch_shared_rep<DT, 3>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 4: launch_shared_rep<DT, 4>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 5: launch_shared_rep<DT, 5>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 6: launch_shared_rep<DT, 6>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    case 7: launch_shared_rep<DT, 7>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
+    default: launch_shared_rep<DT, 8>(p, n_score, chunks_per_seg, repr, grid, lds, stream); break;
   }
 }
 
@@ -597,16 +597,15 @@ int launch_shared(const Geometry& g, const Plan& pl, int dtype, float sm_scale, 
   p.area = scores;
   p.cand = reinterpret_cast<uint64_t*>(ws + pl.ws_cand);
   p.want_list = sel_idx_out ? 1 : 0;
-  p.chunks_per_seg = (pl.max_blocks + p.sc.chunk - 1) / p.sc.chunk;
-  p.n_score = p.chunks_per_seg * pl.nseg;
-  const dim3 grid((unsigned)(p.n_score + pl.nseg * pl.max_splits));
+  const int chunks_per_seg = (pl.max_blocks + p.sc.chunk - 1) / p.sc.chunk, n_score = chunks_per_seg * pl.nseg;
+  const dim3 grid((unsigned)(n_score + pl.nseg * pl.max_splits));
   size_t lds = shared_max(shared_max((size_t)SHARED_LDS_SCORING, (size_t)SHARED_LDS_ATTENTION), topk_lds_bytes(pl.max_blocks));
   const size_t lds_list = SHARED_LDS_SCORING + (size_t)((pl.max_blocks + 31) / 32) * 4;
   if (lds < lds_list) lds = lds_list;
   if (dtype == ABSB_F16)
-    launch_shared_group<ABSB_F16>(p, g.repr, grid, lds, stream);
+    launch_shared_group<ABSB_F16>(p, n_score, chunks_per_seg, g.repr, grid, lds, stream);
   else
-    launch_shared_group<ABSB_BF16>(p, g.repr, grid, lds, stream);
+    launch_shared_group<ABSB_BF16>(p, n_score, chunks_per_seg, g.repr, grid, lds, stream);
   return check_launch();
 }
 
