@@ -46,24 +46,25 @@ constexpr int FUSED_THREADS = DEC_THREADS;
 
 __host__ __device__ constexpr size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
-// Work-group `id` of a row of them: a selection segment (nseg or beyond: none) and which of its `parts` it does.  Segment by
-// segment; but the Rk segments that read one KV head's store do a part one after the other on the same die (work-groups
-// go to the eight dies in turn), whose L2 then has the codes, and the rows that their lists have in common: a selection
-// per query head, 8 x 32K: 41.7 -> 35.1 us a step.
-__device__ __forceinline__ int segment_part(int id, int parts, int Rk, int* part) {
+// Attention work-group `id`: a selection segment (nseg or beyond: none) and which of its splits it does.  Segment by
+// segment; but the Rk segments that read one KV head's rows do a split one after the other on the same die (work-groups
+// go to the eight dies in turn), whose L2 then has the rows that their lists have in common: a selection per query head,
+// 8 x 32K: 43.5 -> 39.0 us a step, 8 x 4000 20.8 -> 17.0, 1 x 128K 21.9 -> 21.9.  (The estimation work-groups in that
+// order, too: 38.9, 17.1, but 23.9.)
+__device__ __forceinline__ int segment_split(int id, int splits, int Rk, int* split) {
   int u = id, r = 0;
   if (Rk > 1) {
     const int y = id >> 3;
     u = ((y / Rk) << 3) + (id & 7);
     r = y % Rk;
   }
-  const int s = u / parts;
-  *part = u - s * parts;
+  const int s = u / splits;
+  *split = u - s * splits;
   return Rk > 1 ? s * Rk + r : s;
 }
 // How many work-groups that takes.
-static int64_t row_of_parts(int nseg, int parts, int Rk) {
-  const int64_t u = (int64_t)(nseg / Rk) * parts;
+static int64_t attention_grid(int nseg, int splits, int Rk) {
+  const int64_t u = (int64_t)(nseg / Rk) * splits;
   return Rk > 1 ? (u + 7) / 8 * 8 * Rk : u;
 }
 
@@ -78,13 +79,11 @@ __global__ __launch_bounds__(FUSED_THREADS, 4) void fused_step_kernel(const int3
   const int bid = blockIdx.x, tid = threadIdx.x;
   if (bid >= n_score) {
     int split;
-    const int s = segment_part(bid - n_score, p.dc.max_splits, Rk, &split);
+    const int s = segment_split(bid - n_score, p.dc.max_splits, Rk, &split);
     if (Rk == 1 || s < p.nseg) decode_split<DT, G, true>(p.dc, s, split, lds);
     return;
   }
-  int chunk;
-  const int s = segment_part(bid, chunks_per_seg, Rk, &chunk), store = Rk == 1 ? s : s / Rk;
-  if (Rk > 1 && s >= p.nseg) return;  // (the last eight parts are not all there)
+  const int s = bid / chunks_per_seg, chunk = bid - s * chunks_per_seg, store = Rk == 1 ? s : s / Rk;
   const int off = cent_off[store], end = cent_off[store + 1];
   fetch_arguments<FUSED_LEADING, sizeof(FusedParams)>();
   const int rows = end - off;
@@ -179,7 +178,7 @@ static void launch_fused_group(const FusedParams& p, int n_score, int chunks_per
 bool fused_one_launch_fits(const Plan& pl) {
   if (pl.max_blocks > TOPK_MAX_BLOCKS) return false;
   const int64_t cps = (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
-  const int64_t grid = (cps + pl.max_splits) * ((int64_t)pl.nseg + 8 * ABSB_MAX_GROUP);  // (or a little less)
+  const int64_t grid = cps * pl.nseg + pl.max_splits * ((int64_t)pl.nseg + 8 * ABSB_MAX_GROUP);  // (or a little less)
   return grid < (int64_t(1) << 31) - 1;
 }
 
@@ -207,8 +206,8 @@ int launch_fused(const Geometry& g, const Plan& pl, int dtype, float sm_scale, c
   // (one work-group a segment writes the lists when every context is covered)
   const int chunks_per_seg = pl.all_dense ? 1 : (pl.max_blocks + pl.score_chunk - 1) / pl.score_chunk;
   p.nseg = pl.nseg;
-  const int n_score = (int)row_of_parts(pl.nseg, chunks_per_seg, g.Rk);
-  const dim3 grid((unsigned)(n_score + row_of_parts(pl.nseg, pl.max_splits, g.Rk)));
+  const int n_score = chunks_per_seg * pl.nseg;
+  const dim3 grid((unsigned)(n_score + attention_grid(pl.nseg, pl.max_splits, g.Rk)));
   const size_t lds = max_sz(max_sz((size_t)DEC_LDS_BYTES, topk_lds_bytes(pl.max_blocks)), score_lds_bytes<1>());
   if (dtype == ABSB_F16)
     launch_fused_group<ABSB_F16>(p, n_score, chunks_per_seg, g.repr, grid, lds, stream);
