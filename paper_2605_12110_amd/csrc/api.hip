@@ -22,6 +22,10 @@ static size_t partial_bytes(const Geometry& g, const Plan& p, int64_t splits) {
   const size_t rows = (size_t)p.nseg * (size_t)splits * g.Gd;
   return align256(rows * ABSB_HEAD_DIM * 4) + align256(rows * 4 * 4);
 }
+// Blocks per estimation work-group: 256 (one batch of loads per lane); in the one-launch step, where estimation
+// work-groups share the CUs with attention work-groups, a large batch does better with two batches per work-group (the
+// prologue is amortised, half as many work-groups).
+static int default_score_chunk(const Plan& p) { return p.total >= 65536 ? 512 : 256; }
 constexpr int MAX_SPLITS_CHOSEN = 64;  // of a segment, unless the caller says what a split is
 
 int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget, int32_t sel_stride_in,
@@ -171,18 +175,22 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       t = std::max<int64_t>(256, ceil_div(ceil_div(p.sum_tokens, 1100), 64) * 64);
     // Segments of (nearly) equal lists: all splits the same size, if that makes two or four work-groups a compute unit (of
     // 256) or hardly fewer, of at least 512 tokens each while two are left: a split's set-up and its part of the
-    // merge are paid less often, and no compute unit has one more than the others.  Before / with: 4 x 64K group maximum,
-    // lists of 8192 tokens 39.7 / 36.3 us a step, 4 x 16K, 8192 31.7 / 30.3, 8 x 64K, 16384 96.6 / 91.0, 3 x 30K, 6000 26.0 /
-    // 24.8.  Other numbers lose: 920 work-groups 61.7 / 62.1 (5 x 40K, 14519), 576 35.3 / 37.6 (9 x 60K, 4096), 768 45.7 /
-    // 47.6 (8 x 40K, 16 heads, 3200); so do splits of which the last is hardly filled, and segments whose selection is
-    // shared (below), whose estimation work-groups keep the attention's from spreading evenly: 36.8 / 43.3 (5 x 72K-150K,
-    // 6506).
+    // merge are paid less often, and no compute unit has one more than the others.  Two only where the estimation
+    // work-groups leave two of the four places of every compute unit free: where they take more, the attention's go to
+    // where places are left or come free first, and two are no longer two everywhere.  Without / with, us a step: 4 x 64K
+    // group maximum, lists of 8192 tokens 39.5 / 37.1, 8 x 64K, lists of 3000 33.5 / 30.3 (512 estimation work-groups), a
+    // selection per query head, 8 x 32K, 4096 72.3 / 65.5 (1024 and 1024); with more than 512 beside two a compute unit it
+    // would be 37.9 / 44.1 (8 x 96K, 4096: 768) and 27.3 / 33.3 (per query head, 4 x 64K, 2048: 1024).  Other numbers
+    // lose: 920 work-groups 61.7 / 62.1 (5 x 40K, 14519), 576 35.3 / 37.6 (9 x 60K, 4096), 768 45.7 / 47.6 (8 x 40K, 16
+    // heads, 3200); so do splits of which the last is hardly filled, and segments whose selection is shared (below), whose
+    // estimation work-groups are many: 36.8 / 43.3 (5 x 72K-150K, 6506).
     if (by_shape && batch->budget_host && p.max_blocks <= 8192 && p.sum_tokens >= 131072 &&
         20 * p.sum_tokens >= 19 * p.nseg * p.max_tokens) {
       int64_t even = std::max<int64_t>({256, std::min<int64_t>(512, ceil_div(p.sum_tokens, 512)), ceil_div(p.sum_tokens, 1024)});
       even = ceil_div(ceil_div(p.max_tokens, std::max<int64_t>(1, p.max_tokens / even)), 64) * 64;
       const int64_t splits = ceil_div(p.max_tokens, even), wgs = p.nseg * splits;
-      if (25 * splits * even <= 26 * p.max_tokens && ((wgs >= 448 && wgs <= 512) || (wgs >= 960 && wgs <= 1024))) t = even;
+      const bool two = wgs >= 448 && wgs <= 512 && p.nseg * ceil_div(p.max_blocks, default_score_chunk(p)) <= 512;
+      if (25 * splits * even <= 26 * p.max_tokens && (two || (wgs >= 960 && wgs <= 1024))) t = even;
     }
     if (t < cap_tok) t = cap_tok;
     st_tok = (int)t;
@@ -208,11 +216,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
   p.shared = p.shared && rows && shared_fits(p);
 
-  // blocks per estimation work-group: 256 (one batch of loads per lane); in the one-launch step,
-  // where estimation work-groups share the CUs with attention work-groups, a large batch does
-  // better with two batches per work-group (the prologue is amortised, half as many work-groups)
-  int sc = opts.score_chunk;
-  p.score_chunk = sc > 0 ? sc : (p.one_launch && p.total >= 65536 ? 512 : 256);
+  p.score_chunk = opts.score_chunk > 0 ? opts.score_chunk : p.one_launch ? default_score_chunk(p) : 256;
 
   // workspace: the split counters of the attention kernel come first, at the same place in every
   // carving (nothing else ever writes there); behind them the three users overlap, since they
