@@ -100,16 +100,16 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       (batch->budget_host[b] >= L ? p.some_dense : p.all_dense) = 1;  // (all_dense holds "some are not" until the end)
     }
     for (int h = 0; h < Hkv; ++h) {
-      const int64_t B = layer->block_size[h];
-      const int64_t N = ceil_div(L, B);
+      const int lb = g.heads.log2_block(h);  // (shifts: a 64-bit division a segment and quantity is most of a plan's time)
+      const int64_t B = int64_t(1) << lb, N = (L + B - 1) >> lb;
       int64_t K = N;
       if (batch->budget_host) {
-        const int64_t kb = ceil_div(batch->budget_host[b], B);
+        const int64_t kb = (batch->budget_host[b] + B - 1) >> lb;
         if (kb < K) K = kb;
         if (K > p.sel_stride) p.sel_stride = (int32_t)K;
       }
       if (sel_stride_in > 0 && sel_stride_in < K) K = sel_stride_in;
-      p.total += ceil_div(cap, B);
+      p.total += (cap + B - 1) >> lb;
       if (N > p.max_blocks) p.max_blocks = (int32_t)N;
       const int64_t tok = K * B;
       if (tok > p.max_tokens) p.max_tokens = tok;

@@ -581,10 +581,13 @@ __global__ __launch_bounds__(BUILD_THREADS) void tail_kernel(AppendParams p) {
 // (What the chain starts with comes as arguments of their own, in scalar registers when a wave
 // starts: a decode loop of 8 tokens and 4 layers 748 -> 735 us, 0.4 an append.)
 template <int DT, int REP>
-__global__ __launch_bounds__(BUILD_THREADS) void append_kernel(const int32_t* seq_lens, const int32_t* page_table, const uint16_t* keys,
-                                                               float* tails, const float* qscale, const float* qmin, int32_t nseg,
-                                                               int32_t Hkv, AppendParams p) {
+__global__ __launch_bounds__(BUILD_THREADS) void append_kernel(addr2 lens_pages, addr2 keys_tails, addr2 qscale_qmin, int2v nseg_Hkv, AppendParams p) {
   constexpr int W = ABSB_HEAD_DIM * (REP + 1);
+  const auto seq_lens = from_addr<const int32_t>(lens_pages.x), page_table = from_addr<const int32_t>(lens_pages.y);
+  const auto keys = from_addr<const uint16_t>(keys_tails.x);
+  const auto tails = from_addr<float>(keys_tails.y);
+  const auto qscale = from_addr<const float>(qscale_qmin.x), qmin = from_addr<const float>(qscale_qmin.y);
+  const int nseg = nseg_Hkv.x, Hkv = nseg_Hkv.y;
   const int tid = threadIdx.x, grp = tid >> 4, li = tid & 15;
   const int s = blockIdx.x * BUILD_GROUPS + grp;
   if (s >= nseg) return;
@@ -651,7 +654,8 @@ template <int DT, int REP>
 static void launch_append_kernel(bool append, const AppendParams& p, hipStream_t stream) {
   const dim3 grid((unsigned)((p.nseg + BUILD_GROUPS - 1) / BUILD_GROUPS)), block(BUILD_THREADS);
   if (append)
-    hipLaunchKernelGGL((append_kernel<DT, REP>), grid, block, 0, stream, p.seq_lens, p.page_table, p.k, p.tail, p.qscale, p.qmin, p.nseg, p.g.Hkv, p);
+    hipLaunchKernelGGL((append_kernel<DT, REP>), grid, block, 0, stream, addr2{addr(p.seq_lens), addr(p.page_table)}, addr2{addr(p.k), addr(p.tail)},
+                       addr2{addr(p.qscale), addr(p.qmin)}, int2v{p.nseg, p.g.Hkv}, p);
   else
     hipLaunchKernelGGL((tail_kernel<DT, REP>), grid, block, 0, stream, p);
 }

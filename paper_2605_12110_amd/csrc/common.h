@@ -184,6 +184,13 @@ ABSB_HIDDEN int launch_head_recall(const float* lse_sel, const float* lse_all, f
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? ABSB_OK : ABSB_ERR_HIP; }
 
+// A kernel's leading arguments, which the build has in scalar registers when a wave starts (14 words), a few to a vector:
+// every argument of a launch costs the host 0.02 us, whatever its size (a decode loop of short steps waits for the host).
+typedef uint64_t addr2 __attribute__((ext_vector_type(2)));
+typedef int32_t int2v __attribute__((ext_vector_type(2)));
+typedef int32_t int4v __attribute__((ext_vector_type(4)));
+inline uint64_t addr(const void* p) { return reinterpret_cast<uint64_t>(p); }
+
 // ------------------------------------------------------------------ device helpers
 #ifdef __HIPCC__
 // Brings the kernel's arguments from byte FROM on into the scalar cache, all lines at once (together with whatever has been
@@ -205,6 +212,12 @@ __device__ __forceinline__ void fetch_arguments() {
       : "=&s"(got)
       : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "n"(FIRST * 64), "n"(LINES));
   __builtin_amdgcn_sched_barrier(0);
+}
+
+// A pointer from a leading argument (to device memory, which the compiler would know of a pointer argument).
+template <typename T>
+__device__ __forceinline__ T* from_addr(uint64_t a) {
+  return (T*)(__attribute__((address_space(1))) T*)a;
 }
 
 // Selection segment t -> request b, selection head hs (first query head = hs * Gd), KV head hk,

@@ -521,9 +521,12 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
 // (What an estimation work-group needs first comes as arguments of their own: see small.hip.)
 constexpr int SHARED_LEADING = 5 * 8 + 4 * 4;  // bytes of them
 template <int DT, int G, int REP>
-__global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(const int32_t* cent_off, const int32_t* seq_lens, const uint8_t* codes,
-                                                                        const uint16_t* q, const float* qscale, int32_t n_score,
-                                                                        int32_t chunks_per_seg, int32_t Rk, int32_t tight, SharedParams p) {
+__global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(addr2 off_lens, addr2 codes_q, int4v shape, uint64_t qscale_, SharedParams p) {
+  const auto cent_off = from_addr<const int32_t>(off_lens.x), seq_lens = from_addr<const int32_t>(off_lens.y);
+  const auto codes = from_addr<const uint8_t>(codes_q.x);
+  const auto q = from_addr<const uint16_t>(codes_q.y);
+  const auto qscale = from_addr<const float>(qscale_);
+  const int n_score = shape.x, chunks_per_seg = shape.y, Rk = shape.z, tight = shape.w;
   extern __shared__ __align__(16) char lds[];
   const int bid = blockIdx.x;
   if (bid >= n_score) {
@@ -544,8 +547,9 @@ __global__ __launch_bounds__(SHARED_THREADS, 4) void shared_step_kernel(const in
 template <int DT, int G>
 static void launch_shared_rep(const SharedParams& p, int n_score, int chunks_per_seg, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(SHARED_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.sc.codes, p.sc.q, p.sc.qscale,
-                       n_score, chunks_per_seg, p.sc.Rk, p.sc.tight, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(SHARED_THREADS), lds, stream,
+                       addr2{addr(p.sc.cent_off), addr(p.sc.seq_lens)}, addr2{addr(p.sc.codes), addr(p.sc.q)},
+                       int4v{n_score, chunks_per_seg, p.sc.Rk, p.sc.tight}, addr(p.sc.qscale), p);
   };
   if (repr == ABSB_REPR_MEAN)
     launch(shared_step_kernel<DT, G, 0>);

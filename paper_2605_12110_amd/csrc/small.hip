@@ -189,10 +189,15 @@ __device__ __forceinline__ void select_in_lds(const SmallShape& g, const int32_t
 // three dimensions say which segment and split it is, without divisions.
 constexpr int SMALL_LEADING = 6 * 8 + 2 * 4;  // bytes of them
 template <int DT, int G, int REP>
-__global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(const int32_t* cent_off, const int32_t* seq_lens, const int32_t* budget,
-                                                                      const uint8_t* codes, const uint16_t* q, const float* qscale,
-                                                                      int32_t Hsel, int32_t tight, SmallParams p) {
+__global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(addr2 off_lens, addr2 budget_codes, addr2 q_qscale,
+                                                                      int2v Hsel_tight, SmallParams p) {
   extern __shared__ __align__(16) char lds[];
+  const auto cent_off = from_addr<const int32_t>(off_lens.x), seq_lens = from_addr<const int32_t>(off_lens.y);
+  const auto budget = from_addr<const int32_t>(budget_codes.x);
+  const auto codes = from_addr<const uint8_t>(budget_codes.y);
+  const auto q = from_addr<const uint16_t>(q_qscale.x);
+  const auto qscale = from_addr<const float>(q_qscale.y);
+  const int Hsel = Hsel_tight.x, tight = Hsel_tight.y;
   // split-major: with a multiple of eight segments, the splits of a segment land on one die
   const int hs = blockIdx.x, b = blockIdx.y, split = blockIdx.z, t = b * Hsel + hs, tid = threadIdx.x;
   // cold lines, all asked for at once
@@ -260,8 +265,9 @@ __global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(const int3
 template <int DT, int G>
 static void launch_small_rep(const SmallParams& p, int repr, dim3 grid, size_t lds, hipStream_t stream) {
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(SMALL_THREADS), lds, stream, p.sc.cent_off, p.sc.seq_lens, p.tk.budget, p.sc.codes, p.sc.q,
-                       p.sc.qscale, p.sc.Hsel, p.sc.tight, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(SMALL_THREADS), lds, stream,
+                       addr2{addr(p.sc.cent_off), addr(p.sc.seq_lens)}, addr2{addr(p.tk.budget), addr(p.sc.codes)},
+                       addr2{addr(p.sc.q), addr(p.sc.qscale)}, int2v{p.sc.Hsel, p.sc.tight}, p);
   };
   if (repr == ABSB_REPR_MEAN)
     launch(small_step_kernel<DT, G, 0>);
