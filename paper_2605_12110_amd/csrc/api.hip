@@ -124,19 +124,18 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if (p.total >= (int64_t(1) << 31) - 1) return ABSB_ERR_BAD_SHAPE;
   if ((int64_t)batch->pt_stride < ceil_div(max_len, P)) return ABSB_ERR_BAD_SHAPE;
 
-  // How absb_decode_fused is enqueued.  Measured on MI355X with cold caches (every step on a copy
-  // of the layer that the last-level cache has forgotten): one launch against one per stage, 1 request of 4K
-  // 14.4 / 16.3 us, 8 of 32K 28.3 / 30.4, 1 of 128K 21.1 / 23.7, 16 of 8K-128K 49.5 / 55.2.  A selection by one
-  // work-group holds 16384 blocks in its registers; beyond (keys re-read) it takes several times longer (67
-  // against 28 us a step at 256K context).  Very long lists (budgets near the context) go to the per-stage
+  // How absb_decode_fused is enqueued.  Measured on MI355X (three copies of a layer in
+  // turn, here and below): one launch against one per stage, 1 request of 4K 9.5 / 15.2 us, 8 of 32K 23.5 / 26.6, 1 of
+  // 128K 17.4 / 21.2, 16 of 8K-128K 42.8 / 49.1.  A selection by one work-group holds 16384 blocks in its registers;
+  // beyond (keys re-read) it takes several times longer (1 request of 256K 63.5 us a step against 20.6 shared, below).  Very long lists (budgets near the context) go to the per-stage
   // path: its attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
   // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything else
   // together, and the work-groups that score a segment share its selection, unless the grid of them is large and
   // mostly empty (mixed lengths) or outgrows the chip: two per compute unit, or four if hardly any of its places
-  // are empty.  256K context, batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 21.0 / 23.0, 25.3 /
-  // 25.6, 37.0 / 29.7 us.  (This is a limit on time, not what makes the waits end: beyond 96128 blocks a
-  // segment three fit a compute unit, not four, and 1024 of them still take 58 us against 92 at 16 segments of
+  // are empty.  256K context in blocks of 8, batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 19.6 /
+  // 23.6, 22.9 / 27.0, 37.2 / 34.9 us.  (This is a limit on time, not what makes the waits end: beyond 96128 blocks a
+  // segment three fit a compute unit, not four, and 1024 of them still take 52 us against 90 at 16 segments of
   // 131072 blocks.  See "Progress" in shared.hip.)
   const int shared_chunk = shared_chunk_blocks(p.max_blocks);
   const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk);
@@ -146,11 +145,11 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
                 : by_shape ? ABSB_STEP_PIPELINED : by_units ? ABSB_STEP_UNITS : ABSB_STEP_PER_STAGE;
   p.one_launch = p.step_form != ABSB_STEP_PER_STAGE;
   // Short segments: every attention work-group scores and selects for itself (small.hip) as long as reading all
-  // of a segment's codes takes less than the hand-overs it saves.  Measured, budgets of 512 and 2048, pipelined /
-  // this: 1 request of 64 blocks 12.2 / 10.2 us, 512 13.1 / 10.8, 1024 13.2 / 11.9, 1536 13.3 / 13.1, 2048 13.3 /
-  // 14.3; 16 requests of 1024 19.2 / 17.9 and 34.9 / 35.0.  Two vectors a block, or a pass per query head, make
-  // the scores dearer (even at 768 blocks; at 2048 blocks x heads).  With a selection per query head the
-  // scores are G times as many: never better there.
+  // of a segment's codes takes less than the hand-overs it saves.  Pipelined / this, 8 heads, blocks of 16: 1 request,
+  // budget 512, 64 blocks 11.8 / 8.4 us, 512 12.9 / 9.5, 768 13.0 / 11.4, 1024 13.0 / 11.9; 16 requests, budget 2048, 512
+  // 32.4 / 28.7, 1024 32.8 / 32.1.  Beyond, by its earlier selection (all four waves together): 1536 13.3 / 13.1, 2048
+  // 13.3 / 14.3.  Two vectors a block, or a pass per query head, make the scores dearer (4 requests, 768 blocks 14.1 /
+  // 13.7; four heads, 512 blocks 14.9 / 13.5).  With a selection per query head the scores are G times as many.
   const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : g.repr == ABSB_REPR_MINMAX ? 768 : SMALL_MAX_BLOCKS;
   p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
   // split-K shape, in 64-token granules (one work-group step).  Swept on MI355X (256 CUs) when three
@@ -207,10 +206,12 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if ((int64_t)p.max_splits * st_tok >= (int64_t(1) << 31)) return ABSB_ERR_BAD_SHAPE;  // positions are 32-bit
 
   // The pipelined form shares the selection, too, where one work-group's passes over a segment take longer than the
-  // two more hand-overs (8 heads, lists of 1024 / 4096 tokens, one work-group / shared: 8192 blocks 17.0 / 17.2
-  // and 19.8 / 19.7 us, 12288 19.2 / 18.0 and 21.8 / 20.0, 16384 19.4 / 18.3 and 21.7 / 19.5).  Not with the
-  // group's maximum, whose scores come a pass per query head: 128K, batch 1, 23.9 / 25.4 us.  (Forced beyond 16384
-  // blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
+  // two more hand-overs.  The line is where the two met when the shared form's chunks waited longer for one another
+  // (8 heads, lists of 1024 / 4096 tokens, one work-group / shared, 8192 blocks 17.0 / 17.2 and 19.8 / 19.7 us, 12288
+  // 19.2 / 18.0 and 21.8 / 20.0).  Now they meet lower: 1 request, 4096 blocks 13.9 / 14.9 and 16.9 / 17.4, 6144 14.9 /
+  // 15.3 and 18.0 / 17.8, 8192 16.5 / 15.7 and 18.9 / 18.0; 8 requests, 2048 18.6 / 18.4 and 33.7 / 32.4, 8192 25.4 / 24.4
+  // and 46.1 / 42.2; and with the group's maximum, which is left to one work-group whatever the length, 16384 blocks 23.4 /
+  // 20.9.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
   p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && !g.agg_max &&
                                                 p.max_blocks > 8192 && p.max_blocks <= 16384 && shared_pays);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
