@@ -419,9 +419,9 @@ __device__ __forceinline__ void poison_rows(const DecodeParams& p, int b, int hs
 // with one split per segment it is normalised and written out; otherwise it goes to slot `split` of
 // the segment's partials, the work-group draws a ticket, and the one that draws ticket nsplit - 1
 // merges the segment's `nsplit` partials with the log-sum-exp rule and writes the output rows.
-// `slots`: partial slots per segment (the stride of the partial arrays).  `on_last`: called by thread 0
-// of the segment's last work-group (the merging one, or the only one), for flags of the segment that
-// have to go back to zero: every other work-group of the segment has drawn its ticket by then.  Every
+// `slots`: partial slots per segment (the stride of the partial arrays).  `on_last`: called by every thread
+// of the segment's last work-group (the merging one, or the only one) ahead of the merge, for words of the segment
+// that have to go back to zero: every other work-group of the segment has drawn its ticket by then.  Every
 // thread of the work-group must call; returns (to all of them) whether this was the segment's last one.
 template <int DT, int G, class OnLast>
 __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b, int hs, int split, int nsplit, int slots,
@@ -498,10 +498,9 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
     __syncthreads();
     if (!s_last) return false;
     // every counter a launch touches is back at zero when the launch ends
-    if (tid == 0) {
+    if (tid == 0)
       __hip_atomic_store(p.tickets + (size_t)s * ABSB_TICKET_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      on_last();
-    }
+    on_last();
 
     // log-sum-exp merge: split lane `sl` of a column takes splits sl, sl + SL, ...; MRG_UNROLL of
     // them per memory round trip, folded into a running (M, Lsum, O)
@@ -571,7 +570,7 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
     }
   }
 
-  if (nsplit <= 1 && tid == 0) on_last();
+  if (nsplit <= 1) on_last();
 
   // ---- normalise and write the group's output rows
   if (tid < NCOL) {
@@ -673,7 +672,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   st.reset();
   attend_positions<DT, G>(p, c, list, pages, pos_begin, pos_end, qb, st);
   finish_split<DT, G>(p, s, b, hs, split, nsplit, p.max_splits, st, lds, [&]() {
-    if (LISTED && listed) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
+    if (LISTED && listed && threadIdx.x == 0) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
   });
 }
 

@@ -33,8 +33,10 @@
 // with lower indices.  Several launches at once hold back at most that many places each.  Every wait is
 // bounded in time; one that runs out sets the status word and leaves NaN in the segment's rows.
 //
-// Counters, histogram rows and counts words must be zero when the launch starts and are zero again when it ends
-// (the work-group that merges a segment's partials clears them).
+// Counters, histogram rows and counts words must be zero when the launch starts and are zero again when it ends:
+// the chunk that finishes last clears what only chunks use, while the attention runs, the work-group that merges a
+// segment's partials the words that the attention reads, ahead of the merge.  (With all of it left to that work-group, behind
+// its merge, a step ended later: 1 x 128K 17.3 us against 16.5, 1 x 256K 20.6 / 19.7.)
 //
 // Compiled with -ffp-contract=off, as the estimation stage requires.
 #include "decode_dev.h"
@@ -46,6 +48,7 @@ namespace absb {
 constexpr int SHARED_THREADS = DEC_THREADS;
 constexpr int SHARED_BINS = SHARED_HIST_BINS;
 constexpr int SHARED_BPT = SHARED_BINS / SHARED_THREADS;              // bins a thread owns
+static_assert(SHARED_BINS == 4 * SHARED_THREADS, "a thread clears four words of a row");
 constexpr int SHARED_PER = SHARED_MAX_CHUNK / SHARED_THREADS;         // blocks of a chunk a thread owns at most
 constexpr int SHARED_MAX_CAND = 512;                                  // longest list of candidates that is ranked
 constexpr uint32_t SHARED_CROWDED = 0x40000000u;                      // counts word: the list comes from the last chunk
@@ -59,7 +62,7 @@ struct SharedParams {
   DecodeParams dc;
   int32_t* arrived;    // [nseg], ABSB_TICKET_STRIDE apart: chunks that have sent their counts; more: one has waited too long
   int32_t* finished;   // [nseg] likewise: chunks whose counts word is out
-  int32_t* listed;     // [nseg] likewise: 1 = the last chunk has read what it needs for the caller's list
+  uint32_t* listed;    // [nseg][SHARED_MAX_CHUNKS]: the counts words once more, for the caller's list
   int32_t* crowd_flag; // [nseg] likewise: 1 = the crowded segment's work list is complete
   uint32_t* hist;      // [nseg][SHARED_BINS]
   uint32_t* counts;    // [nseg][SHARED_MAX_CHUNKS]
@@ -277,6 +280,7 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   if (tid == 0) {
     uint32_t* counts = p.counts + (size_t)t * SHARED_MAX_CHUNKS + c;
     st_i32<true>(reinterpret_cast<int32_t*>(counts), (int32_t)word);
+    if (out) st_i32<true>(reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS + c), (int32_t)word);
     wait_stores_acknowledged();
     s_words[36] = __hip_atomic_fetch_add(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 1, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT) == C - 1;
@@ -284,8 +288,16 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   __syncthreads();
   if (!s_words[36]) return;
 
-  // ---- 4. the segment's last chunk
+  // ---- 4. the segment's last chunk: every other one has read the row and drawn its number
+  __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, tid * 16, 0, 16 /* sc1 */);
+  if (tid == 0) {
+    st_i32<true>(arrived, 0);
+    st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
+  }
+  int32_t* listed = reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS);
+  const uint32_t cw = out && lane < C ? (uint32_t)ld_i32<true>(listed + lane) : 0u;  // lane = chunk
   if (crowded) {
+    if (out && tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);  // (nobody reads them then)
     __syncthreads();  // the words are read; the selection's LDS overlaps them
     TopkParams tk = p.tk;
     if (!p.want_list) tk.sel_idx = nullptr;
@@ -307,9 +319,7 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
 #pragma unroll 1
   for (int w = tid; w < nwords; w += SHARED_THREADS) s_bm[w] = 0;
   __syncthreads();
-  // (the counts words once more, one lane a chunk, as the attention work-groups read them)
   const int64_t seg_place = place - j0;
-  const uint32_t cw = lane < C ? (uint32_t)ld_i32<true>(reinterpret_cast<const int32_t*>(p.counts + (size_t)t * SHARED_MAX_CHUNKS + lane)) : 0u;
   uint32_t sure, ncand;
   const uint32_t ns = cw & 0xffffu, ncd = (cw >> 16) & 0xfffu;
   const uint32_t sure_to = wave_incl_scan_u32(ns, &sure), cand_to = wave_incl_scan_u32(ncd, &ncand);
@@ -332,7 +342,7 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     s_idx[i] = (uint32_t)(pr >> 32);
   }
   __syncthreads();
-  if (tid == 0) st_i32<true>(p.listed + (size_t)t * ABSB_TICKET_STRIDE, 1);  // the counts words may be cleared now
+  if (tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);  // every wave has its copy
 #pragma unroll 1
   for (int k = tid; k < nc; k += SHARED_THREADS) {
     const uint32_t mk = s_key[k], mi = s_idx[k];
@@ -397,6 +407,7 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   int* s_word = reinterpret_cast<int*>(lds + DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4);
   const int chunk = p.sc.chunk, C = (N + chunk - 1) / chunk;
   const bool compete = g.compete();
+  bool crowded = false;
   if (!compete) {
     for (int i = e0 + tid; i < e1; i += SHARED_THREADS) s_list[i - e0] = g.given(i);
     __syncthreads();
@@ -421,7 +432,8 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
       if (split == 0) poison_rows<DT, G>(d, b, hs);
       return;
     }
-    if (__builtin_amdgcn_readfirstlane((int)word) & (int)SHARED_CROWDED) {
+    crowded = __builtin_amdgcn_readfirstlane((int)word) & (int)SHARED_CROWDED;
+    if (crowded) {
       if (!wait_for_flag(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, d.status, s_word)) {
         if (split == 0) poison_rows<DT, G>(d, b, hs);
         return;
@@ -489,33 +501,26 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   AttnState<G> st;
   st.reset();
   attend_positions<DT, G>(d, c, StretchRef{s_list, e0, e1 - 1}, pages, pos_begin, pos_end, qb, st);
-  const bool last = finish_split<DT, G>(d, t, b, hs, split, nsplit, d.max_splits, st, lds, []() {});
+  // The segment's last split: every other one has drawn its ticket, so the words that splits read go back to zero, ahead of
+  // the merge.  (The last chunk clears its own, now or later.)  A count of finished chunks beyond all there are can
+  // only be one that did not start at zero: then nobody was the last chunk, the caller's list may be missing, and the
+  // row is not clear.
+  int fin = 0;
+  const bool last = finish_split<DT, G>(d, t, b, hs, split, nsplit, d.max_splits, st, lds, [&]() __attribute__((always_inline)) {
+    if (!compete) return;
+    if (tid < SHARED_MAX_CHUNKS) st_i32<true>(reinterpret_cast<int32_t*>(p.counts + (size_t)t * SHARED_MAX_CHUNKS) + tid, 0);
+    if (tid == 0) {
+      fin = ld_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE);
+      if (crowded) st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
+    }
+  });
   if (!last || !compete) return;
-  // ---- the segment's last split: what the launch used goes back to zero.  Every other split has drawn its ticket, and
-  // every chunk has counted itself finished before its counts word could be complete for the splits, or does
-  // so right after; the last chunk may still be reading counts words for the caller's list.
-  int* s_gone = s_word + 1;  // (finish_split uses the word before it)
-  if (tid == 0) {
-    const int32_t* fin = p.finished + (size_t)t * ABSB_TICKET_STRIDE;
-    const int32_t* listed = p.listed + (size_t)t * ABSB_TICKET_STRIDE;
-    const bool crowd = ld_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE) != 0;
-    const uint64_t t0 = wall_clock64();
-    bool there;
-    while (!(there = ld_i32<true>(fin) == C && (!p.want_list || crowd || ld_i32<true>(listed))) &&
-           wall_clock64() - t0 < DEC_WAIT_LIMIT_TICKS)
-      __builtin_amdgcn_s_sleep(2);
-    if (!there) st_i32<true>(d.status, 1);
-    *s_gone = !there;
-    st_i32<true>(p.arrived + (size_t)t * ABSB_TICKET_STRIDE, 0);
-    st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
-    st_i32<true>(p.listed + (size_t)t * ABSB_TICKET_STRIDE, 0);
-    st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
-  }
+  if (tid == 0) s_word[1] = fin > C;  // (finish_split uses the word itself)
   __syncthreads();
-  if (*s_gone) poison_rows<DT, G>(d, b, hs);  // (the list may be missing, and a straggler may count after the clearing)
-  if (tid < SHARED_MAX_CHUNKS) p.counts[(size_t)t * SHARED_MAX_CHUNKS + tid] = 0;
-  u32x4* row = reinterpret_cast<u32x4*>(p.hist + (size_t)t * SHARED_BINS);
-  for (int i = tid; i < SHARED_BINS / 4; i += SHARED_THREADS) row[i] = u32x4{0u, 0u, 0u, 0u};
+  if (s_word[1]) {
+    if (tid == 0) st_i32<true>(d.status, 1);
+    poison_rows<DT, G>(d, b, hs);
+  }
 }
 
 // (What an estimation work-group needs first comes as arguments of their own: see small.hip.)
@@ -594,7 +599,7 @@ int launch_shared(const Geometry& g, const Plan& pl, int dtype, float sm_scale, 
   p.dc.status = reinterpret_cast<int32_t*>(ws + pl.ws_status);
   p.arrived = reinterpret_cast<int32_t*>(ws + pl.ws_score_tickets);
   p.finished = reinterpret_cast<int32_t*>(ws + pl.ws_finished);
-  p.listed = reinterpret_cast<int32_t*>(ws + pl.ws_listed);
+  p.listed = reinterpret_cast<uint32_t*>(ws + pl.ws_listed);
   p.crowd_flag = reinterpret_cast<int32_t*>(ws + pl.ws_flags);
   p.hist = reinterpret_cast<uint32_t*>(ws + pl.ws_hist);
   p.counts = reinterpret_cast<uint32_t*>(ws + pl.ws_counts);
