@@ -299,11 +299,9 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   if (crowded) {
     if (out && tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);  // (nobody reads them then)
     __syncthreads();  // the words are read; the selection's LDS overlaps them
-    TopkParams tk = p.tk;
-    if (!p.want_list) tk.sel_idx = nullptr;
     TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
     uint32_t* bitmap = reinterpret_cast<uint32_t*>(lds + ((sizeof(TopkShared) + 15) & ~size_t(15)));
-    topk_segment<SHARED_THREADS, 0, true, true>(tk, t, sh, bitmap);  // raises the segment's flag (tk.flags) itself
+    topk_segment<SHARED_THREADS, 0, true, true>(p.tk, t, sh, bitmap);  // raises the segment's flag itself
     return;
   }
   if (tid == 0) p.tk.sel_cnt[t] = g.K;
