@@ -134,8 +134,9 @@ typedef struct absb_layer {
  * point return ABSB_ERR_BAD_SHAPE before anything is enqueued. */
 typedef enum absb_step_form {
   ABSB_STEP_AUTO = 0,       /* by shape (see absb_decode_fused)                                    */
-  ABSB_STEP_PIPELINED = 1,  /* one launch: estimation work-groups, a segment's last one selects, then
-                               attention work-groups that start on the segment's flag              */
+  ABSB_STEP_PIPELINED = 1,  /* one launch: estimation work-groups, then attention work-groups that start
+                               on their segment's scores and each select from them or, where segments
+                               are long, on the list of the segment's last estimation work-group    */
   ABSB_STEP_UNITS = 2,      /* one launch: the work-groups that score a segment, each a stretch of its
                                blocks, select for it together; attention work-groups as above      */
   ABSB_STEP_PER_STAGE = 3   /* one launch per stage: score, top-k, sparse decode                   */

@@ -30,6 +30,7 @@ _SOURCES = {
     "topk.hip": [],
     "decode.hip": ["-ffp-contract=off"],   # FMAs are written explicitly there
     "fused.hip": ["-ffp-contract=off"],    # holds the estimation stage too
+    "own.hip": ["-ffp-contract=off"],      # likewise
     "shared.hip": ["-ffp-contract=off"],   # likewise
     "small.hip": ["-ffp-contract=off"],    # likewise
     "util.hip": [],

@@ -218,6 +218,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   p.shared = p.shared && rows && shared_fits(p);
 
   p.score_chunk = opts.score_chunk > 0 ? opts.score_chunk : p.one_launch ? default_score_chunk(p) : 256;
+  p.own = p.step_form == ABSB_STEP_PIPELINED && !p.small && !p.shared && own_fits(p);
 
   // workspace: the split counters of the attention kernel come first, at the same place in every
   // carving (nothing else ever writes there); behind them the three users overlap, since they
@@ -410,6 +411,9 @@ static int decode_fused(const absb_layer* layer, const absb_batch* batch, bool l
   if (p.small)
     return launch_small(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
+  if (p.own)
+    return launch_own(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
+                      batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);
   if (p.step_form == ABSB_STEP_PIPELINED && fused_one_launch_fits(p))
     return launch_fused(g, p, layer->dtype, resolve_scale(layer), q, codes, qscale, batch->qmin, k_cache, v_cache, batch->page_table,
                         batch->seq_lens, batch->cent_off, batch->budget, sel_idx_out, sel_cnt, out, lse, ws, st);

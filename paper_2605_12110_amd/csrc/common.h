@@ -55,6 +55,7 @@ struct Plan {
   int32_t split_tokens;     // tokens per split-K work-group
   int32_t max_splits;       // grid.x of the decode kernels
   int32_t small;            // the pipelined step in the form of small.hip
+  int32_t own;              // ... of own.hip
   int32_t some_dense, all_dense;  // requests whose budget covers their context (everything is selected): any, all
   int32_t stream_rows;      // attention: K and V rows are read past the caches
   int32_t one_launch;       // absb_decode_fused: the whole step as one launch (else one launch per stage)
@@ -159,6 +160,15 @@ ABSB_HIDDEN int launch_small(const Geometry& g, const Plan& pl, int dtype, float
                              const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
                              const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
                              char* ws, hipStream_t stream);
+// The whole step in one launch for segments of medium length: every attention work-group selects for itself, from scores that
+// the estimation work-groups hand over.
+constexpr int OWN_MAX_BLOCKS = 4096;
+ABSB_HIDDEN bool own_fits(const Plan& pl);
+ABSB_HIDDEN int launch_own(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
+                           const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
+                           const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,
+                           const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
+                           char* ws, hipStream_t stream);
 ABSB_HIDDEN int launch_workspace_init(const Plan& pl, char* ws, hipStream_t stream);
 // The whole step in one launch for long segments: the work-groups that score a segment select for it together.
 constexpr int SHARED_MAX_CHUNKS = 64;     // of a segment
@@ -181,6 +191,8 @@ ABSB_HIDDEN int launch_stream_read(const void* src, size_t bytes, uint32_t* sink
 
 ABSB_HIDDEN int launch_head_recall(const float* lse_sel, const float* lse_all, float* recall, int nseg, int G,
                                    hipStream_t stream);
+
+__host__ __device__ constexpr size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? ABSB_OK : ABSB_ERR_HIP; }
 

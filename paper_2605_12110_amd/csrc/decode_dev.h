@@ -184,6 +184,13 @@ struct ListRef {
   }
 };
 
+// Entries [first, last] of a list, the work-group's LDS holding those; later ones read the last.
+struct StretchRef {
+  const int32_t* ptr;
+  int first, last;
+  __device__ __forceinline__ int at(int i) const { return ptr[min(i, last) - first]; }
+};
+
 // Query heads are taken in sets of four (the rows of a 4x4x4 product).
 constexpr int head_sets(int G) { return (G + 3) / 4; }
 
@@ -686,6 +693,28 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
   finish_split<DT, G>(p, s, b, hs, split, nsplit, p.max_splits, st, lds, [&]() {
     if (LISTED && listed && threadIdx.x == 0) st_i32<true>(flag, 0);  // every reader of the list has drawn its ticket
   });
+}
+
+// Attention work-group `id`: a selection segment (nseg or beyond: none) and which of its splits it does.  Segment by
+// segment; but the Rk segments that read one KV head's rows do a split one after the other on the same die (work-groups
+// go to the eight dies in turn), whose L2 then has the rows that their lists have in common: a selection per query head,
+// 8 x 32K: 43.5 -> 39.0 us a step, 8 x 4000 20.8 -> 17.0, 1 x 128K 21.9 -> 21.9.  (The estimation work-groups in that
+// order, too: 38.9, 17.1, but 23.9.)
+__device__ __forceinline__ int segment_split(int id, int splits, int Rk, int* split) {
+  int u = id, r = 0;
+  if (Rk > 1) {
+    const int y = id >> 3;
+    u = ((y / Rk) << 3) + (id & 7);
+    r = y % Rk;
+  }
+  const int s = u / splits;
+  *split = u - s * splits;
+  return Rk > 1 ? s * Rk + r : s;
+}
+// How many work-groups that takes.
+inline int64_t attention_grid(int nseg, int splits, int Rk) {
+  const int64_t u = (int64_t)(nseg / Rk) * splits;
+  return Rk > 1 ? (u + 7) / 8 * 8 * Rk : u;
 }
 
 }  // namespace absb

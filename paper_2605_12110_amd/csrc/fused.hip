@@ -44,30 +44,6 @@ struct FusedParams {
 
 constexpr int FUSED_THREADS = DEC_THREADS;
 
-__host__ __device__ constexpr size_t max_sz(size_t a, size_t b) { return a > b ? a : b; }
-
-// Attention work-group `id`: a selection segment (nseg or beyond: none) and which of its splits it does.  Segment by
-// segment; but the Rk segments that read one KV head's rows do a split one after the other on the same die (work-groups
-// go to the eight dies in turn), whose L2 then has the rows that their lists have in common: a selection per query head,
-// 8 x 32K: 43.5 -> 39.0 us a step, 8 x 4000 20.8 -> 17.0, 1 x 128K 21.9 -> 21.9.  (The estimation work-groups in that
-// order, too: 38.9, 17.1, but 23.9.)
-__device__ __forceinline__ int segment_split(int id, int splits, int Rk, int* split) {
-  int u = id, r = 0;
-  if (Rk > 1) {
-    const int y = id >> 3;
-    u = ((y / Rk) << 3) + (id & 7);
-    r = y % Rk;
-  }
-  const int s = u / splits;
-  *split = u - s * splits;
-  return Rk > 1 ? s * Rk + r : s;
-}
-// How many work-groups that takes.
-static int64_t attention_grid(int nseg, int splits, int Rk) {
-  const int64_t u = (int64_t)(nseg / Rk) * splits;
-  return Rk > 1 ? (u + 7) / 8 * 8 * Rk : u;
-}
-
 // (What an estimation work-group needs first comes as arguments of their own: see small.hip.)
 constexpr int FUSED_LEADING = 5 * 8 + 4 * 4;  // bytes of them
 template <int DT, int G, int REP>

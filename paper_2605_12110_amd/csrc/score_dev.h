@@ -437,9 +437,9 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, const ScoreSou
 
 // Blocks [chunk_idx * chunk, + chunk), scores stored to the segment's part of the score array.
 // COH: they are read by another work-group of the same launch.
-template <int DT, int REP, bool COH>
+template <int DT, int REP, bool COH, int PF = 4>
 __device__ __forceinline__ int score_chunk(const ScoreParams& p, const ScoreSource& src, int G, int t, int chunk_idx, int32_t* scores_t, char* lds) {
-  return score_blocks<DT, REP, false, 4>(
+  return score_blocks<DT, REP, false, PF>(
       p, src, G, t, chunk_idx * p.chunk, p.chunk, lds, [&](int j, int32_t sc) { st_i32<COH>(scores_t + j, sc); }, nullptr);
 }
 

@@ -85,27 +85,6 @@ constexpr int SHARED_LDS_ATTENTION = SHARED_LDS_LIST + SHARED_LIST * 4;
 
 __host__ __device__ constexpr size_t shared_max(size_t a, size_t b) { return a > b ? a : b; }
 
-// Shape of a selection segment as every one of its work-groups derives it.
-struct SegShape {
-  int Nall, K;    // blocks in use, blocks to select
-  int lo, hi;     // forced blocks are [0, lo) and [hi, Nall); [lo, hi) compete
-  int nforced;
-  __device__ __forceinline__ bool compete() const { return K < Nall && nforced < K; }
-  // entry i of the ascending list when no score decides anything
-  __device__ __forceinline__ int given(int i) const { return K >= Nall || i < lo ? i : hi + (i - lo); }
-};
-__device__ __forceinline__ SegShape seg_shape(const TopkParams& p, int Nall, int lb, int L, int T) {
-  SegShape g;
-  g.Nall = Nall;
-  g.K = budget_blocks(T, lb, Nall, p.sel_stride);
-  g.lo = 0;
-  g.hi = Nall;
-  if (p.sink_tokens > 0) g.lo = min(Nall, (int)(((int64_t)p.sink_tokens + (1 << lb) - 1) >> lb));
-  if (p.recent_tokens > 0) g.hi = max(g.lo, min(Nall, max(0, L - p.recent_tokens) >> lb));
-  g.nforced = g.lo + (Nall - g.hi);
-  return g;
-}
-
 // The bins of a segment's scores.
 struct ScoreBins {
   uint32_t lo, mul;  // mul: bins per unit of score, in 2^-32; 0: a bin is one score
@@ -367,13 +346,6 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
 }
 
 // ------------------------------------------------------------------ attention
-// Entries [first, last] of a list, the work-group's LDS holding those; later ones read the last.
-struct StretchRef {
-  const int32_t* ptr;
-  int first, last;
-  __device__ __forceinline__ int at(int i) const { return ptr[min(i, last) - first]; }
-};
-
 template <int DT, int G>
 __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int split, char* lds) {
   const DecodeParams& d = p.dc;

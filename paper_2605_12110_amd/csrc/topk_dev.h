@@ -94,6 +94,27 @@ __host__ __device__ constexpr size_t topk_lds_bytes(int max_blocks) {
   return ((sizeof(TopkShared) + 15) & ~size_t(15)) + (size_t)2 * ((max_blocks + 31) / 32) * sizeof(uint32_t);
 }
 
+// Shape of a selection segment as every one of its work-groups derives it.
+struct SegShape {
+  int Nall, K;    // blocks in use, blocks to select
+  int lo, hi;     // forced blocks are [0, lo) and [hi, Nall); [lo, hi) compete
+  int nforced;
+  __device__ __forceinline__ bool compete() const { return K < Nall && nforced < K; }
+  // entry i of the ascending list when no score decides anything
+  __device__ __forceinline__ int given(int i) const { return K >= Nall || i < lo ? i : hi + (i - lo); }
+};
+__device__ __forceinline__ SegShape seg_shape(const TopkParams& p, int Nall, int lb, int L, int T) {
+  SegShape g;
+  g.Nall = Nall;
+  g.K = budget_blocks(T, lb, Nall, p.sel_stride);
+  g.lo = 0;
+  g.hi = Nall;
+  if (p.sink_tokens > 0) g.lo = min(Nall, (int)(((int64_t)p.sink_tokens + (1 << lb) - 1) >> lb));
+  if (p.recent_tokens > 0) g.hi = max(g.lo, min(Nall, max(0, L - p.recent_tokens) >> lb));
+  g.nforced = g.lo + (Nall - g.hi);
+  return g;
+}
+
 struct UMin {
   __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
 };

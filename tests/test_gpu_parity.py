@@ -346,6 +346,37 @@ def test_selection_by_single_waves_at_the_edges_of_its_tiles(blocks, distinct, s
     assert all(torch.equal(outs[0], o) for o in outs[1:])
 
 
+@pytest.mark.parametrize("sink,recent", [(0, 0), (24, 40)])
+@pytest.mark.parametrize("distinct", [0, 40, 700])
+@pytest.mark.parametrize("blocks", [1025, 2048, 2049, 4096, 4097])
+def test_selection_by_every_attention_work_group_at_the_edges_of_its_tiles(blocks, distinct, sink, recent):
+    """Segments of medium length, which every attention work-group selects for itself: numbers of blocks around the register
+    tiles and one beyond the form; keys that are all different, or so few (one value a page) that the threshold bin is
+    crowded and blocks tie.  A small and a large budget; a wrong block of either shows in the log-sum-exp.  The list
+    against the oracle, with the list and without: the same bits."""
+    import torch
+    wl = synth.tiny_workload(seed=blocks + distinct, dtype=synth.F16, Bt=2, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 3, 8 * blocks),
+                             block_size=(8, 16), budget=(96, 8 * (blocks // 3)))
+    if distinct:
+        rng = np.random.default_rng(blocks)
+        pal = synth.f32_to_bits(rng.standard_normal((distinct, wl.head_dim)).astype(np.float32), wl.dtype)
+        wl.k_cache[:] = pal[rng.integers(0, distinct, size=wl.k_cache.shape[:2])][:, :, None, :]
+    ref = O.decode_step(wl, O.build_centroids(wl), sink_tokens=sink, recent_tokens=recent)
+    dw = _dev(wl, sink_tokens=sink, recent_tokens=recent)
+    dw.build()
+    outs = []
+    for want in (True, False):
+        dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7); dw.out.fill_(float("nan"))
+        dw.decode_fused(want_sel=want)
+        _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, list {want}")
+        if want:
+            assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+            assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+        outs.append(dw.out.clone())
+        assert not _hand_over_state(dw).any()
+    assert torch.equal(outs[0], outs[1])
+
+
 def test_split_shapes_do_not_change_the_selection_and_stay_within_tolerance():
     wl = synth.make_workload(1, context=8192, budget=2048)
     st = O.build_centroids(wl)
