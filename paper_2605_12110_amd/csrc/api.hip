@@ -130,27 +130,34 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // beyond (keys re-read) it takes several times longer (1 request of 256K 63.5 us a step against 20.6 shared, below).  Very long lists (budgets near the context) go to the per-stage
   // path: its attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
-  // Segments beyond 16384 blocks: there the selection by one work-group costs more than everything else
-  // together, and the work-groups that score a segment share its selection, unless the grid of them is large and
-  // mostly empty (mixed lengths) or outgrows the chip: two per compute unit, or four if hardly any of its places
-  // are empty.  256K context in blocks of 8, batch 1, 2, 4, lists of 1024 tokens, shared / per stage: 19.6 /
-  // 23.6, 22.9 / 27.0, 37.2 / 34.9 us.  (This is a limit on time, not what makes the waits end: beyond 96128 blocks a
-  // segment three fit a compute unit, not four, and 1024 of them still take 52 us against 90 at 16 segments of
-  // 131072 blocks.  See "Progress" in shared.hip.)
+  // Segments beyond 4096 blocks: the work-groups that score a segment share its selection, unless the grid of them is
+  // large.  They wait for each other, twice as long as the scores alone take, and those that are waiting hold back the
+  // others beyond four a compute unit.  So: at most two a compute unit, or four if hardly any of the grid is empty, or (empty
+  // ones leave at once) as long as the ones with blocks are three a compute unit, four beyond 16384 blocks, where the
+  // alternative is a launch per stage.  One work-group's selection / shared, us a step (work-groups with blocks, of the
+  // grid): 16 x 10K-73K in blocks of 16, max-min 34.4 / 31.8 and 8 % 59.3 / 57.0 (660 of 1152), 8 x 20K-128K, 4096 36.6 / 35.8
+  // (470 of 2048), 16 x 8K-128K 42.0 / 40.8 (575 of 2048); 16 x 5K-128K in blocks of 8 to 128 40.4 / 41.1 (830 of 4096), 16 x
+  // 96K 41.3 / 41.5 (900 of 1536), 16 x 128K in blocks of 16 48.8 / 49.4 (all of 2048); and a grid that is nearly all empty
+  // keeps the few that wait from their places: one request of 131000 beside 16 of 7 to 1000 tokens 21.9 / 27.1 (150 of 2176), two
+  // beside 14 of 2000 31.4 / 31.0 (283 of 2048).  Per stage / shared: 4 x 256K, 2048 30.8 / 29.7 (794 of 2048).  Query heads that select for themselves leave the order in which they find each other's rows in
+  // a die's L2: 2 x 128K 26.5 / 24.3 (906 of 1024), but 16 x 10K-73K 87 / 109 (2600 of 4608).
+  // (This is a limit on time, not what makes the waits end: beyond 96128 blocks a segment three fit a compute unit, not
+  // four, and 1024 of them still take 52 us against 90 at 16 segments of 131072 blocks.  See "Progress" in shared.hip.)
   const int shared_chunk = shared_chunk_blocks(p.max_blocks);
-  const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk);
-  const bool shared_pays = shared_grid <= 512 || (shared_grid <= 1024 && 2 * ceil_div(p.total * g.Rk, shared_chunk) >= shared_grid);
+  const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk), shared_real = ceil_div(p.total * g.Rk, shared_chunk);
+  const bool shared_pays = shared_grid <= 512 || (shared_grid <= 1024 && 2 * shared_real >= shared_grid) ||
+                           (g.Rk == 1 && shared_real <= (p.max_blocks > 16384 ? 1024 : 768) && 8 * shared_real >= shared_grid);
   const bool by_units = !by_shape && p.max_blocks > 16384 && shared_pays;
   p.step_form = opts.step_form != ABSB_STEP_AUTO ? opts.step_form
                 : by_shape ? ABSB_STEP_PIPELINED : by_units ? ABSB_STEP_UNITS : ABSB_STEP_PER_STAGE;
   p.one_launch = p.step_form != ABSB_STEP_PER_STAGE;
   // Short segments: every attention work-group scores and selects for itself (small.hip) as long as reading all
-  // of a segment's codes takes less than the hand-overs it saves.  Pipelined / this, 8 heads, blocks of 16: 1 request,
-  // budget 512, 64 blocks 11.8 / 8.4 us, 512 12.9 / 9.5, 768 13.0 / 11.4, 1024 13.0 / 11.9; 16 requests, budget 2048, 512
-  // 32.4 / 28.7, 1024 32.8 / 32.1.  Beyond, by its earlier selection (all four waves together): 1536 13.3 / 13.1, 2048
-  // 13.3 / 14.3.  Two vectors a block, or a pass per query head, make the scores dearer (4 requests, 768 blocks 14.1 /
-  // 13.7; four heads, 512 blocks 14.9 / 13.5).  With a selection per query head the scores are G times as many.
-  const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : g.repr == ABSB_REPR_MINMAX ? 768 : SMALL_MAX_BLOCKS;
+  // of a segment's codes takes less than the hand-over it saves.  This / scored once (own.hip), 8 heads, blocks of 16: 1 request,
+  // budget 512, 256 blocks 8.7 / 10.5 us, 512 9.7 / 10.9, 768 11.5 / 11.0, 1024 12.0 / 11.0; 4 requests, budget 2048, 512
+  // 14.3 / 14.8, 768 16.0 / 15.0; 16 requests, budget 2048, 512 28.9 / 30.0, 768 31.2 / 30.9.  Max-min rows, 4 requests, 512 12.7 / 13.3,
+  // 768 14.8 / 13.5.  A pass per query head makes the scores dearer (four heads, 512 blocks 12.8 / 13.5, 768 13.4 / 13.7).
+  // With a selection per query head the scores are G times as many.
+  const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : SMALL_MAX_BLOCKS;
   p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
   // split-K shape, in 64-token granules (one work-group step).  Swept on MI355X (256 CUs) when three
   // work-groups fitted a compute unit; four do now, and the sweep has not been repeated: the kernel was
@@ -181,8 +188,8 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     // selection per query head, 8 x 32K, 4096 72.3 / 65.5 (1024 and 1024); with more than 512 beside two a compute unit it
     // would be 37.9 / 44.1 (8 x 96K, 4096: 768) and 27.3 / 33.3 (per query head, 4 x 64K, 2048: 1024).  Other numbers
     // lose: 920 work-groups 61.7 / 62.1 (5 x 40K, 14519), 576 35.3 / 37.6 (9 x 60K, 4096), 768 45.7 / 47.6 (8 x 40K, 16
-    // heads, 3200); so do splits of which the last is hardly filled, and segments whose selection is shared (below), whose
-    // estimation work-groups are many: 36.8 / 43.3 (5 x 72K-150K, 6506).
+    // heads, 3200); so do splits of which the last is hardly filled, and segments beyond 8192 blocks, whose estimation
+    // work-groups are many: 36.8 / 43.3 (5 x 72K-150K, 6506).
     if (by_shape && batch->budget_host && p.max_blocks <= 8192 && p.sum_tokens >= 131072 &&
         20 * p.sum_tokens >= 19 * p.nseg * p.max_tokens) {
       int64_t even = std::max<int64_t>({256, std::min<int64_t>(512, ceil_div(p.sum_tokens, 512)), ceil_div(p.sum_tokens, 1024)});
@@ -205,15 +212,14 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if (p.max_splits > 65535) return ABSB_ERR_BAD_SHAPE;
   if ((int64_t)p.max_splits * st_tok >= (int64_t(1) << 31)) return ABSB_ERR_BAD_SHAPE;  // positions are 32-bit
 
-  // The pipelined form shares the selection, too, where one work-group's passes over a segment take longer than the
-  // two more hand-overs.  The line is where the two met when the shared form's chunks waited longer for one another
-  // (8 heads, lists of 1024 / 4096 tokens, one work-group / shared, 8192 blocks 17.0 / 17.2 and 19.8 / 19.7 us, 12288
-  // 19.2 / 18.0 and 21.8 / 20.0).  Now they meet lower: 1 request, 4096 blocks 13.9 / 14.9 and 16.9 / 17.4, 6144 14.9 /
-  // 15.3 and 18.0 / 17.8, 8192 16.5 / 15.7 and 18.9 / 18.0; 8 requests, 2048 18.6 / 18.4 and 33.7 / 32.4, 8192 25.4 / 24.4
-  // and 46.1 / 42.2; and with the group's maximum, which is left to one work-group whatever the length, 16384 blocks 23.4 /
-  // 20.9.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
+  // The pipelined form shares the selection, too, from where a segment's scores are too many for every attention
+  // work-group to read (own.hip).  Own selection / shared at 4096 blocks: 1 request, 4096 15.7 / 16.5 us, 8 requests, 2048 23.3 / 23.9.
+  // One work-group's selection / shared beyond: 6144 blocks, 1 request, 512 14.5 / 13.8, 4 requests, 2048 21.1 / 19.1.  With the
+  // group's maximum the two are level (8192 blocks, 1 request 18.8 / 18.5, 4 requests 23.3 / 23.9, 8 requests 33.9 / 34.1):
+  // it is left to one work-group whatever the length.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a
+  // segment and to the ascending order.)
   p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && !g.agg_max &&
-                                                p.max_blocks > 8192 && p.max_blocks <= 16384 && shared_pays);
+                                                p.max_blocks > OWN_MAX_BLOCKS && p.max_blocks <= 16384 && shared_pays);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
   p.shared = p.shared && rows && shared_fits(p);
 

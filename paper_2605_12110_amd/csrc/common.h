@@ -154,7 +154,7 @@ ABSB_HIDDEN int launch_fused(const Geometry& g, const Plan& pl, int dtype, float
                              const int32_t* budget, int32_t* sel_idx_out, int32_t* sel_cnt, void* out, float* lse,
                              char* ws, hipStream_t stream);
 // The whole step in one launch for short segments: every attention work-group scores and selects for itself.
-constexpr int SMALL_MAX_BLOCKS = 1024;
+constexpr int SMALL_MAX_BLOCKS = 512;
 ABSB_HIDDEN int launch_small(const Geometry& g, const Plan& pl, int dtype, float sm_scale, const void* q,
                              const uint8_t* codes, const float* qscale, const float* qmin, const void* k_cache,
                              const void* v_cache, const int32_t* page_table, const int32_t* seq_lens, const int32_t* cent_off,

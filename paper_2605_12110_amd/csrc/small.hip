@@ -247,8 +247,6 @@ __global__ __launch_bounds__(SMALL_THREADS, 4) void small_step_kernel(addr2 off_
     }
   } else if (g.hi - g.lo <= 256) {
     select_in_lds<4>(g, s_score, s_list, s_cand, out);
-  } else if (g.hi - g.lo <= 512) {
-    select_in_lds<8>(g, s_score, s_list, s_cand, out);
   } else {
     select_in_lds<SMALL_MAX_BLOCKS / 64>(g, s_score, s_list, s_cand, out);
   }
