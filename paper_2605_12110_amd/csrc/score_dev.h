@@ -40,6 +40,8 @@ struct ScoreParams {
   HeadTable heads;
 };
 
+typedef int32_t int32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int SCORE_PLANES = 5;
 
 inline ScoreParams make_score_params(const Geometry& g, const Plan& pl, const void* q, const uint8_t* codes,
@@ -73,11 +75,12 @@ __device__ __forceinline__ uint32_t or8(uint32_t v) {  // OR over aligned groups
 }
 
 // LDS of one work-group: the four wave maxima, then the digit planes of the weights.  The
-// group-maximum score keeps a set of planes per query head, the run sums of the heads' zero-point
-// products and their fixed-point offsets.
-constexpr size_t SCORE_GMAX_PLANES_AT = 16 + ABSB_MAX_GROUP * 8 * 4 + ABSB_MAX_GROUP * 4;
-constexpr size_t SCORE_GMAX_RANGE_AT =
-    SCORE_GMAX_PLANES_AT + (size_t)ABSB_MAX_GROUP * SCORE_PLANES * (ABSB_HEAD_DIM / 8) * sizeof(uint32_t);
+// group-maximum score keeps the run sums of the heads' zero-point products, their fixed-point offsets, and per query head
+// three digits of its weights, a byte each: [head][digit][odd channels][64].
+constexpr int SCORE_DIGITS = 3;
+constexpr size_t SCORE_GMAX_DIGITS_AT = 16 + ABSB_MAX_GROUP * 8 * 4 + ABSB_MAX_GROUP * 4;
+constexpr size_t SCORE_GMAX_RANGE_AT = SCORE_GMAX_DIGITS_AT + (size_t)ABSB_MAX_GROUP * SCORE_DIGITS * ABSB_HEAD_DIM;
+static_assert(SCORE_GMAX_DIGITS_AT % 16 == 0, "operands are read 16 bytes at a time");
 template <int REP>
 __host__ __device__ constexpr size_t score_range_at() {  // per-wave sums of the negative / positive weights
   return 16 + (size_t)SCORE_PLANES * (ABSB_HEAD_DIM * (REP + 1) / 8) * sizeof(uint32_t);
@@ -116,9 +119,13 @@ __device__ __forceinline__ ScoreSource score_source(const uint16_t* q, const flo
 }
 
 // Group-maximum score (mean pooling): S_j = max_g ( sum_c wq_gc * code_jc + zq_g ) with one exponent
-// for the group; see absb_score.  Same work split as score_chunk below: four lanes per block, the
-// packed 4-bit dots once per query head against that head's digit planes (read from LDS per head),
-// the sum of the codes shared by all heads.
+// for the group; see absb_score.  The dots of a block with every head's weights are a contraction: it runs on the matrix
+// unit.  A wave takes 16 blocks: lane (block = lane % 16, quarter = lane / 16) holds 16 bytes of codes, whose low and high
+// nibbles are bytes 0..15 of two operands (even and odd channels); the other operand's column 4 h + k (lane % 16) is digit k
+// of head h's weights, wq = d0 + 2^7 d1 + 2^14 d2 (d0, d1 in [0, 127], d2 in [-2, 2]; column 4 h + 3 is zero).  Two 16x16x64
+// products give four heads; all sums are exact.  Instructions bound the estimation, not bytes: by packed 4-bit dots, a pass
+// per head, 130 of them for 16 blocks and four heads, this way 45.  Group maximum, 4 x 64K in blocks of 16: 34.0 -> 33.0 us
+// a step, 8 x 128K 33.9 -> 31.5, 1 x 8K 12.5 -> 10.2, eight heads 16.4 -> 12.1.
 struct NoLoads {
   __device__ __forceinline__ void operator()() const {}
 };
@@ -142,20 +149,19 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, const
   float* s_absmax = reinterpret_cast<float*>(lds);                                   // [4]
   float (*s_zrun)[8] = reinterpret_cast<float (*)[8]>(lds + 16);                     // [G][8 runs of 16 channels]
   int32_t* s_zq = reinterpret_cast<int32_t*>(lds + 16 + ABSB_MAX_GROUP * 8 * 4);     // [G]
-  uint32_t (*s_plane)[SCORE_PLANES][W / 8] =
-      reinterpret_cast<uint32_t (*)[SCORE_PLANES][W / 8]>(lds + SCORE_GMAX_PLANES_AT);  // [G][planes][16]
+  uint8_t* s_digit = reinterpret_cast<uint8_t*>(lds + SCORE_GMAX_DIGITS_AT);
 
   int32_t (*s_rng)[ABSB_MAX_GROUP][2] =
       reinterpret_cast<int32_t (*)[ABSB_MAX_GROUP][2]>(lds + SCORE_GMAX_RANGE_AT);     // [2 waves][G][neg, pos]
 
-  const int quarter = tid & 3;
+  const int col = tid & 15, quarter = (tid >> 4) & 3, row = (tid >> 6) * 16 + col;  // row: of 64 blocks
   const int jend = min(N, j0 + jcount);
   const uint8_t* base = src.codes + quarter * 16;
-  uint4 pre[PF];
+  int32x4 pre[PF];
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
-    const int j = min(j0 + u * 64 + (tid >> 2), jend - 1);
-    pre[u] = *reinterpret_cast<const uint4*>(base + (size_t)j * ROW_BYTES);
+    const int j = min(j0 + u * 64 + row, jend - 1);
+    pre[u] = *reinterpret_cast<const int32x4*>(base + (size_t)j * ROW_BYTES);
   }
 
   behind_codes();
@@ -166,13 +172,14 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, const
     float a = 0.0f;
 #pragma unroll
     for (int g = 0; g < ABSB_MAX_GROUP; ++g) {
+      if (g >= G) break;
       const float qv = Elem<DT>::widen(qraw[g]);
       w[g] = qv * scale;
       float ag = __builtin_fabsf(w[g]);
       ag = (ag != ag) ? 0.0f : ag;
-      a = fmaxf(a, g < G ? ag : 0.0f);
+      a = fmaxf(a, ag);
       const float run = row16_sum(qv * zero);  // ((p0+p1)+(p2+p3))+... over the row's 16 channels
-      if (g < G && (tid & 15) == 0) s_zrun[g][tid >> 4] = run;
+      if ((tid & 15) == 0) s_zrun[g][tid >> 4] = run;
     }
     a = wave_max_f32(a);
     if ((tid & 63) == 0) s_absmax[tid >> 6] = a;
@@ -192,20 +199,18 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, const
     s_zq[tid] = (int32_t)zs;
   }
   if (tid < W) {
-    const int sh = 4 * (tid & 7);
 #pragma unroll
     for (int g = 0; g < ABSB_MAX_GROUP; ++g) {
+      if (g >= G) break;
       int32_t wq = 0;
       if (live && w[g] == w[g]) wq = (int32_t)__builtin_rintf(__builtin_ldexpf(w[g], -ex));  // a NaN weight images to 0
-      const uint32_t wo = (uint32_t)(wq + 32768);
-#pragma unroll
-      for (int k = 0; k < SCORE_PLANES; ++k) {
-        const uint32_t packed = or8(((wo >> (4 * k)) & 15u) << sh);
-        if (g < G && (tid & 7) == 0) s_plane[g][k][tid >> 3] = packed;
-      }
+      uint8_t* d = s_digit + (size_t)g * SCORE_DIGITS * W + (tid & 1) * (W / 2) + (tid >> 1);
+      d[0] = (uint8_t)(wq & 127);
+      d[W] = (uint8_t)(wq >> 7 & 127);
+      d[2 * W] = (uint8_t)(wq >> 14);
       if (RANGE) {  // per head: sums of its negative and of its positive weights (exact, order-free)
         const uint32_t neg = wave_reduce_u32((uint32_t)min(wq, 0), IAdd()), pos = wave_reduce_u32((uint32_t)max(wq, 0), IAdd());
-        if (g < G && (tid & 63) == 0) {
+        if ((tid & 63) == 0) {
           s_rng[tid >> 6][g][0] = (int32_t)neg;
           s_rng[tid >> 6][g][1] = (int32_t)pos;
         }
@@ -224,51 +229,54 @@ __device__ __forceinline__ int score_blocks_groupmax(const ScoreParams& p, const
     range->hi = hi;
   }
 
+  // ---- this lane's column: digit col % 4 of head 4 x + col / 4, and that head's offset
+  const int sets = (G + 3) / 4;
+  int32x4 wd[2][2];
+  int32_t zq[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int g = 4 * x + (col >> 2);
+    const bool used = g < G && (col & 3) < SCORE_DIGITS;
+    zq[x] = g < G ? s_zq[g] : INT32_MIN;  // (an absent head's dots are zero: it never wins)
+    const uint8_t* d = s_digit + ((size_t)(used ? g * SCORE_DIGITS + (col & 3) : 0)) * W + quarter * 16;
+#pragma unroll
+    for (int odd = 0; odd < 2; ++odd) {
+      const int32x4 v = *reinterpret_cast<const int32x4*>(d + odd * (W / 2));
+      wd[x][odd] = used ? v : int32x4{0, 0, 0, 0};
+    }
+  }
+  const int digit_shift = 7 * (col & 3);
 #pragma unroll 1
   for (int jb = j0;;) {
-    uint32_t ones[PF];
-    int32_t best[PF];
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
-      uint32_t o = __builtin_amdgcn_udot8(pre[u].x, 0x11111111u, 0u, false);
-      o = __builtin_amdgcn_udot8(pre[u].y, 0x11111111u, o, false);
-      o = __builtin_amdgcn_udot8(pre[u].z, 0x11111111u, o, false);
-      ones[u] = __builtin_amdgcn_udot8(pre[u].w, 0x11111111u, o, false);
-      best[u] = 0;
-    }
-#pragma unroll 1
-    for (int g = 0; g < G; ++g) {
-      uint4 wp[SCORE_PLANES];
+      if (PF > 4 && jb + u * 64 >= jend) break;
+      const int32x4 even = pre[u] & 0x0f0f0f0f, odd = pre[u] >> 4 & 0x0f0f0f0f;
+      int32_t best[4];  // of blocks 4 * quarter + i of the wave's 16, in every lane of the row
 #pragma unroll
-      for (int k = 0; k < SCORE_PLANES; ++k) wp[k] = *reinterpret_cast<const uint4*>(&s_plane[g][k][quarter * 4]);
-      const int32_t zq = s_zq[g];
+      for (int x = 0; x < 2; ++x) {
+        if (x >= sets) break;
+        int32x4 dot = {0, 0, 0, 0};
+        dot = __builtin_amdgcn_mfma_i32_16x16x64_i8(even, wd[x][0], dot, 0, 0, 0);
+        dot = __builtin_amdgcn_mfma_i32_16x16x64_i8(odd, wd[x][1], dot, 0, 0, 0);
 #pragma unroll
-      for (int u = 0; u < PF; ++u) {
-        uint32_t acc = 0;
-#pragma unroll
-        for (int k = 0; k < SCORE_PLANES; ++k) {
-          uint32_t d = __builtin_amdgcn_udot8(pre[u].x, wp[k].x, 0u, false);
-          d = __builtin_amdgcn_udot8(pre[u].y, wp[k].y, d, false);
-          d = __builtin_amdgcn_udot8(pre[u].z, wp[k].z, d, false);
-          d = __builtin_amdgcn_udot8(pre[u].w, wp[k].w, d, false);
-          acc += d << (4 * k);
+        for (int i = 0; i < 4; ++i) {
+          int32_t sc = quad_sum((int32_t)((uint32_t)dot[i] << digit_shift)) + zq[x];
+          sc = max(sc, dpp_i<DPP_ROW_HALF_MIRROR>(sc));
+          sc = max(sc, dpp_i<DPP_ROW_MIRROR>(sc));
+          best[i] = x == 0 ? sc : max(best[i], sc);
         }
-        acc -= ones[u] << 15;
-        const int32_t sc = quad_sum((int32_t)acc) + zq;
-        best[u] = g == 0 ? sc : max(best[u], sc);
       }
-    }
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int j = jb + u * 64 + (tid >> 2);
-      if (j < jend && quarter == 0) sink(j, best[u]);
+      const int j = jb + u * 64 + (tid >> 6) * 16 + quarter * 4 + col;
+      const int32_t mine = col < 2 ? (col == 0 ? best[0] : best[1]) : (col == 2 ? best[2] : best[3]);
+      if (col < 4 && j < jend) sink(j, mine);
     }
     jb += PF * 64;
     if (jb >= jend) break;
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
-      const int j = min(jb + u * 64 + (tid >> 2), jend - 1);
-      pre[u] = *reinterpret_cast<const uint4*>(base + (size_t)j * ROW_BYTES);
+      const int j = min(jb + u * 64 + row, jend - 1);
+      pre[u] = *reinterpret_cast<const int32x4*>(base + (size_t)j * ROW_BYTES);
     }
   }
   return N;
@@ -419,6 +427,7 @@ __device__ __forceinline__ int score_blocks(const ScoreParams& p, const ScoreSou
   for (int jb = j0;;) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
+      if (PF > 4 && jb + u * 64 >= jend) break;
       const int j = jb + u * 64 + (tid >> 2);
       const int32_t sc = dot(pre[u]);
       if (j < jend && quarter == 0) sink(j, sc);

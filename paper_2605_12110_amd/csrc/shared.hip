@@ -71,7 +71,7 @@ struct SharedParams {
 };
 
 // LDS of an estimation work-group behind the estimation's own
-constexpr int SHARED_LDS_SCORE = 3072;                                            // int32 [SHARED_MAX_CHUNK]
+constexpr int SHARED_LDS_SCORE = 4096;                                            // int32 [SHARED_MAX_CHUNK]
 constexpr int SHARED_LDS_HIST = SHARED_LDS_SCORE + SHARED_MAX_CHUNK * 4;          // uint32 [SHARED_BINS]
 constexpr int SHARED_LDS_WORDS = SHARED_LDS_HIST + SHARED_BINS * 4;               // 64 words of scan / broadcast scratch
 constexpr int SHARED_LDS_SCORING = SHARED_LDS_WORDS + 64 * 4;
