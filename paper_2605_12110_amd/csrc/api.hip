@@ -22,10 +22,11 @@ static size_t partial_bytes(const Geometry& g, const Plan& p, int64_t splits) {
   const size_t rows = (size_t)p.nseg * (size_t)splits * g.Gd;
   return align256(rows * ABSB_HEAD_DIM * 4) + align256(rows * 4 * 4);
 }
-// Blocks per estimation work-group: 256 (one batch of loads per lane); in the one-launch step, where estimation
-// work-groups share the CUs with attention work-groups, a large batch does better with two batches per work-group (the
-// prologue is amortised, half as many work-groups).
-static int default_score_chunk(const Plan& p) { return p.total >= 65536 ? 512 : 256; }
+// Blocks per estimation work-group: 256, or 512 where that would make more than two work-groups a compute unit in the
+// one-launch step, which pay their prologue and keep attention work-groups from their places.  256 / 512, us a step: group
+// maximum 4 x 64K 32.1 / 33.0 (512 work-groups of 256), 8 x 32K 21.0 / 21.1 (512); a selection per query head, 8 x 32K 38.3 /
+// 35.7 (2048).
+static int default_score_chunk(const Plan& p) { return p.nseg * ceil_div(p.max_blocks, 256) > 512 ? 512 : 256; }
 constexpr int MAX_SPLITS_CHOSEN = 64;  // of a segment, unless the caller says what a split is
 
 int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget, int32_t sel_stride_in,
@@ -155,10 +156,9 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // of a segment's codes takes less than the hand-over it saves.  This / scored once (own.hip), 8 heads, blocks of 16: 1 request,
   // budget 512, 256 blocks 8.7 / 10.5 us, 512 9.7 / 10.9, 768 11.5 / 11.0, 1024 12.0 / 11.0; 4 requests, budget 2048, 512
   // 14.3 / 14.8, 768 16.0 / 15.0; 16 requests, budget 2048, 512 28.9 / 30.0, 768 31.2 / 30.9.  Max-min rows, 4 requests, 512 12.7 / 13.3,
-  // 768 14.8 / 13.5.  A pass per query head makes the scores dearer (four heads, 512 blocks 12.8 / 13.5, 768 13.4 / 13.7).
-  // With a selection per query head the scores are G times as many.
-  const int small_blocks = g.agg_max ? std::min(SMALL_MAX_BLOCKS, 2048 / g.G) : SMALL_MAX_BLOCKS;
-  p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= small_blocks;
+  // 768 14.8 / 13.5.  Group maximum, 512 blocks, four heads 10.2 / 10.9.  With a selection per query head the scores are G
+  // times as many.
+  p.small = opts.step_form == ABSB_STEP_AUTO && by_shape && g.Rk == 1 && p.max_blocks <= SMALL_MAX_BLOCKS;
   // split-K shape, in 64-token granules (one work-group step).  Swept on MI355X (256 CUs) when three
   // work-groups fitted a compute unit; four do now, and the sweep has not been repeated: the kernel was
   // fastest with about two work-groups per CU, all resident at once and each streaming as long as
@@ -214,11 +214,11 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
 
   // The pipelined form shares the selection, too, from where a segment's scores are too many for every attention
   // work-group to read (own.hip).  Own selection / shared at 4096 blocks: 1 request, 4096 15.7 / 16.5 us, 8 requests, 2048 23.3 / 23.9.
-  // One work-group's selection / shared beyond: 6144 blocks, 1 request, 512 14.5 / 13.8, 4 requests, 2048 21.1 / 19.1.  With the
-  // group's maximum the two are level (8192 blocks, 1 request 18.8 / 18.5, 4 requests 23.3 / 23.9, 8 requests 33.9 / 34.1):
-  // it is left to one work-group whatever the length.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a
+  // One work-group's selection / shared beyond: 6144 blocks, 1 request, 512 14.5 / 13.8, 4 requests, 2048 21.1 / 19.1, group
+  // maximum, 8192, 1 request 17.8 / 16.8, 8 requests 31.5 / 30.1.  (Beyond 8192 blocks the group's maximum keeps to one work-group's
+  // selection; the line there has not been moved.  Forced beyond 16384 blocks, the pipelined form keeps to one work-group a
   // segment and to the ascending order.)
-  p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && !g.agg_max &&
+  p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && (!g.agg_max || p.max_blocks <= 8192) &&
                                                 p.max_blocks > OWN_MAX_BLOCKS && p.max_blocks <= 16384 && shared_pays);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates
   p.shared = p.shared && rows && shared_fits(p);
