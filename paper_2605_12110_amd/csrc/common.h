@@ -201,7 +201,7 @@ inline int check_launch() { return hipGetLastError() == hipSuccess ? ABSB_OK : A
 typedef uint64_t addr2 __attribute__((ext_vector_type(2)));
 typedef int32_t int2v __attribute__((ext_vector_type(2)));
 typedef int32_t int4v __attribute__((ext_vector_type(4)));
-inline uint64_t addr(const void* p) { return reinterpret_cast<uint64_t>(p); }
+__host__ __device__ inline uint64_t addr(const void* p) { return reinterpret_cast<uint64_t>(p); }
 
 // ------------------------------------------------------------------ device helpers
 #ifdef __HIPCC__

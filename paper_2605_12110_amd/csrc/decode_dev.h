@@ -443,23 +443,29 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
   int* s_bcast = reinterpret_cast<int*>(lds + DEC_LDS_STATE + 3 * ABSB_MAX_GROUP * DEC_WAVES * 4);
   float m = st.m, l = st.l, lx = st.lx;
 
-  // ---- the wave's state: m per head (lane = head), l summed over the four groups
+  // ---- the wave's state: m per head (lane = head), l summed over the four groups.  (The addresses that the hand-over below
+  // needs are asked for here, to arrive with the barrier: behind it they would be two more round trips.)
+  uint64_t at_o = addr(p.part_o), at_ml = addr(p.part_ml), at_tickets = addr(p.tickets);
   l = across_rows(l, FAdd());
   lx = across_rows(lx, FAdd());
-  if (lane < G) s_m[lane][wave] = m;
+  constexpr int HEADS = 4 * head_sets(G);
+  if (lane < HEADS) s_m[lane][wave] = m;
+  asm volatile("" : "+s"(at_o), "+s"(at_ml), "+s"(at_tickets));
   __syncthreads();
-  // work-group maximum per head; own state rescaled to it, so that the four states simply add up
+  // work-group maximum per head; own state rescaled to it, so that the four states simply add up.  (Every lane works out its
+  // head's factor, and all read it from there.  A read of LDS per head, behind the writes of the one before, and addresses
+  // fetched where they are used took longer: 1 x 4K 9.5 -> 9.1 us a step, 8 x 32K 20.5 -> 20.3, a step of a decode loop over 4
+  // requests 15.3 -> 14.9.)
   float* s_o = reinterpret_cast<float*>(s_stage);  // [DEC_WAVES][G][128]
+  const float4_t ms = *reinterpret_cast<const float4_t*>(s_m[lane & (HEADS - 1)]);
+  const float rescale = fast_exp2(m - fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3])));
   if (lane < G) {
-    const float M = fmaxf(fmaxf(s_m[lane][0], s_m[lane][1]), fmaxf(s_m[lane][2], s_m[lane][3]));
-    const float a = fast_exp2(m - M);
-    s_l[lane][wave] = l * a;
-    s_lx[lane][wave] = lx * a;
+    s_l[lane][wave] = l * rescale;
+    s_lx[lane][wave] = lx * rescale;
   }
 #pragma unroll
   for (int hd = 0; hd < G; ++hd) {
-    const float M = fmaxf(fmaxf(s_m[hd][0], s_m[hd][1]), fmaxf(s_m[hd][2], s_m[hd][3]));
-    const float a = fast_exp2(s_m[hd][wave] - M);
+    const float a = bitcast<float>(__builtin_amdgcn_readlane(bitcast<int>(rescale), hd));
     *reinterpret_cast<float2*>(s_o + ((size_t)wave * G + hd) * ABSB_HEAD_DIM + lane * 2) =
         make_float2(st.o[hd >> 2][0][hd & 3] * a, st.o[hd >> 2][1][hd & 3] * a);
   }
@@ -488,9 +494,9 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
     constexpr int COHERENT = 16;  // cache-policy operand of the buffer instructions: sc1
     const size_t slot0 = (size_t)s * slots;
     const __amdgpu_buffer_rsrc_t part_o = __builtin_amdgcn_make_buffer_rsrc(
-        p.part_o + slot0 * G * ABSB_HEAD_DIM, 0, slots * G * ABSB_HEAD_DIM * 4, 0x00020000);
+        from_addr<float>(at_o) + slot0 * G * ABSB_HEAD_DIM, 0, slots * G * ABSB_HEAD_DIM * 4, 0x00020000);
     const __amdgpu_buffer_rsrc_t part_ml =
-        __builtin_amdgcn_make_buffer_rsrc(p.part_ml + slot0 * G * 4, 0, slots * G * 16, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(from_addr<float>(at_ml) + slot0 * G * 4, 0, slots * G * 16, 0x00020000);
     if (tid < NCOL) {
       __builtin_amdgcn_raw_buffer_store_b128(bitcast<u32x4>(O), part_o, ((split * G + g) * ABSB_HEAD_DIM + c4 * 4) * 4,
                                              0, COHERENT);
@@ -498,17 +504,17 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
         __builtin_amdgcn_raw_buffer_store_b128(bitcast<u32x4>(float4_t{M, Lsum, Lx, 0.0f}), part_ml,
                                                (split * G + g) * 16, 0, COHERENT);
     }
+    int32_t* ticket = from_addr<int32_t>(at_tickets) + (size_t)s * ABSB_TICKET_STRIDE;
     int& s_last = s_bcast[0];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's stores have been acknowledged
     __syncthreads();                                   // ... and so have everybody's
     if (tid == 0)
-      s_last = __hip_atomic_fetch_add(p.tickets + (size_t)s * ABSB_TICKET_STRIDE, 1, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
+      s_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1;
     __syncthreads();
     if (!s_last) return false;
     // every counter a launch touches is back at zero when the launch ends
     if (tid == 0)
-      __hip_atomic_store(p.tickets + (size_t)s * ABSB_TICKET_STRIDE, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     on_last();
 
     // log-sum-exp merge: split lane `sl` of a column takes splits sl, sl + SL, ..., U of them per memory round trip,
