@@ -266,19 +266,20 @@ ABSB_API int absb_workspace_init(const absb_layer* layer, const absb_batch* batc
  * order (same tolerance against exact arithmetic).  Three ways to enqueue it (batch->opts.step_form;
  * ABSB_STEP_AUTO picks by shape):
  *   ABSB_STEP_PIPELINED  one launch.  The grid holds the estimation work-groups, then the attention
- *                        work-groups; a segment's last estimation work-group runs its selection and
- *                        raises a flag, the segment's attention work-groups start on that flag.
- *                        Chosen while no segment exceeds 16384 blocks and no list 4096 blocks.
- *                        (Inside that range: short segments are scored and selected by every attention
- *                        work-group for itself, long ones by their estimation work-groups together.)
+ *                        work-groups.  Chosen while no segment exceeds 16384 blocks and no list 4096
+ *                        blocks.  Who selects depends on the length: up to 512 blocks every attention
+ *                        work-group scores and selects for itself, up to 4096 it selects for itself from
+ *                        the scores of the estimation work-groups, beyond these select together, or the
+ *                        segment's last one alone, on whose flag the attention starts, where waiting for
+ *                        each other would cost more.
  *   ABSB_STEP_UNITS      one launch.  Every segment is cut into stretches of consecutive blocks; a stretch's
  *                        work-group scores its blocks, adds a histogram of its scores to the segment's, and
  *                        once all have, derives the segment's threshold from it and hands its selected
  *                        blocks over; blocks inside the threshold bin are settled by an exact ranking among
  *                        the segment's candidates.  No work-group ever passes over a whole segment, so the
  *                        cost hardly grows with the context.  Chosen for segments beyond 16384 blocks while
- *                        there are at most two of those work-groups per compute unit, or four if at least
- *                        half of them have blocks to score.
+ *                        there are at most two of those work-groups per compute unit, or four that have
+ *                        blocks to score.
  *   ABSB_STEP_PER_STAGE  three launches (score, top-k, sparse decode).  Otherwise.
  * The one-launch forms hand work between work-groups through the counters at the start of the
  * workspace: they must be zero when the call starts (absb_workspace_init) and are zero again when its

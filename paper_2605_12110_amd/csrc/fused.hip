@@ -18,6 +18,10 @@
 //                       order beyond rounding) and proceeds as in the stand-alone kernel
 //                       (partials, ticket, the last arriver merges).
 //
+// This is the form for segments beyond 4096 blocks whose chunks should not wait for each other (shared.hip): grids of
+// estimation work-groups that outgrow the chip or are nearly all empty, the group's maximum beyond 8192 blocks.  Shorter
+// segments are selected by every attention work-group (own.hip, small.hip).
+//
 // Progress: estimation/selection work-groups never wait for anything.  Attention work-groups wait
 // only for work-groups with lower indices; the hardware starts work-groups in index order, so
 // every work-group waited for is already running or done.  The wait is also bounded in time, so
