@@ -619,7 +619,7 @@ def main():
     wl = wl0
     headline = (args.config == 3 and args.context is None and args.batch is None and args.budget is None
                 and block_repr == 0 and args.select == "group")
-    form_name = {absb.STEP_PIPELINED: "pipelined (one launch; by size in the form of small.hip, fused.hip or shared.hip)", absb.STEP_UNITS: "shared selection (one launch)",
+    form_name = {absb.STEP_PIPELINED: "pipelined (one launch; by size in the form of small.hip, own.hip, shared.hip or fused.hip)", absb.STEP_UNITS: "shared selection (one launch)",
                  absb.STEP_PER_STAGE: "per stage (three launches)"}[m["form"]]
     stages = {k: round(v, 3) for k, v in m["stages"].items()}
     if headline:
