@@ -126,9 +126,9 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   if ((int64_t)batch->pt_stride < ceil_div(max_len, P)) return ABSB_ERR_BAD_SHAPE;
 
   // How absb_decode_fused is enqueued.  Measured on MI355X (three copies of a layer in
-  // turn, here and below): one launch against one per stage, 1 request of 4K 9.5 / 15.2 us, 8 of 32K 23.5 / 26.6, 1 of
-  // 128K 17.4 / 21.2, 16 of 8K-128K 42.8 / 49.1.  A selection by one work-group holds 16384 blocks in its registers;
-  // beyond (keys re-read) it takes several times longer (1 request of 256K 63.5 us a step against 20.6 shared, below).  Very long lists (budgets near the context) go to the per-stage
+  // turn, here and below): one launch against one per stage, 1 request of 4K 9.3 / 15.1 us, 8 of 32K 20.2 / 26.2, 1 of
+  // 128K 16.0 / 20.5, 16 of 8K-128K 40.6 / 47.6.  A selection by one work-group holds 16384 blocks in its registers;
+  // beyond (keys re-read) it takes several times longer (1 request of 256K 63.5 us a step against 19.4 shared, below).  Very long lists (budgets near the context) go to the per-stage
   // path: its attention kernel reads the lists through the L2.
   const bool by_shape = p.max_blocks <= 16384 && p.sel_stride <= 4096;
   // Segments beyond 4096 blocks: the work-groups that score a segment share its selection, unless the grid of them is
