@@ -12,7 +12,7 @@
 //        compete: every chunk finds the bin that holds the K_s-th largest score;
 //     3. writes its blocks above the bin to its own stretch of the segment's list area, the few inside it
 //        (candidates) as (score, index) pairs, and how many of each it has to its counts word;
-//     4. the chunk that gets here last writes the caller's list and count if asked, and takes over where the
+//     4. the chunk that gets here last clears what chunks share, writes the caller's list and count if asked, and takes over where the
 //        bin is too crowded to rank its members (ties): the exact selection of topk_dev.h over the segment's
 //        scores, which the chunks then store instead of lists.
 //   attention work-group (split of segment t): waits for the chunks' counts words, places its stretch of the
@@ -36,7 +36,9 @@
 // Counters, histogram rows and counts words must be zero when the launch starts and are zero again when it ends:
 // the chunk that finishes last clears what only chunks use, while the attention runs, the work-group that merges a
 // segment's partials the words that the attention reads, ahead of the merge.  (With all of it left to that work-group, behind
-// its merge, a step ended later: 1 x 128K 17.3 us against 16.5, 1 x 256K 20.6 / 19.7.)
+// its merge, a step ended later: 1 x 128K 17.3 us against 16.5, 1 x 256K 20.6 / 19.7.)  A counter that did not start at zero
+// shows: a chunk that takes itself for the last one and goes by what the others have found sees whether all their counts words
+// are out, and the work-group that merges sees whether a last chunk has been there and nobody has counted after it.
 //
 // Compiled with -ffp-contract=off, as the estimation stage requires.
 #include "decode_dev.h"
@@ -62,7 +64,7 @@ struct SharedParams {
   DecodeParams dc;
   int32_t* arrived;    // [nseg], ABSB_TICKET_STRIDE apart: chunks that have sent their counts; more: one has waited too long
   int32_t* finished;   // [nseg] likewise: chunks whose counts word is out
-  uint32_t* listed;    // [nseg][SHARED_MAX_CHUNKS]: the counts words once more, for the caller's list
+  uint32_t* listed;    // [nseg][SHARED_MAX_CHUNKS]: the counts words once more, for the last chunk
   int32_t* crowd_flag; // [nseg] likewise: 1 = the crowded segment's work list is complete
   uint32_t* hist;      // [nseg][SHARED_BINS]
   uint32_t* counts;    // [nseg][SHARED_MAX_CHUNKS]
@@ -256,10 +258,11 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   }
   wait_stores_acknowledged();
   __syncthreads();
+  const bool relied = out || crowded;  // the last chunk reads what the others have found
   if (tid == 0) {
     uint32_t* counts = p.counts + (size_t)t * SHARED_MAX_CHUNKS + c;
     st_i32<true>(reinterpret_cast<int32_t*>(counts), (int32_t)word);
-    if (out) st_i32<true>(reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS + c), (int32_t)word);
+    if (relied) st_i32<true>(reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS + c), (int32_t)word);
     wait_stores_acknowledged();
     s_words[36] = __hip_atomic_fetch_add(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 1, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT) == C - 1;
@@ -267,16 +270,43 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   __syncthreads();
   if (!s_words[36]) return;
 
-  // ---- 4. the segment's last chunk: every other one has read the row and drawn its number
+  // ---- 4. the segment's last chunk: every other one has read the row and drawn its number.  Before it goes by what the others
+  // have found, its first wave looks whether all counts words are out: with one missing, `finished` did not start at zero, and
+  // nothing is cleared, which the merging work-group sees.
+  uint32_t* s_key = reinterpret_cast<uint32_t*>(lds);                       // [SHARED_MAX_CAND]
+  uint32_t* s_idx = s_key + SHARED_MAX_CAND;                                // [SHARED_MAX_CAND]
+  uint32_t* s_bm = reinterpret_cast<uint32_t*>(lds + SHARED_LDS_SCORING);   // a bit per block
+  int32_t* s_sure = reinterpret_cast<int32_t*>(s_idx + SHARED_MAX_CAND);    // [SHARED_MAX_CHUNKS]
+  int32_t* s_cand = s_sure + SHARED_MAX_CHUNKS;                             // [SHARED_MAX_CHUNKS]
+  const int nwords = out && !crowded ? (N + 31) >> 5 : 0;
+  if (relied) {
+    if (tid < SHARED_MAX_CHUNKS) {
+      int32_t* word_at = reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS) + lane;  // lane = chunk
+      const uint32_t cw = lane < C ? (uint32_t)ld_i32<true>(word_at) : 0u;
+      const bool missing = __any(lane < C && cw == 0u);
+      if (!missing) st_i32<true>(word_at, 0);
+      uint32_t sure, ncand;
+      const uint32_t ns = cw & 0xffffu, ncd = (cw >> 16) & 0xfffu;
+      const uint32_t sure_to = wave_incl_scan_u32(ns, &sure), cand_to = wave_incl_scan_u32(ncd, &ncand);
+      s_sure[lane] = (int)(sure_to - ns);
+      s_cand[lane] = (int)(cand_to - ncd);
+      if (lane == 0) {
+        s_words[44] = sure;
+        s_words[45] = ncand;
+        s_words[46] = missing;
+      }
+    }
+#pragma unroll 1
+    for (int w = tid; w < nwords; w += SHARED_THREADS) s_bm[w] = 0;
+    __syncthreads();
+    if (s_words[46]) return;
+  }
   __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, tid * 16, 0, 16 /* sc1 */);
   if (tid == 0) {
     st_i32<true>(arrived, 0);
     st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
   }
-  int32_t* listed = reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS);
-  const uint32_t cw = out && lane < C ? (uint32_t)ld_i32<true>(listed + lane) : 0u;  // lane = chunk
   if (crowded) {
-    if (out && tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);  // (nobody reads them then)
     __syncthreads();  // the words are read; the selection's LDS overlaps them
     TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
     uint32_t* bitmap = reinterpret_cast<uint32_t*>(lds + ((sizeof(TopkShared) + 15) & ~size_t(15)));
@@ -286,25 +316,8 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   if (tid == 0) p.tk.sel_cnt[t] = g.K;
   if (!out) return;
   // the caller's ascending list, from the chunks' lists: a bitmap, then one scan
-  uint32_t* s_key = reinterpret_cast<uint32_t*>(lds);                       // [SHARED_MAX_CAND]
-  uint32_t* s_idx = s_key + SHARED_MAX_CAND;                                // [SHARED_MAX_CAND]
-  uint32_t* s_bm = reinterpret_cast<uint32_t*>(lds + SHARED_LDS_SCORING);   // a bit per block
-  int32_t* s_sure = reinterpret_cast<int32_t*>(s_idx + SHARED_MAX_CAND);    // [SHARED_MAX_CHUNKS]
-  int32_t* s_cand = s_sure + SHARED_MAX_CHUNKS;                             // [SHARED_MAX_CHUNKS]
-  __syncthreads();
-  const int nwords = (N + 31) >> 5;
-#pragma unroll 1
-  for (int w = tid; w < nwords; w += SHARED_THREADS) s_bm[w] = 0;
-  __syncthreads();
   const int64_t seg_place = place - j0;
-  uint32_t sure, ncand;
-  const uint32_t ns = cw & 0xffffu, ncd = (cw >> 16) & 0xfffu;
-  const uint32_t sure_to = wave_incl_scan_u32(ns, &sure), cand_to = wave_incl_scan_u32(ncd, &ncand);
-  if (tid < 64) {
-    s_sure[lane] = (int)(sure_to - ns);
-    s_cand[lane] = (int)(cand_to - ncd);
-  }
-  __syncthreads();
+  const uint32_t sure = s_words[44], ncand = s_words[45];
   for (int i = tid; i < (int)sure; i += SHARED_THREADS) {
     const int u = chunk_of(s_sure, C, i);
     const int j = ld_i32<true>(p.area + seg_place + (int64_t)u * chunk + (i - s_sure[u]));
@@ -319,7 +332,6 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     s_idx[i] = (uint32_t)(pr >> 32);
   }
   __syncthreads();
-  if (tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);  // every wave has its copy
 #pragma unroll 1
   for (int k = tid; k < nc; k += SHARED_THREADS) {
     const uint32_t mk = s_key[k], mi = s_idx[k];
@@ -472,25 +484,37 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   st.reset();
   attend_positions<DT, G>(d, c, StretchRef{s_list, e0, e1 - 1}, pages, pos_begin, pos_end, qb, st);
   // The segment's last split: every other one has drawn its ticket, so the words that splits read go back to zero, ahead of
-  // the merge.  (The last chunk clears its own, now or later.)  A count of finished chunks beyond all there are can
-  // only be one that did not start at zero: then nobody was the last chunk, the caller's list may be missing, and the
-  // row is not clear.
-  int fin = 0;
+  // the merge.  The chunks' own counters are back at zero, or about to be, if a last chunk has been there (all counts
+  // words were out long before) and nobody has counted after it; otherwise they did not start there, the caller's list may be
+  // missing, and the row may not be clear.
+  const auto counters = [&]() __attribute__((always_inline)) {
+    return ld_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE) | ld_i32<true>(p.arrived + (size_t)t * ABSB_TICKET_STRIDE);
+  };
+  int left = 0;
   const bool last = finish_split<DT, G>(d, t, b, hs, split, nsplit, d.max_splits, st, lds, [&]() __attribute__((always_inline)) {
     if (!compete) return;
     if (tid < SHARED_MAX_CHUNKS) st_i32<true>(reinterpret_cast<int32_t*>(p.counts + (size_t)t * SHARED_MAX_CHUNKS) + tid, 0);
     if (tid == 0) {
-      fin = ld_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE);
+      left = counters();
       if (crowded) st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
     }
   });
   if (!last || !compete) return;
-  if (tid == 0) s_word[1] = fin > C;  // (finish_split uses the word itself)
+  if (tid == 0) s_word[1] = left;  // (finish_split uses the word itself)
   __syncthreads();
-  if (s_word[1]) {
-    if (tid == 0) st_i32<true>(d.status, 1);
-    poison_rows<DT, G>(d, b, hs);
+  if (!s_word[1]) return;
+  __syncthreads();
+  if (tid == 0) {
+    const uint64_t t0 = wall_clock64();
+    do {
+      __builtin_amdgcn_s_sleep(2);
+      left = counters();
+    } while (left && wall_clock64() - t0 < DEC_WAIT_LIMIT_TICKS);
+    if (left) st_i32<true>(d.status, 1);
+    s_word[1] = left;
   }
+  __syncthreads();
+  if (s_word[1]) poison_rows<DT, G>(d, b, hs);
 }
 
 // (What an estimation work-group needs first comes as arguments of their own: see small.hip.)

@@ -1245,33 +1245,46 @@ def test_one_launch_step_gives_up_waiting_and_says_so_when_a_counter_was_not_cle
     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
 
 
-def test_shared_selection_reports_a_chunk_that_never_counts_itself_finished():
-    """The last split of a segment waits (bounded) until every estimation work-group of the segment has counted itself
-    finished, before it clears their counters.  Forced from the host: one segment's count starts at a value from
-    which it never gets there.  Like every wait that runs out, this one sets the status word and leaves NaN
-    in the segment's rows, and only there; after the counters are cleared again the step works."""
+@pytest.mark.parametrize("start", [-4, -1, 1, 2, 3, 4, 1000])
+def test_shared_selection_reports_a_chunk_that_never_counts_itself_finished(start):
+    """The chunk of a segment that counts itself finished last clears what chunks share and writes the caller's list; the
+    segment's last split sees (bounded in time) whether that has happened.  Forced from the host: one segment's count of
+    finished chunks does not start at zero.  Four chunks: from a start below zero or at their number on none of them is
+    the last one; from 1 to 3 one takes itself for it too early.  It notices if a counts word is missing then; if none
+    is, it has done its work as it should, and whoever counts afterwards leaves the count off zero, unless that fell into the
+    moment before the clearing, when all is as it should be.  What is reported sets the status word and leaves NaN in the segment's rows, and
+    only there; what is not must be right; after the counters are cleared again the step works."""
     import torch
-    wl = synth.make_workload(1, context=4096, budget=256)
+    wl = synth.make_workload(1, context=16384, budget=512, block_sizes=(8,))
+    assert -(-wl.seq_lens[0] // (8 * 512)) == 4
     ref = O.decode_step(wl, O.build_centroids(wl))
     dw = _dev(wl, opts=dict(step_form=2))
     dw.build()
     stuck, G = 3, wl.group
-    dw.workspace.view(torch.int32)[(3 * dw.nsel * 256 + 256) // 4 + stuck * 64] = 1000
+    dw.workspace.view(torch.int32)[(3 * dw.nsel * 256 + 256) // 4 + stuck * 64] = start
+    dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7)
     t0 = time.time()
     dw.decode_fused(); _sync()
     assert time.time() - t0 < 5.0
-    assert dw.status() == 1
+    status = dw.status()
+    _say(f"    finished from {start}: status {status}")
+    assert status == 1 or start in (1, 2, 3)
+    if status == 0:
+        assert not _hand_over_state(dw).any()
     got = dw.out_f32().astype(np.float64)
+    lists, counts = dw.sel_idx.cpu().numpy(), dw.sel_cnt.cpu().numpy()
     for s in range(dw.nsel):
         rows = slice(s * G, (s + 1) * G)
-        if s == stuck:
+        if s == stuck and status:
             assert np.isnan(got[0, rows]).all() and np.isnan(dw.lse.cpu().numpy()[0, rows]).all()
         else:
             assert np.abs(got[0, rows] - ref["out"][0, rows]).max() <= TOL[wl.dtype]
+            assert counts[s] == ref["sel_cnt"][s] and np.array_equal(lists[s], ref["sel_idx"][s, :dw.sel_stride])
     dw.scribble(0x77)
-    dw.decode_fused()
-    _check_out(dw, ref["out"], ref["lse"], "after clearing the counters again")
-    assert dw.status() == 0
+    for want in (True, False):
+        dw.decode_fused(want_sel=want)
+        _check_out(dw, ref["out"], ref["lse"], "after clearing the counters again")
+        assert dw.status() == 0 and not _hand_over_state(dw).any()
     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
 
 
