@@ -88,7 +88,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
     return ABSB_ERR_BAD_SHAPE;
   p.nseg = Bt * Hsel;
   p.nstore = Bt * Hkv;
-  int64_t max_len = 0;
+  int64_t max_len = 0, in_use = 0;  // in_use: blocks of the current lengths (p.total: of the layout's)
   for (int b = 0; b < Bt; ++b) {
     const int64_t L = batch->seq_lens_host[b];
     if (L < 1) return ABSB_ERR_BAD_SHAPE;
@@ -111,6 +111,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
       }
       if (sel_stride_in > 0 && sel_stride_in < K) K = sel_stride_in;
       p.total += (cap + B - 1) >> lb;
+      in_use += N;
       if (N > p.max_blocks) p.max_blocks = (int32_t)N;
       const int64_t tok = K * B;
       if (tok > p.max_tokens) p.max_tokens = tok;
@@ -135,8 +136,8 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // large.  They wait for each other, twice as long as the scores alone take, and those that are waiting hold back the
   // others beyond four a compute unit.  So: at most two a compute unit, or four if hardly any of the grid is empty, or (empty
   // ones leave at once) as long as the ones with blocks are three a compute unit, four beyond 16384 blocks, where the
-  // alternative is a launch per stage.  One work-group's selection / shared, us a step (work-groups with blocks, of the
-  // grid): 16 x 10K-73K in blocks of 16, max-min 34.4 / 31.8 and 8 % 59.3 / 57.0 (660 of 1152), 8 x 20K-128K, 4096 36.6 / 35.8
+  // alternative is a launch per stage.  How many have blocks is taken as how many the blocks in use fill; a layout's room to
+  // grow counts for nothing.  One work-group's selection / shared, us a step (those, of the grid): 16 x 10K-73K in blocks of 16, max-min 34.4 / 31.8 and 8 % 59.3 / 57.0 (660 of 1152), 8 x 20K-128K, 4096 36.6 / 35.8
   // (470 of 2048), 16 x 8K-128K 42.0 / 40.8 (575 of 2048); 16 x 5K-128K in blocks of 8 to 128 40.4 / 41.1 (830 of 4096), 16 x
   // 96K 41.3 / 41.5 (900 of 1536), 16 x 128K in blocks of 16 48.8 / 49.4 (all of 2048); and a grid that is nearly all empty
   // keeps the few that wait from their places: one request of 131000 beside 16 of 7 to 1000 tokens 21.9 / 27.1 (150 of 2176), two
@@ -145,7 +146,7 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // (This is a limit on time, not what makes the waits end: beyond 96128 blocks a segment three fit a compute unit, not
   // four, and 1024 of them still take 52 us against 90 at 16 segments of 131072 blocks.  See "Progress" in shared.hip.)
   const int shared_chunk = shared_chunk_blocks(p.max_blocks);
-  const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk), shared_real = ceil_div(p.total * g.Rk, shared_chunk);
+  const int64_t shared_grid = (int64_t)p.nseg * ceil_div(p.max_blocks, shared_chunk), shared_real = ceil_div(in_use * g.Rk, shared_chunk);
   const bool shared_pays = shared_grid <= 512 || (shared_grid <= 1024 && 2 * shared_real >= shared_grid) ||
                            (g.Rk == 1 && shared_real <= (p.max_blocks > 16384 ? 1024 : 768) && 8 * shared_real >= shared_grid);
   const bool by_units = !by_shape && p.max_blocks > 16384 && shared_pays;

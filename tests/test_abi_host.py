@@ -388,3 +388,20 @@ def test_a_workspace_planned_for_a_long_capacity_serves_the_builds_on_the_way(re
             sizes = {absb.absb_plan(layer, _batch([L] + caps_b[1:], [512] * len(caps_b), cap_lens_host=caps_b,
                                                   pt_stride=1 << 16)).workspace_bytes for L in sorted(on_the_way)}
             assert len(sizes) == 1, (cap, other, sorted(sizes))
+
+
+def test_room_to_grow_does_not_change_the_form_of_the_step():
+    """The form follows the lengths, whatever the layout has room for: batches on both sides of what decides between the
+    shared selection and a launch per stage (how many of its work-groups there are and how many of them have blocks)."""
+    layer = _layer(block_size=[8, 16, 32, 64, 8, 16, 32, 64])
+    def used(lens, cap):
+        batch = _batch(lens, [2048] * len(lens), cap_lens_host=cap, pt_stride=1 << 14)
+        return absb.absb_step_form_used(layer, batch)
+    seen = set()
+    for lens in ([262144] * 4, [200000, 3000, 3000, 3000], [262144] * 12, [150000] + [2000] * 15, [140000] * 2, [300000, 300000, 10000]):
+        want = used(lens, None)
+        seen.add(want)
+        for grow in (1, 2, 4):
+            assert used(lens, [grow * n for n in lens]) == want, (lens, grow)
+        assert used(lens, [1 << 20] * len(lens)) == want, lens
+    assert seen == {absb.STEP_UNITS, absb.STEP_PER_STAGE}
