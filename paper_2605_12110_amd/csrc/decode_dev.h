@@ -531,7 +531,7 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
       constexpr int U = decltype(unroll)::value;
       static_assert(SL * U * G <= DEC_THREADS, "a thread per split and head of a trip");
       for (int i0 = 0; i0 < nsplit; i0 += SL * U) {
-        float4_t ml = {M_INIT, 0.0f, 0.0f, 0.0f};  // of no split: weight 0
+        float4_t ml = {-__builtin_inff(), 0.0f, 0.0f, 0.0f};  // of no split: weight 0, beside M_INIT too
         if (tid < SL * U * G && i0 * G + tid < nsplit * G)
           ml = bitcast<float4_t>(__builtin_amdgcn_raw_buffer_load_b128(part_ml, (i0 * G + tid) * 16, 0, COHERENT));
         float4_t ov[U];

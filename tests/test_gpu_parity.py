@@ -481,6 +481,34 @@ def test_many_splits_per_segment_and_split_counters_left_at_zero():
     _check_out(dw, ref["out"], ref["lse"], "128 splits, stand-alone call on a scribbled workspace")
 
 
+@pytest.mark.parametrize("G", [1, 2, 4])
+@pytest.mark.parametrize("splits", [2, 3, 5, 9, 33])
+def test_merge_of_values_near_the_largest_of_the_type(splits, G):
+    """Partial outputs close to the largest binary32 number: whatever a merge does with lanes that have fewer splits than others,
+    or none, it must not hold multiples of a partial, not even ones that get the weight zero.  One key a split stands out, from
+    split to split by 1.7 more, so that no sum of weights, in whatever order, comes near 2.4 times the largest."""
+    L = 64 * splits - 7
+    wl = synth.tiny_workload(seed=splits, dtype=synth.BF16, Bt=1, Hq=2 * G, Hkv=2, P=16, seq_lens=(L,), block_size=(8, 16), budget=(L,))
+    rng = np.random.default_rng(splits)
+    q = rng.choice(np.float32([-1.0, 1.0]), size=(2, 1, wl.head_dim))
+    wl.q[:] = synth.f32_to_bits(np.broadcast_to(q, (2, G, wl.head_dim)).reshape(1, 2 * G, wl.head_dim).copy(), wl.dtype)
+    wl.k_cache[:] = 0
+    wl.v_cache[:] = synth.f32_to_bits(rng.standard_normal(wl.v_cache.shape).astype(np.float32), wl.dtype)
+    for i in range(splits):                                       # logits 17, 18.7, .. beside zeros
+        t = 64 * i + 11
+        page = wl.page_table[0, t // 16]
+        wl.k_cache[page, :, t % 16] = synth.f32_to_bits(np.float32(1.5 + 0.15 * i) * q[:, 0], wl.dtype)
+        wl.v_cache[page, :, t % 16] = synth.f32_to_bits(1.4e38 * q[:, 0], wl.dtype)
+    ref = O.decode_step(wl, O.build_centroids(wl))
+    for form in (0, 1, 2, 3):
+        dw = _dev(wl, opts=dict(step_form=form, split_tokens=64))
+        dw.build()
+        dw.out.fill_(float("nan"))
+        dw.decode_fused(); _sync()
+        err = np.abs(dw.out_f32().astype(np.float64) - ref["out"]).max()
+        assert err <= TOL[wl.dtype] * 1.4e38, (splits, G, form)   # (false for a NaN)
+
+
 def test_host_side_bounds_checks_of_the_holder_catch_bad_device_contents():
     """The debug aid that stands in for device-side asserts: planted violations are named on the host."""
     import torch
