@@ -412,8 +412,9 @@ __device__ __forceinline__ void write_empty_rows(const DecodeParams& p, int b, i
   }
 }
 
-// A wait ran out: the segment's output cannot be completed.  Its rows are set to NaN so that nobody
-// takes stale values for results.
+// A wait ran out: the segment's output cannot be completed (one split's ticket is missing for good, so nobody merges).  Its rows
+// are set to NaN so that nobody takes stale values for results, by every work-group whose wait did: others of the segment may
+// have come just in time, or have seen a count on its way past the one they wait for.
 template <int DT, int G>
 __device__ __forceinline__ void poison_rows(const DecodeParams& p, int b, int hs) {
   const uint16_t nan16 = DT == ABSB_F16 ? (uint16_t)0x7e00 : (uint16_t)0x7fc0;
@@ -688,7 +689,7 @@ __device__ __forceinline__ void decode_split(const DecodeParams& p, int s, int s
     // The list comes from a work-group with a lower index, which never waits for anything and was
     // dispatched before this one: the wait ends.  The time limit only makes that unconditional.
     if (!wait_for_flag(flag, p.status, s_bcast + 1)) {
-      if (split == 0) poison_rows<DT, G>(p, b, hs);  // nobody will complete this segment's rows
+      poison_rows<DT, G>(p, b, hs);  // nobody will complete this segment's rows
       return;
     }
   }

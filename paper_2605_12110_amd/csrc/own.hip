@@ -211,7 +211,7 @@ __device__ __forceinline__ void own_split(const OwnParams& p, int s, int split, 
   int32_t* arrived = p.arrived + (size_t)s * ABSB_TICKET_STRIDE;
   const bool scored = !p.some_dense || T < L;  // (else the budget covers the context: nobody scores for this request)
   if (scored && !wait_for_count(arrived, (N + p.sc.chunk - 1) / p.sc.chunk, d.status, s_word)) {
-    if (split == 0) poison_rows<DT, G>(d, b, hs);
+    poison_rows<DT, G>(d, b, hs);
     return;
   }
   if (!g.compete()) {  // no score decides anything

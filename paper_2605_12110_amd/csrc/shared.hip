@@ -411,13 +411,13 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
     const int gone = __syncthreads_or(!there);
     if (gone) {
       if (tid == 0) st_i32<true>(d.status, 1);
-      if (split == 0) poison_rows<DT, G>(d, b, hs);
+      poison_rows<DT, G>(d, b, hs);
       return;
     }
     crowded = __builtin_amdgcn_readfirstlane((int)word) & (int)SHARED_CROWDED;
     if (crowded) {
       if (!wait_for_flag(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, d.status, s_word)) {
-        if (split == 0) poison_rows<DT, G>(d, b, hs);
+        poison_rows<DT, G>(d, b, hs);
         return;
       }
       const int32_t* list = p.tk.work_list + (size_t)t * p.tk.sel_stride;
