@@ -60,6 +60,30 @@ def _hand_over_state(dw):
     return dw.workspace[:dw.nsel * (6 * 256 + 4096) + 256].view(torch.int32)
 
 
+# Splits that long are more than the form of medium segments holds (16384): forced into one launch, the step then runs in the
+# form whose selection is one work-group's, whatever its size.
+ONE_WORK_GROUP = dict(step_form=1, split_tokens=16448)
+
+
+def _work_lists(dw):
+    """The lists that a selection by one work-group hands to the attention, [segment][sel_stride], where the workspace has them:
+    members in the order they were found.  The other forms leave this memory alone, but for a segment
+    whose threshold bin is crowded in the shared selection."""
+    import torch
+    rk = dw.nsel // dw.nseg
+    at = dw.nsel * (6 * 256 + (4096 if dw.nsel <= 512 else 0)) + 256 + -(-dw.plan.total_centroids * rk * 4 // 256) * 256
+    return dw.workspace[at:at + dw.nsel * dw.sel_stride * 4].view(torch.int32).view(dw.nsel, dw.sel_stride).cpu().numpy()
+
+
+def _selected_by_one_work_group(dw, ref, dense=()):
+    """Asserts that all segments, but those of the requests in `dense` (whose budget covers them), were selected that way."""
+    lists, per = _work_lists(dw), dw.nsel // dw.wl.batch
+    for t in range(dw.nsel):
+        if t // per not in dense:
+            k = int(ref["sel_cnt"][t])
+            assert np.array_equal(np.sort(lists[t, :k]), ref["sel_idx"][t, :k]), f"segment {t}"
+
+
 def _check_out(dw, want_out, want_lse, what):
     _sync()
     got = dw.out_f32().astype(np.float64)
@@ -170,6 +194,29 @@ def run_all_stages(wl, name, block_repr=O.MEAN, per_query_head=False, group_max=
             again = dw.out.cpu().numpy() if dw.out.dtype == torch.float16 else dw.out.float().cpu().numpy()
             assert np.array_equal(outs[mode], again), f"{FORMS[mode]}: not deterministic, or the list request changes the output"
     assert np.array_equal(first, outs[absb.absb_step_form_used(dw.layer, dw.batch)]), "default form"
+    # the selection by one work-group, which the pipelined form keeps for some long segments, on this one.  Where every
+    # attention work-group selects for itself (segments of up to 4096 blocks) the output is the same bit for bit if the
+    # segments are cut into the same splits: one each, here
+    dense = {b for b in range(wl.batch) if wl.budget[b] >= wl.seq_lens[b]}
+    one = None
+    for want in (False, True):
+        with _opts(dw, **ONE_WORK_GROUP):
+            dw.scribble(0x3C)
+            dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7); dw.out.fill_(float("nan")); dw.lse.fill_(float("nan"))
+            dw.decode_fused(want_sel=want)
+            _check_out(dw, ref["out"], ref["lse"], f"selected by one work-group, list {want}")
+        one = dw.out.clone() if one is None else one
+        assert torch.equal(dw.out, one) and dw.status() == 0
+        _selected_by_one_work_group(dw, ref, dense)
+    assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+    assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :K])
+    tokens = ref["sel_cnt"].reshape(wl.batch, -1) * np.repeat(wl.block_size, dw.nsel // dw.nseg)
+    blocks = max(-(-int(L) // int(B)) for L in wl.seq_lens for B in wl.block_size)
+    if blocks <= 4096 and dw.sel_stride <= 4096 and int(tokens.max()) <= 16384:
+        with _opts(dw, split_tokens=16384):
+            dw.scribble(0x3C)
+            dw.decode_fused(); _sync()
+        assert torch.equal(dw.out, one), "selected by the attention work-groups"
     dw.check_device_contents(lists=True)      # the holder's host-side bounds checks agree with all of that
     dw.scribble(0x99)     # the stand-alone stages do not keep the other counters: clear them again
     _say("    fused: selection bit-exact in every enqueue form, outputs within tolerance, deterministic")
@@ -303,12 +350,13 @@ def test_decode_accepts_any_list_order_partial_last_block_and_empty_lists():
     assert not dw.out_f32()[1, 0:G].any() and np.all(np.isneginf(dw.lse.cpu().numpy()[1, 0:G]))
 
 
-@pytest.mark.parametrize("L,repr_,gmax,G", [(8, 0, False, 4), (1024 * 8, 0, False, 4), (1024 * 8 + 1, 0, False, 4), (768 * 8, 1, False, 2),
-                                            (769 * 8, 1, False, 2), (512 * 8 - 3, 0, True, 4), (1023 * 8 + 5, 0, True, 2)])
+@pytest.mark.parametrize("L,repr_,gmax,G", [(8, 0, False, 4), (512 * 8, 0, False, 4), (512 * 8 + 1, 0, False, 4), (512 * 8, 1, False, 2),
+                                            (512 * 8 + 1, 1, False, 2), (512 * 8 - 3, 0, True, 4), (512 * 8, 0, True, 8),
+                                            (512 * 8 + 1, 0, True, 8), (1023 * 8 + 5, 0, True, 2)])
 def test_short_segments_around_the_limit_of_the_form_that_selects_for_itself(L, repr_, gmax, G):
-    """Up to a number of blocks the default step lets every attention work-group score and select for itself:
-    one block, the limits of each score kind and one beyond, beside a request of a few blocks and one whose
-    budget covers it; the output must be the pipelined form's bit for bit (run_all_stages checks that)."""
+    """Up to 512 blocks the default step lets every attention work-group score and select for itself: one block, the limit
+    with each score kind and one beyond, beside a request of a few blocks and one whose budget covers it; the output
+    must be the bits of a selection by one work-group (run_all_stages checks that)."""
     wl = synth.tiny_workload(seed=37, dtype=synth.F16, Hq=2 * G, Hkv=2, P=16, seq_lens=(L, 100, 333), block_size=(8, 32),
                              budget=(max(8, L // 5), 24, 400))
     run_all_stages(wl, f"short segments L={L}", O.MINMAX if repr_ else O.MEAN, group_max=gmax)
@@ -316,7 +364,7 @@ def test_short_segments_around_the_limit_of_the_form_that_selects_for_itself(L, 
 
 @pytest.mark.parametrize("sink,recent", [(0, 0), (24, 40)])
 @pytest.mark.parametrize("distinct", [0, 3, 40])
-@pytest.mark.parametrize("blocks", [63, 64, 65, 255, 256, 257, 512, 513, 1024])
+@pytest.mark.parametrize("blocks", [63, 64, 65, 255, 256, 257, 511, 512])
 def test_selection_by_single_waves_at_the_edges_of_its_tiles(blocks, distinct, sink, recent):
     """Short segments, selected by waves on their own: numbers of blocks around the register tiles; keys that are all
     different, or so few (one value a page) that the threshold bin holds dozens or hundreds of blocks that tie.  The list
@@ -333,26 +381,28 @@ def test_selection_by_single_waves_at_the_edges_of_its_tiles(blocks, distinct, s
     dw = _dev(wl, sink_tokens=sink, recent_tokens=recent)
     dw.build()
     outs = []
-    for form in (0, 1):
-        with _opts(dw, step_form=form):
+    for form, split in ((0, 0), (1, 0), (0, 16448), (1, 16448)):          # 1, 16448: by one work-group
+        with _opts(dw, step_form=form, split_tokens=split):
             for want in (True, False):
+                dw.scribble(0x3C)
                 dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7); dw.out.fill_(float("nan"))
                 dw.decode_fused(want_sel=want)
-                _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, form {form}, list {want}")
+                _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, form {form}, split {split}, list {want}")
                 if want:
                     assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
                     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
                 outs.append(dw.out.clone())
-    assert all(torch.equal(outs[0], o) for o in outs[1:])
+    _selected_by_one_work_group(dw, ref)
+    assert all(torch.equal(outs[0], o) for o in outs[1:4]) and all(torch.equal(outs[4], o) for o in outs[5:])
 
 
 @pytest.mark.parametrize("sink,recent", [(0, 0), (24, 40)])
 @pytest.mark.parametrize("distinct", [0, 40, 700])
-@pytest.mark.parametrize("blocks", [1025, 2048, 2049, 4096, 4097])
+@pytest.mark.parametrize("blocks", [513, 1024, 1025, 2048, 2049, 4096, 4097])
 def test_selection_by_every_attention_work_group_at_the_edges_of_its_tiles(blocks, distinct, sink, recent):
     """Segments of medium length, which every attention work-group selects for itself: numbers of blocks around the register
-    tiles and one beyond the form; keys that are all different, or so few (one value a page) that the threshold bin is
-    crowded and blocks tie.  A small and a large budget; a wrong block of either shows in the log-sum-exp.  The list
+    tiles, the shortest and longest and one beyond the form; keys that are all different, or so few (one value a page) that blocks
+    tie.  A small and a large budget; a wrong block of either shows in the log-sum-exp.  The list
     against the oracle, with the list and without: the same bits."""
     import torch
     wl = synth.tiny_workload(seed=blocks + distinct, dtype=synth.F16, Bt=2, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 3, 8 * blocks),
@@ -375,6 +425,68 @@ def test_selection_by_every_attention_work_group_at_the_edges_of_its_tiles(block
         outs.append(dw.out.clone())
         assert not _hand_over_state(dw).any()
     assert torch.equal(outs[0], outs[1])
+
+
+def _threshold_bin(scores, K, lo, hi):
+    """What a selection finds in the bin of its K-th block, a bin being what keys have in common in the first eleven of the bits
+    that their range takes: how many of the competing blocks [lo, hi), and how many different scores."""
+    rel = scores[lo:hi].astype(np.int64) - int(scores[lo:hi].min())
+    shift = max(int(rel.max() | 1).bit_length() - 11, 0)
+    kth = np.sort(rel)[::-1][K - lo - (len(scores) - hi) - 1]
+    inside = rel[rel >> shift == kth >> shift]
+    return len(inside), len(np.unique(inside))
+
+
+@pytest.mark.parametrize("sink,recent", [(0, 0), (24, 40)])
+@pytest.mark.parametrize("kind", ["few keys", "outliers"])
+@pytest.mark.parametrize("blocks", [1000, 2048, 2049, 4096])
+def test_crowded_threshold_bins_where_every_attention_work_group_selects(blocks, kind, sink, recent):
+    """Segments of medium length whose threshold bin holds more than the 128 keys that are ranked: three distinct keys, so that it
+    holds one score hundreds of times; a few blocks far out on both sides, so that a thousand different scores share what
+    the first digit leaves of the range and further digits have to part them.  A budget of half the blocks.  With the
+    list and without, in splits and in one (the same bits as a selection by one work-group)."""
+    import torch
+    wl = synth.tiny_workload(seed=blocks, dtype=synth.F16, Bt=2, Hq=8, Hkv=2, P=16, seq_lens=(8 * blocks - 3, 8 * blocks),
+                             block_size=(8, 16), budget=4 * blocks)
+    rng = np.random.default_rng(blocks)
+    pages = wl.k_cache.shape[0]
+    if kind == "few keys":
+        pal = synth.f32_to_bits(rng.standard_normal((3, wl.head_dim)).astype(np.float32), wl.dtype)
+        wl.k_cache[:] = pal[rng.integers(0, 3, size=(pages, 2))][:, :, None, :]
+    else:                                                          # 120 channels tell the outliers, 8 weak ones the others
+        sign = rng.choice(np.float32([-1.0, 1.0]), size=wl.head_dim)
+        weight = np.where(np.arange(wl.head_dim) < 120, np.float32(1.0), np.float32(0.02))
+        wl.q[:] = synth.f32_to_bits(np.broadcast_to(sign * weight, wl.q.shape).copy(), wl.dtype)
+        k = np.zeros((pages, 2, 2, 1, wl.head_dim), np.float32)    # one value a block of 8
+        k[..., 120:] = rng.standard_normal(k[..., 120:].shape)
+        k = np.broadcast_to(k, (pages, 2, 2, 8, wl.head_dim)).reshape(wl.k_cache.shape).copy()
+        for far, at in zip((4.0, -4.0), rng.permutation(pages)[:8].reshape(2, 4)):
+            k[at, :, :, :120] = far * sign[:120]
+        wl.k_cache[:] = synth.f32_to_bits(k, wl.dtype)
+    st = O.build_centroids(wl)
+    ref = O.decode_step(wl, st, sink_tokens=sink, recent_tokens=recent)
+    for t in range(4):
+        L, B = int(wl.seq_lens[t // 2]), int(wl.block_size[t % 2])
+        inside, different = _threshold_bin(ref["scores"][st.off[t]:st.off[t + 1]], int(ref["sel_cnt"][t]), -(-sink // B),
+                                           (L - recent) // B if recent else -(-L // B))
+        assert inside > 128 and (different > 100 if kind == "outliers" else different == 1), (t, inside, different)
+    dw = _dev(wl, sink_tokens=sink, recent_tokens=recent)
+    dw.build()
+    outs = {}
+    for form, split in ((0, 0), (0, 16384), (1, 16448)):
+        with _opts(dw, step_form=form, split_tokens=split):
+            for want in (True, False):
+                dw.scribble(0x3C)
+                dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7); dw.out.fill_(float("nan"))
+                dw.decode_fused(want_sel=want)
+                _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, {kind}, form {form}, split {split}, list {want}")
+                if want:
+                    assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+                    assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+                assert not _hand_over_state(dw).any()
+                assert torch.equal(outs.setdefault(split, dw.out.clone()), dw.out)
+    _selected_by_one_work_group(dw, ref)
+    assert torch.equal(outs[16384], outs[16448])
 
 
 def test_split_shapes_do_not_change_the_selection_and_stay_within_tolerance():
@@ -1206,6 +1318,42 @@ def test_pipelined_step_whose_long_segments_are_selected_by_one_work_group(block
         assert int(_hand_over_state(dw).abs().sum().item()) == 0
 
 
+@pytest.mark.parametrize("blocks,dtype,G,repr_,select,sink", [
+    (4097, synth.BF16, 5, O.MEAN, "group", 0), (8192, synth.F16, 2, O.MINMAX, "group", 0), (8192, synth.BF16, 8, O.MINMAX, "group", 100),
+    (4100, synth.F16, 3, O.MEAN, "per_query_head", 0), (8200, synth.BF16, 7, O.MINMAX, "per_query_head", 40),
+    (16384, synth.BF16, 1, O.MEAN, "group", 0), (9000, synth.BF16, 8, O.MEAN, "group_max", 100), (5000, synth.BF16, 6, O.MEAN, "group_max", 0)])
+def test_default_step_on_a_long_segment_beside_many_short_ones(blocks, dtype, G, repr_, select, sink):
+    """One request of 4097 blocks and more beside many of a few hundred tokens, one of which its budget covers: so few of
+    the estimation work-groups have blocks that they do not share the selection, and it is one work-group's by
+    default (the work lists in the workspace say so) with every kind of selection, pooling, type and group size."""
+    import torch
+    from paper_2605_12110_amd import absb
+    per_q = select == "per_query_head"
+    short = (300, 64, 7, 1000) * (8 if not per_q else 5)
+    wl = synth.tiny_workload(seed=blocks, dtype=dtype, Hq=2 * G, Hkv=2, P=16, seq_lens=(8 * blocks - 5, *short), block_size=(8, 64),
+                             budget=(4096, 300, *[128] * (len(short) - 1)))
+    view = O.per_query_head_view(wl) if per_q else wl
+    ref = O.decode_step(view, O.build_centroids(view, repr_), sink_tokens=sink, recent_tokens=sink, group_max=select == "group_max")
+    dw = _dev(wl, block_repr=repr_, sink_tokens=sink, recent_tokens=sink,
+              selection=dict(group=absb.SELECT_GROUP, per_query_head=absb.SELECT_PER_QUERY_HEAD, group_max=absb.SELECT_GROUP_MAX)[select])
+    dw.build()
+    assert absb.absb_step_form_used(dw.layer, dw.batch) == absb.STEP_PIPELINED
+    dense = {b for b in range(wl.batch) if wl.budget[b] >= wl.seq_lens[b]}
+    first = None
+    for want in (True, False, True):
+        dw.scribble(0xA5)
+        dw.out.fill_(float("nan")); dw.sel_idx.fill_(-7); dw.sel_cnt.fill_(-7)
+        dw.decode_fused(want_sel=want)
+        _check_out(dw, ref["out"], ref["lse"], f"{blocks} blocks, {select}, list {want}")
+        if want:
+            assert np.array_equal(dw.sel_cnt.cpu().numpy(), ref["sel_cnt"])
+            assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
+        _selected_by_one_work_group(dw, ref, dense)
+        first = dw.out.clone() if first is None else first
+        assert torch.equal(dw.out, first)
+        assert not _hand_over_state(dw).any()
+
+
 def test_one_workspace_serves_batches_of_different_shapes_when_cleared_in_between():
     """Requests join and leave: the same workspace runs a batch of three, of one, of five; its counters
     move with the number of segments, so absb_workspace_init runs whenever the shape changes."""
@@ -1591,12 +1739,14 @@ def test_one_request_of_a_batch_is_re_ranged_in_place():
     assert np.array_equal(dw.sel_idx.cpu().numpy(), ref["sel_idx"][:, :dw.sel_stride])
 
 
-def test_stages_ignore_the_unused_rows_of_a_layout_sized_for_longer_contexts():
+@pytest.mark.parametrize("caps,lens", [((999, 2500), (700, 1801)), ((9000, 20000), (4099, 16385)), ((40000, 60000), (37000, 33001))])
+def test_stages_ignore_the_unused_rows_of_a_layout_sized_for_longer_contexts(caps, lens):
     """A store laid out for longer contexts than the current ones: build, score, selection and the
-    step give the same results as the tight layout (the unused rows hold garbage)."""
-    full = synth.tiny_workload(seed=72, dtype=synth.F16, Bt=2, Hq=8, Hkv=4, P=16, seq_lens=(999, 2500),
+    step give the same results as the tight layout (the unused rows hold garbage), with segments that every attention
+    work-group scores and selects, that it selects, and whose selection is shared."""
+    full = synth.tiny_workload(seed=72, dtype=synth.F16, Bt=2, Hq=8, Hkv=4, P=16, seq_lens=caps,
                                block_size=(128, 8, 64, 16), budget=(300, 520))
-    lens = np.array([700, 1801], np.int32)
+    lens = np.array(lens, np.int32)
     view = _view_at(full, lens)
     st = O.build_centroids(view)
     ref = O.decode_step(view, st)
