@@ -278,8 +278,10 @@ ABSB_API int absb_workspace_init(const absb_layer* layer, const absb_batch* batc
  *                        blocks over; blocks inside the threshold bin are settled by an exact ranking among
  *                        the segment's candidates.  No work-group ever passes over a whole segment, so the
  *                        cost hardly grows with the context.  Chosen for segments beyond 16384 blocks while
- *                        there are at most two of those work-groups per compute unit, or four that have
- *                        blocks to score.
+ *                        there are at most two of those work-groups per compute unit; or four, if the blocks
+ *                        in use would fill half of them; or, with one selection per KV head, any number of
+ *                        which the blocks in use would fill at least an eighth and at most four per compute
+ *                        unit.
  *   ABSB_STEP_PER_STAGE  three launches (score, top-k, sparse decode).  Otherwise.
  * The one-launch forms hand work between work-groups through the counters at the start of the
  * workspace: they must be zero when the call starts (absb_workspace_init) and are zero again when its

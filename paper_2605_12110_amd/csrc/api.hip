@@ -216,9 +216,10 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // The pipelined form shares the selection, too, from where a segment's scores are too many for every attention
   // work-group to read (own.hip).  Own selection / shared at 4096 blocks: 1 request, 4096 15.7 / 16.5 us, 8 requests, 2048 23.3 / 23.9.
   // One work-group's selection / shared beyond: 6144 blocks, 1 request, 512 14.5 / 13.8, 4 requests, 2048 21.1 / 19.1, group
-  // maximum, 8192, 1 request 17.8 / 16.8, 8 requests 31.5 / 30.1.  (Beyond 8192 blocks the group's maximum keeps to one work-group's
-  // selection; the line there has not been moved.  Forced beyond 16384 blocks, the pipelined form keeps to one work-group a
-  // segment and to the ascending order.)
+  // maximum, 8192, 1 request 17.8 / 16.8, 8 requests 31.5 / 30.1.  Beyond 8192 blocks the group's maximum keeps to one work-group's
+  // selection, and that costs: group maximum, blocks of 8, lists of 2048, 12288 blocks, 1 request 19.5 / 17.0, 8 requests 38.4 / 38.4, 16384
+  // blocks, 1 request 20.0 / 17.3, 4 requests 28.7 / 25.8.  That line dates from when one work-group's selection was the faster there and has yet
+  // to be moved.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
   p.shared = p.step_form == ABSB_STEP_UNITS || (p.step_form == ABSB_STEP_PIPELINED && !p.small && (!g.agg_max || p.max_blocks <= 8192) &&
                                                 p.max_blocks > OWN_MAX_BLOCKS && p.max_blocks <= 16384 && shared_pays);
   const bool rows = !lean && p.nseg <= SHARED_MAX_SEGMENTS;  // the workspace has histogram rows and room for candidates

@@ -455,8 +455,8 @@ __device__ __forceinline__ bool finish_split(const DecodeParams& p, int s, int b
   __syncthreads();
   // work-group maximum per head; own state rescaled to it, so that the four states simply add up.  (Every lane works out its
   // head's factor, and all read it from there.  A read of LDS per head, behind the writes of the one before, and addresses
-  // fetched where they are used took longer: 1 x 4K 9.5 -> 9.1 us a step, 8 x 32K 20.5 -> 20.3, a step of a decode loop over 4
-  // requests 15.3 -> 14.9.)
+  // fetched where they are used took longer: 1 x 4K 9.4 -> 9.1 us a step, 8 x 32K 20.5 -> 20.3, a step of a decode loop over 4
+  // requests 15.3 -> 14.9; three copies of a layer in turn.)
   float* s_o = reinterpret_cast<float*>(s_stage);  // [DEC_WAVES][G][128]
   const float4_t ms = *reinterpret_cast<const float4_t*>(s_m[lane & (HEADS - 1)]);
   const float rescale = fast_exp2(m - fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3])));

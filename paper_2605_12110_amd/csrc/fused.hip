@@ -20,7 +20,8 @@
 //
 // This is the form for segments beyond 4096 blocks whose chunks should not wait for each other (shared.hip): grids of
 // estimation work-groups that outgrow the chip or are nearly all empty, the group's maximum beyond 8192 blocks.  Shorter
-// segments are selected by every attention work-group (own.hip, small.hip).
+// segments are selected by every attention work-group (own.hip, small.hip), unless the caller asks for splits longer than
+// own.hip holds.
 //
 // Progress: estimation/selection work-groups never wait for anything.  Attention work-groups wait
 // only for work-groups with lower indices; the hardware starts work-groups in index order, so
