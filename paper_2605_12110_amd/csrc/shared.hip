@@ -487,28 +487,32 @@ __device__ __forceinline__ void shared_split(const SharedParams& p, int t, int s
   // the merge.  The chunks' own counters are back at zero, or about to be, if a last chunk has been there (all counts
   // words were out long before) and nobody has counted after it; otherwise they did not start there, the caller's list may be
   // missing, and the row may not be clear.
-  const auto counters = [&]() __attribute__((always_inline)) {
-    return ld_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE) | ld_i32<true>(p.arrived + (size_t)t * ABSB_TICKET_STRIDE);
-  };
-  int left = 0;
+  const int32_t* finished = p.finished + (size_t)t * ABSB_TICKET_STRIDE;
+  const int32_t* arrived = p.arrived + (size_t)t * ABSB_TICKET_STRIDE;
+  int fin = 0, arr = 0;  // (put together behind the merge only: any use ahead of it waits for them and the stores in front)
   const bool last = finish_split<DT, G>(d, t, b, hs, split, nsplit, d.max_splits, st, lds, [&]() __attribute__((always_inline)) {
     if (!compete) return;
     if (tid < SHARED_MAX_CHUNKS) st_i32<true>(reinterpret_cast<int32_t*>(p.counts + (size_t)t * SHARED_MAX_CHUNKS) + tid, 0);
     if (tid == 0) {
-      left = counters();
+      fin = ld_i32<true>(finished);
+      arr = ld_i32<true>(arrived);
       if (crowded) st_i32<true>(p.crowd_flag + (size_t)t * ABSB_TICKET_STRIDE, 0);
     }
   });
   if (!last || !compete) return;
-  if (tid == 0) s_word[1] = left;  // (finish_split uses the word itself)
+  if (tid == 0) {  // (finish_split uses the word in front)
+    s_word[1] = fin;
+    s_word[2] = arr;
+  }
   __syncthreads();
-  if (!s_word[1]) return;
+  if (!(s_word[1] | s_word[2])) return;
   __syncthreads();
   if (tid == 0) {
     const uint64_t t0 = wall_clock64();
+    int left;
     do {
       __builtin_amdgcn_s_sleep(2);
-      left = counters();
+      left = ld_i32<true>(finished) | ld_i32<true>(arrived);
     } while (left && wall_clock64() - t0 < DEC_WAIT_LIMIT_TICKS);
     if (left) st_i32<true>(d.status, 1);
     s_word[1] = left;
