@@ -279,34 +279,35 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
   int32_t* s_sure = reinterpret_cast<int32_t*>(s_idx + SHARED_MAX_CAND);    // [SHARED_MAX_CHUNKS]
   int32_t* s_cand = s_sure + SHARED_MAX_CHUNKS;                             // [SHARED_MAX_CHUNKS]
   const int nwords = out && !crowded ? (N + 31) >> 5 : 0;
+  int32_t* listed = reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS);
+  u32x4 sums = {0u, 0u, 0u, 0u};  // blocks above the bin, candidates, whether a word is missing
   if (relied) {
-    if (tid < SHARED_MAX_CHUNKS) {
-      int32_t* word_at = reinterpret_cast<int32_t*>(p.listed + (size_t)t * SHARED_MAX_CHUNKS) + lane;  // lane = chunk
-      const uint32_t cw = lane < C ? (uint32_t)ld_i32<true>(word_at) : 0u;
-      const bool missing = __any(lane < C && cw == 0u);
-      if (!missing) st_i32<true>(word_at, 0);
-      uint32_t sure, ncand;
-      const uint32_t ns = cw & 0xffffu, ncd = (cw >> 16) & 0xfffu;
-      const uint32_t sure_to = wave_incl_scan_u32(ns, &sure), cand_to = wave_incl_scan_u32(ncd, &ncand);
-      s_sure[lane] = (int)(sure_to - ns);
-      s_cand[lane] = (int)(cand_to - ncd);
-      if (lane == 0) {
-        s_words[44] = sure;
-        s_words[45] = ncand;
-        s_words[46] = missing;
-      }
-    }
+    const uint32_t cw = wave == 0 && lane < C ? (uint32_t)ld_i32<true>(listed + lane) : 0u;  // lane = chunk
 #pragma unroll 1
     for (int w = tid; w < nwords; w += SHARED_THREADS) s_bm[w] = 0;
+    if (wave == 0) {
+      const uint32_t ns = cw & 0xffffu, ncd = (cw >> 16) & 0xfffu;
+      uint32_t sure, ncand;
+      const uint32_t sure_to = wave_incl_scan_u32(ns, &sure), cand_to = wave_incl_scan_u32(ncd, &ncand);
+      const uint32_t missing = __any(lane < C && cw == 0u);
+      s_sure[lane] = (int)(sure_to - ns);
+      s_cand[lane] = (int)(cand_to - ncd);
+      if (lane == 0) *reinterpret_cast<u32x4*>(s_words + 44) = u32x4{sure, ncand, missing, 0u};
+    }
     __syncthreads();
-    if (s_words[46]) return;
+    sums = *reinterpret_cast<const u32x4*>(s_words + 44);
+    if (sums.z) return;
   }
-  __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, tid * 16, 0, 16 /* sc1 */);
-  if (tid == 0) {
-    st_i32<true>(arrived, 0);
-    st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
-  }
+  const auto clear = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, rsrc, tid * 16, 0, 16 /* sc1 */);
+    if (relied && tid < SHARED_MAX_CHUNKS) st_i32<true>(listed + tid, 0);
+    if (tid == 0) {
+      st_i32<true>(arrived, 0);
+      st_i32<true>(p.finished + (size_t)t * ABSB_TICKET_STRIDE, 0);
+    }
+  };
   if (crowded) {
+    clear();
     __syncthreads();  // the words are read; the selection's LDS overlaps them
     TopkShared& sh = *reinterpret_cast<TopkShared*>(lds);
     uint32_t* bitmap = reinterpret_cast<uint32_t*>(lds + ((sizeof(TopkShared) + 15) & ~size_t(15)));
@@ -314,10 +315,13 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     return;
   }
   if (tid == 0) p.tk.sel_cnt[t] = g.K;
-  if (!out) return;
+  if (!out) {
+    clear();
+    return;
+  }
   // the caller's ascending list, from the chunks' lists: a bitmap, then one scan
   const int64_t seg_place = place - j0;
-  const uint32_t sure = s_words[44], ncand = s_words[45];
+  const uint32_t sure = sums.x, ncand = sums.y;
   for (int i = tid; i < (int)sure; i += SHARED_THREADS) {
     const int u = chunk_of(s_sure, C, i);
     const int j = ld_i32<true>(p.area + seg_place + (int64_t)u * chunk + (i - s_sure[u]));
@@ -332,6 +336,7 @@ __device__ __forceinline__ void shared_chunk(const SharedParams& p, const ScoreS
     s_idx[i] = (uint32_t)(pr >> 32);
   }
   __syncthreads();
+  clear();  // (ahead of the loads above these would wait for its acknowledgement: 1 x 256K with the list, 0.1 us a step)
 #pragma unroll 1
   for (int k = tid; k < nc; k += SHARED_THREADS) {
     const uint32_t mk = s_key[k], mi = s_idx[k];
