@@ -216,7 +216,9 @@ int make_plan(const absb_layer* layer, const absb_batch* batch, bool need_budget
   // The pipelined form shares the selection, too, from where a segment's scores are too many for every attention
   // work-group to read (own.hip).  Own selection / shared at 4096 blocks: 1 request, 4096 15.7 / 16.5 us, 8 requests, 2048 23.3 / 23.9.
   // One work-group's selection / shared beyond: 6144 blocks, 1 request, 512 14.5 / 13.8, 4 requests, 2048 21.1 / 19.1, group
-  // maximum, 8192, 1 request 17.8 / 16.8, 8 requests 31.5 / 30.1.  Beyond 8192 blocks the group's maximum keeps to one work-group's
+  // maximum, 8192, 1 request 17.8 / 16.8, 8 requests 31.5 / 30.1.  Level with max-min rows and a list for the caller: 8 x 9K-75K (4700
+  // blocks), 1024 20.5 / 20.6, 2048 27.7 / 26.9, 4096 34.8 / 34.9; without it 20.7 / 20.6, 28.0 / 26.9, 34.5 / 33.6; mean rows with it
+  // 19.1 / 18.3, 27.3 / 24.9, 34.0 / 32.5.  Beyond 8192 blocks the group's maximum keeps to one work-group's
   // selection, and that costs: group maximum, blocks of 8, lists of 2048, 12288 blocks, 1 request 19.5 / 17.0, 8 requests 38.4 / 38.4, 16384
   // blocks, 1 request 20.0 / 17.3, 4 requests 28.7 / 25.8.  That line dates from when one work-group's selection was the faster there and has yet
   // to be moved.  (Forced beyond 16384 blocks, the pipelined form keeps to one work-group a segment and to the ascending order.)
